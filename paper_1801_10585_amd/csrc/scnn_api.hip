@@ -20,7 +20,7 @@ static thread_local char g_err[256] = "";
 static thread_local int g_conv_path = 0;
 static thread_local const char* g_last_conv_kernel = "";
 
-enum class ConvKernel { kValu, kPair, kQuad };
+enum class ConvKernel { kValu, kPair, kQuad, kSplit };
 
 // Which kernel multiplies.  The quad kernel (output-stationary, registers only) takes C_in in {8, .., 64} and up to
 // 128 output channels (a launch per 64) with at most 32 taps, also C_in = 96 and 128 where the pair-list kernel does
@@ -31,6 +31,7 @@ static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long 
     const bool pair_ok = conv_mfma_supported(g, c_in, c_out, nnz_in);
     if (g_conv_path == 3) return pair_ok ? ConvKernel::kPair : ConvKernel::kValu;
     const bool quad_ok = conv_quad_supported(g, c_in, c_out, nnz_in);
+    if (conv_split_supported(g, c_in, c_out, nnz_in)) return ConvKernel::kSplit;
     if (g_conv_path == 2) return quad_ok ? ConvKernel::kQuad : (pair_ok ? ConvKernel::kPair : ConvKernel::kValu);
     // 8, 16 and 24 input channels pay for the matrix-core kernels' look-ups and lists only on layers whose rows carry
     // enough multiply-adds per neighbour: C_in x C_out of at least 256 with at least 24 output channels (8->32,
@@ -239,6 +240,8 @@ struct ConvWs {
     unsigned short* block_tap;
     float* wb;
     float* wq;
+    unsigned short* wsplit;  // filter and input rows of the split kernel
+    unsigned short* xsplit;
     uint2* tile_hdr;
     long long block_cap;
     ConvKernel kernel;
@@ -303,6 +306,9 @@ static void carve_conv(void* base, const Geom& g, const Geom& gp, long long nnz_
     w->wb = c.take<float>(w->block_cap ? (size_t)g.T * round_up(c_in, 32) * c_out : 0);
     w->tile_hdr = c.take<uint2>(w->block_cap ? w->tiles_cap : 0);
     w->wq = c.take<float>(w->kernel == ConvKernel::kQuad ? quad_groups(c_out) * quad_filter_floats(g.T, c_in) : 0);
+    const bool split = w->kernel == ConvKernel::kSplit;
+    w->wsplit = c.take<unsigned short>(split ? quad_groups(c_out) * split_filter_elems(g.T, c_in) : 0);
+    w->xsplit = c.take<unsigned short>(split ? (size_t)nnz_in * round_up(c_in, 32) * 3 : 0);
     w->tmp_coords = c.take<int32_t>(pool ? (size_t)cand_cap * (1 + g.ndim) : 0);
     w->tmp_feats = c.take<float>(pool ? (size_t)cand_cap * c_out : 0);
     w->pool_key = c.take<long long>(pool ? w->pool_cap : 0);
@@ -396,8 +402,11 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
     // the matrix-core kernels load input rows 16 bytes at a time
     const ConvKernel kernel = ((uintptr_t)in_feats & 15) == 0 ? ws.kernel : ConvKernel::kValu;
     SCNN_TRY(launch_prepare(g, w, c_in, c_out, 0, ws.c_out_pad, ws.wp, kernel == ConvKernel::kPair ? ws.wb : nullptr,
-                            kernel == ConvKernel::kQuad ? ws.wq : nullptr, ws.tap_active, ws.tap_coord, workspace,
+                            kernel == ConvKernel::kQuad ? ws.wq : nullptr,
+                            kernel == ConvKernel::kSplit ? ws.wsplit : nullptr, ws.tap_active, ws.tap_coord, workspace,
                             ws.zero_bytes, s));
+    if (kernel == ConvKernel::kSplit)
+        SCNN_TRY(launch_split_rows(in_feats, nnz_in, (const long long*)nnz_in_dev, nnz_in, c_in, ws.xsplit, s));
     // with a device-resident count, nnz_in is only the capacity of the input arrays: rows past the true count are
     // never indexed, so no look-up can return them
     SCNN_TRY(launch_index_build(g, in_coords, nnz_in, (const long long*)nnz_in_dev, nnz_in, ws.occ, ws.occ_prefix,
@@ -417,7 +426,13 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
                                   ws.tile_start, ws.rows16_start, ws.ctr, s));
     }
     timer.mark();
-    if (kernel == ConvKernel::kQuad) {
+    if (kernel == ConvKernel::kSplit) {
+        timer.mark();
+        SCNN_TRY(launch_conv_split(g, ws.occ, ws.occ_prefix, nnz_in, ws.xsplit, c_in, ws.wsplit, c_out, bias,
+                                   ws.tap_active, ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, ws.resp,
+                                   device_cu_count(), s));
+        g_last_conv_kernel = "k_conv_quad";
+    } else if (kernel == ConvKernel::kQuad) {
         const int cus = device_cu_count();
         timer.mark();
         SCNN_TRY(launch_conv_quad(g, ws.occ, ws.occ_prefix, nnz_in, in_feats, c_in, ws.wq, c_out, bias, ws.tap_active,
@@ -572,7 +587,7 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
     // adjoint filter (taps negated, channels transposed) in the layout of the convolution kernel that will run;
     // the same launch clears the counters and the occupancy bitmap
     SCNN_TRY(launch_prepare(g, w, c_out, c_in, 1, ws.c_in_pad, ws.wp, use_mfma ? ws.wb : nullptr, nullptr,
-                            ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
+                            nullptr, ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
     SCNN_TRY(launch_index_build(g, g_coords, g_rows, nullptr, g_rows, ws.occ, ws.occ_prefix, ws.ctr, s));
     SCNN_TRY(launch_rows_sample_bounds(g, in_coords, nnz_in, ws.cand_start, ws.tile_start, ws.ctr, s));
     SCNN_TRY(launch_bwd_sites(g, in_coords, nnz_in, ws.cand_start, ws.cand_lin, ws.rows16_start, ws.ctr, s));

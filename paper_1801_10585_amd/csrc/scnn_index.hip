@@ -254,9 +254,9 @@ __device__ inline float filter_at(const float* __restrict__ w, int T, int c_in, 
 
 __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict__ w, int c_in, int c_out, int adjoint,
                                                  int c_out_pad, double* __restrict__ wp, float* __restrict__ wb,
-                                                 float* __restrict__ wq, int* __restrict__ tap_active,
-                                                 int* __restrict__ tap_coord, uint4* __restrict__ zero_p,
-                                                 size_t zero_n16) {
+                                                 float* __restrict__ wq, unsigned short* __restrict__ ws,
+                                                 int* __restrict__ tap_active, int* __restrict__ tap_coord,
+                                                 uint4* __restrict__ zero_p, size_t zero_n16) {
     if ((int)blockIdx.x >= g.T) {
         const size_t stride = (size_t)(gridDim.x - g.T) * blockDim.x;
         for (size_t i = (size_t)(blockIdx.x - g.T) * blockDim.x + threadIdx.x; i < zero_n16; i += stride)
@@ -283,6 +283,23 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
                 const float v =
                     (ic < c_in && oc < cg) ? filter_at(w, g.T, c_in, c_out, adjoint, t, ic, col0 + oc) : 0.0f;
                 wq_g[(size_t)t * n + i] = v;
+                any |= (v != 0.0f);
+            }
+        }
+    } else if (ws) {
+        // operand order of the split kernel: [tap][chunk][h | m | l][16 output channels][lane][8], lane = 16 * (channel
+        // / 8) + output channel; columns past the real ones are zero.  Groups of 64 output channels one after the other.
+        const int nch = (c_in + 31) / 32;
+        for (int col0 = 0; col0 < c_out; col0 += 64) {
+            const int cg = c_out - col0 < 64 ? c_out - col0 : 64, nb = cg > 32 ? 4 : 2;
+            unsigned short* ws_g = ws + (size_t)(col0 >> 6) * split_filter_elems(g.T, c_in) + (size_t)t * nch * nb * 1536;
+            for (int i = threadIdx.x; i < nch * nb * 512; i += blockDim.x) {
+                const int e = i & 7, lane = (i >> 3) & 63, r = i >> 9, cb = r % nb, c = r / nb;
+                const int ic = c * 32 + (lane >> 4) * 8 + e, oc = cb * 16 + (lane & 15);
+                const float v =
+                    (ic < c_in && oc < cg) ? filter_at(w, g.T, c_in, c_out, adjoint, t, ic, col0 + oc) : 0.0f;
+                unsigned short* dst = ws_g + (size_t)c * nb * 1536 + cb * 512 + (i & 511);
+                split3(v, dst[0], dst[nb * 512], dst[2 * nb * 512]);
                 any |= (v != 0.0f);
             }
         }
@@ -320,13 +337,13 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
 }
 
 hipError_t launch_prepare(const Geom& g, const float* w, int c_in, int c_out, int adjoint, int c_out_pad, double* wp,
-                          float* wb, float* wq, int* tap_active, int* tap_coord, void* zero_p, size_t zero_bytes,
-                          hipStream_t s) {
+                          float* wb, float* wq, unsigned short* ws, int* tap_active, int* tap_coord, void* zero_p,
+                          size_t zero_bytes, hipStream_t s) {
     const size_t n16 = (zero_bytes + 15) / 16;
     size_t zb = (n16 + 255) / 256;
     if (zb > 2048) zb = 2048;
     hipLaunchKernelGGL(k_prepare, dim3((unsigned)(g.T + zb)), dim3(256), 0, s, g, w, c_in, c_out, adjoint, c_out_pad, wp,
-                       wb, wq, tap_active, tap_coord, (uint4*)zero_p, n16);
+                       wb, wq, ws, tap_active, tap_coord, (uint4*)zero_p, n16);
     return hipGetLastError();
 }
 

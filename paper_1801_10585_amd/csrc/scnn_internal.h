@@ -209,6 +209,23 @@ __device__ inline bool wave_or_runs(long long word, unsigned long long& bits) {
     return lane == 0 || pw != word;
 }
 
+// Three bf16 numbers whose sum is x.  (Finite x; a magnitude that would round to infinity is cut instead, and below
+// 2^-109 the last ones run into bf16's smallest number.)
+__device__ __forceinline__ void split3(float x, unsigned short& h, unsigned short& m, unsigned short& l) {
+    auto rounded = [](float v) {
+        const unsigned u = __float_as_uint(v);
+        const unsigned r = u + 0x7fffu + ((u >> 16) & 1u);
+        return ((r & 0x7f800000u) == 0x7f800000u ? u : r) >> 16;
+    };
+    const unsigned uh = rounded(x);
+    const float r1 = x - __uint_as_float(uh << 16);
+    const unsigned um = rounded(r1);
+    const float r2 = r1 - __uint_as_float(um << 16);
+    h = (unsigned short)uh;
+    m = (unsigned short)um;
+    l = (unsigned short)rounded(r2);
+}
+
 // Exclusive scan across a 256-thread block; `total` receives the block sum.
 // Contains __syncthreads(): every thread of the block must call it.
 __device__ inline unsigned block_exclusive_scan_256(unsigned v, unsigned* s_wave /*[4], shared*/, unsigned& total) {
@@ -289,11 +306,11 @@ namespace scnn {
 hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_imm, const long long* n_dev,
                               long long n_cap, unsigned long long* occ, unsigned* occ_prefix, Counters* ctr,
                               hipStream_t s);
-// wp / wb / wq: the filter in the layout of the vector / pair-list matrix-core / quad matrix-core kernel (exactly the
-// one that will run is non-null)
+// wp / wb / wq / ws: the filter in the layout of the vector / pair-list matrix-core / quad / split quad kernel (of wb,
+// wq and ws at most the one that will run is non-null; wp is used when all three are null)
 hipError_t launch_prepare(const Geom& g, const float* w, int c_in, int c_out, int adjoint, int c_out_pad, double* wp,
-                          float* wb, float* wq, int* tap_active, int* tap_coord, void* zero_p, size_t zero_bytes,
-                          hipStream_t s);
+                          float* wb, float* wq, unsigned short* ws, int* tap_active, int* tap_coord, void* zero_p,
+                          size_t zero_bytes, hipStream_t s);
 // chunk_sums: null, or (for more than kEmitSmallWords and at most kEmitMidWords words) counters that receive the
 // candidate counts of chunks of 16 words (up to 32768 words) or 256 words (beyond), for launch_cand_emit_mid
 hipError_t launch_cand_dilate(const Geom& g, const unsigned long long* occ, const int* tap_active,
@@ -358,6 +375,18 @@ hipError_t launch_conv_quad(const Geom& g, const unsigned long long* occ, const 
                             const float* feats, int c_in, const float* wq, int c_out, const float* bias,
                             const int* tap_active, const unsigned* cand_lin, const int* cand_start,
                             const int* tile_start, Counters* ctr, float* resp, int cus, hipStream_t s);
+
+// scnn_conv_split.hip
+// bf16 values of the split kernel's filter per group of 64 output channels: [tap][32-channel chunk][part][16 output
+// channels][lane][8]; groups of at most 32 output channels use half of it
+__host__ __device__ inline size_t split_filter_elems(int taps, int c_in) { return (size_t)taps * ((c_in + 31) / 32) * (3 * 4 * 512); }
+bool conv_split_supported(const Geom& g, int c_in, int c_out, long long nnz_in);
+hipError_t launch_split_rows(const float* feats, long long n_imm, const long long* n_dev, long long n_cap, int c_in,
+                             unsigned short* xs, hipStream_t s);
+hipError_t launch_conv_split(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix, long long nnz_in,
+                             const unsigned short* xs, int c_in, const unsigned short* ws, int c_out, const float* bias,
+                             const int* tap_active, const unsigned* cand_lin, const int* cand_start,
+                             const int* tile_start, Counters* ctr, float* resp, int cus, hipStream_t s);
 
 // scnn_bwd.hip
 hipError_t launch_bwd_sites(const Geom& g, const int32_t* coords, long long rows, const int* cand_start,
