@@ -101,17 +101,22 @@ size_t sparse_conv_fwd_workspace(int ndim, const int32_t* extent, int batch, int
  * leaving the grid are dropped -- Alg. 1 steps 5-9).  Inputs, weights and
  * responses are fp32.  The vector kernels sum each response in fp64 and round
  * to fp32 once.  The matrix-core kernels first add the at most 32 products of
- * one tap and 32-channel chunk in fp32; the quad kernel then adds these partial
+ * one tap and 32-channel chunk in fp32; the quad kernels then add these partial
  * sums in fp32 where a response has at most 32 of them (filters of up to 32
- * taps on up to 32 input channels, 16 taps on 64: the r = 128 layer's 27 x 1),
- * in fp64 otherwise; the pair-list kernel always adds them in fp64.  All stay
+ * taps on up to 32 input channels: the r = 128 layer's 27 x 1), in fp64
+ * otherwise; the pair-list kernel always adds them in fp64.  The quad kernel
+ * for 16 or more input channels multiplies on the bf16 matrix cores with both
+ * operands split into three bf16 numbers whose sum they are (exactly, for
+ * magnitudes from 2^-109 up; what is smaller keeps an absolute error below
+ * 2^-134); the parts' products left out are below 2^-23 of a product together,
+ * and the result is as close to the exact sum as fp32 products'.  All stay
  * within 1e-5 relative + 1e-6 absolute of the exact sum on the workloads this
  * library is tested on.  In general the error of a matrix-core response follows
  * the magnitudes it is summed from, not its own: about 2e-8 * A, A = the sum of
  * |w * in| over its products (fp32 roundings of partial sums of that size),
  * which the stated tolerance covers while A stays below about 50 (the r = 128
  * workload: A around 20); scnn_set_conv_path(1) sums everything in fp64 for
- * data beyond that.  The vector kernels and the quad kernel add in an order
+ * data beyond that.  The vector kernels and the quad kernels add in an order
  * fixed by the data alone and are reproducible bit for bit; the pair-list
  * kernel adds its per-tap partial sums with LDS atomics in no fixed order, so a
  * run can differ from another in the last bits of the fp64 sum, which survives
@@ -278,17 +283,20 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
  *     layers whose workspace holds at least 1024 tiles of 128 candidate
  *     sites - 128 tiles when C_in is 16 or 24 and C_out at least 24 - with
  *     C_in * C_out >= 256 and C_out >= 24, or C_in * C_out >= 384)
- *     take the quad matrix-core kernel where C_in is 8, 16, 24, 32, 40, 48 or
- *     64 (or 96 or 128 with a C_out the pair-list kernel does not take), C_out
- *     at most 128, the filter has at most 32 taps and in_feats is 16-byte
- *     aligned; else the pair-list matrix-core
- *     kernel where C_in is 16 or a multiple of 32 up to 128 (any number of
- *     taps) and C_out a multiple of 16 up to 64.  Everything else takes the
+ *     take a quad matrix-core kernel where C_in is 8, 16, 24, 32, 40, 48, 64,
+ *     96 or 128, C_out at most 128, the filter has at most 32 taps and
+ *     in_feats is 16-byte aligned: the one on fp32 matrix cores for C_in = 8,
+ *     for workspaces of fewer than 192 tiles (512 with C_in 16 or 24) and for
+ *     inputs whose split copy (6 bytes per value, C_in rounded up to 32) does
+ *     not fit 2^31 bytes, else the one on split operands.  Filters of more
+ *     taps (and layers of fewer than 1024 tiles with C_in > 64 and C_out at
+ *     most 32) take the pair-list matrix-core kernel where C_in is 16 or a multiple of 32 up to
+ *     128 and C_out a multiple of 16 up to 64.  Everything else takes the
  *     vector kernels;
  * 1 = always the vector kernels;
  * 2 = a matrix-core kernel whenever one takes the shape, whatever the size:
- *     the quad kernel wherever it takes the shape (also 96 and 128 input
- *     channels, and 8, 16, 24 on small layers);
+ *     a quad kernel wherever one takes the shape (8, 16, 24 input channels on
+ *     small layers too);
  * 3 = the pair-list matrix-core kernel where it takes the shape (C_in = 16 or
  *     a multiple of 32 up to 128, C_out a multiple of 16 up to 64).
  * All compute the same sums to the same rounding rule; the switch exists so

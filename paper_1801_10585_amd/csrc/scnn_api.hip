@@ -22,17 +22,18 @@ static thread_local const char* g_last_conv_kernel = "";
 
 enum class ConvKernel { kValu, kPair, kQuad, kSplit };
 
-// Which kernel multiplies.  The quad kernel (output-stationary, registers only) takes C_in in {8, .., 64} and up to
-// 128 output channels (a launch per 64) with at most 32 taps, also C_in = 96 and 128 where the pair-list kernel does
-// not take the output width; the pair-list kernel remains for more than 32 taps and for 96 and 128 input channels.  With 8, 16 or 24 input channels the matrix cores pay only on layers of enough tiles (128 or 1024, by
-// shape) with enough output channels; narrower and smaller layers are faster on the vector kernels.
+// Which kernel multiplies.  The split kernel (bf16 matrix cores on split operands) takes 16 to 128 input channels and up
+// to 128 output channels (a launch per 64) with at most 32 taps; the quad kernel (fp32 matrix cores) eight input
+// channels, small layers, and inputs whose split copy does not fit 31-bit offsets; the pair-list kernel filters of more
+// than 32 taps.
+// With 8, 16 or 24 input channels the matrix cores pay only on layers of enough tiles (128 or 1024, by shape) with
+// enough output channels; narrower and smaller layers take the vector kernels (fp64 sums).
 static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long nnz_in, long long tiles_cap) {
     if (g_conv_path == 1) return ConvKernel::kValu;
     const bool pair_ok = conv_mfma_supported(g, c_in, c_out, nnz_in);
     if (g_conv_path == 3) return pair_ok ? ConvKernel::kPair : ConvKernel::kValu;
     const bool quad_ok = conv_quad_supported(g, c_in, c_out, nnz_in);
-    if (conv_split_supported(g, c_in, c_out, nnz_in)) return ConvKernel::kSplit;
-    if (g_conv_path == 2) return quad_ok ? ConvKernel::kQuad : (pair_ok ? ConvKernel::kPair : ConvKernel::kValu);
+    const bool split_ok = conv_split_supported(g, c_in, c_out, nnz_in);
     // 8, 16 and 24 input channels pay for the matrix-core kernels' look-ups and lists only on layers whose rows carry
     // enough multiply-adds per neighbour: C_in x C_out of at least 256 with at least 24 output channels (8->32,
     // 16->24), or of at least 384 (24->16); narrower layers (8->8, 8->16, 16->16: the first blocks of the paper's
@@ -43,12 +44,23 @@ static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long 
     const long long min_tiles = (c_in >= 16 && c_out >= 24) ? 128 : 1024;
     const bool wide = c_in >= 32 || ((c_in == 8 || c_in == 16 || c_in == 24) && tiles_cap >= min_tiles &&
                                      ((mac >= 256 && c_out >= 24) || mac >= 384));
-    // 96 and 128 input channels: three or four chunks per tap put the quad kernel's sums in fp64 registers (two waves
-    // per SIMD); where the pair-list kernel takes the shape it is 10-35 % faster there, and the quad kernel takes
-    // what it does not (output channels beyond 64 or no multiple of 16), which used to fall to the vector kernels
-    if (pair_ok && wide && c_in > 64) return ConvKernel::kPair;
-    if (quad_ok && wide) return ConvKernel::kQuad;
-    if (pair_ok && wide) return ConvKernel::kPair;
+    if (wide || g_conv_path == 2) {
+        // split against quad, index build + convolution, eight samples of 64^3 shells / four of 32^3 (us): 16->32 120 /
+        // 57 against 137 / 58, 24->64 159 / 67 against 221 / 78, 32->32 124 / 59 against 186 / 71, 32->96 255 / 102
+        // against 424 / 144, 48->64 324 / 113 against 537 / 160, 64->64 330 / 114 against 538 / 158; with eight
+        // channels three quarters of a chunk are padding: 8->64 156 against 146.  On small layers a unit of 256 sites
+        // is the whole run time and the quad kernel's pieces of sixteen sites win: workspaces of 21 to 132 tiles
+        // 32->64 57-61 against 65, 64->64 90-96 against 110, 64->32 71 against 89; of 243 tiles 32->64 76 against 67,
+        // 64->64 119 against 111; 16->32 49 against 57 at 243 tiles, 57 against 56 at 527; 24->24 55 against 56 at 243,
+        // 64 against 56 at 527.  Against the pair lists: 96->32 306 / 116 against 341 / 108, 96->64 447 / 150 against
+        // 605 / 177, 128->64 626 / 197 against 856 / 228: these keep small layers of at most 32 output channels.
+        const bool small = tiles_cap < (c_in >= 32 ? 192 : 512);
+        if (pair_ok && c_in > 64 && c_out <= 32 && tiles_cap < 1024 && g_conv_path != 2) return ConvKernel::kPair;
+        if (split_ok && !(small && quad_ok && g_conv_path != 2)) return ConvKernel::kSplit;
+        if (pair_ok && c_in > 64 && g_conv_path != 2) return ConvKernel::kPair;
+        if (quad_ok) return ConvKernel::kQuad;
+        if (pair_ok) return ConvKernel::kPair;
+    }
     return ConvKernel::kValu;
 }
 
@@ -405,12 +417,10 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
                             kernel == ConvKernel::kQuad ? ws.wq : nullptr,
                             kernel == ConvKernel::kSplit ? ws.wsplit : nullptr, ws.tap_active, ws.tap_coord, workspace,
                             ws.zero_bytes, s));
-    if (kernel == ConvKernel::kSplit)
-        SCNN_TRY(launch_split_rows(in_feats, nnz_in, (const long long*)nnz_in_dev, nnz_in, c_in, ws.xsplit, s));
     // with a device-resident count, nnz_in is only the capacity of the input arrays: rows past the true count are
     // never indexed, so no look-up can return them
     SCNN_TRY(launch_index_build(g, in_coords, nnz_in, (const long long*)nnz_in_dev, nnz_in, ws.occ, ws.occ_prefix,
-                                ws.ctr, s));
+                                ws.ctr, in_feats, c_in, kernel == ConvKernel::kSplit ? ws.xsplit : nullptr, s));
     timer.mark();
     const bool emit_mid = nw > kEmitSmallWords && nw <= kEmitMidWords;
     SCNN_TRY(launch_cand_dilate(g, ws.occ, ws.tap_active, ws.cand, ws.cand_prefix, emit_mid ? ws.block_sums : nullptr, s));
@@ -588,7 +598,8 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
     // the same launch clears the counters and the occupancy bitmap
     SCNN_TRY(launch_prepare(g, w, c_out, c_in, 1, ws.c_in_pad, ws.wp, use_mfma ? ws.wb : nullptr, nullptr,
                             nullptr, ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
-    SCNN_TRY(launch_index_build(g, g_coords, g_rows, nullptr, g_rows, ws.occ, ws.occ_prefix, ws.ctr, s));
+    SCNN_TRY(launch_index_build(g, g_coords, g_rows, nullptr, g_rows, ws.occ, ws.occ_prefix, ws.ctr, nullptr, 0,
+                                nullptr, s));
     SCNN_TRY(launch_rows_sample_bounds(g, in_coords, nnz_in, ws.cand_start, ws.tile_start, ws.ctr, s));
     SCNN_TRY(launch_bwd_sites(g, in_coords, nnz_in, ws.cand_start, ws.cand_lin, ws.rows16_start, ws.ctr, s));
     timer.mark();

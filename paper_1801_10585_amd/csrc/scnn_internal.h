@@ -305,6 +305,7 @@ namespace scnn {
 // scnn_index.hip
 hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_imm, const long long* n_dev,
                               long long n_cap, unsigned long long* occ, unsigned* occ_prefix, Counters* ctr,
+                              const float* feats, int c_in, unsigned short* xs /* nullable: also split the rows */,
                               hipStream_t s);
 // wp / wb / wq / ws: the filter in the layout of the vector / pair-list matrix-core / quad / split quad kernel (of wb,
 // wq and ws at most the one that will run is non-null; wp is used when all three are null)
@@ -381,8 +382,6 @@ hipError_t launch_conv_quad(const Geom& g, const unsigned long long* occ, const 
 // channels][lane][8]; groups of at most 32 output channels use half of it
 __host__ __device__ inline size_t split_filter_elems(int taps, int c_in) { return (size_t)taps * ((c_in + 31) / 32) * (3 * 4 * 512); }
 bool conv_split_supported(const Geom& g, int c_in, int c_out, long long nnz_in);
-hipError_t launch_split_rows(const float* feats, long long n_imm, const long long* n_dev, long long n_cap, int c_in,
-                             unsigned short* xs, hipStream_t s);
 hipError_t launch_conv_split(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix, long long nnz_in,
                              const unsigned short* xs, int c_in, const unsigned short* ws, int c_out, const float* bias,
                              const int* tap_active, const unsigned* cand_lin, const int* cand_start,

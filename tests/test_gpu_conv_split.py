@@ -1,0 +1,94 @@
+"""The split-operand convolution (fp32 operands as three bf16 numbers) at the sizes where it can go wrong: units of 256
+candidate sites with remainders, ends of samples, odd channel counts, filters other than 3x3x3, wide magnitudes, and the
+kernel that takes over where its 31-bit offsets end."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1801_10585_amd as scnn
+from tests.test_gpu_parity import check_conv_against_oracle, say
+from workloads.generators import make_filter, random_sparse_sites
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("extent,batch,c_in,c_out,ksize,density", [
+    ((1, 1, 1), 1, 32, 64, (3, 3, 3), 1.0),          # one site
+    ((3, 3, 3), 5, 32, 33, (3, 3, 3), 0.2),          # samples of less than a tile, odd number of tiles
+    ((6, 7, 6), 1, 32, 17, (3, 3, 3), 0.6),          # 252 sites: just below a unit
+    ((8, 8, 4), 1, 64, 64, (3, 3, 3), 0.9),          # exactly one unit, every tap present
+    ((7, 37, 1), 1, 32, 1, (3, 3, 3), 0.5),          # 259 sites: just above a unit
+    ((9, 9, 9), 3, 24, 65, (3, 3, 3), 0.3),          # a second group of one output channel, padded input chunk
+    ((300, 5), 2, 48, 16, (5, 5), 0.2),              # 2-D, 25 taps
+    ((40, 70), 1, 96, 48, (3, 9), 0.3),              # three chunks, 27 taps that are no 3x3x3
+    ((2, 2, 90), 1, 40, 31, (1, 1, 31), 0.2),        # one filter line over two bitmap words
+    ((13, 11, 130), 1, 128, 100, (3, 3, 3), 0.05),   # four chunks, rows longer than a bitmap word
+])
+def test_split_convolution_edges(extent, batch, c_in, c_out, ksize, density):
+    rng = np.random.default_rng(c_in * 1000 + c_out)
+    coords = random_sparse_sites(rng, extent, batch, density)
+    if coords.shape[0] == 0:
+        coords = np.zeros((1, 1 + len(extent)), dtype=np.int32)
+    feats = (1.0 - rng.random((coords.shape[0], c_in))).astype(np.float32)
+    w = make_filter(rng, ksize, c_in, c_out, 0.8, 0.2)
+    bias = rng.normal(size=c_out).astype(np.float32)
+    n = int(np.prod(extent))
+    scnn.set_conv_path(2)
+    try:
+        for rho, mode in ((1.0, scnn.ABS), (0.3, scnn.SIGNED)):
+            say(f"split {extent} B={batch} {c_in}->{c_out} {ksize} rho={rho}")
+            check_conv_against_oracle(extent, batch, coords, feats, ksize, w, bias, scnn.k_from_rho(rho, n), rho, mode,
+                                      tag=f"split {extent} {c_in}->{c_out}")
+        assert scnn.last_conv_kernel() == "k_conv_quad"
+    finally:
+        scnn.set_conv_path(0)
+
+
+@pytest.mark.parametrize("c_in,c_out", [(32, 64), (64, 32)])
+def test_split_convolution_over_wide_magnitudes(c_in, c_out):
+    """Rows and weights spread over many binades.  A response's error is bounded by its roundings: per (tap, chunk) six
+    of sums no larger than A = the sum of its products' magnitudes, and the products left out (below 2^-23 each):
+    at most (27 * 6 + 2) * 2^-24 * A, whatever the magnitudes."""
+    rng = np.random.default_rng(c_in)
+    ext, batch = (12, 12, 12), 2
+    coords = random_sparse_sites(rng, ext, batch, 0.3)
+    scale = 2.0 ** rng.integers(-40, 40, size=(coords.shape[0], 1))
+    feats = (rng.normal(size=(coords.shape[0], c_in)) * scale * 2.0 ** rng.integers(-12, 12, size=(1, c_in))).astype(np.float32)
+    w = (rng.normal(size=(27, c_in, c_out)) * 2.0 ** rng.integers(-10, 10, size=(27, c_in, c_out))).astype(np.float32)
+    d = torch.device("cuda")
+    oc, of, _ = scnn.sparse_conv_fwd(ext, batch, torch.from_numpy(coords).to(d), torch.from_numpy(feats).to(d), (3, 3, 3),
+                                     torch.from_numpy(w).to(d))
+    grid = np.full((batch, 14, 14, 14), -1)
+    grid[tuple(coords[:, 0:1].T) + tuple(coords[:, 1:].T + 1)] = np.arange(coords.shape[0])
+    oc, of = oc.cpu().numpy(), of.cpu().numpy()
+    ref, mag = np.zeros(of.shape), np.zeros(of.shape)
+    x64, w64 = np.vstack([feats, np.zeros((1, c_in))]).astype(np.float64), w.astype(np.float64)
+    for t, (i, j, k) in enumerate(np.ndindex(3, 3, 3)):
+        r = grid[oc[:, 0], oc[:, 1] + i, oc[:, 2] + j, oc[:, 3] + k]
+        ref += x64[r] @ w64[t]
+        mag += np.abs(x64[r]) @ np.abs(w64[t])
+    worst = float((np.abs(of - ref) / np.maximum(mag, 1e-300)).max())
+    say(f"split wide magnitudes {c_in}->{c_out}: worst |error| / A = {worst:.3g}")
+    assert worst <= (27 * 6 + 2) * 2.0 ** -24
+    assert oc.shape[0] > 0
+
+
+def test_inputs_beyond_the_split_kernels_offsets():
+    """A layer sized for more than 2^31 / 192 rows of 32 channels runs on the fp32 quad kernel; same responses within the
+    parity tolerance, rows past the device count never read."""
+    ext, batch, cap = (24, 24, 24), 1, (1 << 31) // 192 + 1000
+    rng = np.random.default_rng(5)
+    coords = random_sparse_sites(rng, ext, batch, 0.1)
+    feats = (1.0 - rng.random((coords.shape[0], 32))).astype(np.float32)
+    w = torch.from_numpy(make_filter(rng, (3, 3, 3), 32, 64, 1.0, 0.2)).cuda()
+    c, f = torch.from_numpy(coords).cuda(), torch.from_numpy(feats).cuda()
+    big_c = torch.zeros((cap, 4), dtype=torch.int32, device="cuda")
+    big_f = torch.zeros((cap, 32), dtype=torch.float32, device="cuda")
+    big_c[:c.shape[0]], big_f[:c.shape[0]] = c, f
+    small = scnn.sparse_conv_fwd(ext, batch, c, f, (3, 3, 3), w)
+    lay = scnn.ChainedLayer(ext, batch, cap, 32, (3, 3, 3), w)
+    oc, of, nnz = lay(big_c, big_f, torch.tensor([c.shape[0]], dtype=torch.int64, device="cuda"))
+    n = int(nnz.cpu()[0])
+    assert n == small[0].shape[0] and torch.equal(oc[:n], small[0])
+    a, b = of[:n].double(), small[1].double()
+    assert bool(((a - b).abs() <= 1e-5 * b.abs() + 1e-6).all())
