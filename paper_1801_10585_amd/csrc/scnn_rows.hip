@@ -382,8 +382,11 @@ hipError_t launch_validate(const Geom& g, const int32_t* coords, long long rows,
 }
 
 // ------------------------------------------------------------------ sparseToDense
-// dense[b][c][lin] = feats[row(b, lin)][c]; every other element 0.  The fill and the scatter are two launches on
-// the same stream.  Rows outside the grid are skipped.
+// dense[b][c][lin] = feats[row(b, lin)][c]; every other element 0.  Rows outside the grid are skipped.
+// Small outputs: a fill and a scatter.  Large ones (bound by the write of `dense`): a scatter touches nearly every
+// cache line of it a second time, four bytes at a time, so the row of every site is noted first, in the array's own
+// first plane of each sample (row + 1, 0 = no row), and every plane is then written once, in order, by the threads that
+// own its sites.  Neither form asks for sorted rows.
 __global__ __launch_bounds__(256) void k_dense_fill(float* __restrict__ dense, size_t n) {
     const size_t n4 = n / 4;  // dense is 16-byte aligned
     float4* d4 = (float4*)dense;
@@ -412,9 +415,78 @@ __global__ __launch_bounds__(256) void k_dense_scatter(Geom g, const int32_t* __
     }
 }
 
+__global__ __launch_bounds__(256) void k_dense_clear_plane(float* __restrict__ dense, long long n_sites, size_t sample) {
+    float* plane = dense + (size_t)blockIdx.y * sample;
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n_sites; i += stride) plane[i] = 0.f;
+}
+
+__global__ __launch_bounds__(256) void k_dense_note_rows(Geom g, const int32_t* __restrict__ coords, long long rows_cap,
+                                                         const long long* __restrict__ rows_dev, size_t sample,
+                                                         unsigned* __restrict__ dense) {
+    const int stride = 1 + g.ndim;
+    long long rows = rows_dev ? *rows_dev : rows_cap;
+    if (rows > rows_cap) rows = rows_cap;
+    for (long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x; r < rows; r += (long long)gridDim.x * blockDim.x) {
+        int b, c0, c1, c2;
+        load_site(g, coords + r * stride, b, c0, c1, c2);
+        if (site_in_grid(g, b, c0, c1, c2)) dense[(size_t)b * sample + (size_t)lin_of(g, c0, c1, c2)] = (unsigned)r + 1u;
+    }
+}
+
+// Thread = site; VEC = rows are 16-byte aligned and a multiple of four channels.
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_dense_expand(const float* __restrict__ feats, int channels, long long n_sites,
+                                                      size_t sample, float* dense) {
+    float* out = dense + (size_t)blockIdx.y * sample;
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n_sites; i += stride) {
+        const unsigned id = ((const unsigned*)out)[i];
+        const float* row = feats + (size_t)(id - 1u) * channels;
+        int c = 0;
+        if (VEC) {
+#pragma unroll 4
+            for (; c < channels; c += 4) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (id) v = *(const float4*)(row + c);
+                float* o = out + (size_t)c * n_sites + i;
+                o[0] = v.x;
+                o[n_sites] = v.y;
+                o[2 * n_sites] = v.z;
+                o[3 * n_sites] = v.w;
+            }
+        } else {
+#pragma unroll 4
+            for (; c < channels; ++c) out[(size_t)c * n_sites + i] = id ? row[c] : 0.f;
+        }
+    }
+}
+
+// From this size on the planes are written once.  us per call, two launches / this: 280 MB (two samples of 90^3, 48
+// channels, a ninth of the sites occupied) 157 / 96, 537 MB (128^3 x 64, a fiftieth) 213 / 122, 101 MB 35 / 24, 35 MB
+// 16.1 / 15.4, but 17 MB of eight channels 12.4 / 15.1, and with one channel, where the notes are another two passes
+// over the whole array, 17 / 36.
+constexpr size_t kDenseOncePassBytes = (size_t)32 << 20;
+constexpr int kDenseOncePassChannels = 8;
+
 hipError_t launch_to_dense(const Geom& g, const int32_t* coords, const float* feats, long long rows,
                            const long long* rows_dev, int channels, float* dense, hipStream_t s) {
-    const size_t n = (size_t)g.batch * channels * (size_t)g.N;
+    const size_t sample = (size_t)channels * (size_t)g.N, n = (size_t)g.batch * sample;
+    if (rows > 0 && n * 4 >= kDenseOncePassBytes && channels >= kDenseOncePassChannels && g.batch <= 65535) {
+        long long sb = (g.N + 255) / 256;
+        if (sb * g.batch > 16384) sb = (16384 + g.batch - 1) / g.batch;
+        long long rb = (rows + 255) / 256;
+        if (rb > 4096) rb = 4096;
+        const dim3 grid((unsigned)sb, (unsigned)g.batch);
+        hipLaunchKernelGGL(k_dense_clear_plane, grid, dim3(256), 0, s, dense, g.N, sample);
+        hipLaunchKernelGGL(k_dense_note_rows, dim3((unsigned)rb), dim3(256), 0, s, g, coords, rows, rows_dev, sample,
+                           (unsigned*)dense);
+        if (channels % 4 == 0 && ((uintptr_t)feats & 15) == 0)
+            hipLaunchKernelGGL(k_dense_expand<true>, grid, dim3(256), 0, s, feats, channels, g.N, sample, dense);
+        else
+            hipLaunchKernelGGL(k_dense_expand<false>, grid, dim3(256), 0, s, feats, channels, g.N, sample, dense);
+        return hipGetLastError();
+    }
     size_t fb = (n / 4 + 255) / 256;
     if (fb < 1) fb = 1;
     if (fb > 4096) fb = 4096;
