@@ -21,8 +21,6 @@ namespace scnn {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBwdTapChunk = 32;  // taps whose neighbour rows are staged in LDS at a time (vector kernel)
-
 // ------------------------------------------------------------------ input rows as the list of output sites
 // cand_lin[r] = site index of input row r; rows16_start[b] = 16-row groups of all earlier samples (the unit in
 // which the pair lists reserve their space).  Rows outside the grid or out of order are reported.
@@ -125,43 +123,57 @@ hipError_t launch_bwd_data_write(const Geom& g, const float* resp, const float* 
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ bp_filter, vector kernel (any shape)
-// Work item = (block of 256 consecutive filter elements in [t][ic][oc] order, share of the tiles).  A thread owns
-// one element and walks the rows of its tiles: row q contributes x[q, ic] * g[q - delta_t, oc] when the gradient
-// has a row at q - delta_t.  The neighbour rows of a tile are looked up once per tap and shared through LDS.
-// fp64 throughout; the partial sum of the share is stored (no atomics), zero included.
-__global__ __launch_bounds__(256) void k_bwd_filter_valu(Geom g, const unsigned long long* __restrict__ occ,
-                                                         const unsigned* __restrict__ occ_prefix, long long g_rows,
-                                                         const float* __restrict__ gf, int c_out,
-                                                         const float* __restrict__ x, int c_in,
-                                                         const int* __restrict__ tap_active /* adjoint tap order */,
-                                                         const unsigned* __restrict__ cand_lin,
-                                                         const int* __restrict__ cand_start,
-                                                         const int* __restrict__ tile_start,
-                                                         const Counters* __restrict__ ctr, int n_eb, int n_chunks,
-                                                         double* __restrict__ fpart) {
-    __shared__ int s_nbr[kTileRows][kBwdTapChunk + 1];
+// ------------------------------------------------------------------ bp_filter in fp64 (any shape)
+// Per tap the contraction D[ic][oc] = sum over input rows q of x[q][ic] * g[q - delta_t][oc] (0 where the gradient has no
+// row) on the fp64 matrix cores: v_mfma_f64_16x16x4_f64, the rows of a tile as K, four per instruction.  Work item =
+// (slab, share of the tiles), a slab being up to 32 taps of one 16 x 16 block of channels; wave w owns the slab's taps
+// w and w + 16.  The tile's values of x and its neighbour rows, looked up once per tile, are shared through LDS.  Inputs of the paper's own layers have a gradient
+// row behind nearly every (row, tap), so the rows are not packed.  Bound by the latency of the look-ups and of the
+// gathers (8 -> 16 channels, 47 k rows, 27 taps: 319 k instructions, 10 us of matrix time; 53 us measured, 167 with a
+// thread per filter element that read both operands of every product).  Partial sums of a share are stored (no
+// atomics), zero included.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kBwdSlabTaps = 32;                       // taps of a slab
+constexpr int kBwdWaves = 16;                          // waves of a workgroup: two taps each
+constexpr int kBwdWaveTaps = kBwdSlabTaps / kBwdWaves;
+
+__global__ __launch_bounds__(64 * kBwdWaves) void k_bwd_filter_f64(Geom g, const unsigned long long* __restrict__ occ,
+                                                        const unsigned* __restrict__ occ_prefix, long long g_rows,
+                                                        const float* __restrict__ gf, int c_out,
+                                                        const float* __restrict__ x, int c_in,
+                                                        const int* __restrict__ tap_active /* adjoint tap order */,
+                                                        const unsigned* __restrict__ cand_lin,
+                                                        const int* __restrict__ cand_start,
+                                                        const int* __restrict__ tile_start,
+                                                        const Counters* __restrict__ ctr, int n_icb, int n_ocb,
+                                                        int n_slabs, int n_chunks, double* __restrict__ fpart) {
+    constexpr int NT = 64 * kBwdWaves;
+    __shared__ int s_nbr[kTileRows][kBwdSlabTaps + 1];
     __shared__ int s_site[kTileRows][3];
+    __shared__ float s_x[kTileRows][17];
     const int n_tiles = (int)ctr->n_tiles;
-    const int cc = c_in * c_out;
-    const long long n_elem = (long long)g.T * cc;
-    const int eb = (int)(blockIdx.x % (unsigned)n_eb), chunk = (int)(blockIdx.x / (unsigned)n_eb);
-    const long long e = (long long)eb * 256 + threadIdx.x;
-    const bool valid = e < n_elem;
-    const int t_e = valid ? (int)(e / cc) : -1;
-    const int ic = valid ? (int)((e % cc) / c_out) : 0, oc = valid ? (int)(e % c_out) : 0;
-    const int t_lo = (int)(((long long)eb * 256) / cc);
-    long long e_hi = (long long)eb * 256 + 255;
-    if (e_hi > n_elem - 1) e_hi = n_elem - 1;
-    const int t_hi = (int)(e_hi / cc);
-    double acc = 0.0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = lane & 15, kq = lane >> 4;
+    const int slab = (int)(blockIdx.x % (unsigned)n_slabs), chunk = (int)(blockIdx.x / (unsigned)n_slabs);
+    const int blk = slab % (n_icb * n_ocb), t_lo = slab / (n_icb * n_ocb) * kBwdSlabTaps;
+    const int t_hi = (t_lo + kBwdSlabTaps < g.T ? t_lo + kBwdSlabTaps : g.T) - 1;
+    const int ic0 = blk / n_ocb * 16, oc0 = blk % n_ocb * 16;
+    const bool oc_ok = oc0 + m < c_out;
+    f64x4 acc[kBwdWaveTaps];
+#pragma unroll
+    for (int j = 0; j < kBwdWaveTaps; ++j) acc[j] = f64x4{0.0, 0.0, 0.0, 0.0};
 
     for (int tile = chunk; tile < n_tiles; tile += n_chunks) {
         const int b = sample_of_tile(tile_start, g.batch, tile);
         const int first = cand_start[b] + (tile - tile_start[b]) * kTileRows;
         int nrows = cand_start[b + 1] - first;
         if (nrows > kTileRows) nrows = kTileRows;
-        __syncthreads();  // readers of s_site / s_nbr of the previous tile are done
+        __syncthreads();  // readers of the previous tile are done
+#pragma unroll
+        for (int i = threadIdx.x; i < kTileRows * 16; i += NT) {
+            const int r = i >> 4, c = i & 15;
+            s_x[r][c] = r < nrows && ic0 + c < c_in ? x[(size_t)(first + r) * c_in + ic0 + c] : 0.0f;
+        }
         if (threadIdx.x < kTileRows) {
             int c0 = 0, c1 = 0, c2 = 0;
             if (threadIdx.x < nrows) site_of(g, cand_lin[first + threadIdx.x], c0, c1, c2);
@@ -169,62 +181,77 @@ __global__ __launch_bounds__(256) void k_bwd_filter_valu(Geom g, const unsigned 
             s_site[threadIdx.x][1] = c1;
             s_site[threadIdx.x][2] = c2;
         }
-        for (int tc = t_lo; tc <= t_hi; tc += kBwdTapChunk) {
-            __syncthreads();
-            // The gradient row of (row, tap t) sits at site - delta_t = site + delta of the mirrored tap T-1-t, so the
-            // look-ups run over the mirrored (adjoint) tap indices, per filter line: the taps of a line look at
-            // adjacent sites and share one pair of bitmap words.  tap_active is in adjoint order already.
-            {
-                const int t_last = (tc + kBwdTapChunk - 1) < t_hi ? (tc + kBwdTapChunk - 1) : t_hi;
-                const int a_lo = g.T - 1 - t_last, a_hi = g.T - 1 - tc;  // adjoint taps [a_lo, a_hi]
-                const int l_first = a_lo / g.K[2];
-                const int n_seg = a_hi / g.K[2] - l_first + 1;
-                for (int i = threadIdx.x; i < kTileRows * n_seg; i += 256) {
-                    const int r = i & (kTileRows - 1), l = l_first + (i >> 7);
-                    const int aa = a_lo > l * g.K[2] ? a_lo : l * g.K[2];
-                    const int ab = (a_hi + 1) < (l + 1) * g.K[2] ? (a_hi + 1) : (l + 1) * g.K[2];
-                    const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
-                    int* dst = &s_nbr[r][0];
-                    lookup_line(g, occ, occ_prefix, g_rows, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2], t0,
-                                t1, aa - l * g.K[2], ab - aa, tap_active + aa,
-                                [&](int k, int n) { dst[g.T - 1 - (aa + k) - tc] = n; });
-                }
+        __syncthreads();
+        // The gradient row of (row, tap t) sits at site - delta_t = site + delta of the mirrored tap T-1-t, so the
+        // look-ups run over the mirrored (adjoint) tap indices, per filter line: the taps of a line look at
+        // adjacent sites and share one pair of bitmap words.  tap_active is in adjoint order already.
+        {
+            const int a_lo = g.T - 1 - t_hi, a_hi = g.T - 1 - t_lo;  // adjoint taps [a_lo, a_hi]
+            const int l_first = a_lo / g.K[2];
+            const int n_seg = a_hi / g.K[2] - l_first + 1;
+            for (int i = threadIdx.x; i < kTileRows * n_seg; i += NT) {
+                const int r = i & (kTileRows - 1), l = l_first + (i >> 7);
+                const int aa = a_lo > l * g.K[2] ? a_lo : l * g.K[2];
+                const int ab = (a_hi + 1) < (l + 1) * g.K[2] ? (a_hi + 1) : (l + 1) * g.K[2];
+                const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
+                int* dst = &s_nbr[r][0];
+                lookup_line(g, occ, occ_prefix, g_rows, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2], t0,
+                            t1, aa - l * g.K[2], ab - aa, tap_active + aa,
+                            [&](int k, int n) { dst[g.T - 1 - (aa + k) - t_lo] = n; });
             }
-            __syncthreads();
-            if (valid && t_e >= tc && t_e < tc + kBwdTapChunk) {
-                const int tt = t_e - tc;
-                // eight rows at a time, their loads independent of one another; the sum keeps the row order
-                for (int r0 = 0; r0 < nrows; r0 += 8) {
-                    float xv[8], gv[8];
-                    bool on[8];
+        }
+        __syncthreads();
+        if (t_lo + wave > t_hi) continue;
+        float a[kTileRows / 4];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int r = r0 + u;
-                        const int n = r < nrows ? s_nbr[r][tt] : -1;
-                        on[u] = n >= 0;
-                        xv[u] = x[(size_t)(first + (r < nrows ? r : 0)) * c_in + ic];
-                        gv[u] = on[u] ? gf[(size_t)n * c_out + oc] : 0.0f;  // (no gradient row: nothing is read)
-                    }
+        for (int s = 0; s < kTileRows / 4; ++s) a[s] = s_x[4 * s + kq][m];
+        const float* gcol = gf + oc0 + m;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (on[u]) acc = fma((double)xv[u], (double)gv[u], acc);
+        for (int j = 0; j < kBwdWaveTaps; ++j) {
+            const int tt = wave + kBwdWaves * j;
+            if (t_lo + tt > t_hi) continue;
+#pragma unroll
+            for (int s0 = 0; s0 < kTileRows / 4; s0 += 16) {
+                if (4 * s0 >= nrows) continue;
+                float gv[16];
+#pragma unroll
+                for (int s = 0; s < 16; ++s) {
+                    const int n = s_nbr[4 * (s0 + s) + kq][tt];
+                    gv[s] = n >= 0 && oc_ok ? gcol[(size_t)n * c_out] : 0.0f;  // (no gradient row: nothing is read)
                 }
+#pragma unroll
+                for (int s = 0; s < 16; ++s)
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s0 + s], (double)gv[s], acc[j], 0, 0, 0);
             }
         }
     }
-    if (valid) fpart[(size_t)chunk * n_elem + e] = acc;
+    // element v of a lane: input channel 4 v + kq, output channel m of the block
+    double* out = fpart + (size_t)chunk * g.T * c_in * c_out;
+#pragma unroll
+    for (int j = 0; j < kBwdWaveTaps; ++j) {
+        const int t = t_lo + wave + kBwdWaves * j;
+        if (t > t_hi) continue;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int ic = ic0 + 4 * v + kq;
+            if (ic < c_in && oc_ok) out[((size_t)t * c_in + ic) * c_out + oc0 + m] = acc[j][v];
+        }
+    }
 }
 
-hipError_t launch_bwd_filter_valu(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix,
-                                  long long g_rows, const float* gf, int c_out, const float* x, int c_in,
-                                  const int* tap_active, const unsigned* cand_lin, const int* cand_start,
-                                  const int* tile_start, const Counters* ctr, int n_chunks, double* fpart,
-                                  hipStream_t s) {
-    const long long n_elem = (long long)g.T * c_in * c_out;
-    const int n_eb = (int)((n_elem + 255) / 256);
-    hipLaunchKernelGGL(k_bwd_filter_valu, dim3((unsigned)((long long)n_eb * n_chunks)), dim3(256), 0, s, g, occ,
-                       occ_prefix, g_rows, gf, c_out, x, c_in, tap_active, cand_lin, cand_start, tile_start, ctr,
-                       n_eb, n_chunks, fpart);
+static long long bwd_f64_slabs(const Geom& g, int c_in, int c_out) {
+    return (long long)((g.T + kBwdSlabTaps - 1) / kBwdSlabTaps) * ((c_in + 15) / 16) * ((c_out + 15) / 16);
+}
+
+hipError_t launch_bwd_filter_f64(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix,
+                                 long long g_rows, const float* gf, int c_out, const float* x, int c_in,
+                                 const int* tap_active, const unsigned* cand_lin, const int* cand_start,
+                                 const int* tile_start, const Counters* ctr, int n_chunks, double* fpart,
+                                 hipStream_t s) {
+    const long long n_slabs = bwd_f64_slabs(g, c_in, c_out);
+    hipLaunchKernelGGL(k_bwd_filter_f64, dim3((unsigned)(n_slabs * n_chunks)), dim3(64 * kBwdWaves), 0, s, g, occ, occ_prefix,
+                       g_rows, gf, c_out, x, c_in, tap_active, cand_lin, cand_start, tile_start, ctr, (c_in + 15) / 16,
+                       (c_out + 15) / 16, (int)n_slabs, n_chunks, fpart);
     return hipGetLastError();
 }
 
@@ -435,9 +462,9 @@ int bwd_filter_chunks(const Geom& g, int c_in, int c_out, long long tiles_cap, b
         if (chunks < kXcds) chunks = kXcds;
         if (chunks > 256) chunks = 256;
     } else {
-        const long long n_eb = ((long long)g.T * c_in * c_out + 255) / 256;
-        chunks = (4096 + n_eb - 1) / n_eb;
-        if (chunks > 512) chunks = 512;
+        // two workgroups per CU; every share's partial filter is stored and added up again
+        const long long slabs = bwd_f64_slabs(g, c_in, c_out);
+        chunks = (2 * device_cu_count() + slabs - 1) / slabs;
     }
     if (chunks > tiles_cap) chunks = tiles_cap;
     if (chunks < 1) chunks = 1;
@@ -464,29 +491,36 @@ hipError_t launch_bwd_filter_mfma(const Geom& g, const float* x, int c_in, const
 
 // ------------------------------------------------------------------ bp_filter: add the partials, mask, round
 // Eq. 3, second line: a weight that is exactly zero (pruned) receives no gradient.
-__global__ __launch_bounds__(256) void k_bwd_filter_finish(const double* __restrict__ fpart, int n_chunks,
-                                                           long long n_elem, const float* __restrict__ w,
-                                                           float* __restrict__ bp_filter) {
-    // 64 elements per workgroup; four threads per element each add a quarter of the partials (ascending), then
-    // the quarters are added in ascending order: the order of the additions never depends on timing
-    __shared__ double s_q[4][64];
+// Also writes the call's status words: {input rows, gradient rows, flags, 0}.
+constexpr int kFinishParts = 16;
+__global__ __launch_bounds__(64 * kFinishParts) void k_bwd_filter_finish(const double* __restrict__ fpart, int n_chunks,
+                                                                         long long n_elem, const float* __restrict__ w,
+                                                                         float* __restrict__ bp_filter,
+                                                                         const Counters* __restrict__ ctr,
+                                                                         long long nnz_in, long long g_rows,
+                                                                         long long* __restrict__ info) {
+    // 64 elements per workgroup; sixteen threads per element each add a sixteenth of the partials (ascending, eight
+    // loads in flight), then those sums are added in ascending order: the order of the additions never depends on
+    // timing.  (Four threads with one load in flight each took 20.6 us for
+    // 293 shares of 3456 elements; this takes 6.2 for 372.)
+    __shared__ double s_q[kFinishParts][64];
     const int el = threadIdx.x & 63, q = threadIdx.x >> 6;
     const long long e = (long long)blockIdx.x * 64 + el;
     double sum = 0.0;
     const bool live = e < n_elem && w[e] != 0.0f;
     if (live) {
-        const int c0 = (int)((long long)q * n_chunks / 4), c1 = (int)((long long)(q + 1) * n_chunks / 4);
+        const int c0 = (int)((long long)q * n_chunks / kFinishParts), c1 = (int)((long long)(q + 1) * n_chunks / kFinishParts);
+#pragma unroll 8
         for (int c = c0; c < c1; ++c) sum += fpart[(size_t)c * n_elem + e];
     }
     s_q[q][el] = sum;
     __syncthreads();
-    if (q == 0 && e < n_elem) bp_filter[e] = (float)(((s_q[0][el] + s_q[1][el]) + s_q[2][el]) + s_q[3][el]);
-}
-
-// also the place where the call's status words are written: {input rows, gradient rows, flags, 0}
-__global__ void k_bwd_status(const Counters* __restrict__ ctr, long long nnz_in, long long g_rows,
-                             long long* __restrict__ info) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+    if (q == 0 && e < n_elem) {
+#pragma unroll
+        for (int i = 1; i < kFinishParts; ++i) sum += s_q[i][el];
+        bp_filter[e] = (float)sum;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         info[0] = nnz_in;
         info[1] = g_rows;
         info[2] = (long long)ctr->flags;
@@ -497,9 +531,8 @@ __global__ void k_bwd_status(const Counters* __restrict__ ctr, long long nnz_in,
 hipError_t launch_bwd_filter_finish(const double* fpart, int n_chunks, long long n_elem, const float* w,
                                     float* bp_filter, const Counters* ctr, long long nnz_in, long long g_rows,
                                     long long* info, hipStream_t s) {
-    hipLaunchKernelGGL(k_bwd_filter_finish, dim3((unsigned)((n_elem + 63) / 64)), dim3(256), 0, s, fpart, n_chunks,
-                       n_elem, w, bp_filter);
-    hipLaunchKernelGGL(k_bwd_status, dim3(1), dim3(64), 0, s, ctr, nnz_in, g_rows, info);
+    hipLaunchKernelGGL(k_bwd_filter_finish, dim3((unsigned)((n_elem + 63) / 64)), dim3(64 * kFinishParts), 0, s, fpart,
+                       n_chunks, n_elem, w, bp_filter, ctr, nnz_in, g_rows, info);
     return hipGetLastError();
 }
 

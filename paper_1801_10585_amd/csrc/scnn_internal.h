@@ -395,7 +395,7 @@ hipError_t launch_bwd_data_write(const Geom& g, const float* resp, const float* 
                                  hipStream_t s);
 bool bwd_filter_mfma_supported(int c_in, int c_out, long long g_rows);
 int bwd_filter_chunks(const Geom& g, int c_in, int c_out, long long tiles_cap, bool mfma);
-hipError_t launch_bwd_filter_valu(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix,
+hipError_t launch_bwd_filter_f64(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix,
                                   long long g_rows, const float* gf, int c_out, const float* x, int c_in,
                                   const int* tap_active, const unsigned* cand_lin, const int* cand_start,
                                   const int* tile_start, const Counters* ctr, int n_chunks, double* fpart,
