@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
     const int* __restrict__ cand_start, const int* __restrict__ tile_start, Counters* __restrict__ ctr,
     float* __restrict__ resp) {
     constexpr int NS = 4;                                // groups per wave: wave, wave + 4, ..
-    constexpr unsigned ROWB = NCH * 192;                 // bytes of a split row
+    constexpr unsigned ROWB = 192;                       // bytes of a row's chunk, split
     typedef typename std::conditional<ACC64 != 0, double, float>::type acc_t;
     extern __shared__ __align__(16) unsigned smem_u[];
     const int T = K3 ? 27 : g.T, K0 = K3 ? 3 : g.K[0], K1 = K3 ? 3 : g.K[1], K2 = K3 ? 3 : g.K[2];
@@ -74,7 +74,8 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
     unsigned* s_step = s_pass + (T * NCH + 1);                       // [steps + 3] (tap * 256 + group * 16) * 4 | chunk << 20
 
     const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc((void*)xs, 0, (int)(nnz_in * (long long)ROWB), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc((void*)xs, 0, (int)(nnz_in * (long long)(NCH * ROWB)), 0x00020000);
+    const unsigned plane = (unsigned)nnz_in * ROWB;      // of one chunk
     const unsigned act_mask = (unsigned)__ballot(lane < T && tap_active[lane < T ? lane : 0] != 0);
 
     // order of the units: as in k_conv_quad (workgroup i runs on XCD i % kXcds; an XCD owns chunks of consecutive units)
@@ -220,16 +221,18 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
         const int n_pass = NCH * (int)__popc(has);
         const int n_step = NCH * (int)__builtin_amdgcn_readlane((unsigned)incl, 31);
         if (lane < T && ((has >> lane) & 1u)) {
-            const int p0 = NCH * (int)__popc(has & ((1u << lane) - 1u)), e0 = NCH * (incl - cnt);
+            // (all taps of a chunk, then the next chunk: taps next to each other read nearly the same rows, and half of
+            // a row's bytes at a time stay in the cache until then)
+            const int p0 = (int)__popc(has & ((1u << lane) - 1u)), e0 = incl - cnt;
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) s_pass[p0 + c] = (unsigned)lane | (unsigned)c << 8 | sets << 16;
+            for (int c = 0; c < NCH; ++c) s_pass[c * (n_pass / NCH) + p0] = (unsigned)lane | (unsigned)c << 8 | sets << 16;
             int at = 0;
 #pragma unroll
             for (int s = 0; s < NS; ++s)
                 if (sets & (1u << s)) {
 #pragma unroll
                     for (int c = 0; c < NCH; ++c)
-                        s_step[e0 + c * cnt + at] = (unsigned)((lane * kSplitSites + (s * 4 + wave) * 16) * 4) | (unsigned)c << 20;
+                        s_step[c * (n_step / NCH) + e0 + at] = (unsigned)((lane * kSplitSites + (s * 4 + wave) * 16) * 4) | (unsigned)c << 20;
                     ++at;
                 }
         }
@@ -258,10 +261,10 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
                 return *(const __attribute__((address_space(3))) unsigned*)(size_t)(tab_lane + (e & 0xffffu));
             };
             auto load_a = [&](unsigned o, unsigned e) {
-                const unsigned vo = o + (kg_off + (NCH > 1 ? ((e >> 20) & 7u) * 192u : 0u));
-                a_next[0] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo, 0, 0);
-                a_next[1] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo + 64u, 0, 0);
-                a_next[2] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo + 128u, 0, 0);
+                const unsigned vo = o + kg_off, so = NCH > 1 ? ((e >> 20) & 7u) * plane : 0u;
+                a_next[0] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo, so, 0);
+                a_next[1] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo + 64u, so, 0);
+                a_next[2] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo + 128u, so, 0);
             };
             auto fetch_b = [&](unsigned info) {
                 const u32x4* q = ws + (size_t)((info & 0xffu) * NCH + ((info >> 8) & 0xffu)) * (3 * NB * 64);

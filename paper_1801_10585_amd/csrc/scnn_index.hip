@@ -186,11 +186,12 @@ hipError_t launch_exclusive_scan(unsigned* vals, long long capacity, long long n
 }
 
 // ------------------------------------------------------------------ index build
-// Input rows as the split convolution reads them: [row][32-channel chunk][h | m | l][32] bf16 (192 bytes per row and
-// chunk), so that a lane's eight channels of a part are one 16-byte load.  Done by extra workgroups of the index build
+// Input rows as the split convolution reads them: [32-channel chunk][row][h | m | l][32] bf16, so that a lane's eight
+// channels of a part are one 16-byte load, and rows are 192 bytes apart whatever the channel count (sixteen rows to
+// sixteen lanes take 33 clocks of a load then, 58 where the distance is a multiple of 128).  Done by extra workgroups of the index build
 // (as a launch of its own 5 us more); bound by memory: 4 bytes read and 6 written per value, 226 k rows of 32 channels
 // in 18 us (4 TB/s).
-__device__ inline void split_rows(const float* __restrict__ feats, long long n, int c_in,
+__device__ inline void split_rows(const float* __restrict__ feats, long long n, long long n_cap, int c_in,
                                   unsigned short* __restrict__ xs, int block, int n_blocks) {
     const int nch = (c_in + 31) / 32, per_row = nch * 4;  // pieces of eight channels
     const long long total = n * per_row;
@@ -208,7 +209,7 @@ __device__ inline void split_rows(const float* __restrict__ feats, long long n, 
         unsigned short part[3][8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) split3(v[e], part[0][e], part[1][e], part[2][e]);
-        uint4* dst = (uint4*)(xs + (row * nch + chunk) * 96 + piece * 8);
+        uint4* dst = (uint4*)(xs + (chunk * n_cap + row) * 96 + piece * 8);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
             dst[k * 4] = make_uint4(part[k][0] | (unsigned)part[k][1] << 16, part[k][2] | (unsigned)part[k][3] << 16,
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(256) void k_index_build(Geom g, const int32_t* __re
     if (n > n_cap) n = n_cap;  // a device-resident count never reaches past the arrays
     if (n < 0) n = 0;
     if ((int)blockIdx.x >= index_blocks) {
-        split_rows(feats, n, c_in, xs, (int)blockIdx.x - index_blocks, (int)gridDim.x - index_blocks);
+        split_rows(feats, n, n_cap, c_in, xs, (int)blockIdx.x - index_blocks, (int)gridDim.x - index_blocks);
         return;
     }
     const int stride = 1 + g.ndim;
