@@ -250,10 +250,9 @@ struct ConvWs {
     unsigned long long side_cap;
     unsigned* pairs;
     unsigned short* block_tap;
-    float* wb;
     float* wq;
-    unsigned short* wsplit;  // filter and input rows of the split kernel
-    unsigned short* xsplit;
+    unsigned short* wsplit;  // filter of the split and pair-list kernels
+    unsigned short* xsplit;  // input rows of the split kernel
     uint2* tile_hdr;
     long long block_cap;
     ConvKernel kernel;
@@ -315,11 +314,10 @@ static void carve_conv(void* base, const Geom& g, const Geom& gp, long long nnz_
     w->block_cap = w->kernel == ConvKernel::kPair ? (long long)g.T * (cand_cap / 16 + w->tiles_cap) : 0;
     w->pairs = c.take<unsigned>((size_t)w->block_cap * 16);
     w->block_tap = c.take<unsigned short>((size_t)w->block_cap);
-    w->wb = c.take<float>(w->block_cap ? (size_t)g.T * round_up(c_in, 32) * c_out : 0);
     w->tile_hdr = c.take<uint2>(w->block_cap ? w->tiles_cap : 0);
     w->wq = c.take<float>(w->kernel == ConvKernel::kQuad ? quad_groups(c_out) * quad_filter_floats(g.T, c_in) : 0);
     const bool split = w->kernel == ConvKernel::kSplit;
-    w->wsplit = c.take<unsigned short>(split ? quad_groups(c_out) * split_filter_elems(g.T, c_in) : 0);
+    w->wsplit = c.take<unsigned short>(split || w->block_cap ? quad_groups(c_out) * split_filter_elems(g.T, c_in) : 0);
     w->xsplit = c.take<unsigned short>(split ? (size_t)nnz_in * round_up(c_in, 32) * 3 : 0);
     w->tmp_coords = c.take<int32_t>(pool ? (size_t)cand_cap * (1 + g.ndim) : 0);
     w->tmp_feats = c.take<float>(pool ? (size_t)cand_cap * c_out : 0);
@@ -413,10 +411,10 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
     timer.mark();
     // the matrix-core kernels load input rows 16 bytes at a time
     const ConvKernel kernel = ((uintptr_t)in_feats & 15) == 0 ? ws.kernel : ConvKernel::kValu;
-    SCNN_TRY(launch_prepare(g, w, c_in, c_out, 0, ws.c_out_pad, ws.wp, kernel == ConvKernel::kPair ? ws.wb : nullptr,
+    SCNN_TRY(launch_prepare(g, w, c_in, c_out, 0, ws.c_out_pad, ws.wp, nullptr,
                             kernel == ConvKernel::kQuad ? ws.wq : nullptr,
-                            kernel == ConvKernel::kSplit ? ws.wsplit : nullptr, ws.tap_active, ws.tap_coord, workspace,
-                            ws.zero_bytes, s));
+                            kernel == ConvKernel::kSplit || kernel == ConvKernel::kPair ? ws.wsplit : nullptr,
+                            ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
     // with a device-resident count, nnz_in is only the capacity of the input arrays: rows past the true count are
     // never indexed, so no look-up can return them
     SCNN_TRY(launch_index_build(g, in_coords, nnz_in, (const long long*)nnz_in_dev, nnz_in, ws.occ, ws.occ_prefix,
@@ -453,8 +451,8 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
                                    ws.cand_start, ws.tile_start, ws.rows16_start, ws.ctr, ws.pairs, ws.block_tap,
                                    ws.tile_hdr, ws.block_cap, ws.tiles_cap, nullptr, s));
         timer.mark();
-        SCNN_TRY(launch_conv_mfma(g, nnz_in, in_feats, c_in, ws.wb, c_out, bias, ws.pairs, ws.block_tap, ws.tile_hdr,
-                                  ws.ctr, ws.resp, s));
+        SCNN_TRY(launch_conv_mfma_split(g, nnz_in, in_feats, c_in, ws.wsplit, c_out, bias, ws.pairs, ws.block_tap,
+                                        ws.tile_hdr, ws.ctr, ws.resp, s));
         g_last_conv_kernel = "k_conv_mfma";
     } else {
         timer.mark();

@@ -869,6 +869,7 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
 // through the LDS atomic, so the order of the fp64 additions is not fixed.
 // ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr unsigned kPadPair = (unsigned)kTileRows << kPairRowShift;  // list padding: dummy accumulator row, input row 0
 constexpr int kStageBlocks = 208;                 // 16-pair blocks staged in LDS at a time by the contraction
@@ -1308,6 +1309,345 @@ static hipError_t launch_conv_mfma_t(int taps, long long nnz_in, const float* fe
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// The same contraction on the bf16 matrix cores, both operands as three bf16 numbers each (split3; the rows split after
+// the load, the filter beforehand): the forward pass's pair-list kernel.  A block's 32 channels take 384 clocks of
+// matrix time per 64 output channels instead of 1024, the sums of two chunks are added in fp32 before they go to the
+// fp64 accumulators (half the LDS atomics), and the weights of one chunk at a time are held in registers.  256^3, 64->64
+// channels, 125 taps, 1.3 M candidates: 3.68 -> 1.95 ms, now bound by the weights and rows that vector memory returns (a
+// round's chunk asks for 12 + 4 KB for at most two blocks); error against 64 bits 1.04e-7 -> 6.3e-8 of the result's norm.
+// The backward pass keeps the fp32 kernel above: its gradient rows are mostly zeros, a chain over them rounds less often
+// than 32 channels at once do, and the split form was 1.4 times further off there (5.4e-8 -> 7.6e-8; it took 271 us
+// instead of 335).
+// HALF: C_in = 16 (KC = 1): the upper sixteen channels of the chunk are zero in the filter.
+// Operands of one 32-channel chunk of a round (up to RB consecutive 16-pair blocks of ONE tap), fetched one chunk ahead
+// of their use.
+template <int NB, int RB>
+struct ChunkRegs {
+    u32x4 a[RB][2];   // input rows in fp32: lane holds x[in(pair 16j + jj)][32 kc + 8 gq .. + 8), its 16-byte halves in
+                      // the order (jj odd: upper first)
+    u32x4 b[3][NB];   // filter in bf16 thirds (split3): lane holds w[tap][32 kc + 8 gq + i][16 cb + jj], i = 0..7
+};
+
+template <int KC /* C_in / 32 */, int NB /* C_out / 16 */, int HALF = 0>
+__global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma_split(int taps, long long nnz_in,
+                                                               const float* __restrict__ feats,
+                                                               const u32x4* __restrict__ ws,
+                                                               const float* __restrict__ bias,
+                                                               const unsigned* __restrict__ pairs,
+                                                               const unsigned short* __restrict__ block_tap,
+                                                               const uint2* __restrict__ tile_hdr,
+                                                               Counters* __restrict__ ctr,
+                                                               float* __restrict__ resp) {
+    static_assert(!HALF || KC == 1, "the half chunk stands alone");
+    constexpr int C_IN = HALF ? 16 : KC * 32, C_OUT = NB * 16, CS = C_OUT + 1 /* padded accumulator row */;
+    constexpr int RB = NB <= 2 ? 3 : 2;  // blocks per round
+    constexpr int NBP = NB > 2 ? 4 : 2;  // blocks of output channels in the filter's layout
+    constexpr int NT = kConvWaves * 64;
+    static_assert(kStageBlocks % 4 == 0 && kStageBlocks <= 256, "stage size");
+    extern __shared__ __align__(16) unsigned char smem[];
+    double* s_c = (double*)smem;                                               // [129][CS]; row 128 absorbs padding
+    unsigned* s_flat = (unsigned*)(s_c + (kTileRows + 1) * CS);                // [kStageBlocks][16] packed pairs
+    unsigned short* s_btap = (unsigned short*)(s_flat + kStageBlocks * 16);    // [kStageBlocks]
+    unsigned* s_rmeta = (unsigned*)(s_btap + kStageBlocks);  // [kStageBlocks] first block | blocks << 8 | tap << 16
+    int* s_wlo = (int*)(s_rmeta + kStageBlocks);  // [kConvWaves + 1] first round of each wave; the last = all rounds
+    int* s_next = s_wlo + kConvWaves + 1;         // [2] the workgroup's next tile (alternating slots)
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int jj = lane & 15, gq = lane >> 4;
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    const int n_tiles = (int)ctr->n_tiles;
+    // LDS byte address of this lane's channel in accumulator row 0 (a generic pointer to LDS carries the LDS
+    // address in its low 32 bits); accumulator addresses are formed once per block, at load time
+    const unsigned lane_off = (unsigned)(size_t)s_c + (unsigned)jj * (unsigned)sizeof(double);
+
+    // XCD-aware tile order: workgroup i runs on XCD i % kXcds; give each XCD one contiguous span of tiles so that
+    // the input rows shared by neighbouring tiles stay in that XCD's L2.  Within its span a workgroup starts with
+    // the tile of its slot and then draws tiles, in ascending order, from the span's counter (then from the other
+    // spans' counters): tiles differ in work, and a fixed assignment would leave workgroups idle at the end.
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, per_xcd = gridDim.x / kXcds;
+    const int span = (n_tiles + kXcds - 1) / kXcds;
+    const int tile_end = (xcd + 1) * span < n_tiles ? (xcd + 1) * span : n_tiles;
+
+    for (int i = threadIdx.x; i < kTileRows * CS; i += NT) s_c[i] = 0.0;  // the dummy row needs no reset
+    // The stage buffer only ever holds entries written by the pair builder (or these zeros), so whatever a clamped
+    // read past the end of a tile's list finds there names a valid input row.
+    for (int i = threadIdx.x; i < kStageBlocks * 16; i += NT) s_flat[i] = 0u;
+
+    int parity = 0;
+    for (int tile = xcd * span + slot < tile_end ? xcd * span + slot : -1; tile >= 0; parity ^= 1) {
+        const uint2 hdr = tile_hdr[tile];
+        for (unsigned s0 = 0; s0 < hdr.y; s0 += kStageBlocks) {
+            const int n_blocks = (int)((hdr.y - s0) < (unsigned)kStageBlocks ? (hdr.y - s0) : (unsigned)kStageBlocks);
+            __syncthreads();  // previous stage consumed (and, for the first stage, the accumulators are zero)
+            {   // ---- stage this tile's next blocks: a contiguous copy, 16 bytes per thread and step
+                const uint4* src = (const uint4*)(pairs + (size_t)(hdr.x + s0) * 16);
+                uint4* dst = (uint4*)s_flat;
+                for (int i = threadIdx.x; i < n_blocks * 4; i += NT) dst[i] = src[i];
+                for (int i = threadIdx.x; i < n_blocks; i += NT) s_btap[i] = block_tap[hdr.x + s0 + i];
+            }
+            __syncthreads();
+            // ---- round list: a round = up to RB consecutive blocks of one tap.  It starts at every RB-th block of
+            //      a tap's run (and at the start of the stage); entry = first block | blocks << 8 | tap << 16.
+            //      Wave w takes the rounds that start in the w-th quarter of the stage's blocks: contiguous, and
+            //      within one round of an even share of the blocks.
+            if (wave == 0) {
+                int base = 0;
+                int lo[kConvWaves];
+#pragma unroll
+                for (int w = 0; w < kConvWaves; ++w) lo[w] = 0;
+                for (int i0 = 0; i0 < n_blocks; i0 += 64) {
+                    const int i = i0 + lane;
+                    unsigned bt[RB];
+#pragma unroll
+                    for (int d = 0; d < RB; ++d) bt[d] = s_btap[(i + d) < n_blocks ? (i + d) : n_blocks - 1];
+                    const bool start = i < n_blocks && (i == 0 || ((bt[0] >> 8) % RB) == 0);
+                    int nb = 1;
+#pragma unroll
+                    for (int d = 1; d < RB; ++d)
+                        if (nb == d && i + d < n_blocks && ((bt[d] >> 8) % RB) != 0) nb = d + 1;
+                    const unsigned long long m = __ballot(start);
+                    if (start)
+                        s_rmeta[base + __popcll(m & lt_mask)] = (unsigned)i | (unsigned)nb << 8 | (bt[0] & 0xffu) << 16;
+                    base += __popcll(m);
+#pragma unroll
+                    for (int w = 1; w < kConvWaves; ++w)  // rounds that start before the w-th share of the blocks
+                        lo[w] += __popcll(__ballot(start && i * kConvWaves < w * n_blocks));
+                }
+                if (lane == 0) {
+#pragma unroll
+                    for (int w = 0; w < kConvWaves; ++w) s_wlo[w] = lo[w];
+                    s_wlo[kConvWaves] = base;
+                }
+            }
+            __syncthreads();
+            const int r_lo = __builtin_amdgcn_readfirstlane(s_wlo[wave]);
+            const int my_rounds = __builtin_amdgcn_readfirstlane(s_wlo[wave + 1]) - r_lo;
+            if (my_rounds > 0) {
+                // The wave's pipeline, per round: list entry (LDS) -> pair entries of its blocks (LDS) -> operands
+                // (global, one 32-channel chunk at a time) -> compute.  Each step is issued a round (operands: a
+                // chunk) before its result is needed, so that no LDS or memory round trip sits between two chunks'
+                // matrix instructions.  All reads are unconditional: a round past the end repeats the wave's last
+                // one (never computed), a block past a round's end repeats list entries and is never computed.
+                struct Entries {
+                    unsigned in[RB];  // pair jj of each block (its input row)
+                    uint4 out[RB];    // pairs 4*gq .. 4*gq + 3 of each block (their result rows)
+                };
+                auto meta_at = [&](int j) { return s_rmeta[r_lo + (j < my_rounds ? j : my_rounds - 1)]; };
+                auto read_entries = [&](unsigned meta, Entries& E) {
+                    const int first = (int)(meta & 0xffu);
+#pragma unroll
+                    for (int k = 0; k < RB; ++k) {
+                        const int blk = (first + k) < kStageBlocks ? (first + k) : kStageBlocks - 1;
+                        E.in[k] = s_flat[16 * blk + jj];
+                        E.out[k] = *(const uint4*)(s_flat + 16 * blk + 4 * gq);
+                    }
+                };
+                // Rows are a multiple of 64 bytes apart, mostly of 256: sixteen lanes that read the same 16 bytes of
+                // sixteen such rows take 58 clocks a load; with every other row's halves swapped, 35.
+                const unsigned half0 = (unsigned)(jj & 1) * 16u;
+                auto load_chunk = [&](unsigned meta, const unsigned (&in)[RB], int kc, ChunkRegs<NB, RB>& R) {
+                    int tt = (int)((meta >> 16) & 0xffu);
+                    tt = tt < taps ? tt : taps - 1;
+                    const u32x4* wt = ws + (size_t)(tt * KC + kc) * (3 * NBP * 64);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+#pragma unroll
+                        for (int cb = 0; cb < NB; ++cb) R.b[q][cb] = (wt + (q * NBP + cb) * 64)[lane];
+#pragma unroll
+                    for (int k = 0; k < RB; ++k) {
+                        // (C_in = 16: the lanes of the absent channels read the others' again)
+                        const char* src = (const char*)feats + (size_t)in[k] * (C_IN * 4) + (HALF ? gq & 1 : kc * 4 + gq) * 32;
+                        R.a[k][0] = *(const u32x4*)(src + half0);
+                        R.a[k][1] = *(const u32x4*)(src + (16u - half0));
+                    }
+                };
+                // A block = NB chains of six bf16 products per 32 input channels, smallest products first (split3); the
+                // sums of two chunks are added in fp32, and these 16 x 16 results (rows = pairs 4*gq + v, column =
+                // channel 16*cb + jj) to the fp64 accumulators (half the LDS atomics of one addition per chunk; four
+                // chunks in one fp32 chain left the parity tolerance).  Padding pairs land in the dummy row.  Blocks
+                // are guarded one by one (uniform branches).
+                f32x4 acc[RB][NB];
+                auto compute_chunk = [&](unsigned meta, const ChunkRegs<NB, RB>& R, bool first) {
+                    const int nb = (int)((meta >> 8) & 0xffu);  // 1 .. RB
+                    constexpr int PX[6] = {2, 0, 1, 1, 0, 0}, PW[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                    for (int k = 0; k < RB; ++k) {
+                        if (k == 0 || k < nb) {  // (a round has at least one block)
+                            u32x4 x[2], part[3];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                x[0][e] = half0 ? R.a[k][1][e] : R.a[k][0][e];
+                                x[1][e] = half0 ? R.a[k][0][e] : R.a[k][1][e];
+                            }
+                            split8(x, part);
+                            if (HALF) {  // absent channels: 0 against 0, also where a row holds infinities
+#pragma unroll
+                                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) part[q][e] = gq < 2 ? part[q][e] : 0u;
+                            }
+                            f32x4 d[NB];
+#pragma unroll
+                            for (int cb = 0; cb < NB; ++cb) d[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                                for (int cb = 0; cb < NB; ++cb)
+                                    d[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                        __builtin_bit_cast(bf16x8, part[PX[q]]), __builtin_bit_cast(bf16x8, R.b[PW[q]][cb]),
+                                        d[cb], 0, 0, 0);
+#pragma unroll
+                            for (int cb = 0; cb < NB; ++cb)
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) acc[k][cb][v] = first ? d[cb][v] : acc[k][cb][v] + d[cb][v];
+                        }
+                    }
+                };
+                auto add_round = [&](unsigned meta, const Entries& E) {
+                    const int nb = (int)((meta >> 8) & 0xffu);
+#pragma unroll
+                    for (int k = 0; k < RB; ++k) {
+                        if (k == 0 || k < nb) {
+                            const unsigned o[4] = {E.out[k].x, E.out[k].y, E.out[k].z, E.out[k].w};
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const unsigned at = (o[v] >> kPairRowShift) * (unsigned)(CS * sizeof(double)) + lane_off;
+#pragma unroll
+                                for (int cb = 0; cb < NB; ++cb)
+                                    __hip_atomic_fetch_add((__attribute__((address_space(3))) double*)(size_t)at + cb * 16,
+                                                           (double)acc[k][cb][v], __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                            }
+                        }
+                    }
+                };
+                auto rows_of = [&](const Entries& E, unsigned (&in)[RB]) {
+                    // (a stale entry past the end of the list may name any row, but such a block is not computed)
+#pragma unroll
+                    for (int k = 0; k < RB; ++k) {
+                        in[k] = E.in[k] & kPairInMask;
+                        // opaque: seen through, the compiler takes the product with the row size for a 24-bit one, drops
+                        // the mask as superfluous, and then multiplies all 32 bits of the entry
+                        asm volatile("" : "+v"(in[k]));
+                    }
+                };
+                constexpr int U = KC % 2 ? 2 : 1;  // rounds per turn of the loop: the two operand sets swap roles
+                ChunkRegs<NB, RB> r[2];
+                Entries e0, e1;   // of round j and of round j + 1
+                unsigned in0[RB], in1[RB];
+                unsigned m0 = __builtin_amdgcn_readfirstlane(meta_at(0));
+                unsigned m1 = __builtin_amdgcn_readfirstlane(meta_at(1));
+                unsigned m_ahead = meta_at(2);
+                read_entries(m0, e0);
+                read_entries(m1, e1);
+                rows_of(e0, in0);
+                load_chunk(m0, in0, 0, r[0]);
+                for (int j0 = 0; j0 < my_rounds; j0 += U) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int j = j0 + u;
+                        if (j < my_rounds) {
+                            rows_of(e1, in1);
+                            const unsigned m2 = __builtin_amdgcn_readfirstlane(m_ahead);
+                            m_ahead = meta_at(j + 3);
+                            Entries e2;
+                            read_entries(m2, e2);
+#pragma unroll
+                            for (int kc = 0; kc < KC; ++kc) {
+                                ChunkRegs<NB, RB>& now = r[(u * KC + kc) & 1];
+                                ChunkRegs<NB, RB>& next = r[(u * KC + kc + 1) & 1];
+                                if (kc + 1 < KC)
+                                    load_chunk(m0, in0, kc + 1, next);
+                                else
+                                    load_chunk(m1, in1, 0, next);
+                                compute_chunk(m0, now, kc % 2 == 0);
+                                if (kc % 2 == 1 || kc + 1 == KC) add_round(m0, e0);
+                            }
+                            e0 = e1;
+                            e1 = e2;
+#pragma unroll
+                            for (int k = 0; k < RB; ++k) in0[k] = in1[k];
+                            m0 = m1;
+                            m1 = m2;
+                        }
+                    }
+                }
+            }
+        }
+        // Draw the next tile: from the own span, and once that is used up from the other spans, so that no XCD ends
+        // before the others.  The last wave does it when its share of the tile is done: it has the smallest share
+        // on average and would otherwise only wait at the barrier, which hides the atomic's round trip.
+        if (threadIdx.x == NT - 64) {
+            int t = -1;
+            for (int d = 0; d < kXcds && t < 0; ++d) {
+                const int x = (xcd + d) % kXcds;
+                const int end_x = (x + 1) * span < n_tiles ? (x + 1) * span : n_tiles;
+                if (x * span + per_xcd >= end_x) continue;  // (a span with no tiles to draw)
+                const int cand = x * span + per_xcd + (int)atomicAdd(&ctr->conv_ticket[x * kTicketStride], 1u);
+                if (cand < end_x) t = cand;
+            }
+            s_next[parity] = t;
+        }
+        __syncthreads();
+        const int next_tile = s_next[parity];
+        // ---- epilogue: one rounding to fp32, bias on the non-zero entries, planar store; the accumulators are
+        //      reset on the way.  A lane takes one row, a wave one channel at a time: consecutive rows lie
+        //      CS doubles apart, i.e. 2 banks (mod 64), so the 64 reads of a wave spread over all LDS banks, and
+        //      the wave's stores form one contiguous 256-byte run of the planar tile.
+        {
+            constexpr int OCW = (C_OUT + kConvWaves - 1) / kConvWaves, H = kTileRows / 64;
+            double acc[OCW][H];
+#pragma unroll
+            for (int j = 0; j < OCW; ++j) {  // all reads first: one LDS latency for the lot
+                const int oc = (wave + j * kConvWaves) < C_OUT ? (wave + j * kConvWaves) : C_OUT - 1;
+#pragma unroll
+                for (int h = 0; h < H; ++h) acc[j][h] = s_c[(h * 64 + lane) * CS + oc];
+            }
+#pragma unroll
+            for (int j = 0; j < OCW; ++j) {
+                const int oc = wave + j * kConvWaves;
+                if (C_OUT % kConvWaves == 0 || oc < C_OUT) {
+                    // (the weights stand in as a readable address when there is no bias)
+                    const float bl = (bias ? bias : (const float*)ws)[oc];
+                    const float bv = bias ? bl : 0.0f;
+#pragma unroll
+                    for (int h = 0; h < H; ++h) {
+                        const int r = h * 64 + lane;
+                        s_c[r * CS + oc] = 0.0;
+                        float x = (float)acc[j][h];
+                        if (x != 0.0f) x += bv;
+                        resp[((size_t)tile * C_OUT + oc) * kTileRows + r] = x;
+                    }
+                }
+            }
+        }
+        tile = next_tile;
+    }
+}
+
+template <int KC, int NB, int HALF = 0>
+static hipError_t launch_conv_mfma_split_t(int taps, long long nnz_in, const float* feats, const u32x4* ws,
+                                           const float* bias,
+                                     const unsigned* pairs, const unsigned short* block_tap, const uint2* tile_hdr,
+                                     Counters* ctr, float* resp, hipStream_t s) {
+    const size_t lds = conv_mfma_lds_bytes(NB * 16);
+    // (set on every launch: the attribute belongs to the current device's copy of the kernel, and a flag remembering
+    // that it was set would have to be kept per device and guarded between threads for the sake of a microsecond)
+    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_split<KC, NB, HALF>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    int per_cu = (int)((160 * 1024) / lds);
+    if (per_cu < 1) per_cu = 1;
+    if (per_cu > 4) per_cu = 4;    // 16 waves per CU
+    const int grid = (device_cu_count() * per_cu + kXcds - 1) / kXcds * kXcds;  // one span of tiles per XCD
+    hipLaunchKernelGGL((k_conv_mfma_split<KC, NB, HALF>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, ws,
+                       bias,
+                       pairs, block_tap, tile_hdr, ctr, resp);
+    return hipGetLastError();
+}
+
 bool conv_mfma_supported(const Geom& g, int c_in, int c_out, long long nnz_in) {
     if (g.T > 255) return false;  // block_tap holds the tap in one byte
     return ((c_in % 32 == 0 && c_in <= 128) || c_in == 16) && c_out % 16 == 0 && c_out <= 64 && nnz_in > 0 &&
@@ -1332,5 +1672,28 @@ hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats,
 #undef SCNN_MFMA_HALF
     return hipErrorInvalidValue;
 }
+
+hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
+                                  int c_out, const float* bias, const unsigned* pairs,
+                                  const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
+                                  hipStream_t s) {
+#define SCNN_MFMA_CASE(KC_, NB_)                                                                                  \
+    if (c_in == KC_ * 32 && c_out == NB_ * 16)                                                                    \
+        return launch_conv_mfma_split_t<KC_, NB_>(g.T, nnz_in, feats, (const u32x4*)ws, bias, pairs, block_tap,   \
+                                                  tile_hdr, ctr, resp, s);
+    SCNN_MFMA_CASE(1, 1) SCNN_MFMA_CASE(1, 2) SCNN_MFMA_CASE(1, 3) SCNN_MFMA_CASE(1, 4)
+    SCNN_MFMA_CASE(2, 1) SCNN_MFMA_CASE(2, 2) SCNN_MFMA_CASE(2, 3) SCNN_MFMA_CASE(2, 4)
+    SCNN_MFMA_CASE(3, 1) SCNN_MFMA_CASE(3, 2) SCNN_MFMA_CASE(3, 3) SCNN_MFMA_CASE(3, 4)
+    SCNN_MFMA_CASE(4, 1) SCNN_MFMA_CASE(4, 2) SCNN_MFMA_CASE(4, 3) SCNN_MFMA_CASE(4, 4)
+#undef SCNN_MFMA_CASE
+#define SCNN_MFMA_HALF(NB_)                                                                                       \
+    if (c_in == 16 && c_out == NB_ * 16)                                                                          \
+        return launch_conv_mfma_split_t<1, NB_, 1>(g.T, nnz_in, feats, (const u32x4*)ws, bias, pairs, block_tap,  \
+                                                   tile_hdr, ctr, resp, s);
+    SCNN_MFMA_HALF(1) SCNN_MFMA_HALF(2) SCNN_MFMA_HALF(3) SCNN_MFMA_HALF(4)
+#undef SCNN_MFMA_HALF
+    return hipErrorInvalidValue;
+}
+
 
 }  // namespace scnn

@@ -23,7 +23,6 @@ namespace scnn {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kQuadWaves = 4;            // waves per workgroup
 constexpr int kQuadRows = 64;            // candidate sites per wave

@@ -19,7 +19,6 @@
 namespace scnn {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kSplitSites = 256;             // candidate sites per unit of work (a workgroup of four waves)

@@ -209,14 +209,20 @@ __device__ inline bool wave_or_runs(long long word, unsigned long long& bits) {
     return lane == 0 || pw != word;
 }
 
-// Three bf16 numbers whose sum is x.  (Finite x; a magnitude that would round to infinity is cut instead, and below
-// 2^-109 the last ones run into bf16's smallest number.)
+// Three bf16 numbers whose sum is x.  (A magnitude that would round to infinity is cut instead, and below 2^-109 the
+// last ones run into bf16's smallest number.  Infinities and NaN are the third number, which meets only the other
+// operand's first: an infinity times h, not times the m and l of either sign.)
 __device__ __forceinline__ void split3(float x, unsigned short& h, unsigned short& m, unsigned short& l) {
     auto rounded = [](float v) {
         const unsigned u = __float_as_uint(v);
         const unsigned r = u + 0x7fffu + ((u >> 16) & 1u);
         return ((r & 0x7f800000u) == 0x7f800000u ? u : r) >> 16;
     };
+    if ((__float_as_uint(x) & 0x7f800000u) == 0x7f800000u) {
+        h = m = 0;
+        l = (unsigned short)((__float_as_uint(x) >> 16) | (x != x ? 0x40u : 0u));
+        return;
+    }
     const unsigned uh = rounded(x);
     const float r1 = x - __uint_as_float(uh << 16);
     const unsigned um = rounded(r1);
@@ -224,6 +230,29 @@ __device__ __forceinline__ void split3(float x, unsigned short& h, unsigned shor
     h = (unsigned short)uh;
     m = (unsigned short)um;
     l = (unsigned short)rounded(r2);
+}
+
+// Eight fp32 values as eight h, eight m and eight l: split3 on pairs, with the conversion instruction.  (h and m are kept
+// finite; what is left of an infinity or NaN is in l.)
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void split8(const u32x4 (&x)[2], u32x4 (&part)[3]) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        f32x2 v;
+        v.x = __uint_as_float(x[i >> 1][(2 * i) & 3]);
+        v.y = __uint_as_float(x[i >> 1][(2 * i + 1) & 3]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            constexpr float kTop = 3.3895313892515355e38f;  // bf16's largest
+            const f32x2 u = k == 2 ? v : f32x2{__builtin_amdgcn_fmed3f(v.x, -kTop, kTop), __builtin_amdgcn_fmed3f(v.y, -kTop, kTop)};
+            const unsigned p = __builtin_bit_cast(unsigned, __builtin_convertvector(u, bf16x2));
+            part[k][i] = p;
+            v.x -= __uint_as_float(p << 16);
+            v.y -= __uint_as_float(p & 0xffff0000u);
+        }
+    }
 }
 
 // Exclusive scan across a 256-thread block; `total` receives the block sum.
@@ -307,8 +336,8 @@ hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_
                               long long n_cap, unsigned long long* occ, unsigned* occ_prefix, Counters* ctr,
                               const float* feats, int c_in, unsigned short* xs /* nullable: also split the rows */,
                               hipStream_t s);
-// wp / wb / wq / ws: the filter in the layout of the vector / pair-list matrix-core / quad / split quad kernel (of wb,
-// wq and ws at most the one that will run is non-null; wp is used when all three are null)
+// wp / wb / wq / ws: the filter in the layout of the vector / fp32 pair-list / fp32 quad / split kernels (of wb, wq and
+// ws at most the one that will run is non-null; wp is used when all three are null)
 hipError_t launch_prepare(const Geom& g, const float* w, int c_in, int c_out, int adjoint, int c_out_pad, double* wp,
                           float* wb, float* wq, unsigned short* ws, int* tap_active, int* tap_coord, void* zero_p,
                           size_t zero_bytes, hipStream_t s);
@@ -365,6 +394,11 @@ hipError_t launch_pair_build(const Geom& g, const unsigned long long* occ, const
 hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats, int c_in, const float* wb, int c_out,
                             const float* bias, const unsigned* pairs, const unsigned short* block_tap,
                             const uint2* tile_hdr, Counters* ctr, float* resp, hipStream_t s);
+// (on split operands: the forward pass)
+hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
+                                  int c_out, const float* bias, const unsigned* pairs,
+                                  const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
+                                  hipStream_t s);
 
 // scnn_conv_quad.hip
 constexpr int kQuadMaxCout = 128;  // two groups of 64 output channels, one launch each

@@ -92,3 +92,38 @@ def test_inputs_beyond_the_split_kernels_offsets():
     assert n == small[0].shape[0] and torch.equal(oc[:n], small[0])
     a, b = of[:n].double(), small[1].double()
     assert bool(((a - b).abs() <= 1e-5 * b.abs() + 1e-6).all())
+
+
+@pytest.mark.parametrize("c_in,ksize", [(32, (3, 3, 3)), (24, (3, 3, 3)), (16, (5, 5, 5)), (64, (5, 5, 5))])
+def test_infinities_and_nan_stay_what_they_are(c_in, ksize):
+    """One row with an infinity, one with a NaN, one with the largest fp32 number: sites that see the infinity get it with
+    the sign of the weight, sites that see the NaN get NaN, and no other response stops being finite.  The split and the
+    pair-list kernel (the 5x5x5 filters)."""
+    rng = np.random.default_rng(c_in)
+    ext, c_out = (24, 24, 24), 32
+    coords = random_sparse_sites(rng, ext, 1, 0.1)
+    feats = (1.0 - rng.random((coords.shape[0], c_in))).astype(np.float32)
+    t = int(np.prod(ksize))
+    w = rng.normal(size=(t, c_in, c_out)).astype(np.float32) * np.float32(0.1)
+    n = coords.shape[0]
+    feats[n // 4, c_in - 1], feats[n // 2, 0], feats[3 * n // 4, 3] = np.inf, np.nan, np.finfo(np.float32).max
+    d = torch.device("cuda")
+    scnn.set_conv_path(2)
+    try:
+        oc, of, _ = scnn.sparse_conv_fwd(ext, 1, torch.from_numpy(coords).to(d), torch.from_numpy(feats).to(d), ksize,
+                                         torch.from_numpy(w).to(d))
+        say(f"non-finite rows {c_in} {ksize}: {scnn.last_conv_kernel()}")
+    finally:
+        scnn.set_conv_path(0)
+    p = ksize[0] // 2
+    grid = np.full((24 + 2 * p,) * 3, -1)
+    grid[tuple(coords[:, 1:].T + p)] = np.arange(n)
+    oc, of = oc.cpu().numpy(), of.cpu().numpy()
+    ref = np.zeros(of.shape)
+    x64 = np.vstack([feats, np.zeros((1, c_in))]).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        for k, (a, b, c) in enumerate(np.ndindex(*ksize)):
+            ref += x64[grid[oc[:, 1] + a, oc[:, 2] + b, oc[:, 3] + c]] @ w[k].astype(np.float64)
+    assert np.isinf(ref).any() and np.isnan(ref).any()
+    assert np.array_equal(np.isnan(of), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(of), of, 0), np.where(np.isinf(ref), ref, 0))
