@@ -21,6 +21,8 @@ if ROOT not in sys.path:
 
 PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_FP32_TFLOPS = 157.3
+# fp32 products as six bf16 ones (the forward matrix-core kernels of 16 or more input channels): dense bf16 peak / 6
+PEAK_MFMA_SPLIT_TFLOPS = 2500.0 / 6.0
 PEAK_FP64_VECTOR_TFLOPS = 78.6
 
 
@@ -375,9 +377,10 @@ def main():
         except Exception:
             traffic = None
     on_matrix_cores = conv_kernel in ("k_conv_quad", "k_conv_mfma")
-    # the matrix-core kernel is priced against the fp32 MFMA peak, the vector kernel (fp64 FMA) against the fp64
-    # vector peak
-    conv_peak = PEAK_MFMA_FP32_TFLOPS if on_matrix_cores else PEAK_FP64_VECTOR_TFLOPS
+    # the matrix-core kernels are priced against the bf16 peak over the six products they make of one (with fewer than
+    # 16 input channels: the fp32 MFMA peak), the vector kernel (fp64 FMA) against the fp64 vector peak
+    mfma_peak = PEAK_MFMA_SPLIT_TFLOPS if c_in >= 16 else PEAK_MFMA_FP32_TFLOPS
+    conv_peak = mfma_peak if on_matrix_cores else PEAK_FP64_VECTOR_TFLOPS
     line = {
         "metric": "effective non-zero GMAC/s of sparse conv+attention; % of HBM roofline",
         "value": gmacs, "unit": "GMAC/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -391,15 +394,15 @@ def main():
                      "achieved": conv_tflops, "peak": conv_peak, "unit": "TFLOP/s", "frac": conv_tflops / conv_peak,
                      "traffic": traffic, "traffic_source": traffic_source,
                      "kernel_ms": conv_ms, "kernel_launches_timed": conv_calls, "flops_per_launch": 2 * int(mac_nz),
-                     # the whole layer against its own bound: max(algorithmic bytes / 8 TB/s, flops / fp32 MFMA peak)
+                     # the whole layer against its own bound: max(algorithmic bytes / 8 TB/s, flops / matrix peak)
                      # over the step time
                      "layer_frac": max(bytes_alg["alg"] / (PEAK_HBM_GBS * 1e9),
-                                       2.0 * mac_nz / (PEAK_MFMA_FP32_TFLOPS * 1e12)) / (ms_per_step * 1e-3)},
+                                       2.0 * mac_nz / (mfma_peak * 1e12)) / (ms_per_step * 1e-3)},
         "hbm": {"algorithmic_bytes": bytes_alg["alg"], "achieved_GBs": bytes_alg["alg"] / (ms_per_step * 1e-3) / 1e9,
                 "frac_of_8TBs": bytes_alg["alg"] / (ms_per_step * 1e-3) / 1e9 / PEAK_HBM_GBS,
                 "copy_kernel_GBs": copy_gbs,
                 "whole_layer_roofline_frac": max(bytes_alg["alg"] / (PEAK_HBM_GBS * 1e9),
-                                                 2.0 * mac_nz / (PEAK_MFMA_FP32_TFLOPS * 1e12)) / (ms_per_step * 1e-3)},
+                                                 2.0 * mac_nz / (mfma_peak * 1e12)) / (ms_per_step * 1e-3)},
         "stage_ms": {k: v / max(calls, 1) for k, v in stage_ms.items() if not k.startswith("bwd_")},
         "ms_per_step_with_stage_events": dt_stages / args.steps * 1e3,
         "ms_per_step_without_events": dt_plain / args.steps * 1e3,

@@ -43,10 +43,12 @@ __host__ __device__ constexpr int split_waves_per_simd(int nb, int acc64) { retu
 // a group: on shell surfaces 0.37-0.49 of the multiplied rows are neighbours within 64 sites, 0.41-0.55 within 128,
 // 0.45-0.61 within 256); then wave i walks the taps for the groups i, i + 4, i + 8, i + 12 with their sums in registers.
 //
-// What bounds it is the 64 bytes a clock that a compute unit's vector memory returns: a step's three row loads take 48
-// clocks of it (absent neighbours included) for 96 (NB = 4) clocks of a SIMD's matrix pipe, and the 12 KB of weights of
-// a (tap, chunk) would take 192 per wave.  So the four waves walk the taps together and get the weights through LDS:
-// a wave fetches a quarter of the next ones while it multiplies the current ones.
+// What bounds it is what a compute unit's vector memory returns: a row load (sixteen rows 192 bytes apart) takes about 33
+// clocks of it, absent neighbours included, so a step's three take 99 for the 384 clocks (NB = 4) that its 24 matrix
+// instructions hold one of the four SIMDs; the 12 KB of weights of a (tap, chunk) would take 180 per wave.  So the four
+// waves walk the taps together and get the weights through LDS: a wave fetches a quarter of the next ones while it
+// multiplies the current ones.  Matrix pipes busy half of the time.  Against k_conv_quad, 32 -> 64 channels, 27 taps:
+// 437 -> 218 us at 731 k candidates, 144 -> 80 at 146 k; one-wave units of 64 / 128 sites took 295 / 243 at 731 k.
 // NCH = 32-channel chunks of the input; NB = blocks of 16 output channels (2 or 4);
 // ACC64: sums over taps and chunks in fp64, else fp32; K3 = 3x3x3 filter (its loops are straight code).
 template <int NCH, int NB, int ACC64, int K3>
