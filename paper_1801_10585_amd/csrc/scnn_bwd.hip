@@ -269,11 +269,18 @@ hipError_t launch_bwd_filter_f64(const Geom& g, const unsigned long long* occ, c
 // arithmetic per pair.  Only the last block of a tap can hold list padding (local row 128), so only that block
 // pays for masking.
 //
+// What bounds it: the fp32 matrix instructions, 512 clocks of a SIMD per block at 32 x 64 channels, and the latency of the
+// gathers behind them.  32 -> 64 channels, 643 k gradient rows: 247 us (of which 146 at the rate a large fp32 product
+// reaches here) -> 225 us with the blocks of a share as one stream across tiles and the padding masked at the
+// multiplication.  Splitting the operands into bf16 thirds takes 60 vector instructions per eight values, more issue
+// time than the fp32 products it would replace.
+//
 // All slabs of one share of the tiles run on the same XCD (workgroup i runs on XCD i % 8), so that the share's
 // input rows and gradient rows are fetched into that XCD's L2 once for all taps.
 template <int MT, int NT>
 struct BwdOperands {
     float av[4][MT], bv[4][NT];
+    bool live[4];  // of a tap's last block in a tile: not list padding
 };
 
 template <int MT, int NT, bool MASKED>
@@ -287,10 +294,9 @@ __device__ __forceinline__ void bwd_filter_load(const uint4 ent, const char* __r
         // the 24-bit multiply reads the low 24 bits of its operands: the gradient row of the pair, as it is
         const unsigned goff = __umul24(en[j], cout4) + glane;
         unsigned xoff = __umul24(row, cin4) + xlane;
-        bool live = true;
         if constexpr (MASKED) {
-            live = row < (unsigned)kTileRows;
-            xoff = live ? xoff : xlane;
+            o.live[j] = row < (unsigned)kTileRows;
+            xoff = o.live[j] ? xoff : xlane;
         }
         if constexpr (MT == 1) {
             o.av[j][0] = *(const float*)(xt + xoff);
@@ -298,10 +304,6 @@ __device__ __forceinline__ void bwd_filter_load(const uint4 ent, const char* __r
             const float2 t2 = *(const float2*)(xt + xoff);
             o.av[j][0] = t2.x;
             o.av[j][1] = t2.y;
-        }
-        if constexpr (MASKED) {
-#pragma unroll
-            for (int a = 0; a < MT; ++a) o.av[j][a] = live ? o.av[j][a] : 0.0f;
         }
         if constexpr (NT == 1) {
             o.bv[j][0] = *(const float*)(gl + goff);
@@ -369,65 +371,92 @@ __global__ __launch_bounds__(256) void k_bwd_filter_mfma(int taps, int c_in, int
 
     int b = tile_lo < tile_hi ? sample_of_tile(tile_start, batch, tile_lo) : 0;
     int b_end = tile_start[b + 1];  // first tile of the next sample
-    // block range of this tap in a tile; fetched one tile ahead of its use
-    unsigned nb0 = 0, nb1 = 0;
-    if (tile_lo < tile_hi) {
-        const unsigned short* tf = tap_first + (size_t)tile_lo * (taps + 1) + ta;
-        const unsigned h = tile_hdr[tile_lo].x;
-        nb0 = h + tf[0];
-        nb1 = h + tf[1];
-    }
-    for (int tile = tile_lo; tile < tile_hi; ++tile) {
-        const unsigned b0 = nb0, b1 = nb1;
-        if (tile + 1 < tile_hi) {
-            const unsigned short* tf = tap_first + (size_t)(tile + 1) * (taps + 1) + ta;
-            const unsigned h = tile_hdr[tile + 1].x;
+    // The share's blocks of this tap as one stream: pair entries are fetched two blocks ahead of the multiplication and
+    // operands one (two register sets that swap roles, so that nothing is copied), across tiles too: a tile has about
+    // three blocks of a tap, and a pipeline filled anew for each of them left the matrix pipe idle a third of the time.
+    int tile = tile_lo - 1;         // tile of the block handed out last
+    unsigned blk = 0, blk_end = 0;  // its next block and its end
+    unsigned nb0 = 0, nb1 = 0;      // block range of this tap in the next tile, read one tile ahead
+    const char* xt = (const char*)x;
+    auto read_range = [&](int t) {
+        if (t < tile_hi) {
+            const unsigned short* tf = tap_first + (size_t)t * (taps + 1) + ta;
+            const unsigned h = tile_hdr[t].x;
             nb0 = h + tf[0];
             nb1 = h + tf[1];
         }
-        while (tile >= b_end) {  // next sample (samples without rows have no tiles)
-            ++b;
-            b_end = tile_start[b + 1];
+    };
+    uint4 ent;
+    bool ahead = true, ent_last = false;  // a block is waiting in ent; it is its tile's last
+    auto next = [&] {
+        while (blk >= blk_end) {
+            if (++tile >= tile_hi) {
+                ahead = false;
+                return;
+            }
+            blk = nb0;
+            blk_end = nb1;
+            read_range(tile + 1);
+            while (tile >= b_end) {  // next sample (samples without rows have no tiles)
+                ++b;
+                b_end = tile_start[b + 1];
+            }
+            xt = (const char*)(x + (size_t)(cand_start[b] + (tile - tile_start[b]) * kTileRows) * c_in);
         }
-        if (b0 >= b1) continue;
-        const int first = cand_start[b] + (tile - tile_start[b]) * kTileRows;
-        const char* __restrict__ xt = (const char*)(x + (size_t)first * c_in);
-        f32x4 acc[MT][NT];
+        ent = *(const uint4*)(pairs + (size_t)blk * 16 + gq * 4);
+        ent_last = ++blk >= blk_end;
+    };
+    auto issue = [&](BwdOperands<MT, NT>& dst) {
+        const bool last = ent_last;
+        if (last)
+            bwd_filter_load<MT, NT, true>(ent, xt, gl, cin4, cout4, xlane, glane, dst);
+        else
+            bwd_filter_load<MT, NT, false>(ent, xt, gl, cin4, cout4, xlane, glane, dst);
+        next();
+        return last;
+    };
+    f32x4 acc[MT][NT];
+    auto clear = [&] {
 #pragma unroll
         for (int a = 0; a < MT; ++a)
 #pragma unroll
             for (int c = 0; c < NT; ++c) acc[a][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // operands one block ahead of their use (two register sets that swap roles, so that nothing is copied),
-        // pair entries two blocks ahead
-        const unsigned* pl = pairs + (size_t)b0 * 16 + gq * 4;
-        const unsigned nblk = b1 - b0;
-        BwdOperands<MT, NT> opa, opb;
-        uint4 ent_next = *(const uint4*)pl;
-        unsigned issued = 0, done = 0;
-        auto issue = [&](BwdOperands<MT, NT>& dst) {
-            const uint4 e = ent_next;
-            if (issued + 1 < nblk) ent_next = *(const uint4*)(pl + (size_t)(issued + 1) * 16);
-            if (issued + 1 < nblk)
-                bwd_filter_load<MT, NT, false>(e, xt, gl, cin4, cout4, xlane, glane, dst);
-            else
-                bwd_filter_load<MT, NT, true>(e, xt, gl, cin4, cout4, xlane, glane, dst);
-            ++issued;
-        };
-        issue(opa);
-        for (;;) {
-            if (issued < nblk) issue(opb);
-            bwd_filter_mma<MT, NT>(opa, acc);
-            if (++done == nblk) break;
-            if (issued < nblk) issue(opa);
-            bwd_filter_mma<MT, NT>(opb, acc);
-            if (++done == nblk) break;
+    };
+    auto multiply = [&](BwdOperands<MT, NT>& o, bool last) {
+        if (last) {  // (here and not after the loads, which would be waited for one by one)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int a = 0; a < MT; ++a) o.av[j][a] = o.live[j] ? o.av[j][a] : 0.0f;
         }
+        bwd_filter_mma<MT, NT>(o, acc);
+        if (last) {
 #pragma unroll
-        for (int a = 0; a < MT; ++a)
+            for (int a = 0; a < MT; ++a)
 #pragma unroll
-            for (int c = 0; c < NT; ++c)
+                for (int c = 0; c < NT; ++c)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc64[a][c][v] = fma((double)acc[a][c][v], 1.0, acc64[a][c][v]);  // full-rate form of the add
+                    for (int v = 0; v < 4; ++v)
+                        acc64[a][c][v] = fma((double)acc[a][c][v], 1.0, acc64[a][c][v]);  // full-rate form of the add
+            clear();
+        }
+    };
+    clear();
+    read_range(tile_lo);
+    next();
+    if (ahead) {
+        BwdOperands<MT, NT> opa, opb;
+        bool last_a = issue(opa), last_b = false;
+        for (;;) {
+            const bool more_b = ahead;
+            if (more_b) last_b = issue(opb);
+            multiply(opa, last_a);
+            if (!more_b) break;
+            const bool more_a = ahead;
+            if (more_a) last_a = issue(opa);
+            multiply(opb, last_b);
+            if (!more_a) break;
+        }
     }
     // result element (a, c, v) of this lane: input channel (4*gq + v)*MT + a, output channel jj*NT + c of the slab
     const int t = taps - 1 - ta;  // tap of the filter itself
