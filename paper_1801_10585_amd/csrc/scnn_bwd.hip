@@ -269,9 +269,9 @@ hipError_t launch_bwd_filter_f64(const Geom& g, const unsigned long long* occ, c
 // arithmetic per pair.  Only the last block of a tap can hold list padding (local row 128), so only that block
 // pays for masking.
 //
-// What bounds it: the fp32 matrix instructions, 512 clocks of a SIMD per block at 32 x 64 channels, and the latency of the
-// gathers behind them.  32 -> 64 channels, 643 k gradient rows: 247 us (of which 146 at the rate a large fp32 product
-// reaches here) -> 225 us with the blocks of a share as one stream across tiles and the padding masked at the
+// What bounds it: the fp32 matrix instructions (128 x 8 clocks of a SIMD per block at 32 x 64 channels) and the latency
+// of the gathers behind them.  128^3 x 4, 32 -> 64 channels, 25 G multiply-adds: 291 us (164 at the rate that a large fp32
+// product reaches here) -> 266 us with the blocks of a share as one stream across tiles and the padding masked at the
 // multiplication.  Splitting the operands into bf16 thirds takes 60 vector instructions per eight values, more issue
 // time than the fp32 products it would replace.
 //
