@@ -213,15 +213,18 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_bwd_filter_f64(Geom g, const
 #pragma unroll
             for (int s0 = 0; s0 < kTileRows / 4; s0 += 16) {
                 if (4 * s0 >= nrows) continue;
-                float gv[16];
+                float gv[16], xv[16];
 #pragma unroll
                 for (int s = 0; s < 16; ++s) {
+                    // no gradient row: nothing is read, and the product is 0 * 0 whatever the row holds (an infinity or
+                    // NaN of x belongs to the pairs that exist)
                     const int n = s_nbr[4 * (s0 + s) + kq][tt];
-                    gv[s] = n >= 0 && oc_ok ? gcol[(size_t)n * c_out] : 0.0f;  // (no gradient row: nothing is read)
+                    gv[s] = n >= 0 && oc_ok ? gcol[(size_t)n * c_out] : 0.0f;
+                    xv[s] = n >= 0 ? a[s0 + s] : 0.0f;
                 }
 #pragma unroll
                 for (int s = 0; s < 16; ++s)
-                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s0 + s], (double)gv[s], acc[j], 0, 0, 0);
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xv[s], (double)gv[s], acc[j], 0, 0, 0);
             }
         }
     }
