@@ -21,7 +21,7 @@ if ROOT not in sys.path:
 
 PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_FP32_TFLOPS = 157.3
-# fp32 products as six bf16 ones (the forward matrix-core kernels of 16 or more input channels): dense bf16 peak / 6
+# fp32 products as six bf16 ones (the split-operand kernels): dense bf16 peak / 6
 PEAK_MFMA_SPLIT_TFLOPS = 2500.0 / 6.0
 PEAK_FP64_VECTOR_TFLOPS = 78.6
 
@@ -247,9 +247,10 @@ def main():
     ap.add_argument("--layer", type=int, default=1,
                     help="which layer of a multi-layer configuration to time (1-based; its input is produced by the "
                          "library from the layers before it, untimed); not the headline")
-    ap.add_argument("--conv-path", type=int, default=0, choices=[0, 1, 2, 3],
-                    help="convolution kernel family (scnn_set_conv_path): 0 the library's choice (the headline), "
-                         "1 vector kernels, 2 matrix cores wherever possible, 3 the pair-list matrix-core kernel")
+    ap.add_argument("--conv-path", type=int, default=0, choices=[0, 1, 2, 3, 5],
+                    help="convolution kernel (scnn_set_conv_path): 0 the library's choice (the headline), 1 vector "
+                         "kernels, 2 fp32 matrix cores wherever possible, 3 the pair-list matrix-core kernel, "
+                         "5 the split-operand kernel")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on one GPU only (the layer shards by sample with no exchange; "
@@ -371,15 +372,15 @@ def main():
     if not args.paper_runtime and args.layer == 1 and os.path.exists(tpath):
         try:
             rec = json.load(open(tpath))
-            if rec.get("kernel", "").startswith(conv_kernel):
+            if rec.get("kernel", "").split("<")[0] == conv_kernel:
                 traffic = rec.get("hbm_bytes_per_launch")
                 traffic_source = "profiles/" + os.path.basename(tpath) + ": " + rec.get("source", "")
         except Exception:
             traffic = None
-    on_matrix_cores = conv_kernel in ("k_conv_quad", "k_conv_mfma")
-    # the matrix-core kernels are priced against the bf16 peak over the six products they make of one (with fewer than
-    # 16 input channels: the fp32 MFMA peak), the vector kernel (fp64 FMA) against the fp64 vector peak
-    mfma_peak = PEAK_MFMA_SPLIT_TFLOPS if c_in >= 16 else PEAK_MFMA_FP32_TFLOPS
+    # the split-operand kernels are priced against the bf16 peak over the six products they make of one, the fp32 quad
+    # kernel against the fp32 MFMA peak, the vector kernel (fp64 FMA) against the fp64 vector peak
+    on_matrix_cores = conv_kernel.startswith(("k_conv_quad", "k_conv_mfma"))
+    mfma_peak = PEAK_MFMA_SPLIT_TFLOPS if conv_kernel.endswith("_split") else PEAK_MFMA_FP32_TFLOPS
     conv_peak = mfma_peak if on_matrix_cores else PEAK_FP64_VECTOR_TFLOPS
     line = {
         "metric": "effective non-zero GMAC/s of sparse conv+attention; % of HBM roofline",

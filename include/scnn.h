@@ -284,28 +284,32 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
  *     layers whose workspace holds at least 1024 tiles of 128 candidate
  *     sites - 128 tiles when C_in is 16 or 24 and C_out at least 24 - with
  *     C_in * C_out >= 256 and C_out >= 24, or C_in * C_out >= 384)
- *     take a quad matrix-core kernel where C_in is 8, 16, 24, 32, 40, 48, 64,
- *     96 or 128, C_out at most 128, the filter has at most 32 taps and
- *     in_feats is 16-byte aligned: the one on fp32 matrix cores for C_in = 8,
- *     for workspaces of fewer than 192 tiles (512 with C_in 16 or 24) and for
- *     inputs whose split copy (6 bytes per value, C_in rounded up to 32) does
- *     not fit 2^31 bytes, else the one on split operands.  Filters of more
- *     taps (and layers of fewer than 1024 tiles with C_in > 64 and C_out at
- *     most 32) take the pair-list matrix-core kernel where C_in is 16 or a multiple of 32 up to
- *     128 and C_out a multiple of 16 up to 64.  Everything else takes the
- *     vector kernels;
+ *     take a matrix-core kernel where in_feats is 16-byte aligned.  Filters of
+ *     at most 32 taps with C_in 8, 16, 24, 32, 40, 48, 64, 96 or 128 and C_out at
+ *     most 128, by the first line that applies:
+ *     - C_in 96 or 128 and C_out a multiple of 16 up to 64, on workspaces of
+ *       fewer than 192 tiles (1024 with C_out 16 or 32) or with an input whose
+ *       split copy (6 bytes per value, C_in rounded up to 32) does not fit 2^31
+ *       bytes: the pair-list kernel ("k_conv_mfma_split");
+ *     - C_in = 8, workspaces of fewer than 192 tiles (512 with C_in 16 or 24), or
+ *       an input whose split copy does not fit: the quad kernel on fp32 matrix
+ *       cores ("k_conv_quad");
+ *     - the quad kernel on split operands ("k_conv_quad_split").
+ *     Filters of more taps with C_in 16 or a multiple of 32 up to 128 and C_out a
+ *     multiple of 16 up to 64: the pair-list kernel.
+ *     Everything else takes the vector kernels ("k_conv_valu");
  * 1 = always the vector kernels;
- * 2 = a matrix-core kernel whenever one takes the shape, whatever the size:
- *     a quad kernel wherever one takes the shape (8, 16, 24 input channels on
- *     small layers too);
+ * 2 = the fp32 quad kernel wherever it takes the shape, whatever the size, else
+ *     the pair-list kernel wherever that does;
  * 3 = the pair-list matrix-core kernel where it takes the shape (C_in = 16 or
- *     a multiple of 32 up to 128, C_out a multiple of 16 up to 64).
+ *     a multiple of 32 up to 128, C_out a multiple of 16 up to 64);
+ * 5 = the quad kernel on split operands wherever it takes the shape (4 is
+ *     refused).
  * All compute the same sums to the same rounding rule; the switch exists so
  * that tests and measurements can reach each.  The setting enters the
  * workspace size: query the workspace under the setting the call will run with.
- * scnn_last_conv_kernel() names the kernel family the calling thread's last
- * sparse_conv_fwd call launched ("k_conv_quad", "k_conv_mfma", "k_conv_valu";
- * "" before the first call). */
+ * scnn_last_conv_kernel() names the kernel that the calling thread's last
+ * sparse_conv_fwd call launched, by the names above; "" before the first call. */
 const char* scnn_last_conv_kernel(void);
 int scnn_set_conv_path(int path);
 

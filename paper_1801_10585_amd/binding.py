@@ -480,14 +480,15 @@ def profile_collect():
 
 
 def set_conv_path(path: int) -> None:
-    """0 = choose the convolution kernel by shape and size, 1 = always the vector kernels, 2 = a matrix-core kernel
-    whenever one takes the shape, 3 = the pair-list matrix-core kernel where it takes the shape."""
+    """0 = choose the convolution kernel by shape and size, 1 = always the vector kernels, 2 = the fp32 quad kernel where
+    it takes the shape, else the pair-list kernel, 3 = the pair-list matrix-core kernel where it takes the shape, 5 = the
+    split-operand kernel where it takes the shape."""
     L = load_library()
     _check(L, L.scnn_set_conv_path(int(path)))
 
 
 def last_conv_kernel() -> str:
-    """Kernel family launched by this thread's last sparse_conv_fwd call."""
+    """Convolution kernel launched by this thread's last sparse_conv_fwd call."""
     return load_library().scnn_last_conv_kernel().decode()
 
 

@@ -33,7 +33,9 @@ static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long 
     const bool pair_ok = conv_mfma_supported(g, c_in, c_out, nnz_in);
     if (g_conv_path == 3) return pair_ok ? ConvKernel::kPair : ConvKernel::kValu;
     const bool quad_ok = conv_quad_supported(g, c_in, c_out, nnz_in);
+    if (g_conv_path == 2) return quad_ok ? ConvKernel::kQuad : (pair_ok ? ConvKernel::kPair : ConvKernel::kValu);
     const bool split_ok = conv_split_supported(g, c_in, c_out, nnz_in);
+    if (g_conv_path == 5) return split_ok ? ConvKernel::kSplit : ConvKernel::kValu;
     // 8, 16 and 24 input channels pay for the matrix-core kernels' look-ups and lists only on layers whose rows carry
     // enough multiply-adds per neighbour: C_in x C_out of at least 256 with at least 24 output channels (8->32,
     // 16->24), or of at least 384 (24->16); narrower layers (8->8, 8->16, 16->16: the first blocks of the paper's
@@ -44,7 +46,7 @@ static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long 
     const long long min_tiles = (c_in >= 16 && c_out >= 24) ? 128 : 1024;
     const bool wide = c_in >= 32 || ((c_in == 8 || c_in == 16 || c_in == 24) && tiles_cap >= min_tiles &&
                                      ((mac >= 256 && c_out >= 24) || mac >= 384));
-    if (wide || g_conv_path == 2) {
+    if (wide) {
         // split against quad, index build + convolution, eight samples of 64^3 shells / four of 32^3 (us): 16->32 120 /
         // 57 against 137 / 58, 24->64 159 / 67 against 221 / 78, 32->32 124 / 59 against 186 / 71, 32->96 255 / 102
         // against 424 / 144, 48->64 324 / 113 against 537 / 160, 64->64 330 / 114 against 538 / 158; with eight
@@ -55,9 +57,9 @@ static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long 
         // 64 against 56 at 527.  Against the pair lists: 96->32 306 / 116 against 341 / 108, 96->64 447 / 150 against
         // 605 / 177, 128->64 626 / 197 against 856 / 228: these keep small layers of at most 32 output channels.
         const bool small = tiles_cap < (c_in >= 32 ? 192 : 512);
-        if (pair_ok && c_in > 64 && c_out <= 32 && tiles_cap < 1024 && g_conv_path != 2) return ConvKernel::kPair;
-        if (split_ok && !(small && quad_ok && g_conv_path != 2)) return ConvKernel::kSplit;
-        if (pair_ok && c_in > 64 && g_conv_path != 2) return ConvKernel::kPair;
+        if (pair_ok && c_in > 64 && c_out <= 32 && tiles_cap < 1024) return ConvKernel::kPair;
+        if (split_ok && !(small && quad_ok)) return ConvKernel::kSplit;
+        if (pair_ok && c_in > 64) return ConvKernel::kPair;
         if (quad_ok) return ConvKernel::kQuad;
         if (pair_ok) return ConvKernel::kPair;
     }
@@ -439,7 +441,7 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
         SCNN_TRY(launch_conv_split(g, ws.occ, ws.occ_prefix, nnz_in, ws.xsplit, c_in, ws.wsplit, c_out, bias,
                                    ws.tap_active, ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, ws.resp,
                                    device_cu_count(), s));
-        g_last_conv_kernel = "k_conv_quad";
+        g_last_conv_kernel = "k_conv_quad_split";
     } else if (kernel == ConvKernel::kQuad) {
         const int cus = device_cu_count();
         timer.mark();
@@ -453,7 +455,7 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
         timer.mark();
         SCNN_TRY(launch_conv_mfma_split(g, nnz_in, in_feats, c_in, ws.wsplit, c_out, bias, ws.pairs, ws.block_tap,
                                         ws.tile_hdr, ws.ctr, ws.resp, s));
-        g_last_conv_kernel = "k_conv_mfma";
+        g_last_conv_kernel = "k_conv_mfma_split";
     } else {
         timer.mark();
         SCNN_TRY(launch_conv_valu(g, ws.occ, ws.occ_prefix, nnz_in, in_feats, c_in, ws.wp, c_out, ws.c_out_pad, bias,
@@ -654,8 +656,8 @@ int sparse_conv_fwd_chained(int ndim, const int32_t* extent, int batch, const in
 }
 
 int scnn_set_conv_path(int path) {
-    if (path < 0 || path > 3)
-        return fail(SCNN_EINVAL, "conv path must be 0 (auto), 1 (vector kernels), 2 (matrix cores where possible) or 3 (pair-list matrix-core kernel)");
+    if (path < 0 || path == 4 || path > 5)
+        return fail(SCNN_EINVAL, "conv path must be 0 (auto), 1 (vector kernels), 2 (fp32 matrix cores where possible), 3 (pair-list matrix-core kernel) or 5 (split-operand kernel)");
     g_conv_path = path;
     return SCNN_OK;
 }

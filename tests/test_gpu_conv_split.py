@@ -33,50 +33,87 @@ def test_split_convolution_edges(extent, batch, c_in, c_out, ksize, density):
     w = make_filter(rng, ksize, c_in, c_out, 0.8, 0.2)
     bias = rng.normal(size=c_out).astype(np.float32)
     n = int(np.prod(extent))
-    scnn.set_conv_path(2)
+    scnn.set_conv_path(5)
     try:
         for rho, mode in ((1.0, scnn.ABS), (0.3, scnn.SIGNED)):
             say(f"split {extent} B={batch} {c_in}->{c_out} {ksize} rho={rho}")
             check_conv_against_oracle(extent, batch, coords, feats, ksize, w, bias, scnn.k_from_rho(rho, n), rho, mode,
                                       tag=f"split {extent} {c_in}->{c_out}")
-        assert scnn.last_conv_kernel() == "k_conv_quad"
+        assert scnn.last_conv_kernel() == "k_conv_quad_split"
     finally:
         scnn.set_conv_path(0)
 
 
-@pytest.mark.parametrize("c_in,c_out", [(32, 64), (64, 32)])
-def test_split_convolution_over_wide_magnitudes(c_in, c_out):
-    """Rows and weights spread over many binades.  A response's error is bounded by its roundings: per (tap, chunk) six
-    of sums no larger than A = the sum of its products' magnitudes, and the products left out (below 2^-23 each):
-    at most (27 * 6 + 2) * 2^-24 * A, whatever the magnitudes."""
+@pytest.mark.parametrize("path,c_in,c_out,k", [(5, 32, 64, 3), (5, 64, 32, 3), (3, 32, 64, 5), (3, 64, 32, 5)])
+def test_split_convolution_over_wide_magnitudes(path, c_in, c_out, k):
+    """Rows and weights spread over many binades, on the quad and on the pair-list form.  With A = the sum of a response's
+    product magnitudes and u = 2^-24: per (tap, 32-channel chunk) the parts' products left out are below 2 u A together,
+    the six instructions and the additions of their sums round by at most 4 u A; then at most taps fp32 additions where
+    the outer sums are fp32 (32 channels, quad form), else one rounding: (7 + taps) u A or 7 u A, whatever the magnitudes.
+    (One of the six products left out would give 6.9e-6 A = 115 u A or more on this data.)"""
     rng = np.random.default_rng(c_in)
     ext, batch = (12, 12, 12), 2
     coords = random_sparse_sites(rng, ext, batch, 0.3)
     scale = 2.0 ** rng.integers(-40, 40, size=(coords.shape[0], 1))
     feats = (rng.normal(size=(coords.shape[0], c_in)) * scale * 2.0 ** rng.integers(-12, 12, size=(1, c_in))).astype(np.float32)
-    w = (rng.normal(size=(27, c_in, c_out)) * 2.0 ** rng.integers(-10, 10, size=(27, c_in, c_out))).astype(np.float32)
+    taps, p = k ** 3, k // 2
+    w = (rng.normal(size=(taps, c_in, c_out)) * 2.0 ** rng.integers(-10, 10, size=(taps, c_in, c_out))).astype(np.float32)
     d = torch.device("cuda")
-    oc, of, _ = scnn.sparse_conv_fwd(ext, batch, torch.from_numpy(coords).to(d), torch.from_numpy(feats).to(d), (3, 3, 3),
-                                     torch.from_numpy(w).to(d))
-    grid = np.full((batch, 14, 14, 14), -1)
-    grid[tuple(coords[:, 0:1].T) + tuple(coords[:, 1:].T + 1)] = np.arange(coords.shape[0])
+    scnn.set_conv_path(path)
+    try:
+        oc, of, _ = scnn.sparse_conv_fwd(ext, batch, torch.from_numpy(coords).to(d), torch.from_numpy(feats).to(d), (k,) * 3,
+                                         torch.from_numpy(w).to(d))
+        assert scnn.last_conv_kernel() == ("k_conv_quad_split" if path == 5 else "k_conv_mfma_split")
+    finally:
+        scnn.set_conv_path(0)
+    grid = np.full((batch, *(e + 2 * p for e in ext)), -1)
+    grid[tuple(coords[:, 0:1].T) + tuple(coords[:, 1:].T + p)] = np.arange(coords.shape[0])
     oc, of = oc.cpu().numpy(), of.cpu().numpy()
     ref, mag = np.zeros(of.shape), np.zeros(of.shape)
     x64, w64 = np.vstack([feats, np.zeros((1, c_in))]).astype(np.float64), w.astype(np.float64)
-    for t, (i, j, k) in enumerate(np.ndindex(3, 3, 3)):
-        r = grid[oc[:, 0], oc[:, 1] + i, oc[:, 2] + j, oc[:, 3] + k]
+    for t, (i, j, l) in enumerate(np.ndindex(k, k, k)):
+        r = grid[oc[:, 0], oc[:, 1] + i, oc[:, 2] + j, oc[:, 3] + l]
         ref += x64[r] @ w64[t]
         mag += np.abs(x64[r]) @ np.abs(w64[t])
     worst = float((np.abs(of - ref) / np.maximum(mag, 1e-300)).max())
-    say(f"split wide magnitudes {c_in}->{c_out}: worst |error| / A = {worst:.3g}")
-    assert worst <= (27 * 6 + 2) * 2.0 ** -24
+    say(f"split wide magnitudes {c_in}->{c_out} k={k}: worst |error| / A = {worst:.3g}")
+    assert worst <= (7 + (taps if path == 5 and c_in == 32 else 0)) * 2.0 ** -24
     assert oc.shape[0] > 0
 
 
+@pytest.mark.parametrize("seed", range(6))
+def test_split_and_vector_kernels_agree_over_layer_sizes(seed):
+    """Layer sizes from less than one unit of 256 candidate sites per workgroup to several, with one and with eight chunks
+    of units per XCD: every response, selection bypassed, against the vector kernels (fp64 sums, compared with the oracle
+    elsewhere)."""
+    from tests.parity import ATOL, RTOL
+    rng = np.random.default_rng(7100 + seed)
+    c_in, c_out = [(32, 64), (16, 24), (32, 96), (48, 48), (24, 24), (64, 32)][seed]
+    e = [20, 64, 48, 40, 72, 56][seed]
+    extent, batch = (e, e, int(rng.integers(8, e + 1))), 1 + seed % 3 * 2
+    coords = random_sparse_sites(rng, extent, batch, float(rng.choice([0.02, 0.05, 0.3])))
+    feats = rng.normal(size=(coords.shape[0], c_in)).astype(np.float32)
+    w = (rng.normal(size=(27, c_in, c_out)) * 0.04).astype(np.float32)
+    out = {}
+    try:
+        for path in (1, 5):
+            scnn.set_conv_path(path)
+            oc, of, n = scnn.sparse_conv_fwd(extent, batch, *(torch.from_numpy(a).cuda() for a in (coords, feats)),
+                                             (3, 3, 3), torch.from_numpy(w).cuda())
+            assert int(n[2]) == 0
+            out[path] = (oc, of.double(), scnn.last_conv_kernel())
+    finally:
+        scnn.set_conv_path(0)
+    say(f"split sizes seed={seed} extent={extent} B={batch} {c_in}->{c_out} sites out={out[1][0].shape[0]}")
+    assert out[1][2] == "k_conv_valu" and out[5][2] == "k_conv_quad_split"
+    assert torch.equal(out[1][0], out[5][0])
+    assert bool(((out[1][1] - out[5][1]).abs() <= RTOL * out[1][1].abs() + ATOL).all())
+
+
 def test_inputs_beyond_the_split_kernels_offsets():
-    """A layer sized for more than 2^31 / 192 rows of 32 channels runs on the fp32 quad kernel; same responses within the
-    parity tolerance, rows past the device count never read."""
-    ext, batch, cap = (24, 24, 24), 1, (1 << 31) // 192 + 1000
+    """A layer sized for more than 2^31 / 192 rows of 32 channels runs on the fp32 quad kernel, one of the same grid sized
+    for its rows on the split kernel; same responses within the parity tolerance, rows past the device count never read."""
+    ext, batch, cap = (32, 32, 32), 1, (1 << 31) // 192 + 1000   # (257 tiles: more than the small layers' 192)
     rng = np.random.default_rng(5)
     coords = random_sparse_sites(rng, ext, batch, 0.1)
     feats = (1.0 - rng.random((coords.shape[0], 32))).astype(np.float32)
@@ -86,8 +123,10 @@ def test_inputs_beyond_the_split_kernels_offsets():
     big_f = torch.zeros((cap, 32), dtype=torch.float32, device="cuda")
     big_c[:c.shape[0]], big_f[:c.shape[0]] = c, f
     small = scnn.sparse_conv_fwd(ext, batch, c, f, (3, 3, 3), w)
+    assert scnn.last_conv_kernel() == "k_conv_quad_split"
     lay = scnn.ChainedLayer(ext, batch, cap, 32, (3, 3, 3), w)
     oc, of, nnz = lay(big_c, big_f, torch.tensor([c.shape[0]], dtype=torch.int64, device="cuda"))
+    assert scnn.last_conv_kernel() == "k_conv_quad"
     n = int(nnz.cpu()[0])
     assert n == small[0].shape[0] and torch.equal(oc[:n], small[0])
     a, b = of[:n].double(), small[1].double()
@@ -108,11 +147,12 @@ def test_infinities_and_nan_stay_what_they_are(c_in, ksize):
     n = coords.shape[0]
     feats[n // 4, c_in - 1], feats[n // 2, 0], feats[3 * n // 4, 3] = np.inf, np.nan, np.finfo(np.float32).max
     d = torch.device("cuda")
-    scnn.set_conv_path(2)
+    scnn.set_conv_path(5 if ksize == (3, 3, 3) else 3)
     try:
         oc, of, _ = scnn.sparse_conv_fwd(ext, 1, torch.from_numpy(coords).to(d), torch.from_numpy(feats).to(d), ksize,
                                          torch.from_numpy(w).to(d))
         say(f"non-finite rows {c_in} {ksize}: {scnn.last_conv_kernel()}")
+        assert scnn.last_conv_kernel() == ("k_conv_quad_split" if ksize == (3, 3, 3) else "k_conv_mfma_split")
     finally:
         scnn.set_conv_path(0)
     p = ksize[0] // 2
