@@ -103,14 +103,15 @@ size_t sparse_conv_fwd_workspace(int ndim, const int32_t* extent, int batch, int
  * to fp32 once.  The matrix-core kernels first add the at most 32 products of
  * one tap and 32-channel chunk in fp32; the quad kernels then add these partial
  * sums in fp32 where a response has at most 32 of them (filters of up to 32
- * taps on up to 32 input channels: the r = 128 layer's 27 x 1), in fp64
- * otherwise; the pair-list kernel adds the sums of two chunks of a tap in fp32
- * and these in fp64.  The quad kernel for 16 or more input channels and the
- * pair-list kernel multiply on the bf16 matrix cores with both operands split
- * into three bf16 numbers whose sum they are (exactly, for magnitudes from
- * 2^-109 to 3.38e38; what is smaller keeps an absolute error below 2^-134);
- * the parts' products left out are below 2^-23 of a product together, and the
- * result is as close to the exact sum as fp32 products'.  All stay
+ * taps on up to 32 input channels: the r = 128 layer's 27 x 1; the fp32 quad
+ * kernel also up to 16 taps on 64), in fp64 otherwise; the pair-list kernel
+ * always adds them in fp64.  The quad kernel on split operands and the pair-list
+ * kernel multiply on the bf16 matrix cores, both operands split into three bf16
+ * numbers whose sum they are (exactly, for magnitudes from 2^-109 to 3.38e38;
+ * what is smaller keeps an absolute error below 2^-134); the parts' products
+ * left out are below 2^-23 of a product together, and the result is as close to
+ * the exact sum as fp32 products' or closer, on full rows and on rows that are
+ * mostly zeros.  All stay
  * within 1e-5 relative + 1e-6 absolute of the exact sum on the workloads this
  * library is tested on.  In general the error of a matrix-core response follows
  * the magnitudes it is summed from, not its own: about 2e-8 * A, A = the sum of

@@ -19,7 +19,6 @@
 
 namespace scnn {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ input rows as the list of output sites
 // cand_lin[r] = site index of input row r; rows16_start[b] = 16-row groups of all earlier samples (the unit in

@@ -868,8 +868,6 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
 // cores could consume.  Waves of a workgroup share the tile's accumulators
 // through the LDS atomic, so the order of the fp64 additions is not fixed.
 // ---------------------------------------------------------------------------
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr unsigned kPadPair = (unsigned)kTileRows << kPairRowShift;  // list padding: dummy accumulator row, input row 0
 constexpr int kStageBlocks = 208;                 // 16-pair blocks staged in LDS at a time by the contraction
@@ -1312,13 +1310,12 @@ static hipError_t launch_conv_mfma_t(int taps, long long nnz_in, const float* fe
 // ---------------------------------------------------------------------------
 // The same contraction on the bf16 matrix cores, both operands as three bf16 numbers each (split3; the rows split after
 // the load, the filter beforehand): the forward pass's pair-list kernel.  A block's 32 channels take 384 clocks of
-// matrix time per 64 output channels instead of 1024, the sums of two chunks are added in fp32 before they go to the
-// fp64 accumulators (half the LDS atomics), and the weights of one chunk at a time are held in registers.  256^3, 64->64
-// channels, 125 taps, 1.3 M candidates: 3.68 -> 1.95 ms, now bound by the weights and rows that vector memory returns (a
-// round's chunk asks for 12 + 4 KB for at most two blocks); error against 64 bits 1.04e-7 -> 6.3e-8 of the result's norm.
-// The backward pass keeps the fp32 kernel above: its gradient rows are mostly zeros, a chain over them rounds less often
-// than 32 channels at once do, and the split form was 1.4 times further off there (5.4e-8 -> 7.6e-8; it took 271 us
-// instead of 335).
+// matrix time per 64 output channels instead of 1024, the sums of two chunks are added in fp64 registers before they go
+// to the accumulators (half the LDS atomics), and the weights of one chunk at a time are held in registers.  256^3, 64->64
+// channels, 125 taps, 1.3 M candidates: call 3.96 -> 2.50 ms, now bound by the weights and rows that vector memory
+// returns (a round's chunk asks for 12 + 4 KB for at most two blocks); error against 64 bits 1.08e-7 -> 4.6e-8 of the
+// result's norm, on rows with a sixth of their entries 5.4e-8 -> 3.8e-8.
+// The backward pass keeps the fp32 kernel above.
 // HALF: C_in = 16 (KC = 1): the upper sixteen channels of the chunk are zero in the filter.
 // Operands of one 32-channel chunk of a round (up to RB consecutive 16-pair blocks of ONE tap), fetched one chunk ahead
 // of their use.
@@ -1330,7 +1327,7 @@ struct ChunkRegs {
 };
 
 template <int KC /* C_in / 32 */, int NB /* C_out / 16 */, int HALF = 0>
-__global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma_split(int taps, long long nnz_in,
+__global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_split(int taps, long long nnz_in,
                                                                const float* __restrict__ feats,
                                                                const u32x4* __restrict__ ws,
                                                                const float* __restrict__ bias,
@@ -1463,15 +1460,15 @@ __global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma_split(int taps, l
                         R.a[k][1] = *(const u32x4*)(src + (16u - half0));
                     }
                 };
-                // A block = NB chains of six bf16 products per 32 input channels, smallest products first (split3); the
-                // sums of two chunks are added in fp32, and these 16 x 16 results (rows = pairs 4*gq + v, column =
-                // channel 16*cb + jj) to the fp64 accumulators (half the LDS atomics of one addition per chunk; four
-                // chunks in one fp32 chain left the parity tolerance).  Padding pairs land in the dummy row.  Blocks
-                // are guarded one by one (uniform branches).
-                f32x4 acc[RB][NB];
-                auto compute_chunk = [&](unsigned meta, const ChunkRegs<NB, RB>& R, bool first) {
+                // A block = six bf16 products per 32 input and 16 output channels (split_products).  The results of two
+                // chunks are added in fp64, and these 16 x 16 sums (rows = pairs 4*gq + v, column = channel 16*cb + jj) to
+                // the fp64 accumulators: half the LDS atomics of one addition per chunk (256^3, 64 -> 64 channels, 125
+                // taps: call 2.51 against 2.57 ms), and no rounding that one would not make (adding the two in fp32:
+                // 2.41 ms, but on rows with few entries further from 64 bits than fp32 products).  Padding pairs land in
+                // the dummy row.  Blocks are guarded one by one (uniform branches).
+                float held[RB][NB][4];
+                auto compute_chunk = [&](unsigned meta, const ChunkRegs<NB, RB>& R, const Entries& E, bool first, bool hold) {
                     const int nb = (int)((meta >> 8) & 0xffu);  // 1 .. RB
-                    constexpr int PX[6] = {2, 0, 1, 1, 0, 0}, PW[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
                     for (int k = 0; k < RB; ++k) {
                         if (k == 0 || k < nb) {  // (a round has at least one block)
@@ -1488,37 +1485,24 @@ __global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma_split(int taps, l
 #pragma unroll
                                     for (int e = 0; e < 4; ++e) part[q][e] = gq < 2 ? part[q][e] : 0u;
                             }
-                            f32x4 d[NB];
-#pragma unroll
-                            for (int cb = 0; cb < NB; ++cb) d[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                            for (int q = 0; q < 6; ++q)
-#pragma unroll
-                                for (int cb = 0; cb < NB; ++cb)
-                                    d[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                        __builtin_bit_cast(bf16x8, part[PX[q]]), __builtin_bit_cast(bf16x8, R.b[PW[q]][cb]),
-                                        d[cb], 0, 0, 0);
-#pragma unroll
-                            for (int cb = 0; cb < NB; ++cb)
-#pragma unroll
-                                for (int v = 0; v < 4; ++v) acc[k][cb][v] = first ? d[cb][v] : acc[k][cb][v] + d[cb][v];
-                        }
-                    }
-                };
-                auto add_round = [&](unsigned meta, const Entries& E) {
-                    const int nb = (int)((meta >> 8) & 0xffu);
-#pragma unroll
-                    for (int k = 0; k < RB; ++k) {
-                        if (k == 0 || k < nb) {
                             const unsigned o[4] = {E.out[k].x, E.out[k].y, E.out[k].z, E.out[k].w};
+                            unsigned at[4];
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                const unsigned at = (o[v] >> kPairRowShift) * (unsigned)(CS * sizeof(double)) + lane_off;
+                            for (int v = 0; v < 4; ++v) at[v] = (o[v] >> kPairRowShift) * (unsigned)(CS * sizeof(double)) + lane_off;
 #pragma unroll
-                                for (int cb = 0; cb < NB; ++cb)
-                                    __hip_atomic_fetch_add((__attribute__((address_space(3))) double*)(size_t)at + cb * 16,
-                                                           (double)acc[k][cb][v], __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                            for (int cb = 0; cb < NB; ++cb) {
+                                f32x4 large, small;
+                                split_products(part, R.b[0][cb], R.b[1][cb], R.b[2][cb], large, small);
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) {
+                                    const float d = large[v] + small[v];
+                                    if (hold)
+                                        held[k][cb][v] = d;
+                                    else
+                                        __hip_atomic_fetch_add((__attribute__((address_space(3))) double*)(size_t)at[v] + cb * 16,
+                                                               first ? (double)d : (double)held[k][cb][v] + (double)d,
+                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                                }
                             }
                         }
                     }
@@ -1562,8 +1546,7 @@ __global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma_split(int taps, l
                                     load_chunk(m0, in0, kc + 1, next);
                                 else
                                     load_chunk(m1, in1, 0, next);
-                                compute_chunk(m0, now, kc % 2 == 0);
-                                if (kc % 2 == 1 || kc + 1 == KC) add_round(m0, e0);
+                                compute_chunk(m0, now, e0, kc % 2 == 0, kc % 2 == 0 && kc + 1 < KC);
                             }
                             e0 = e1;
                             e1 = e2;

@@ -24,7 +24,6 @@
 
 namespace scnn {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kQuadWaves = 4;            // waves per workgroup

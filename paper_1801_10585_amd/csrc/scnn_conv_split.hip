@@ -3,10 +3,9 @@
 // The bf16 matrix instructions of gfx950 do sixteen times the multiply-adds of the fp32 ones.  An fp32 number is the
 // exact sum of three bf16 numbers, h + m + l, each the rounding of what the ones before it leave (8 significant bits
 // each), so a product of two fp32 numbers is the sum of nine bf16 products, every one of them exact in fp32.  Six are
-// multiplied, smallest first: x_l w_h + x_h w_l + x_m w_m + x_m w_h + x_h w_m + x_h w_h; the three left out are below
-// 2^-24 of the product together.  A (tap, 32-channel chunk) of a group of sites is then six instructions per 16 output
-// channels, each of which rounds its fp32 sum once, where the fp32 instructions round after every channel: the
-// result is closer to the exact sum than theirs, at 2.7 times their rate.
+// multiplied (split_products); the three left out are below 2^-23 of the product together.  A (tap, 32-channel chunk) of
+// a group of sites is then six instructions per 16 output channels at 2.7 times the fp32 instructions' rate, and the
+// result is no further from the exact sum than theirs, on full rows and on rows with few entries.
 //
 // The rest follows k_conv_quad: a wave owns consecutive candidate sites, sorts them by neighbour pattern, and
 // multiplies groups of similar sites against the taps that any site of the group has; here a group is the sixteen
@@ -17,9 +16,6 @@
 #include "scnn_internal.h"
 
 namespace scnn {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kSplitSites = 256;             // candidate sites per unit of work (a workgroup of four waves)
 constexpr int kSplitSteal = 2;               // XCDs after its own that a workgroup helps once its own has nothing left
@@ -283,8 +279,8 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
             unsigned off_1 = tab_at(e_1);
             unsigned e_raw = s_step[2];
             int step = 0;
-            // One step = one group against one pass: six products per 16 output channels, smallest first
-            // ((l,h) (h,l) (m,m) (m,h) (h,m) (h,h)), and their sum added to the group's.
+            // One step = one group against one pass: six products per 16 output channels (split_products), and their sum
+            // added to the group's.
             auto run_step = [&](acc_t (&ac)[NB][4]) {
                 // (the copies and the barrier keep the loads in front of the products: left alone, the compiler loads
                 // straight into the operands, the last of them only after its last product)
@@ -300,22 +296,12 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
                 e_raw = s_step[step + 3];
                 ++step;
                 __builtin_amdgcn_sched_barrier(0);
-                constexpr int PX[6] = {2, 0, 1, 1, 0, 0}, PW[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-                for (int n2 = 0; n2 < NB; n2 += 2) {
-                    f32x4 d[2];
+                for (int nb = 0; nb < NB; ++nb) {
+                    f32x4 large, small;
+                    split_products(a, bw[0][nb], bw[1][nb], bw[2][nb], large, small);
 #pragma unroll
-                    for (int nb = 0; nb < 2; ++nb) d[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int q = 0; q < 6; ++q)
-#pragma unroll
-                        for (int nb = 0; nb < 2; ++nb)
-                            d[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[PX[q]]),
-                                                                            __builtin_bit_cast(bf16x8, bw[PW[q]][n2 + nb]), d[nb], 0, 0, 0);
-#pragma unroll
-                    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) ac[n2 + nb][v] += (acc_t)d[nb][v];
+                    for (int v = 0; v < 4; ++v) ac[nb][v] += (acc_t)(large[v] + small[v]);
                 }
             };
             for (int p = 0;;) {

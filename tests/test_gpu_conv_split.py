@@ -48,8 +48,9 @@ def test_split_convolution_edges(extent, batch, c_in, c_out, ksize, density):
 def test_split_convolution_over_wide_magnitudes(path, c_in, c_out, k):
     """Rows and weights spread over many binades, on the quad and on the pair-list form.  With A = the sum of a response's
     product magnitudes and u = 2^-24: per (tap, 32-channel chunk) the parts' products left out are below 2 u A together,
-    the six instructions and the additions of their sums round by at most 4 u A; then at most taps fp32 additions where
-    the outer sums are fp32 (32 channels, quad form), else one rounding: (7 + taps) u A or 7 u A, whatever the magnitudes.
+    the instructions and the addition of their two sums round by at most 7 u A (the large products' 32 terms make most of
+    it); then at most taps fp32 additions where the outer sums are fp32 (32 channels, quad form), else one rounding:
+    (10 + taps) u A or 10 u A, whatever the magnitudes.
     (One of the six products left out would give 6.9e-6 A = 115 u A or more on this data.)"""
     rng = np.random.default_rng(c_in)
     ext, batch = (12, 12, 12), 2
@@ -77,8 +78,47 @@ def test_split_convolution_over_wide_magnitudes(path, c_in, c_out, k):
         mag += np.abs(x64[r]) @ np.abs(w64[t])
     worst = float((np.abs(of - ref) / np.maximum(mag, 1e-300)).max())
     say(f"split wide magnitudes {c_in}->{c_out} k={k}: worst |error| / A = {worst:.3g}")
-    assert worst <= (7 + (taps if path == 5 and c_in == 32 else 0)) * 2.0 ** -24
+    assert worst <= (10 + (taps if path == 5 and c_in == 32 else 0)) * 2.0 ** -24
     assert oc.shape[0] > 0
+
+
+@pytest.mark.parametrize("share", [1.0, 1 / 6, 1 / 40])
+@pytest.mark.parametrize("path,c_in,c_out,k", [(5, 16, 32, 3), (5, 32, 64, 3), (5, 64, 64, 3), (5, 128, 64, 3), (3, 32, 64, 5),
+                                               (3, 64, 64, 5), (3, 128, 64, 5)])
+def test_split_convolution_is_no_further_from_64_bits_than_fp32_products(path, c_in, c_out, k, share):
+    """Rows with all, a sixth (what a selection and ReLU leave) and a 40th of their entries: relative 2-norm of the error
+    over all responses.  Up to 32 taps the fp32 quad kernel's on the same data bounds it.  Where the outer sums are fp64,
+    two independent roundings to fp32 (a chunk's and the response's, 2.53e-8 each: u / sqrt(3), averaged over mantissas)
+    make 3.6e-8; what the instruction and the products left out add raises it to at most 4.9e-8 on full rows, and with
+    the few products of sparse ones to 4.0e-8."""
+    rng = np.random.default_rng(c_in + k)
+    ext, taps, p = (24, 24, 24), k ** 3, k // 2
+    coords = random_sparse_sites(rng, ext, 1, 0.1)
+    n = coords.shape[0]
+    feats = (np.abs(rng.normal(size=(n, c_in))) * (rng.random((n, c_in)) < share)).astype(np.float32)
+    w = (rng.normal(size=(taps, c_in, c_out)) * 0.2).astype(np.float32)
+    c, f, wt = (torch.from_numpy(a).cuda() for a in (coords, feats, w))
+    err = {}
+    for run in (path, 2) if k == 3 else (path,):
+        scnn.set_conv_path(run)
+        try:
+            oc, of, _ = scnn.sparse_conv_fwd(ext, 1, c, f, (k, k, k), wt)
+            kernel = scnn.last_conv_kernel()
+        finally:
+            scnn.set_conv_path(0)
+        assert kernel == {5: "k_conv_quad_split", 3: "k_conv_mfma_split", 2: "k_conv_quad"}[run]
+        grid = torch.full([e + 2 * p for e in ext], n, device="cuda")
+        grid[tuple(c[:, 1 + a].long() + p for a in range(3))] = torch.arange(n, device="cuda")
+        x64, ref = torch.cat([f.double(), torch.zeros((1, c_in), device="cuda", dtype=torch.float64)]), 0
+        o = oc.long()
+        for t, (i, j, l) in enumerate(np.ndindex(k, k, k)):
+            ref = ref + x64[grid[o[:, 1] + i, o[:, 2] + j, o[:, 3] + l]] @ wt[t].double()
+        err[run] = float((of.double() - ref).norm() / ref.norm())
+    say(f"split accuracy {c_in}->{c_out} k={k} share={share:.3f}: {err}")
+    if k == 3:
+        assert err[5] <= err[2]
+    if k == 5 or c_in > 32:
+        assert err[path] <= (4.9e-8 if share == 1 else 4.0e-8)
 
 
 @pytest.mark.parametrize("seed", range(6))
