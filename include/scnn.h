@@ -107,9 +107,11 @@ size_t sparse_conv_fwd_workspace(int ndim, const int32_t* extent, int batch, int
  * kernel also up to 16 taps on 64), in fp64 otherwise; the pair-list kernel
  * always adds them in fp64.  The quad kernel on split operands and the pair-list
  * kernel multiply on the bf16 matrix cores, both operands split into three bf16
- * numbers whose sum they are (exactly, for magnitudes from 2^-109 to 3.38e38;
- * what is smaller keeps an absolute error below 2^-134); the parts' products
- * left out are below 2^-23 of a product together, and the result is as close to
+ * numbers whose sum they are (a call with a row value or weight whose magnitude
+ * is neither 0 nor from 2^-109 up to 2^58, infinities and NaN among them,
+ * multiplies in fp32 throughout, at about half the speed); the parts'
+ * products left out are below 2^-23 of a product together, and the result is as
+ * close to
  * the exact sum as fp32 products' or closer, on full rows and on rows that are
  * mostly zeros.  All stay
  * within 1e-5 relative + 1e-6 absolute of the exact sum on the workloads this

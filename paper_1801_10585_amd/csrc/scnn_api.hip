@@ -420,7 +420,8 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
     // with a device-resident count, nnz_in is only the capacity of the input arrays: rows past the true count are
     // never indexed, so no look-up can return them
     SCNN_TRY(launch_index_build(g, in_coords, nnz_in, (const long long*)nnz_in_dev, nnz_in, ws.occ, ws.occ_prefix,
-                                ws.ctr, in_feats, c_in, kernel == ConvKernel::kSplit ? ws.xsplit : nullptr, s));
+                                ws.ctr, kernel == ConvKernel::kSplit || kernel == ConvKernel::kPair ? in_feats : nullptr,
+                                c_in, kernel == ConvKernel::kSplit ? ws.xsplit : nullptr, ws.tap_active, s));
     timer.mark();
     const bool emit_mid = nw > kEmitSmallWords && nw <= kEmitMidWords;
     SCNN_TRY(launch_cand_dilate(g, ws.occ, ws.tap_active, ws.cand, ws.cand_prefix, emit_mid ? ws.block_sums : nullptr, s));
@@ -438,8 +439,8 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
     timer.mark();
     if (kernel == ConvKernel::kSplit) {
         timer.mark();
-        SCNN_TRY(launch_conv_split(g, ws.occ, ws.occ_prefix, nnz_in, ws.xsplit, c_in, ws.wsplit, c_out, bias,
-                                   ws.tap_active, ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, ws.resp,
+        SCNN_TRY(launch_conv_split(g, ws.occ, ws.occ_prefix, nnz_in, in_feats, ws.xsplit, c_in, w, ws.wsplit, c_out,
+                                   bias, ws.tap_active, ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, ws.resp,
                                    device_cu_count(), s));
         g_last_conv_kernel = "k_conv_quad_split";
     } else if (kernel == ConvKernel::kQuad) {
@@ -453,8 +454,8 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
                                    ws.cand_start, ws.tile_start, ws.rows16_start, ws.ctr, ws.pairs, ws.block_tap,
                                    ws.tile_hdr, ws.block_cap, ws.tiles_cap, nullptr, s));
         timer.mark();
-        SCNN_TRY(launch_conv_mfma_split(g, nnz_in, in_feats, c_in, ws.wsplit, c_out, bias, ws.pairs, ws.block_tap,
-                                        ws.tile_hdr, ws.ctr, ws.resp, s));
+        SCNN_TRY(launch_conv_mfma_split(g, nnz_in, in_feats, c_in, ws.wsplit, w, c_out, bias, ws.pairs,
+                                        ws.block_tap, ws.tile_hdr, ws.ctr, ws.resp, s));
         g_last_conv_kernel = "k_conv_mfma_split";
     } else {
         timer.mark();
@@ -599,7 +600,7 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
     SCNN_TRY(launch_prepare(g, w, c_out, c_in, 1, ws.c_in_pad, ws.wp, use_mfma ? ws.wb : nullptr, nullptr,
                             nullptr, ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
     SCNN_TRY(launch_index_build(g, g_coords, g_rows, nullptr, g_rows, ws.occ, ws.occ_prefix, ws.ctr, nullptr, 0,
-                                nullptr, s));
+                                nullptr, nullptr, s));
     SCNN_TRY(launch_rows_sample_bounds(g, in_coords, nnz_in, ws.cand_start, ws.tile_start, ws.ctr, s));
     SCNN_TRY(launch_bwd_sites(g, in_coords, nnz_in, ws.cand_start, ws.cand_lin, ws.rows16_start, ws.ctr, s));
     timer.mark();

@@ -1330,6 +1330,7 @@ template <int KC /* C_in / 32 */, int NB /* C_out / 16 */, int HALF = 0>
 __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_split(int taps, long long nnz_in,
                                                                const float* __restrict__ feats,
                                                                const u32x4* __restrict__ ws,
+                                                               const float* __restrict__ w,
                                                                const float* __restrict__ bias,
                                                                const unsigned* __restrict__ pairs,
                                                                const unsigned short* __restrict__ block_tap,
@@ -1355,6 +1356,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
     const int jj = lane & 15, gq = lane >> 4;
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
     const int n_tiles = (int)ctr->n_tiles;
+    const bool odd = __builtin_amdgcn_readfirstlane(ctr->odd) != 0;
     // LDS byte address of this lane's channel in accumulator row 0 (a generic pointer to LDS carries the LDS
     // address in its low 32 bits); accumulator addresses are formed once per block, at load time
     const unsigned lane_off = (unsigned)(size_t)s_c + (unsigned)jj * (unsigned)sizeof(double);
@@ -1421,7 +1423,47 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
             __syncthreads();
             const int r_lo = __builtin_amdgcn_readfirstlane(s_wlo[wave]);
             const int my_rounds = __builtin_amdgcn_readfirstlane(s_wlo[wave + 1]) - r_lo;
-            if (my_rounds > 0) {
+            if (odd && my_rounds > 0) {
+                // values that the parts do not hold: fp32 instructions on rows and weights as they are (not pipelined)
+#pragma unroll 1
+                for (int j = 0; j < my_rounds; ++j) {
+                    const unsigned meta = __builtin_amdgcn_readfirstlane(s_rmeta[r_lo + j]);
+                    const int first = (int)(meta & 0xffu), nb = (int)((meta >> 8) & 0xffu), t = (int)((meta >> 16) & 0xffu);
+#pragma unroll 1
+                    for (int k = 0; k < nb; ++k) {
+                        unsigned in = s_flat[16 * (first + k) + jj] & kPairInMask;
+                        asm volatile("" : "+v"(in));  // (as in rows_of)
+                        const uint4 out = *(const uint4*)(s_flat + 16 * (first + k) + 4 * gq);
+                        const unsigned o[4] = {out.x, out.y, out.z, out.w};
+#pragma unroll 1
+                        for (int kc = 0; kc < KC; ++kc) {
+                            const bool real = !HALF || gq < 2;  // (C_in = 16)
+                            const int ch = kc * 32 + (real ? gq * 8 : 0);
+                            const float* row = feats + (size_t)in * C_IN + ch;
+                            f32x4 d[NB];
+#pragma unroll
+                            for (int cb = 0; cb < NB; ++cb) d[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) {
+                                const float x = real ? row[i] : 0.0f;
+#pragma unroll
+                                for (int cb = 0; cb < NB; ++cb) {
+                                    const float wv = real ? w[((size_t)t * C_IN + ch + i) * C_OUT + cb * 16 + jj] : 0.0f;
+                                    d[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wv, d[cb], 0, 0, 0);
+                                }
+                            }
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const unsigned at = (o[v] >> kPairRowShift) * (unsigned)(CS * sizeof(double)) + lane_off;
+#pragma unroll
+                                for (int cb = 0; cb < NB; ++cb)
+                                    __hip_atomic_fetch_add((__attribute__((address_space(3))) double*)(size_t)at + cb * 16,
+                                                           (double)d[cb][v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            }
+                        }
+                    }
+                }
+            } else if (my_rounds > 0) {
                 // The wave's pipeline, per round: list entry (LDS) -> pair entries of its blocks (LDS) -> operands
                 // (global, one 32-channel chunk at a time) -> compute.  Each step is issued a round (operands: a
                 // chunk) before its result is needed, so that no LDS or memory round trip sits between two chunks'
@@ -1479,7 +1521,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
                                 x[1][e] = half0 ? R.a[k][0][e] : R.a[k][1][e];
                             }
                             split8(x, part);
-                            if (HALF) {  // absent channels: 0 against 0, also where a row holds infinities
+                            if (HALF) {  // absent channels: 0
 #pragma unroll
                                 for (int q = 0; q < 3; ++q)
 #pragma unroll
@@ -1612,7 +1654,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
 
 template <int KC, int NB, int HALF = 0>
 static hipError_t launch_conv_mfma_split_t(int taps, long long nnz_in, const float* feats, const u32x4* ws,
-                                           const float* bias,
+                                           const float* w, const float* bias,
                                      const unsigned* pairs, const unsigned short* block_tap, const uint2* tile_hdr,
                                      Counters* ctr, float* resp, hipStream_t s) {
     const size_t lds = conv_mfma_lds_bytes(NB * 16);
@@ -1626,8 +1668,7 @@ static hipError_t launch_conv_mfma_split_t(int taps, long long nnz_in, const flo
     if (per_cu > 4) per_cu = 4;    // 16 waves per CU
     const int grid = (device_cu_count() * per_cu + kXcds - 1) / kXcds * kXcds;  // one span of tiles per XCD
     hipLaunchKernelGGL((k_conv_mfma_split<KC, NB, HALF>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, ws,
-                       bias,
-                       pairs, block_tap, tile_hdr, ctr, resp);
+                       w, bias, pairs, block_tap, tile_hdr, ctr, resp);
     return hipGetLastError();
 }
 
@@ -1657,12 +1698,12 @@ hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats,
 }
 
 hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
-                                  int c_out, const float* bias, const unsigned* pairs,
+                                  const float* w, int c_out, const float* bias, const unsigned* pairs,
                                   const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
                                   hipStream_t s) {
 #define SCNN_MFMA_CASE(KC_, NB_)                                                                                  \
     if (c_in == KC_ * 32 && c_out == NB_ * 16)                                                                    \
-        return launch_conv_mfma_split_t<KC_, NB_>(g.T, nnz_in, feats, (const u32x4*)ws, bias, pairs, block_tap,   \
+        return launch_conv_mfma_split_t<KC_, NB_>(g.T, nnz_in, feats, (const u32x4*)ws, w, bias, pairs, block_tap,   \
                                                   tile_hdr, ctr, resp, s);
     SCNN_MFMA_CASE(1, 1) SCNN_MFMA_CASE(1, 2) SCNN_MFMA_CASE(1, 3) SCNN_MFMA_CASE(1, 4)
     SCNN_MFMA_CASE(2, 1) SCNN_MFMA_CASE(2, 2) SCNN_MFMA_CASE(2, 3) SCNN_MFMA_CASE(2, 4)
@@ -1671,7 +1712,7 @@ hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* 
 #undef SCNN_MFMA_CASE
 #define SCNN_MFMA_HALF(NB_)                                                                                       \
     if (c_in == 16 && c_out == NB_ * 16)                                                                          \
-        return launch_conv_mfma_split_t<1, NB_, 1>(g.T, nnz_in, feats, (const u32x4*)ws, bias, pairs, block_tap,  \
+        return launch_conv_mfma_split_t<1, NB_, 1>(g.T, nnz_in, feats, (const u32x4*)ws, w, bias, pairs, block_tap,  \
                                                    tile_hdr, ctr, resp, s);
     SCNN_MFMA_HALF(1) SCNN_MFMA_HALF(2) SCNN_MFMA_HALF(3) SCNN_MFMA_HALF(4)
 #undef SCNN_MFMA_HALF

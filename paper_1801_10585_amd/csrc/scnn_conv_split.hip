@@ -2,10 +2,11 @@
 //
 // The bf16 matrix instructions of gfx950 do sixteen times the multiply-adds of the fp32 ones.  An fp32 number is the
 // exact sum of three bf16 numbers, h + m + l, each the rounding of what the ones before it leave (8 significant bits
-// each), so a product of two fp32 numbers is the sum of nine bf16 products, every one of them exact in fp32.  Six are
-// multiplied (split_products); the three left out are below 2^-23 of the product together.  A (tap, 32-channel chunk) of
-// a group of sites is then six instructions per 16 output channels at 2.7 times the fp32 instructions' rate, and the
-// result is no further from the exact sum than theirs, on full rows and on rows with few entries.
+// each; split_exact says for which numbers), so a product of two fp32 numbers is the sum of nine bf16 products, every one
+// of them exact in fp32.  Six are multiplied (split_products); the three left out are below 2^-23 of the product
+// together.  A (tap, 32-channel chunk) of a group of sites is then six instructions per 16 output channels at 2.7 times
+// the fp32 instructions' rate, and the result is no further from the exact sum than theirs, on full rows and on rows with
+// few entries.
 //
 // The rest follows k_conv_quad: a wave owns consecutive candidate sites, sorts them by neighbour pattern, and
 // multiplies groups of similar sites against the taps that any site of the group has; here a group is the sixteen
@@ -47,13 +48,14 @@ __host__ __device__ constexpr int split_waves_per_simd(int nb, int acc64) { retu
 // 437 -> 218 us at 731 k candidates, 144 -> 80 at 146 k; one-wave units of 64 / 128 sites took 295 / 243 at 731 k.
 // NCH = 32-channel chunks of the input; NB = blocks of 16 output channels (2 or 4);
 // ACC64: sums over taps and chunks in fp64, else fp32; K3 = 3x3x3 filter (its loops are straight code).
-template <int NCH, int NB, int ACC64, int K3>
-__global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_quad_split(
+// ODD: values that the parts do not hold (split_exact) are multiplied on fp32 instructions.
+template <int NCH, int NB, int ACC64, int K3, int ODD>
+__device__ __forceinline__ void split_units(
     Geom g, const unsigned long long* __restrict__ occ, const unsigned* __restrict__ occ_prefix, long long nnz_in,
-    const unsigned short* __restrict__ xs, const u32x4* __restrict__ ws, const float* __restrict__ bias, int c_out,
-    int col0, int c_out_all, const int* __restrict__ tap_active, const unsigned* __restrict__ cand_lin,
-    const int* __restrict__ cand_start, const int* __restrict__ tile_start, Counters* __restrict__ ctr,
-    float* __restrict__ resp) {
+    const float* __restrict__ feats, const unsigned short* __restrict__ xs, int c_in, const float* __restrict__ w,
+    const u32x4* __restrict__ ws, const float* __restrict__ bias, int c_out, int col0, int c_out_all,
+    const unsigned* __restrict__ cand_lin, const int* __restrict__ cand_start, const int* __restrict__ tile_start,
+    Counters* __restrict__ ctr, float* __restrict__ resp, int n_tiles, unsigned act_mask) {
     constexpr int NS = 4;                                // groups per wave: wave, wave + 4, ..
     constexpr unsigned ROWB = 192;                       // bytes of a row's chunk, split
     typedef typename std::conditional<ACC64 != 0, double, float>::type acc_t;
@@ -73,10 +75,9 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)xs, 0, (int)(nnz_in * (long long)(NCH * ROWB)), 0x00020000);
     const unsigned plane = (unsigned)nnz_in * ROWB;      // of one chunk
-    const unsigned act_mask = (unsigned)__ballot(lane < T && tap_active[lane < T ? lane : 0] != 0);
 
     // order of the units: as in k_conv_quad (workgroup i runs on XCD i % kXcds; an XCD owns chunks of consecutive units)
-    const int n_tiles = (int)ctr->n_tiles, n_un = (n_tiles + 1) / 2;
+    const int n_un = (n_tiles + 1) / 2;
     const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, per_xcd = gridDim.x / kXcds;
     const int n_chunks = n_un >= kXcds * kSplitChunks * kSplitChunkMin ? kSplitChunks : 1;
     const int chunk = n_un > 0 ? (n_un + kXcds * n_chunks - 1) / (kXcds * n_chunks) : 1;
@@ -246,7 +247,51 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[s][nb][v] = (acc_t)0;
 
-        if (n_pass > 0) {
+        if constexpr (ODD) {
+            // ---- the same walk on fp32 instructions, rows and weights as they are, and only the sums of (site, tap) pairs
+            //      that exist added, so that infinities and NaN reach what they belong to.  Not pipelined: 32 -> 64
+            //      channels on 128^3 x 4, whole call 830 us against 442.
+#pragma unroll 1
+            for (int p = 0; p < n_pass; ++p) {
+                const unsigned info = __builtin_amdgcn_readfirstlane(s_pass[p]);
+                const int t = (int)(info & 0xffu), ch = (int)((info >> 8) & 0xffu) * 32 + (lane >> 4) * 8;
+                float wv[NB][8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const int oc = nb * 16 + (lane & 15);
+                        wv[nb][i] = ch < c_in && oc < c_out ? w[((size_t)t * c_in + ch + i) * c_out_all + col0 + oc] : 0.0f;
+                    }
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    if (!(info & (0x10000u << s))) continue;
+                    const unsigned* at = s_tab + t * kSplitSites + (s * 4 + wave) * 16;
+                    const unsigned o = at[lane & 15];
+                    float4 x[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+                    if (o < plane && ch < c_in) {
+                        const float4* row = (const float4*)(feats + (size_t)(o / ROWB) * c_in + ch);
+                        x[0] = row[0];
+                        x[1] = row[1];
+                    }
+                    const float xv[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
+                    f32x4 d[NB];
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) d[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+                            d[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], wv[nb][i], d[nb], 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const bool pair = at[4 * (lane >> 4) + v] < plane;
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) acc[s][nb][v] += pair ? (acc_t)d[nb][v] : (acc_t)0;
+                    }
+                }
+            }
+        } else if (n_pass > 0) {
             // ---- the walk.  Pipeline per step: list entry two steps ahead (LDS), the group's neighbour offsets one
             //      step ahead (LDS), the gathered rows one step ahead (buffer loads); per pass: the wave's share of the
             //      weights one pass ahead.
@@ -386,6 +431,26 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
     }
 }
 
+// (two copies of the loop: with the fp32 walk as a branch inside one, its operands' registers cost the other 3-5 %)
+template <int NCH, int NB, int ACC64, int K3>
+__global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_quad_split(
+    Geom g, const unsigned long long* __restrict__ occ, const unsigned* __restrict__ occ_prefix, long long nnz_in,
+    const float* __restrict__ feats, const unsigned short* __restrict__ xs, int c_in, const float* __restrict__ w,
+    const u32x4* __restrict__ ws, const float* __restrict__ bias, int c_out, int col0, int c_out_all,
+    const int* __restrict__ tap_active, const unsigned* __restrict__ cand_lin, const int* __restrict__ cand_start,
+    const int* __restrict__ tile_start,
+    Counters* __restrict__ ctr, float* __restrict__ resp) {
+    // (with the flag: one wait for all three)
+    const int n_tiles = (int)ctr->n_tiles, T = K3 ? 27 : g.T, lane = threadIdx.x & 63;
+    const unsigned act_mask = (unsigned)__ballot(lane < T && tap_active[lane < T ? lane : 0] != 0);
+    if (__builtin_amdgcn_readfirstlane(ctr->odd))
+        split_units<NCH, NB, ACC64, K3, 1>(g, occ, occ_prefix, nnz_in, feats, xs, c_in, w, ws, bias, c_out, col0, c_out_all,
+                                           cand_lin, cand_start, tile_start, ctr, resp, n_tiles, act_mask);
+    else
+        split_units<NCH, NB, ACC64, K3, 0>(g, occ, occ_prefix, nnz_in, feats, xs, c_in, w, ws, bias, c_out, col0, c_out_all,
+                                           cand_lin, cand_start, tile_start, ctr, resp, n_tiles, act_mask);
+}
+
 bool conv_split_supported(const Geom& g, int c_in, int c_out, long long nnz_in) {
     const bool shape = (c_in == 16 || c_in == 24 || c_in == 32 || c_in == 40 || c_in == 48 || c_in == 64 || c_in == 96 ||
                         c_in == 128) &&
@@ -395,10 +460,11 @@ bool conv_split_supported(const Geom& g, int c_in, int c_out, long long nnz_in) 
 
 template <int NCH, int NB, int ACC64, int K3>
 static hipError_t launch_conv_split_t(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix,
-                                      long long nnz_in, const unsigned short* xs, const unsigned short* ws,
-                                      const float* bias, int c_out, int col0, int c_out_all, const int* tap_active,
-                                      const unsigned* cand_lin, const int* cand_start, const int* tile_start,
-                                      Counters* ctr, float* resp, int cus, hipStream_t s) {
+                                      long long nnz_in, const float* feats, const unsigned short* xs, int c_in,
+                                      const float* w, const unsigned short* ws, const float* bias, int c_out, int col0,
+                                      int c_out_all, const int* tap_active, const unsigned* cand_lin,
+                                      const int* cand_start, const int* tile_start, Counters* ctr, float* resp, int cus,
+                                      hipStream_t s) {
     const size_t lds = (size_t)split_lds_words(g.T, NCH, NB) * 4;
     hipError_t e = hipFuncSetAttribute((const void*)k_conv_quad_split<NCH, NB, ACC64, K3>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -408,15 +474,16 @@ static hipError_t launch_conv_split_t(const Geom& g, const unsigned long long* o
     while (per_cu > 1 && (size_t)per_cu * lds > 160 * 1024) --per_cu;
     const int grid = (cus * per_cu + kXcds - 1) / kXcds * kXcds;
     hipLaunchKernelGGL((k_conv_quad_split<NCH, NB, ACC64, K3>), dim3(grid), dim3(256), lds, s, g, occ, occ_prefix,
-                       nnz_in, xs, (const u32x4*)ws, bias, c_out, col0, c_out_all, tap_active, cand_lin, cand_start,
-                       tile_start, ctr, resp);
+                       nnz_in, feats, xs, c_in, w, (const u32x4*)ws, bias, c_out, col0, c_out_all, tap_active, cand_lin,
+                       cand_start, tile_start, ctr, resp);
     return hipGetLastError();
 }
 
 hipError_t launch_conv_split(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix, long long nnz_in,
-                             const unsigned short* xs, int c_in, const unsigned short* ws, int c_out, const float* bias,
-                             const int* tap_active, const unsigned* cand_lin, const int* cand_start,
-                             const int* tile_start, Counters* ctr, float* resp, int cus, hipStream_t s) {
+                             const float* feats, const unsigned short* xs, int c_in, const float* w,
+                             const unsigned short* ws, int c_out, const float* bias, const int* tap_active,
+                             const unsigned* cand_lin, const int* cand_start, const int* tile_start, Counters* ctr,
+                             float* resp, int cus, hipStream_t s) {
     const int nch = (c_in + 31) / 32;
     const bool k3 = g.K[0] == 3 && g.K[1] == 3 && g.K[2] == 3;
     for (int col0 = 0; col0 < c_out; col0 += 64) {
@@ -424,7 +491,7 @@ hipError_t launch_conv_split(const Geom& g, const unsigned long long* occ, const
         const unsigned short* ws_g = ws + (size_t)(col0 >> 6) * split_filter_elems(g.T, c_in);
         const float* bias_g = bias ? bias + col0 : nullptr;
         hipError_t e = hipErrorInvalidValue;
-#define SCNN_SPLIT_ARGS g, occ, occ_prefix, nnz_in, xs, ws_g, bias_g, cg, col0, c_out, tap_active, cand_lin, cand_start, tile_start, ctr, resp, cus, s
+#define SCNN_SPLIT_ARGS g, occ, occ_prefix, nnz_in, feats, xs, c_in, w, ws_g, bias_g, cg, col0, c_out, tap_active, cand_lin, cand_start, tile_start, ctr, resp, cus, s
 #define SCNN_SPLIT_CASE(CH, ACC)                                                                                      \
     if (nch == CH) {                                                                                                  \
         if (cg > 32)                                                                                                  \

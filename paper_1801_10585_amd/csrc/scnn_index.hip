@@ -190,31 +190,40 @@ hipError_t launch_exclusive_scan(unsigned* vals, long long capacity, long long n
 // channels of a part are one 16-byte load, and rows are 192 bytes apart whatever the channel count (sixteen rows to
 // sixteen lanes take 33 clocks of a load then, 58 where the distance is a multiple of 128).  Done by extra workgroups of the index build
 // (as a launch of its own 5 us more); bound by memory: 4 bytes read and 6 written per value, 226 k rows of 32 channels
-// in 18 us (4 TB/s).
+// in 18 us (4 TB/s).  Also notes whether all values and all taps are split_exact, which is all that the pair-list kernel
+// asks for (xs null: it splits the rows itself).
 __device__ inline void split_rows(const float* __restrict__ feats, long long n, long long n_cap, int c_in,
-                                  unsigned short* __restrict__ xs, int block, int n_blocks) {
+                                  unsigned short* __restrict__ xs, const int* __restrict__ tap_active, int taps,
+                                  Counters* ctr, int block, int n_blocks) {
     const int nch = (c_in + 31) / 32, per_row = nch * 4;  // pieces of eight channels
     const long long total = n * per_row;
+    unsigned least = ~0u, most = 0;  // of the values' magnitudes (bits), zeros left out of the least
     for (long long i = (long long)block * blockDim.x + threadIdx.x; i < total; i += (long long)n_blocks * blockDim.x) {
         const long long row = i / per_row;
         const int p = (int)(i - row * per_row), chunk = p >> 2, piece = p & 3, c0 = chunk * 32 + piece * 8;
-        float v[8];
-        const float4* src = (const float4*)(feats + row * c_in + c0);
+        const u32x4* src = (const u32x4*)(feats + row * c_in + c0);
+        u32x4 x[2], part[3];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (c0 + 4 * q < c_in) f = src[q];
-            v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
+            x[q] = u32x4{0u, 0u, 0u, 0u};
+            if (c0 + 4 * q < c_in) x[q] = src[q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const unsigned u = x[q][e] & 0x7fffffffu;
+                least = min(least, u - 1u);
+                most = max(most, u);
+            }
         }
-        unsigned short part[3][8];
+        if (!xs) continue;
+        split8(x, part);
+        u32x4* dst = (u32x4*)(xs + (chunk * n_cap + row) * 96 + piece * 8);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) split3(v[e], part[0][e], part[1][e], part[2][e]);
-        uint4* dst = (uint4*)(xs + (chunk * n_cap + row) * 96 + piece * 8);
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            dst[k * 4] = make_uint4(part[k][0] | (unsigned)part[k][1] << 16, part[k][2] | (unsigned)part[k][3] << 16,
-                                    part[k][4] | (unsigned)part[k][5] << 16, part[k][6] | (unsigned)part[k][7] << 16);
+        for (int k = 0; k < 3; ++k) dst[k * 4] = part[k];
     }
+    bool odd = least < kSplitLeast - 1u || most >= kSplitEnd;
+    if (block == n_blocks - 1)
+        for (int t = threadIdx.x; t < taps; t += blockDim.x) odd |= (tap_active[t] & kTapOdd) != 0;
+    if (odd) atomicOr(&ctr->odd, 1u);
 }
 
 // One thread per input row: set the row's bit; the first row of each word
@@ -225,12 +234,14 @@ __global__ __launch_bounds__(256) void k_index_build(Geom g, const int32_t* __re
                                                      unsigned long long* __restrict__ occ,
                                                      unsigned* __restrict__ occ_prefix, Counters* ctr,
                                                      int index_blocks, const float* __restrict__ feats, int c_in,
-                                                     unsigned short* __restrict__ xs) {
+                                                     unsigned short* __restrict__ xs,
+                                                     const int* __restrict__ tap_active) {
     long long n = n_dev ? *n_dev : n_imm;
     if (n > n_cap) n = n_cap;  // a device-resident count never reaches past the arrays
     if (n < 0) n = 0;
     if ((int)blockIdx.x >= index_blocks) {
-        split_rows(feats, n, n_cap, c_in, xs, (int)blockIdx.x - index_blocks, (int)gridDim.x - index_blocks);
+        split_rows(feats, n, n_cap, c_in, xs, tap_active, g.T, ctr, (int)blockIdx.x - index_blocks,
+                   (int)gridDim.x - index_blocks);
         return;
     }
     const int stride = 1 + g.ndim;
@@ -266,19 +277,19 @@ __global__ __launch_bounds__(256) void k_index_build(Geom g, const int32_t* __re
 
 hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_imm, const long long* n_dev,
                               long long n_cap, unsigned long long* occ, unsigned* occ_prefix, Counters* ctr,
-                              const float* feats, int c_in, unsigned short* xs, hipStream_t s) {
+                              const float* feats, int c_in, unsigned short* xs, const int* tap_active, hipStream_t s) {
     long long blocks = (n_cap + 255) / 256;
     if (blocks < 1) blocks = 1;
     if (blocks > 4096) blocks = 4096;
-    long long split_blocks = xs ? (n_cap * ((c_in + 31) / 32) * 4 + 255) / 256 : 0;
+    long long split_blocks = feats ? (n_cap * ((c_in + 31) / 32) * 4 + 255) / 256 : 0;
     if (split_blocks > 4096) split_blocks = 4096;
     hipLaunchKernelGGL(k_index_build, dim3((unsigned)(blocks + split_blocks)), dim3(256), 0, s, g, coords, n_imm, n_dev,
-                       n_cap, occ, occ_prefix, ctr, (int)blocks, feats, c_in, xs);
+                       n_cap, occ, occ_prefix, ctr, (int)blocks, feats, c_in, xs, tap_active);
     return hipGetLastError();
 }
 
 // Everything that has to happen before the input is indexed, in one launch.  Block t < T prepares tap t of the
-// filter: tap_active[t] = "has a non-zero weight", tap_coord[t] = its offset, and its weights in the layout of the
+// filter: tap_active[t] = "has a non-zero weight" (and kTapOdd, for the split kernels), tap_coord[t] = its offset, and its weights in the layout of the
 // convolution kernel that will run -- wb (matrix-core operand order:
 // wb[((t * KC + kc) * NB + cb) * 64 + lane][s] = w[t][kc*32 + 8*gq + s][cb*16 + jj], lane = 16*gq + jj, so that a
 // lane fetches its eight values of one (tap, kc, cb) with two 16-byte loads) or wp (fp64, rows padded to
@@ -302,9 +313,9 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
             zero_p[i] = make_uint4(0, 0, 0, 0);
         return;
     }
-    __shared__ int s_any;
+    __shared__ int s_any, s_odd;
     const int t = blockIdx.x;
-    if (threadIdx.x == 0) s_any = 0;
+    if (threadIdx.x == 0) s_any = s_odd = 0;
     __syncthreads();
     int any = 0;
     if (wq) {
@@ -339,7 +350,7 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
                     (ic < c_in && oc < cg) ? filter_at(w, g.T, c_in, c_out, adjoint, t, ic, col0 + oc) : 0.0f;
                 unsigned short* dst = ws_g + (size_t)c * nb * 1536 + cb * 512 + (i & 511);
                 split3(v, dst[0], dst[nb * 512], dst[2 * nb * 512]);
-                any |= (v != 0.0f);
+                any |= (v != 0.0f) | (split_exact(__float_as_uint(v)) ? 0 : kTapOdd);
             }
         }
     } else if (wb) {
@@ -366,10 +377,11 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
             any |= (v != 0.0f);
         }
     }
-    if (any) s_any = 1;
+    if (any & 1) s_any = 1;
+    if (any & kTapOdd) s_odd = kTapOdd;
     __syncthreads();
     if (threadIdx.x == 0) {
-        tap_active[t] = s_any;
+        tap_active[t] = s_any | s_odd;
         // tap coordinates (t0, t1, t2), one byte each: delta = coordinate - H
         tap_coord[t] = (t / (g.K[2] * g.K[1])) | (((t / g.K[2]) % g.K[1]) << 8) | ((t % g.K[2]) << 16);
     }

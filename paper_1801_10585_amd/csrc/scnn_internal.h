@@ -61,6 +61,7 @@ struct Counters {
     unsigned ticket;      // next tile of the compaction pass
     unsigned bracket_failed;  // some column's threshold lay outside its sampled bracket
     unsigned cols_done;       // columns whose selection has ended
+    unsigned odd;             // a row or weight of a split kernel is not split_exact
     // tiles handed out so far in each of the contraction kernels' tile spans (one per XCD); one counter per 128-byte line:
     // read-modify-writes on one line are served one after the other, whichever word they address
     // (two sets: the quad kernel runs once per group of 64 output channels, up to two groups)
@@ -209,20 +210,23 @@ __device__ inline bool wave_or_runs(long long word, unsigned long long& bits) {
     return lane == 0 || pw != word;
 }
 
-// Three bf16 numbers whose sum is x.  (A magnitude that would round to infinity is cut instead, and below 2^-109 the
-// last ones run into bf16's smallest number.  Infinities and NaN are the third number, which meets only the other
-// operand's first: an infinity times h, not times the m and l of either sign.)
+// Values that the split kernels multiply as three bf16 numbers: 0 and the magnitudes from 2^-109 (below, the third number
+// runs into bf16's smallest) up to 2^58 (sums of 2^10 products stay below 2^127).  A call with any other row or weight -
+// infinities and NaN among them, of which the parts' products would make NaN - multiplies in fp32 instead.
+constexpr unsigned kSplitLeast = (127u - 109u) << 23, kSplitEnd = (127u + 58u) << 23;  // (as bits)
+__host__ __device__ inline bool split_exact(unsigned bits) {
+    const unsigned u = bits & 0x7fffffffu;
+    return u == 0 || (u >= kSplitLeast && u < kSplitEnd);
+}
+
+constexpr int kTapOdd = 2;  // bit of tap_active: a weight of the tap is not split_exact
+
+// Three bf16 numbers whose sum is x (for those values).
 __device__ __forceinline__ void split3(float x, unsigned short& h, unsigned short& m, unsigned short& l) {
     auto rounded = [](float v) {
         const unsigned u = __float_as_uint(v);
-        const unsigned r = u + 0x7fffu + ((u >> 16) & 1u);
-        return ((r & 0x7f800000u) == 0x7f800000u ? u : r) >> 16;
+        return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
     };
-    if ((__float_as_uint(x) & 0x7f800000u) == 0x7f800000u) {
-        h = m = 0;
-        l = (unsigned short)((__float_as_uint(x) >> 16) | (x != x ? 0x40u : 0u));
-        return;
-    }
     const unsigned uh = rounded(x);
     const float r1 = x - __uint_as_float(uh << 16);
     const unsigned um = rounded(r1);
@@ -232,8 +236,7 @@ __device__ __forceinline__ void split3(float x, unsigned short& h, unsigned shor
     l = (unsigned short)rounded(r2);
 }
 
-// Eight fp32 values as eight h, eight m and eight l: split3 on pairs, with the conversion instruction.  (h and m are kept
-// finite; what is left of an infinity or NaN is in l.)
+// Eight fp32 values as eight h, eight m and eight l: split3 on pairs, with the conversion instruction.
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void split8(const u32x4 (&x)[2], u32x4 (&part)[3]) {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -245,9 +248,7 @@ __device__ __forceinline__ void split8(const u32x4 (&x)[2], u32x4 (&part)[3]) {
         v.y = __uint_as_float(x[i >> 1][(2 * i + 1) & 3]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            constexpr float kTop = 3.3895313892515355e38f;  // bf16's largest
-            const f32x2 u = k == 2 ? v : f32x2{__builtin_amdgcn_fmed3f(v.x, -kTop, kTop), __builtin_amdgcn_fmed3f(v.y, -kTop, kTop)};
-            const unsigned p = __builtin_bit_cast(unsigned, __builtin_convertvector(u, bf16x2));
+            const unsigned p = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
             part[k][i] = p;
             v.x -= __uint_as_float(p << 16);
             v.y -= __uint_as_float(p & 0xffff0000u);
@@ -356,8 +357,8 @@ namespace scnn {
 // scnn_index.hip
 hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_imm, const long long* n_dev,
                               long long n_cap, unsigned long long* occ, unsigned* occ_prefix, Counters* ctr,
-                              const float* feats, int c_in, unsigned short* xs /* nullable: also split the rows */,
-                              hipStream_t s);
+                              const float* feats /* nullable: rows of a split kernel */, int c_in,
+                              unsigned short* xs /* nullable: also split them */, const int* tap_active, hipStream_t s);
 // wp / wb / wq / ws: the filter in the layout of the vector / fp32 pair-list / fp32 quad / split kernels (of wb, wq and
 // ws at most the one that will run is non-null; wp is used when all three are null)
 hipError_t launch_prepare(const Geom& g, const float* w, int c_in, int c_out, int adjoint, int c_out_pad, double* wp,
@@ -416,9 +417,9 @@ hipError_t launch_pair_build(const Geom& g, const unsigned long long* occ, const
 hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats, int c_in, const float* wb, int c_out,
                             const float* bias, const unsigned* pairs, const unsigned short* block_tap,
                             const uint2* tile_hdr, Counters* ctr, float* resp, hipStream_t s);
-// (on split operands: the forward pass)
+// (on split operands: the forward pass; w = the filter as it is)
 hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
-                                  int c_out, const float* bias, const unsigned* pairs,
+                                  const float* w, int c_out, const float* bias, const unsigned* pairs,
                                   const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
                                   hipStream_t s);
 
@@ -439,7 +440,8 @@ hipError_t launch_conv_quad(const Geom& g, const unsigned long long* occ, const 
 __host__ __device__ inline size_t split_filter_elems(int taps, int c_in) { return (size_t)taps * ((c_in + 31) / 32) * (3 * 4 * 512); }
 bool conv_split_supported(const Geom& g, int c_in, int c_out, long long nnz_in);
 hipError_t launch_conv_split(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix, long long nnz_in,
-                             const unsigned short* xs, int c_in, const unsigned short* ws, int c_out, const float* bias,
+                             const float* feats, const unsigned short* xs, int c_in, const float* w,
+                             const unsigned short* ws, int c_out, const float* bias,
                              const int* tap_active, const unsigned* cand_lin, const int* cand_start,
                              const int* tile_start, Counters* ctr, float* resp, int cus, hipStream_t s);
 

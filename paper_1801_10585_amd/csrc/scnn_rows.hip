@@ -313,7 +313,7 @@ hipError_t launch_maxpool(const Geom& g, const Geom& gp, const int32_t* coords, 
                           int32_t* out_coords, float* out_feats, long long out_capacity, Counters* ctr,
                           long long* nnz_out, long long aux_imm, int aux_is_cand, hipStream_t s) {
     // occ / pbits must be zero on entry
-    hipError_t e = launch_index_build(g, coords, n_imm, n_dev, n_cap, occ, occ_prefix, ctr, nullptr, 0, nullptr, s);
+    hipError_t e = launch_index_build(g, coords, n_imm, n_dev, n_cap, occ, occ_prefix, ctr, nullptr, 0, nullptr, nullptr, s);
     if (e != hipSuccess) return e;
     long long blocks = (n_cap + 255) / 256;
     if (blocks < 1) blocks = 1;

@@ -207,3 +207,58 @@ def test_infinities_and_nan_stay_what_they_are(c_in, ksize):
     assert np.isinf(ref).any() and np.isnan(ref).any()
     assert np.array_equal(np.isnan(of), np.isnan(ref))
     assert np.array_equal(np.where(np.isinf(of), of, 0), np.where(np.isinf(ref), ref, 0))
+
+
+@pytest.mark.parametrize("path,c_in,c_out,ksize", [(5, 16, 32, (3, 3, 3)), (5, 64, 64, (3, 3, 3)), (5, 96, 48, (3, 3, 3)),
+                                                   (5, 128, 65, (3, 3, 1)), (3, 64, 64, (3, 3, 3)), (3, 32, 48, (5, 5, 5)),
+                                                   (3, 96, 32, (5, 5, 5))])
+@pytest.mark.parametrize("kind", ["row", "row_large_weights", "weight", "both", "overflow", "tiny"])
+def test_values_that_three_bf16_numbers_do_not_hold(path, c_in, c_out, ksize, kind):
+    """Infinite and NaN rows against weights of hundreds (whose middle parts are beyond 1 with either sign), an infinite
+    and a NaN weight, an infinite row against an infinite weight, finite values whose products overflow, and values below
+    2^-109: each response is what the sum over its own (row, tap) pairs gives - infinities with their sign, NaN, and finite
+    values (all but the overflow kind's) to a few roundings of its products' magnitudes."""
+    rng = np.random.default_rng(c_in + len(kind))
+    ext, t = (16, 15, 17), int(np.prod(ksize))
+    coords = random_sparse_sites(rng, ext, 1, 0.1)
+    n = coords.shape[0]
+    feats = (1.0 - rng.random((n, c_in))).astype(np.float32)
+    w = (rng.normal(size=(t, c_in, c_out)) * (700 if kind == "row_large_weights" else 0.1)).astype(np.float32)
+    if kind in ("row", "row_large_weights"):
+        feats[n // 4, c_in - 1], feats[n // 2, 0], feats[3 * n // 4, 3] = np.inf, np.nan, -np.inf
+    elif kind == "weight":
+        w[1, 2, 5], w[t - 2, c_in - 1, c_out - 1], w[t // 2, 0, 0] = np.inf, np.nan, -np.inf
+    elif kind == "both":
+        feats[n // 3, 1], feats[n // 5, c_in - 2], w[0, 1, 3], w[t - 1, c_in - 2, 4] = np.inf, -np.inf, np.inf, -np.inf
+    elif kind == "overflow":
+        feats[n // 3, 1], feats[n // 2, 2], w[:, 1, :5] = 3e38, -3e38, np.float32(1e10) * rng.normal(size=(t, 5))
+    else:
+        feats = (feats * np.float32(2.0 ** -122)).astype(np.float32)
+        w = (w * np.float32(2.0 ** 60)).astype(np.float32)
+    scnn.set_conv_path(path)
+    try:
+        oc, of, _ = scnn.sparse_conv_fwd(ext, 1, *(torch.from_numpy(a).cuda() for a in (coords, feats)), ksize,
+                                         torch.from_numpy(w).cuda())
+        assert scnn.last_conv_kernel() == ("k_conv_quad_split" if path == 5 else "k_conv_mfma_split")
+    finally:
+        scnn.set_conv_path(0)
+    p = [k // 2 for k in ksize]
+    grid = np.full([e + 2 * h for e, h in zip(ext, p)], -1)
+    grid[tuple(coords[:, 1 + a] + p[a] for a in range(3))] = np.arange(n)
+    oc, of = oc.cpu().numpy(), of.cpu().numpy()
+    ref, mag = np.zeros(of.shape), np.zeros(of.shape)
+    with np.errstate(invalid="ignore", over="ignore"):
+        for k, off in enumerate(np.ndindex(*ksize)):
+            r = grid[tuple(oc[:, 1 + a] + off[a] for a in range(3))]
+            at = r >= 0
+            ref[at] += feats[r[at]].astype(np.float64) @ w[k].astype(np.float64)
+            mag[at] += np.abs(feats[r[at]]).astype(np.float64) @ np.abs(w[k]).astype(np.float64)
+        ref = ref.astype(np.float32).astype(np.float64)
+    say(f"split special values {kind} {c_in}->{c_out} {ksize} path={path}: {int(np.isinf(ref).sum())} inf, "
+        f"{int(np.isnan(ref).sum())} NaN of {ref.size}")
+    assert kind == "tiny" or not np.isfinite(ref).all()
+    assert np.array_equal(np.isnan(of), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(of), of, 0), np.where(np.isinf(ref), ref, 0))
+    ok = np.isfinite(ref) & np.isfinite(mag)
+    # (fp32 chains of at most 32 products: half a rounding of their magnitudes on each; 27 fp32 additions of these)
+    assert ok.any() and (np.abs(of[ok] - ref[ok]) <= (32 + 27) * 2.0 ** -24 * mag[ok] + 2.0 ** -149).all()
