@@ -290,12 +290,11 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
  *     take a matrix-core kernel where in_feats is 16-byte aligned.  Filters of
  *     at most 32 taps with C_in 8, 16, 24, 32, 40, 48, 64, 96 or 128 and C_out at
  *     most 128, by the first line that applies:
- *     - C_in 96 or 128 and C_out a multiple of 16 up to 64, on workspaces of
- *       fewer than 192 tiles (1024 with C_out 16 or 32) or with an input whose
- *       split copy (6 bytes per value, C_in rounded up to 32) does not fit 2^31
- *       bytes: the pair-list kernel ("k_conv_mfma_split");
- *     - C_in = 8, workspaces of fewer than 192 tiles (512 with C_in 16 or 24), or
- *       an input whose split copy does not fit: the quad kernel on fp32 matrix
+ *     - C_in 96 or 128 and C_out a multiple of 16 up to 64: the pair-list kernel
+ *       ("k_conv_mfma_split");
+ *     - C_in = 8, workspaces of fewer than 384 tiles (512 with C_in 16 or 24;
+ *       576 and 768 in 2-D), C_in = 16 in 2-D, or an input whose split copy (6 bytes per value, C_in
+ *       rounded up to 32) does not fit 2^31 bytes: the quad kernel on fp32 matrix
  *       cores ("k_conv_quad");
  *     - the quad kernel on split operands ("k_conv_quad_split").
  *     Filters of more taps with C_in 16 or a multiple of 32 up to 128 and C_out a

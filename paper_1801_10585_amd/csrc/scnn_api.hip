@@ -24,8 +24,8 @@ enum class ConvKernel { kValu, kPair, kQuad, kSplit };
 
 // Which kernel multiplies.  The split kernel (bf16 matrix cores on split operands) takes 16 to 128 input channels and up
 // to 128 output channels (a launch per 64) with at most 32 taps; the quad kernel (fp32 matrix cores) eight input
-// channels, small layers, and inputs whose split copy does not fit 31-bit offsets; the pair-list kernel filters of more
-// than 32 taps.
+// channels, small layers, and inputs whose split copy does not fit 31-bit offsets; the pair-list kernel 96 and 128 input
+// channels and filters of more than 32 taps.
 // With 8, 16 or 24 input channels the matrix cores pay only on layers of enough tiles (128 or 1024, by shape) with
 // enough output channels; narrower and smaller layers take the vector kernels (fp64 sums).
 static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long nnz_in, long long tiles_cap) {
@@ -47,19 +47,22 @@ static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long 
     const bool wide = c_in >= 32 || ((c_in == 8 || c_in == 16 || c_in == 24) && tiles_cap >= min_tiles &&
                                      ((mac >= 256 && c_out >= 24) || mac >= 384));
     if (wide) {
-        // split against quad, index build + convolution, eight samples of 64^3 shells / four of 32^3 (us): 16->32 120 /
-        // 57 against 137 / 58, 24->64 159 / 67 against 221 / 78, 32->32 124 / 59 against 186 / 71, 32->96 255 / 102
-        // against 424 / 144, 48->64 324 / 113 against 537 / 160, 64->64 330 / 114 against 538 / 158; with eight
-        // channels three quarters of a chunk are padding: 8->64 156 against 146.  On small layers a unit of 256 sites
-        // is the whole run time and the quad kernel's pieces of sixteen sites win: workspaces of 21 to 132 tiles
-        // 32->64 57-61 against 65, 64->64 90-96 against 110, 64->32 71 against 89; of 243 tiles 32->64 76 against 67,
-        // 64->64 119 against 111; 16->32 49 against 57 at 243 tiles, 57 against 56 at 527; 24->24 55 against 56 at 243,
-        // 64 against 56 at 527.  Against the pair lists: 96->32 306 / 116 against 341 / 108, 96->64 447 / 150 against
-        // 605 / 177, 128->64 626 / 197 against 856 / 228: these keep small layers of at most 32 output channels.
-        const bool small = tiles_cap < (c_in >= 32 ? 192 : 512);
-        if (pair_ok && c_in > 64 && c_out <= 32 && tiles_cap < 1024) return ConvKernel::kPair;
-        if (split_ok && !(small && quad_ok)) return ConvKernel::kSplit;
+        // Whole calls with nothing selected, us (tiles = capacity of the workspace; a call fills a third to two thirds).
+        // 96 and 128 channels: pair lists against split, 27 taps, 506 / 3593 tiles: 96->48 155 / 381 against 206 / 490,
+        // 128->64 190 / 522 against 252 / 629, 96->32 136 / 313 against 160 / 330; 0.52 to 1.01 times the split kernel's
+        // time from 39 to 5641 tiles.
         if (pair_ok && c_in > 64) return ConvKernel::kPair;
+        // Quad against split: on small layers a unit of 256 sites is the whole run time and the quad kernel's pieces of
+        // sixteen sites win.  27 taps, 226 / 352 / 506 / 3593 tiles: 32->64 91 / 123 / 138 / 315 against 90 / 120 / 123 /
+        // 248, 64->64 130 / 160 / 197 / 517 against 135 / 165 / 167 / 388; the lines cross at about 230 tiles in use.  In
+        // 2-D capacities are further above that: 25 taps, 222 tiles in use of 556, 64->64 154 against 160; 9 taps, 274 of
+        // 518, 107 against 100, 2235 of 4144, 307 against 266.  16 or 24 channels leave half or a quarter of a chunk
+        // empty: 24->64 116 against 120 at 352 tiles, 127 against 123 at 506; 16->32 97 / 103 / 200 against 100 / 101 /
+        // 188 at 352 / 506 / 3593; in 2-D, with its fewer taps, 16->32 154 against 165 at 5641 tiles (300 x 300 images).
+        // With eight channels three quarters are empty: 8->64 146 against 156 on 64^3 x 8.
+        const long long few = (c_in >= 32 ? 192 : 256) * (g.ndim == 2 ? 3 : 2);
+        const bool small = tiles_cap < few || (c_in == 16 && g.ndim == 2);
+        if (split_ok && !(small && quad_ok)) return ConvKernel::kSplit;
         if (quad_ok) return ConvKernel::kQuad;
         if (pair_ok) return ConvKernel::kPair;
     }

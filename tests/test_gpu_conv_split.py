@@ -153,7 +153,7 @@ def test_split_and_vector_kernels_agree_over_layer_sizes(seed):
 def test_inputs_beyond_the_split_kernels_offsets():
     """A layer sized for more than 2^31 / 192 rows of 32 channels runs on the fp32 quad kernel, one of the same grid sized
     for its rows on the split kernel; same responses within the parity tolerance, rows past the device count never read."""
-    ext, batch, cap = (32, 32, 32), 1, (1 << 31) // 192 + 1000   # (257 tiles: more than the small layers' 192)
+    ext, batch, cap = (40, 40, 40), 1, (1 << 31) // 192 + 1000   # (501 tiles: more than the small layers' 384)
     rng = np.random.default_rng(5)
     coords = random_sparse_sites(rng, ext, batch, 0.1)
     feats = (1.0 - rng.random((coords.shape[0], 32))).astype(np.float32)
@@ -262,3 +262,30 @@ def test_values_that_three_bf16_numbers_do_not_hold(path, c_in, c_out, ksize, ki
     ok = np.isfinite(ref) & np.isfinite(mag)
     # (fp32 chains of at most 32 products: half a rounding of their magnitudes on each; 27 fp32 additions of these)
     assert ok.any() and (np.abs(of[ok] - ref[ok]) <= (32 + 27) * 2.0 ** -24 * mag[ok] + 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("extent,tiles,c_in,c_out,k,kernel", [
+    ((48, 48, 48), 600, 96, 48, 3, "k_conv_mfma_split"),    # 96 and 128 channels: pair lists where they take the width ..
+    ((48, 48, 48), 300, 128, 64, 3, "k_conv_mfma_split"),
+    ((48, 48, 48), 600, 96, 40, 3, "k_conv_quad_split"),    # .. else as the narrower ones
+    ((48, 48, 48), 383, 64, 64, 3, "k_conv_quad"),          # small layers
+    ((48, 48, 48), 384, 64, 64, 3, "k_conv_quad_split"),
+    ((48, 48, 48), 511, 16, 32, 3, "k_conv_quad"),
+    ((48, 48, 48), 512, 16, 32, 3, "k_conv_quad_split"),
+    ((400, 400), 1000, 16, 32, 5, "k_conv_quad"),           # 16 channels in 2-D
+    ((400, 400), 575, 32, 32, 5, "k_conv_quad"),
+    ((400, 400), 576, 32, 32, 5, "k_conv_quad_split"),
+])
+def test_the_kernel_by_shape_and_size(extent, tiles, c_in, c_out, k, kernel):
+    """The library's choice on both sides of each line of its rule (workspaces of `tiles` tiles; a solid block of sites, so
+    that its candidates fit them and rows x taps does not bound them)."""
+    rng = np.random.default_rng(tiles)
+    edge = 15 if len(extent) == 3 else 72
+    coords = np.stack([np.zeros(edge ** len(extent)), *(i.reshape(-1) for i in np.indices((edge,) * len(extent)))], 1)
+    coords = np.ascontiguousarray(coords.astype(np.int32))
+    args = [torch.from_numpy(a).cuda() for a in (coords, rng.random((coords.shape[0], c_in)).astype(np.float32))]
+    w = torch.from_numpy(rng.normal(size=(k ** len(extent), c_in, c_out)).astype(np.float32)).cuda()
+    cap = (tiles - 1) * 128
+    _, _, n = scnn.sparse_conv_fwd(extent, 1, *args, (k,) * len(extent), w, cand_capacity=cap, out_capacity=cap)
+    say(f"kernel choice {extent} {tiles} tiles {c_in}->{c_out}: {scnn.last_conv_kernel()}")
+    assert int(n[2]) == 0 and scnn.last_conv_kernel() == kernel
