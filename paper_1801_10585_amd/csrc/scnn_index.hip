@@ -229,24 +229,12 @@ __device__ inline void split_rows(const float* __restrict__ feats, long long n, 
 // One thread per input row: set the row's bit; the first row of each word
 // records its own index as that word's prefix.  Rows outside the grid are
 // skipped and reported; a row not strictly above its predecessor is reported.
-__global__ __launch_bounds__(256) void k_index_build(Geom g, const int32_t* __restrict__ coords, long long n_imm,
-                                                     const long long* __restrict__ n_dev, long long n_cap,
-                                                     unsigned long long* __restrict__ occ,
-                                                     unsigned* __restrict__ occ_prefix, Counters* ctr,
-                                                     int index_blocks, const float* __restrict__ feats, int c_in,
-                                                     unsigned short* __restrict__ xs,
-                                                     const int* __restrict__ tap_active) {
-    long long n = n_dev ? *n_dev : n_imm;
-    if (n > n_cap) n = n_cap;  // a device-resident count never reaches past the arrays
-    if (n < 0) n = 0;
-    if ((int)blockIdx.x >= index_blocks) {
-        split_rows(feats, n, n_cap, c_in, xs, tap_active, g.T, ctr, (int)blockIdx.x - index_blocks,
-                   (int)gridDim.x - index_blocks);
-        return;
-    }
+__device__ __forceinline__ void index_rows(const Geom& g, const int32_t* __restrict__ coords, long long n, int blocks,
+                                           unsigned long long* __restrict__ occ, unsigned* __restrict__ occ_prefix,
+                                           Counters* ctr) {
     const int stride = 1 + g.ndim;
     const int lane = threadIdx.x & 63;
-    for (long long base = (long long)blockIdx.x * blockDim.x; base < n; base += (long long)index_blocks * blockDim.x) {
+    for (long long base = (long long)blockIdx.x * blockDim.x; base < n; base += (long long)blocks * blockDim.x) {
         const long long r = base + threadIdx.x;
         long long key = -1;
         if (r < n) {
@@ -275,16 +263,52 @@ __global__ __launch_bounds__(256) void k_index_build(Geom g, const int32_t* __re
     }
 }
 
+// A device-resident count never reaches past the arrays.
+__device__ __forceinline__ long long row_count(long long n_imm, const long long* __restrict__ n_dev, long long n_cap) {
+    long long n = n_dev ? *n_dev : n_imm;
+    if (n > n_cap) n = n_cap;
+    return n < 0 ? 0 : n;
+}
+
+__global__ __launch_bounds__(256) void k_index_build(Geom g, const int32_t* __restrict__ coords, long long n_imm,
+                                                     const long long* __restrict__ n_dev, long long n_cap,
+                                                     unsigned long long* __restrict__ occ,
+                                                     unsigned* __restrict__ occ_prefix, Counters* ctr) {
+    index_rows(g, coords, row_count(n_imm, n_dev, n_cap), (int)gridDim.x, occ, occ_prefix, ctr);
+}
+
+// The same for the split kernels: workgroups from index_blocks on take the rows' values.
+__global__ __launch_bounds__(256) void k_index_build_split(Geom g, const int32_t* __restrict__ coords, long long n_imm,
+                                                           const long long* __restrict__ n_dev, long long n_cap,
+                                                           unsigned long long* __restrict__ occ,
+                                                           unsigned* __restrict__ occ_prefix, Counters* ctr,
+                                                           int index_blocks, const float* __restrict__ feats, int c_in,
+                                                           unsigned short* __restrict__ xs,
+                                                           const int* __restrict__ tap_active) {
+    const long long n = row_count(n_imm, n_dev, n_cap);
+    if ((int)blockIdx.x < index_blocks)
+        index_rows(g, coords, n, index_blocks, occ, occ_prefix, ctr);
+    else
+        split_rows(feats, n, n_cap, c_in, xs, tap_active, g.T, ctr, (int)blockIdx.x - index_blocks,
+                   (int)gridDim.x - index_blocks);
+}
+
 hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_imm, const long long* n_dev,
                               long long n_cap, unsigned long long* occ, unsigned* occ_prefix, Counters* ctr,
                               const float* feats, int c_in, unsigned short* xs, const int* tap_active, hipStream_t s) {
     long long blocks = (n_cap + 255) / 256;
     if (blocks < 1) blocks = 1;
     if (blocks > 4096) blocks = 4096;
-    long long split_blocks = feats ? (n_cap * ((c_in + 31) / 32) * 4 + 255) / 256 : 0;
+    if (!feats) {
+        hipLaunchKernelGGL(k_index_build, dim3((unsigned)blocks), dim3(256), 0, s, g, coords, n_imm, n_dev, n_cap, occ,
+                           occ_prefix, ctr);
+        return hipGetLastError();
+    }
+    long long split_blocks = (n_cap * ((c_in + 31) / 32) * 4 + 255) / 256;
+    if (split_blocks < 1) split_blocks = 1;
     if (split_blocks > 4096) split_blocks = 4096;
-    hipLaunchKernelGGL(k_index_build, dim3((unsigned)(blocks + split_blocks)), dim3(256), 0, s, g, coords, n_imm, n_dev,
-                       n_cap, occ, occ_prefix, ctr, (int)blocks, feats, c_in, xs, tap_active);
+    hipLaunchKernelGGL(k_index_build_split, dim3((unsigned)(blocks + split_blocks)), dim3(256), 0, s, g, coords, n_imm,
+                       n_dev, n_cap, occ, occ_prefix, ctr, (int)blocks, feats, c_in, xs, tap_active);
     return hipGetLastError();
 }
 
@@ -302,11 +326,12 @@ __device__ inline float filter_at(const float* __restrict__ w, int T, int c_in, 
     return adjoint ? w[((size_t)(T - 1 - t) * c_out + oc) * c_in + ic] : w[((size_t)t * c_in + ic) * c_out + oc];
 }
 
+enum PrepareLayout { kLayoutVector, kLayoutPair, kLayoutQuad, kLayoutSplit };  // (one kernel each: a small layer waits for it)
+template <int LAYOUT>
 __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict__ w, int c_in, int c_out, int adjoint,
-                                                 int c_out_pad, double* __restrict__ wp, float* __restrict__ wb,
-                                                 float* __restrict__ wq, unsigned short* __restrict__ ws,
-                                                 int* __restrict__ tap_active, int* __restrict__ tap_coord,
-                                                 uint4* __restrict__ zero_p, size_t zero_n16) {
+                                                 int c_out_pad, void* __restrict__ dst, int* __restrict__ tap_active,
+                                                 int* __restrict__ tap_coord, uint4* __restrict__ zero_p,
+                                                 size_t zero_n16) {
     if ((int)blockIdx.x >= g.T) {
         const size_t stride = (size_t)(gridDim.x - g.T) * blockDim.x;
         for (size_t i = (size_t)(blockIdx.x - g.T) * blockDim.x + threadIdx.x; i < zero_n16; i += stride)
@@ -315,10 +340,14 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
     }
     __shared__ int s_any, s_odd;
     const int t = blockIdx.x;
-    if (threadIdx.x == 0) s_any = s_odd = 0;
+    if (threadIdx.x == 0) {
+        s_any = 0;
+        if (LAYOUT == kLayoutSplit) s_odd = 0;
+    }
     __syncthreads();
     int any = 0;
-    if (wq) {
+    if constexpr (LAYOUT == kLayoutQuad) {
+        float* __restrict__ wq = (float*)dst;
         // operand order of the quad kernel: [tap][32-channel chunk][channel / 4][lane][channel % 4], lane = output
         // channel (modulo 32 when there are at most 32 of them); channels and columns past the real ones are zero
         // With more than 64 output channels: one such filter per group of 64, one after the other.
@@ -336,7 +365,8 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
                 any |= (v != 0.0f);
             }
         }
-    } else if (ws) {
+    } else if constexpr (LAYOUT == kLayoutSplit) {
+        unsigned short* __restrict__ ws = (unsigned short*)dst;
         // operand order of the split kernel: [tap][chunk][h | m | l][16 output channels][lane][8], lane = 16 * (channel
         // / 8) + output channel; columns past the real ones are zero.  Groups of 64 output channels one after the other.
         const int nch = (c_in + 31) / 32;
@@ -348,12 +378,13 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
                 const int ic = c * 32 + (lane >> 4) * 8 + e, oc = cb * 16 + (lane & 15);
                 const float v =
                     (ic < c_in && oc < cg) ? filter_at(w, g.T, c_in, c_out, adjoint, t, ic, col0 + oc) : 0.0f;
-                unsigned short* dst = ws_g + (size_t)c * nb * 1536 + cb * 512 + (i & 511);
-                split3(v, dst[0], dst[nb * 512], dst[2 * nb * 512]);
+                unsigned short* part = ws_g + (size_t)c * nb * 1536 + cb * 512 + (i & 511);
+                split3(v, part[0], part[nb * 512], part[2 * nb * 512]);
                 any |= (v != 0.0f) | (split_exact(__float_as_uint(v)) ? 0 : kTapOdd);
             }
         }
-    } else if (wb) {
+    } else if constexpr (LAYOUT == kLayoutPair) {
+        float* __restrict__ wb = (float*)dst;
         // C_in = 16 is laid out like one 32-channel chunk: a lane's first four values are channels 4 gq .. 4 gq + 3,
         // its other four are zero
         const bool half = c_in == 16;
@@ -368,6 +399,7 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
             any |= (v != 0.0f);
         }
     } else {
+        double* __restrict__ wp = (double*)dst;
         const int n = c_in * c_out_pad;
         for (int i = threadIdx.x; i < n; i += blockDim.x) {
             const int ic = i / c_out_pad, oc = i % c_out_pad;
@@ -378,10 +410,10 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
         }
     }
     if (any & 1) s_any = 1;
-    if (any & kTapOdd) s_odd = kTapOdd;
+    if (LAYOUT == kLayoutSplit && (any & kTapOdd)) s_odd = kTapOdd;
     __syncthreads();
     if (threadIdx.x == 0) {
-        tap_active[t] = s_any | s_odd;
+        tap_active[t] = LAYOUT == kLayoutSplit ? s_any | s_odd : s_any;
         // tap coordinates (t0, t1, t2), one byte each: delta = coordinate - H
         tap_coord[t] = (t / (g.K[2] * g.K[1])) | (((t / g.K[2]) % g.K[1]) << 8) | ((t % g.K[2]) << 16);
     }
@@ -393,8 +425,19 @@ hipError_t launch_prepare(const Geom& g, const float* w, int c_in, int c_out, in
     const size_t n16 = (zero_bytes + 15) / 16;
     size_t zb = (n16 + 255) / 256;
     if (zb > 2048) zb = 2048;
-    hipLaunchKernelGGL(k_prepare, dim3((unsigned)(g.T + zb)), dim3(256), 0, s, g, w, c_in, c_out, adjoint, c_out_pad, wp,
-                       wb, wq, ws, tap_active, tap_coord, (uint4*)zero_p, n16);
+    const dim3 grid((unsigned)(g.T + zb)), block(256);
+#define SCNN_PREPARE(LAYOUT, DST)                                                                                    \
+    hipLaunchKernelGGL(k_prepare<LAYOUT>, grid, block, 0, s, g, w, c_in, c_out, adjoint, c_out_pad, (void*)(DST), tap_active, \
+                       tap_coord, (uint4*)zero_p, n16)
+    if (wq)
+        SCNN_PREPARE(kLayoutQuad, wq);
+    else if (ws)
+        SCNN_PREPARE(kLayoutSplit, ws);
+    else if (wb)
+        SCNN_PREPARE(kLayoutPair, wb);
+    else
+        SCNN_PREPARE(kLayoutVector, wp);
+#undef SCNN_PREPARE
     return hipGetLastError();
 }
 
