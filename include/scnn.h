@@ -106,25 +106,24 @@ size_t sparse_conv_fwd_workspace(int ndim, const int32_t* extent, int batch, int
  * taps on up to 32 input channels: the r = 128 layer's 27 x 1; the fp32 quad
  * kernel also up to 16 taps on 64), in fp64 otherwise; the pair-list kernel
  * always adds them in fp64.  The quad kernel on split operands and the pair-list
- * kernel multiply on the bf16 matrix cores, both operands split into three bf16
- * numbers whose sum they are (a call with a row value or weight whose magnitude
- * is neither 0 nor from 2^-109 up to 2^58, infinities and NaN among them,
- * multiplies in fp32 throughout, at about half the speed); the parts'
- * products left out are below 2^-23 of a product together, and the result is as
- * close to
- * the exact sum as fp32 products' or closer, on full rows and on rows that are
- * mostly zeros.  All stay
- * within 1e-5 relative + 1e-6 absolute of the exact sum on the workloads this
- * library is tested on.  In general the error of a matrix-core response follows
- * the magnitudes it is summed from, not its own: about 2e-8 * A, A = the sum of
- * |w * in| over its products (fp32 roundings of partial sums of that size),
- * which the stated tolerance covers while A stays below about 50 (the r = 128
- * workload: A around 20); scnn_set_conv_path(1) sums everything in fp64 for
- * data beyond that.  The vector kernels and the quad kernels add in an order
- * fixed by the data alone and are reproducible bit for bit; the pair-list
- * kernel adds its per-tap partial sums with LDS atomics in no fixed order, so a
- * run can differ from another in the last bits of the fp64 sum, which survives
- * the rounding to fp32 for about one response in 10^8.  Responses that are
+ * kernel (C_in of 32 or more) multiply on the bf16 matrix cores, both operands
+ * split into three bf16 numbers whose sum they are (a call with a row value or
+ * weight whose magnitude is neither 0 nor from 2^-109 up to 2^58, infinities and
+ * NaN among them, multiplies in fp32 throughout, at about half the speed); the
+ * parts' products left out are below 2^-23 of a product together, and the result
+ * is as close to the exact sum as fp32 products' or closer, on full rows and on
+ * rows that are mostly zeros.  All stay within 1e-5 relative + 1e-6 absolute of
+ * the exact sum on the workloads this library is tested on.  In general the
+ * error of a matrix-core response follows the magnitudes it is summed from, not
+ * its own: about 2e-8 * A, A = the sum of |w * in| over its products (fp32
+ * roundings of partial sums of that size), which the stated tolerance covers
+ * while A stays below about 50 (the r = 128 workload: A around 20);
+ * scnn_set_conv_path(1) sums everything in fp64 for data beyond that.  The
+ * vector kernels and the quad kernels add in an order fixed by the data alone
+ * and are reproducible bit for bit; the pair-list kernel adds its per-tap
+ * partial sums with LDS atomics in no fixed order, so a run can differ from
+ * another in the last bits of the fp64 sum, which survives the rounding to fp32
+ * for about one response in 10^8.  Responses that are
  * exactly 0 are not entries (step 13).  bias (nullable, device, [c_out]) is added to the
  * entries (step 14); an entry whose biased value is exactly 0 stops being one.
  * Per (sample b, output channel oc) only the k = scnn_k_from_rho(rho_up, N)
@@ -298,7 +297,8 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
  *       cores ("k_conv_quad");
  *     - the quad kernel on split operands ("k_conv_quad_split").
  *     Filters of more taps with C_in 16 or a multiple of 32 up to 128 and C_out a
- *     multiple of 16 up to 64: the pair-list kernel.
+ *     multiple of 16 up to 64: the pair-list kernel, with C_in = 16 on fp32 matrix
+ *     cores ("k_conv_mfma").
  *     Everything else takes the vector kernels ("k_conv_valu");
  * 1 = always the vector kernels;
  * 2 = the fp32 quad kernel wherever it takes the shape, whatever the size, else

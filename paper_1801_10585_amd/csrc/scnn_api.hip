@@ -20,7 +20,7 @@ static thread_local char g_err[256] = "";
 static thread_local int g_conv_path = 0;
 static thread_local const char* g_last_conv_kernel = "";
 
-enum class ConvKernel { kValu, kPair, kQuad, kSplit };
+enum class ConvKernel { kValu, kPair, kPairSplit, kQuad, kSplit };
 
 // Which kernel multiplies.  The split kernel (bf16 matrix cores on split operands) takes 16 to 128 input channels and up
 // to 128 output channels (a launch per 64) with at most 32 taps; the quad kernel (fp32 matrix cores) eight input
@@ -30,10 +30,13 @@ enum class ConvKernel { kValu, kPair, kQuad, kSplit };
 // enough output channels; narrower and smaller layers take the vector kernels (fp64 sums).
 static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long nnz_in, long long tiles_cap) {
     if (g_conv_path == 1) return ConvKernel::kValu;
+    // (pair lists of sixteen channels: half of a split chunk would be empty.  125 taps, 96^3, fp32 against split, us:
+    // 16->32 306 against 322, 16->48 337 against 330, 16->64 370 against 358; 32^3: 180 against 189, 191 / 195, 202 / 209)
     const bool pair_ok = conv_mfma_supported(g, c_in, c_out, nnz_in);
-    if (g_conv_path == 3) return pair_ok ? ConvKernel::kPair : ConvKernel::kValu;
+    const ConvKernel pair = c_in == 16 ? ConvKernel::kPair : ConvKernel::kPairSplit;
+    if (g_conv_path == 3) return pair_ok ? pair : ConvKernel::kValu;
     const bool quad_ok = conv_quad_supported(g, c_in, c_out, nnz_in);
-    if (g_conv_path == 2) return quad_ok ? ConvKernel::kQuad : (pair_ok ? ConvKernel::kPair : ConvKernel::kValu);
+    if (g_conv_path == 2) return quad_ok ? ConvKernel::kQuad : (pair_ok ? pair : ConvKernel::kValu);
     const bool split_ok = conv_split_supported(g, c_in, c_out, nnz_in);
     if (g_conv_path == 5) return split_ok ? ConvKernel::kSplit : ConvKernel::kValu;
     // 8, 16 and 24 input channels pay for the matrix-core kernels' look-ups and lists only on layers whose rows carry
@@ -51,7 +54,7 @@ static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long 
         // 96 and 128 channels: pair lists against split, 27 taps, 506 / 3593 tiles: 96->48 155 / 381 against 206 / 490,
         // 128->64 190 / 522 against 252 / 629, 96->32 136 / 313 against 160 / 330; 0.52 to 1.01 times the split kernel's
         // time from 39 to 5641 tiles.
-        if (pair_ok && c_in > 64) return ConvKernel::kPair;
+        if (pair_ok && c_in > 64) return pair;
         // Quad against split: on small layers a unit of 256 sites is the whole run time and the quad kernel's pieces of
         // sixteen sites win.  27 taps, 226 / 352 / 506 / 3593 tiles: 32->64 91 / 123 / 138 / 315 against 90 / 120 / 123 /
         // 248, 64->64 130 / 160 / 197 / 517 against 135 / 165 / 167 / 388; the lines cross at about 230 tiles in use.  In
@@ -64,7 +67,7 @@ static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long 
         const bool small = tiles_cap < few || (c_in == 16 && g.ndim == 2);
         if (split_ok && !(small && quad_ok)) return ConvKernel::kSplit;
         if (quad_ok) return ConvKernel::kQuad;
-        if (pair_ok) return ConvKernel::kPair;
+        if (pair_ok) return pair;
     }
     return ConvKernel::kValu;
 }
@@ -256,7 +259,8 @@ struct ConvWs {
     unsigned* pairs;
     unsigned short* block_tap;
     float* wq;
-    unsigned short* wsplit;  // filter of the split and pair-list kernels
+    float* wb;               // filter of the fp32 pair-list kernel
+    unsigned short* wsplit;  // filter of the split kernels
     unsigned short* xsplit;  // input rows of the split kernel
     uint2* tile_hdr;
     long long block_cap;
@@ -316,13 +320,15 @@ static void carve_conv(void* base, const Geom& g, const Geom& gp, long long nnz_
     w->side = c.take<uint2>((size_t)w->side_cap);
     w->kernel = conv_kernel_for(g, c_in, c_out, nnz_in, w->tiles_cap);
     // pair-list kernel: every (input row, tap) gives at most one pair; a tile reserves whole blocks per active tap
-    w->block_cap = w->kernel == ConvKernel::kPair ? (long long)g.T * (cand_cap / 16 + w->tiles_cap) : 0;
+    const bool pair = w->kernel == ConvKernel::kPair || w->kernel == ConvKernel::kPairSplit;
+    w->block_cap = pair ? (long long)g.T * (cand_cap / 16 + w->tiles_cap) : 0;
     w->pairs = c.take<unsigned>((size_t)w->block_cap * 16);
     w->block_tap = c.take<unsigned short>((size_t)w->block_cap);
     w->tile_hdr = c.take<uint2>(w->block_cap ? w->tiles_cap : 0);
     w->wq = c.take<float>(w->kernel == ConvKernel::kQuad ? quad_groups(c_out) * quad_filter_floats(g.T, c_in) : 0);
     const bool split = w->kernel == ConvKernel::kSplit;
-    w->wsplit = c.take<unsigned short>(split || w->block_cap ? quad_groups(c_out) * split_filter_elems(g.T, c_in) : 0);
+    w->wb = c.take<float>(w->kernel == ConvKernel::kPair ? (size_t)g.T * round_up(c_in, 32) * c_out : 0);
+    w->wsplit = c.take<unsigned short>(split || w->kernel == ConvKernel::kPairSplit ? quad_groups(c_out) * split_filter_elems(g.T, c_in) : 0);
     w->xsplit = c.take<unsigned short>(split ? (size_t)nnz_in * round_up(c_in, 32) * 3 : 0);
     w->tmp_coords = c.take<int32_t>(pool ? (size_t)cand_cap * (1 + g.ndim) : 0);
     w->tmp_feats = c.take<float>(pool ? (size_t)cand_cap * c_out : 0);
@@ -416,15 +422,16 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
     timer.mark();
     // the matrix-core kernels load input rows 16 bytes at a time
     const ConvKernel kernel = ((uintptr_t)in_feats & 15) == 0 ? ws.kernel : ConvKernel::kValu;
-    SCNN_TRY(launch_prepare(g, w, c_in, c_out, 0, ws.c_out_pad, ws.wp, nullptr,
-                            kernel == ConvKernel::kQuad ? ws.wq : nullptr,
-                            kernel == ConvKernel::kSplit || kernel == ConvKernel::kPair ? ws.wsplit : nullptr,
+    SCNN_TRY(launch_prepare(g, w, c_in, c_out, 0, ws.c_out_pad, ws.wp,
+                            kernel == ConvKernel::kPair ? ws.wb : nullptr, kernel == ConvKernel::kQuad ? ws.wq : nullptr,
+                            kernel == ConvKernel::kSplit || kernel == ConvKernel::kPairSplit ? ws.wsplit : nullptr,
                             ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
     // with a device-resident count, nnz_in is only the capacity of the input arrays: rows past the true count are
     // never indexed, so no look-up can return them
     SCNN_TRY(launch_index_build(g, in_coords, nnz_in, (const long long*)nnz_in_dev, nnz_in, ws.occ, ws.occ_prefix,
-                                ws.ctr, kernel == ConvKernel::kSplit || kernel == ConvKernel::kPair ? in_feats : nullptr,
-                                c_in, kernel == ConvKernel::kSplit ? ws.xsplit : nullptr, ws.tap_active, s));
+                                ws.ctr,
+                                kernel == ConvKernel::kSplit || kernel == ConvKernel::kPairSplit ? in_feats : nullptr, c_in,
+                                kernel == ConvKernel::kSplit ? ws.xsplit : nullptr, ws.tap_active, s));
     timer.mark();
     const bool emit_mid = nw > kEmitSmallWords && nw <= kEmitMidWords;
     SCNN_TRY(launch_cand_dilate(g, ws.occ, ws.tap_active, ws.cand, ws.cand_prefix, emit_mid ? ws.block_sums : nullptr, s));
@@ -452,14 +459,20 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
         SCNN_TRY(launch_conv_quad(g, ws.occ, ws.occ_prefix, nnz_in, in_feats, c_in, ws.wq, c_out, bias, ws.tap_active,
                                   ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, ws.resp, cus, s));
         g_last_conv_kernel = "k_conv_quad";
-    } else if (kernel == ConvKernel::kPair) {
+    } else if (kernel == ConvKernel::kPair || kernel == ConvKernel::kPairSplit) {
         SCNN_TRY(launch_pair_build(g, ws.occ, ws.occ_prefix, nnz_in, ws.tap_active, ws.tap_coord, ws.cand_lin,
                                    ws.cand_start, ws.tile_start, ws.rows16_start, ws.ctr, ws.pairs, ws.block_tap,
                                    ws.tile_hdr, ws.block_cap, ws.tiles_cap, nullptr, s));
         timer.mark();
-        SCNN_TRY(launch_conv_mfma_split(g, nnz_in, in_feats, c_in, ws.wsplit, w, c_out, bias, ws.pairs,
-                                        ws.block_tap, ws.tile_hdr, ws.ctr, ws.resp, s));
-        g_last_conv_kernel = "k_conv_mfma_split";
+        if (kernel == ConvKernel::kPair) {
+            SCNN_TRY(launch_conv_mfma(g, nnz_in, in_feats, c_in, ws.wb, c_out, bias, ws.pairs, ws.block_tap, ws.tile_hdr,
+                                      ws.ctr, ws.resp, s));
+            g_last_conv_kernel = "k_conv_mfma";
+        } else {
+            SCNN_TRY(launch_conv_mfma_split(g, nnz_in, in_feats, c_in, ws.wsplit, w, c_out, bias, ws.pairs,
+                                            ws.block_tap, ws.tile_hdr, ws.ctr, ws.resp, s));
+            g_last_conv_kernel = "k_conv_mfma_split";
+        }
     } else {
         timer.mark();
         SCNN_TRY(launch_conv_valu(g, ws.occ, ws.occ_prefix, nnz_in, in_feats, c_in, ws.wp, c_out, ws.c_out_pad, bias,

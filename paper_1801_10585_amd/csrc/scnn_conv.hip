@@ -1315,8 +1315,7 @@ static hipError_t launch_conv_mfma_t(int taps, long long nnz_in, const float* fe
 // channels, 125 taps, 1.3 M candidates: call 3.96 -> 2.50 ms, now bound by the weights and rows that vector memory
 // returns (a round's chunk asks for 12 + 4 KB for at most two blocks); error against 64 bits 1.08e-7 -> 4.6e-8 of the
 // result's norm, on rows with a sixth of their entries 5.4e-8 -> 3.8e-8.
-// The backward pass keeps the fp32 kernel above.
-// HALF: C_in = 16 (KC = 1): the upper sixteen channels of the chunk are zero in the filter.
+// The backward pass and layers of sixteen input channels keep the fp32 kernel above.
 // Operands of one 32-channel chunk of a round (up to RB consecutive 16-pair blocks of ONE tap), fetched one chunk ahead
 // of their use.
 template <int NB, int RB>
@@ -1326,7 +1325,7 @@ struct ChunkRegs {
     u32x4 b[3][NB];   // filter in bf16 thirds (split3): lane holds w[tap][32 kc + 8 gq + i][16 cb + jj], i = 0..7
 };
 
-template <int KC /* C_in / 32 */, int NB /* C_out / 16 */, int HALF = 0>
+template <int KC /* C_in / 32 */, int NB /* C_out / 16 */>
 __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_split(int taps, long long nnz_in,
                                                                const float* __restrict__ feats,
                                                                const u32x4* __restrict__ ws,
@@ -1337,8 +1336,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
                                                                const uint2* __restrict__ tile_hdr,
                                                                Counters* __restrict__ ctr,
                                                                float* __restrict__ resp) {
-    static_assert(!HALF || KC == 1, "the half chunk stands alone");
-    constexpr int C_IN = HALF ? 16 : KC * 32, C_OUT = NB * 16, CS = C_OUT + 1 /* padded accumulator row */;
+    constexpr int C_IN = KC * 32, C_OUT = NB * 16, CS = C_OUT + 1 /* padded accumulator row */;
     constexpr int RB = NB <= 2 ? 3 : 2;  // blocks per round
     constexpr int NBP = NB > 2 ? 4 : 2;  // blocks of output channels in the filter's layout
     constexpr int NT = kConvWaves * 64;
@@ -1437,18 +1435,17 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
                         const unsigned o[4] = {out.x, out.y, out.z, out.w};
 #pragma unroll 1
                         for (int kc = 0; kc < KC; ++kc) {
-                            const bool real = !HALF || gq < 2;  // (C_in = 16)
-                            const int ch = kc * 32 + (real ? gq * 8 : 0);
+                            const int ch = kc * 32 + gq * 8;
                             const float* row = feats + (size_t)in * C_IN + ch;
                             f32x4 d[NB];
 #pragma unroll
                             for (int cb = 0; cb < NB; ++cb) d[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                             for (int i = 0; i < 8; ++i) {
-                                const float x = real ? row[i] : 0.0f;
+                                const float x = row[i];
 #pragma unroll
                                 for (int cb = 0; cb < NB; ++cb) {
-                                    const float wv = real ? w[((size_t)t * C_IN + ch + i) * C_OUT + cb * 16 + jj] : 0.0f;
+                                    const float wv = w[((size_t)t * C_IN + ch + i) * C_OUT + cb * 16 + jj];
                                     d[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wv, d[cb], 0, 0, 0);
                                 }
                             }
@@ -1496,8 +1493,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
                         for (int cb = 0; cb < NB; ++cb) R.b[q][cb] = (wt + (q * NBP + cb) * 64)[lane];
 #pragma unroll
                     for (int k = 0; k < RB; ++k) {
-                        // (C_in = 16: the lanes of the absent channels read the others' again)
-                        const char* src = (const char*)feats + (size_t)in[k] * (C_IN * 4) + (HALF ? gq & 1 : kc * 4 + gq) * 32;
+                        const char* src = (const char*)feats + (size_t)in[k] * (C_IN * 4) + (kc * 4 + gq) * 32;
                         R.a[k][0] = *(const u32x4*)(src + half0);
                         R.a[k][1] = *(const u32x4*)(src + (16u - half0));
                     }
@@ -1521,12 +1517,6 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
                                 x[1][e] = half0 ? R.a[k][0][e] : R.a[k][1][e];
                             }
                             split8(x, part);
-                            if (HALF) {  // absent channels: 0
-#pragma unroll
-                                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                                    for (int e = 0; e < 4; ++e) part[q][e] = gq < 2 ? part[q][e] : 0u;
-                            }
                             const unsigned o[4] = {E.out[k].x, E.out[k].y, E.out[k].z, E.out[k].w};
                             unsigned at[4];
 #pragma unroll
@@ -1652,7 +1642,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
     }
 }
 
-template <int KC, int NB, int HALF = 0>
+template <int KC, int NB>
 static hipError_t launch_conv_mfma_split_t(int taps, long long nnz_in, const float* feats, const u32x4* ws,
                                            const float* w, const float* bias,
                                      const unsigned* pairs, const unsigned short* block_tap, const uint2* tile_hdr,
@@ -1660,14 +1650,14 @@ static hipError_t launch_conv_mfma_split_t(int taps, long long nnz_in, const flo
     const size_t lds = conv_mfma_lds_bytes(NB * 16);
     // (set on every launch: the attribute belongs to the current device's copy of the kernel, and a flag remembering
     // that it was set would have to be kept per device and guarded between threads for the sake of a microsecond)
-    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_split<KC, NB, HALF>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_split<KC, NB>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     int per_cu = (int)((160 * 1024) / lds);
     if (per_cu < 1) per_cu = 1;
     if (per_cu > 4) per_cu = 4;    // 16 waves per CU
     const int grid = (device_cu_count() * per_cu + kXcds - 1) / kXcds * kXcds;  // one span of tiles per XCD
-    hipLaunchKernelGGL((k_conv_mfma_split<KC, NB, HALF>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, ws,
+    hipLaunchKernelGGL((k_conv_mfma_split<KC, NB>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, ws,
                        w, bias, pairs, block_tap, tile_hdr, ctr, resp);
     return hipGetLastError();
 }
@@ -1710,14 +1700,7 @@ hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* 
     SCNN_MFMA_CASE(3, 1) SCNN_MFMA_CASE(3, 2) SCNN_MFMA_CASE(3, 3) SCNN_MFMA_CASE(3, 4)
     SCNN_MFMA_CASE(4, 1) SCNN_MFMA_CASE(4, 2) SCNN_MFMA_CASE(4, 3) SCNN_MFMA_CASE(4, 4)
 #undef SCNN_MFMA_CASE
-#define SCNN_MFMA_HALF(NB_)                                                                                       \
-    if (c_in == 16 && c_out == NB_ * 16)                                                                          \
-        return launch_conv_mfma_split_t<1, NB_, 1>(g.T, nnz_in, feats, (const u32x4*)ws, w, bias, pairs, block_tap,  \
-                                                   tile_hdr, ctr, resp, s);
-    SCNN_MFMA_HALF(1) SCNN_MFMA_HALF(2) SCNN_MFMA_HALF(3) SCNN_MFMA_HALF(4)
-#undef SCNN_MFMA_HALF
     return hipErrorInvalidValue;
 }
-
 
 }  // namespace scnn

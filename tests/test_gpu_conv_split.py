@@ -192,7 +192,8 @@ def test_infinities_and_nan_stay_what_they_are(c_in, ksize):
         oc, of, _ = scnn.sparse_conv_fwd(ext, 1, torch.from_numpy(coords).to(d), torch.from_numpy(feats).to(d), ksize,
                                          torch.from_numpy(w).to(d))
         say(f"non-finite rows {c_in} {ksize}: {scnn.last_conv_kernel()}")
-        assert scnn.last_conv_kernel() == ("k_conv_quad_split" if ksize == (3, 3, 3) else "k_conv_mfma_split")
+        assert scnn.last_conv_kernel() == ("k_conv_quad_split" if ksize == (3, 3, 3) else "k_conv_mfma" if c_in == 16
+                                           else "k_conv_mfma_split")
     finally:
         scnn.set_conv_path(0)
     p = ksize[0] // 2
@@ -273,6 +274,8 @@ def test_values_that_three_bf16_numbers_do_not_hold(path, c_in, c_out, ksize, ki
     ((48, 48, 48), 511, 16, 32, 3, "k_conv_quad"),
     ((48, 48, 48), 512, 16, 32, 3, "k_conv_quad_split"),
     ((400, 400), 1000, 16, 32, 5, "k_conv_quad"),           # 16 channels in 2-D
+    ((48, 48, 48), 600, 16, 48, 5, "k_conv_mfma"),          # more than 32 taps
+    ((48, 48, 48), 600, 32, 48, 5, "k_conv_mfma_split"),
     ((400, 400), 575, 32, 32, 5, "k_conv_quad"),
     ((400, 400), 576, 32, 32, 5, "k_conv_quad_split"),
 ])
