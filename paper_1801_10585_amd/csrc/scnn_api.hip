@@ -642,7 +642,7 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
                                         ws.cand_start, ws.tile_start, ws.ctr, n_chunks, ws.fpart, s));
     else
         SCNN_TRY(launch_bwd_filter_f64(g, ws.occ, ws.occ_prefix, g_rows, g_feats, c_out, in_feats, c_in,
-                                        ws.tap_active, ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, n_chunks,
+                                        ws.tap_active, ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, ws.tiles_cap, n_chunks,
                                         ws.fpart, s));
     SCNN_TRY(launch_bwd_filter_finish(ws.fpart, n_chunks, n_elem, w, bp_filter, ws.ctr, nnz_in, g_rows,
                                       (long long*)info, s));

@@ -125,18 +125,17 @@ hipError_t launch_bwd_data_write(const Geom& g, const float* resp, const float* 
 // ------------------------------------------------------------------ bp_filter in fp64 (any shape)
 // Per tap the contraction D[ic][oc] = sum over input rows q of x[q][ic] * g[q - delta_t][oc] (0 where the gradient has no
 // row) on the fp64 matrix cores: v_mfma_f64_16x16x4_f64, the rows of a tile as K, four per instruction.  Work item =
-// (slab, share of the tiles), a slab being up to 32 taps of one 16 x 16 block of channels; wave w owns the slab's taps
-// w and w + 16.  The tile's values of x and its neighbour rows, looked up once per tile, are shared through LDS.  Inputs of the paper's own layers have a gradient
-// row behind nearly every (row, tap), so the rows are not packed.  Bound by the latency of the look-ups and of the
-// gathers (8 -> 16 channels, 47 k rows, 27 taps: 319 k instructions, 10 us of matrix time; 53 us measured, 167 with a
-// thread per filter element that read both operands of every product).  Partial sums of a share are stored (no
-// atomics), zero included.
+// (slab, share of the tiles), a slab being one block of 16 input channels against up to 32 (tap, block of 16 output
+// channels) slots, two to a wave.  The tile's values of x and its neighbour rows, looked up once per tile, are shared
+// through LDS.  Inputs of the paper's own layers have a gradient row behind nearly every (row, tap), so the rows are not
+// packed.  Bound by the latency of the look-ups and of the gathers (8 -> 16 channels, 47 k rows, 27 taps: 319 k
+// instructions, 10 us of matrix time; 53 us measured, 167 with a thread per filter element that read both operands of
+// every product).  Partial sums of a share are stored (no atomics), zero included.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-constexpr int kBwdSlabTaps = 32;                       // taps of a slab
-constexpr int kBwdWaves = 16;                          // waves of a workgroup: two taps each
-constexpr int kBwdWaveTaps = kBwdSlabTaps / kBwdWaves;
-
-__global__ __launch_bounds__(64 * kBwdWaves) void k_bwd_filter_f64(Geom g, const unsigned long long* __restrict__ occ,
+// W waves of two (tap, block of 16 output channels) slots each; nt taps and no blocks to a slab, nt * no <= 2 W (MULTI:
+// no may be more than 1).
+template <int W, int MULTI>
+__global__ __launch_bounds__(64 * W) void k_bwd_filter_f64(Geom g, const unsigned long long* __restrict__ occ,
                                                         const unsigned* __restrict__ occ_prefix, long long g_rows,
                                                         const float* __restrict__ gf, int c_out,
                                                         const float* __restrict__ x, int c_in,
@@ -144,23 +143,33 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_bwd_filter_f64(Geom g, const
                                                         const unsigned* __restrict__ cand_lin,
                                                         const int* __restrict__ cand_start,
                                                         const int* __restrict__ tile_start,
-                                                        const Counters* __restrict__ ctr, int n_icb, int n_ocb,
-                                                        int n_slabs, int n_chunks, double* __restrict__ fpart) {
-    constexpr int NT = 64 * kBwdWaves;
-    __shared__ int s_nbr[kTileRows][kBwdSlabTaps + 1];
+                                                        const Counters* __restrict__ ctr, int nt, int no, int n_icb,
+                                                        int n_og, int n_slabs, int n_chunks,
+                                                        double* __restrict__ fpart) {
+    constexpr int NT = 64 * W;
+    __shared__ int s_nbr[kTileRows][2 * W + 1];
     __shared__ int s_site[kTileRows][3];
     __shared__ float s_x[kTileRows][17];
     const int n_tiles = (int)ctr->n_tiles;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane & 15, kq = lane >> 4;
     const int slab = (int)(blockIdx.x % (unsigned)n_slabs), chunk = (int)(blockIdx.x / (unsigned)n_slabs);
-    const int blk = slab % (n_icb * n_ocb), t_lo = slab / (n_icb * n_ocb) * kBwdSlabTaps;
-    const int t_hi = (t_lo + kBwdSlabTaps < g.T ? t_lo + kBwdSlabTaps : g.T) - 1;
-    const int ic0 = blk / n_ocb * 16, oc0 = blk % n_ocb * 16;
-    const bool oc_ok = oc0 + m < c_out;
-    f64x4 acc[kBwdWaveTaps];
+    const int blk = slab % (n_icb * n_og), t_lo = slab / (n_icb * n_og) * nt;
+    const int t_hi = (t_lo + nt < g.T ? t_lo + nt : g.T) - 1;
+    const int ic0 = blk / n_og * 16, oc0 = blk % n_og * no * 16;
+    // the wave's slots: tap t_lo + tap[j], output channels col[j] .. col[j] + 15 (those past the layer's are dropped)
+    int tap[2], col[2];
+    bool on[2];
+    f64x4 acc[2];
 #pragma unroll
-    for (int j = 0; j < kBwdWaveTaps; ++j) acc[j] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < 2; ++j) {
+        const int slot = MULTI ? __builtin_amdgcn_readfirstlane(wave + W * j) : wave + W * j;
+        const int block = MULTI ? slot / nt : 0;
+        tap[j] = slot - block * nt;
+        col[j] = oc0 + block * 16;
+        on[j] = t_lo + tap[j] <= t_hi && (!MULTI || (block < no && col[j] < c_out));
+        acc[j] = f64x4{0.0, 0.0, 0.0, 0.0};
+    }
 
     for (int tile = chunk; tile < n_tiles; tile += n_chunks) {
         const int b = sample_of_tile(tile_start, g.batch, tile);
@@ -200,15 +209,15 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_bwd_filter_f64(Geom g, const
             }
         }
         __syncthreads();
-        if (t_lo + wave > t_hi) continue;
+        if (!on[0] && !on[1]) continue;
         float a[kTileRows / 4];
 #pragma unroll
         for (int s = 0; s < kTileRows / 4; ++s) a[s] = s_x[4 * s + kq][m];
-        const float* gcol = gf + oc0 + m;
 #pragma unroll
-        for (int j = 0; j < kBwdWaveTaps; ++j) {
-            const int tt = wave + kBwdWaves * j;
-            if (t_lo + tt > t_hi) continue;
+        for (int j = 0; j < 2; ++j) {
+            if (!on[j]) continue;
+            const int c = col[j] + m;
+            const float* gcol = gf + c;
 #pragma unroll
             for (int s0 = 0; s0 < kTileRows / 4; s0 += 16) {
                 if (4 * s0 >= nrows) continue;
@@ -217,8 +226,8 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_bwd_filter_f64(Geom g, const
                 for (int s = 0; s < 16; ++s) {
                     // no gradient row: nothing is read, and the product is 0 * 0 whatever the row holds (an infinity or
                     // NaN of x belongs to the pairs that exist)
-                    const int n = s_nbr[4 * (s0 + s) + kq][tt];
-                    gv[s] = n >= 0 && oc_ok ? gcol[(size_t)n * c_out] : 0.0f;
+                    const int n = s_nbr[4 * (s0 + s) + kq][tap[j]];
+                    gv[s] = n >= 0 && c < c_out ? gcol[(size_t)n * c_out] : 0.0f;
                     xv[s] = n >= 0 ? a[s0 + s] : 0.0f;
                 }
 #pragma unroll
@@ -230,30 +239,160 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_bwd_filter_f64(Geom g, const
     // element v of a lane: input channel 4 v + kq, output channel m of the block
     double* out = fpart + (size_t)chunk * g.T * c_in * c_out;
 #pragma unroll
-    for (int j = 0; j < kBwdWaveTaps; ++j) {
-        const int t = t_lo + wave + kBwdWaves * j;
-        if (t > t_hi) continue;
+    for (int j = 0; j < 2; ++j) {
+        if (!on[j]) continue;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int ic = ic0 + 4 * v + kq;
-            if (ic < c_in && oc_ok) out[((size_t)t * c_in + ic) * c_out + oc0 + m] = acc[j][v];
+            if (ic < c_in && col[j] + m < c_out)
+                out[((size_t)(t_lo + tap[j]) * c_in + ic) * c_out + col[j] + m] = acc[j][v];
         }
     }
 }
 
-static long long bwd_f64_slabs(const Geom& g, int c_in, int c_out) {
-    return (long long)((g.T + kBwdSlabTaps - 1) / kBwdSlabTaps) * ((c_in + 15) / 16) * ((c_out + 15) / 16);
+// ------------------------------------------------------------------ bp_filter, vector kernel (long filters, few channels)
+// Work item = (block of 256 consecutive filter elements in [t][ic][oc] order, share of the tiles).  A thread owns
+// one element and walks the rows of its tiles: row q contributes x[q, ic] * g[q - delta_t, oc] when the gradient
+// has a row at q - delta_t.  The neighbour rows of a tile are looked up once per tap and shared through LDS.
+// fp64 throughout; the partial sum of the share is stored (no atomics), zero included.
+// Where a 16 x 16 block of channels holds at most 16 products the matrix form above does sixteen times the work of this
+// one and is slower once there are more than two slabs of taps: 125 taps, 47 k / 105 k rows, call in us, this / that:
+// 1->8 209 / 385 against 289 / 578, 1->16 333 / 631 against 373 / 736, 3->5 304 / 562 against 329 / 626; 49 taps, 32 k
+// rows of 2-D: 98 against 102, 141 against 132, 125 against 128; but 8->8 470 against 293, 27 taps 1->8 101 against 90,
+// and on 2.6 k rows 125 taps 77 against 71.
+constexpr int kBwdTapChunk = 32;  // taps whose neighbour rows are staged in LDS at a time
+__global__ __launch_bounds__(256) void k_bwd_filter_valu(Geom g, const unsigned long long* __restrict__ occ,
+                                                         const unsigned* __restrict__ occ_prefix, long long g_rows,
+                                                         const float* __restrict__ gf, int c_out,
+                                                         const float* __restrict__ x, int c_in,
+                                                         const int* __restrict__ tap_active /* adjoint tap order */,
+                                                         const unsigned* __restrict__ cand_lin,
+                                                         const int* __restrict__ cand_start,
+                                                         const int* __restrict__ tile_start,
+                                                         const Counters* __restrict__ ctr, int n_eb, int n_chunks,
+                                                         double* __restrict__ fpart) {
+    __shared__ int s_nbr[kTileRows][kBwdTapChunk + 1];
+    __shared__ int s_site[kTileRows][3];
+    const int n_tiles = (int)ctr->n_tiles;
+    const int cc = c_in * c_out;
+    const long long n_elem = (long long)g.T * cc;
+    const int eb = (int)(blockIdx.x % (unsigned)n_eb), chunk = (int)(blockIdx.x / (unsigned)n_eb);
+    const long long e = (long long)eb * 256 + threadIdx.x;
+    const bool valid = e < n_elem;
+    const int t_e = valid ? (int)(e / cc) : -1;
+    const int ic = valid ? (int)((e % cc) / c_out) : 0, oc = valid ? (int)(e % c_out) : 0;
+    const int t_lo = (int)(((long long)eb * 256) / cc);
+    long long e_hi = (long long)eb * 256 + 255;
+    if (e_hi > n_elem - 1) e_hi = n_elem - 1;
+    const int t_hi = (int)(e_hi / cc);
+    double acc = 0.0;
+
+    for (int tile = chunk; tile < n_tiles; tile += n_chunks) {
+        const int b = sample_of_tile(tile_start, g.batch, tile);
+        const int first = cand_start[b] + (tile - tile_start[b]) * kTileRows;
+        int nrows = cand_start[b + 1] - first;
+        if (nrows > kTileRows) nrows = kTileRows;
+        __syncthreads();  // readers of s_site / s_nbr of the previous tile are done
+        if (threadIdx.x < kTileRows) {
+            int c0 = 0, c1 = 0, c2 = 0;
+            if (threadIdx.x < nrows) site_of(g, cand_lin[first + threadIdx.x], c0, c1, c2);
+            s_site[threadIdx.x][0] = c0;
+            s_site[threadIdx.x][1] = c1;
+            s_site[threadIdx.x][2] = c2;
+        }
+        for (int tc = t_lo; tc <= t_hi; tc += kBwdTapChunk) {
+            __syncthreads();
+            // The gradient row of (row, tap t) sits at site - delta_t = site + delta of the mirrored tap T-1-t, so the
+            // look-ups run over the mirrored (adjoint) tap indices, per filter line: the taps of a line look at
+            // adjacent sites and share one pair of bitmap words.  tap_active is in adjoint order already.
+            {
+                const int t_last = (tc + kBwdTapChunk - 1) < t_hi ? (tc + kBwdTapChunk - 1) : t_hi;
+                const int a_lo = g.T - 1 - t_last, a_hi = g.T - 1 - tc;  // adjoint taps [a_lo, a_hi]
+                const int l_first = a_lo / g.K[2];
+                const int n_seg = a_hi / g.K[2] - l_first + 1;
+                for (int i = threadIdx.x; i < kTileRows * n_seg; i += 256) {
+                    const int r = i & (kTileRows - 1), l = l_first + (i >> 7);
+                    const int aa = a_lo > l * g.K[2] ? a_lo : l * g.K[2];
+                    const int ab = (a_hi + 1) < (l + 1) * g.K[2] ? (a_hi + 1) : (l + 1) * g.K[2];
+                    const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
+                    int* dst = &s_nbr[r][0];
+                    lookup_line(g, occ, occ_prefix, g_rows, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2], t0,
+                                t1, aa - l * g.K[2], ab - aa, tap_active + aa,
+                                [&](int k, int n) { dst[g.T - 1 - (aa + k) - tc] = n; });
+                }
+            }
+            __syncthreads();
+            if (valid && t_e >= tc && t_e < tc + kBwdTapChunk) {
+                const int tt = t_e - tc;
+                // eight rows at a time, their loads independent of one another; the sum keeps the row order
+                for (int r0 = 0; r0 < nrows; r0 += 8) {
+                    float xv[8], gv[8];
+                    bool on[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int r = r0 + u;
+                        const int n = r < nrows ? s_nbr[r][tt] : -1;
+                        on[u] = n >= 0;
+                        xv[u] = x[(size_t)(first + (r < nrows ? r : 0)) * c_in + ic];
+                        gv[u] = on[u] ? gf[(size_t)n * c_out + oc] : 0.0f;  // (no gradient row: nothing is read)
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (on[u]) acc = fma((double)xv[u], (double)gv[u], acc);
+                }
+            }
+        }
+    }
+    if (valid) fpart[(size_t)chunk * n_elem + e] = acc;
+}
+
+// How bp_filter outside the matrix-core lists is cut.  waves = 0: the vector kernel, `slabs` blocks of 256 elements.
+// Taps x blocks of output channels of at most 8 take four waves and everything in one slab (1 x 1, 47 k rows: 24->24 118
+// -> 61 us a call, 100->100 1300 -> 240 with all blocks of channels in the workgroup that looks the rows up; 9 taps 24->24
+// 160 -> 136); but a workgroup per block where these do not fill the chip (one 28 x 28 image, 24->24: 50 us against 57).
+struct BwdF64Shape {
+    int waves, nt, no, n_icb, n_og;
+    long long slabs;
+};
+static BwdF64Shape bwd_f64_shape(const Geom& g, int c_in, int c_out, long long tiles_cap) {
+    BwdF64Shape s;
+    if (g.T > 48 && c_in * c_out <= 16 && tiles_cap > 64) {
+        s = BwdF64Shape{0, 0, 0, 0, 0, ((long long)g.T * c_in * c_out + 255) / 256};
+        return s;
+    }
+    const int n_ocb = (c_out + 15) / 16;
+    s.waves = (long long)g.T * n_ocb <= 8 ? 4 : 16;
+    s.nt = g.T < 2 * s.waves ? g.T : 2 * s.waves;
+    s.n_icb = (c_in + 15) / 16;
+    const long long groups = (long long)((g.T + s.nt - 1) / s.nt) * s.n_icb;
+    s.no = 2 * s.waves / s.nt < n_ocb ? 2 * s.waves / s.nt : n_ocb;
+    if (groups * n_ocb * tiles_cap <= device_cu_count()) s.no = 1;
+    s.n_og = (n_ocb + s.no - 1) / s.no;
+    s.slabs = groups * s.n_og;
+    return s;
 }
 
 hipError_t launch_bwd_filter_f64(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix,
                                  long long g_rows, const float* gf, int c_out, const float* x, int c_in,
                                  const int* tap_active, const unsigned* cand_lin, const int* cand_start,
-                                 const int* tile_start, const Counters* ctr, int n_chunks, double* fpart,
-                                 hipStream_t s) {
-    const long long n_slabs = bwd_f64_slabs(g, c_in, c_out);
-    hipLaunchKernelGGL(k_bwd_filter_f64, dim3((unsigned)(n_slabs * n_chunks)), dim3(64 * kBwdWaves), 0, s, g, occ, occ_prefix,
-                       g_rows, gf, c_out, x, c_in, tap_active, cand_lin, cand_start, tile_start, ctr, (c_in + 15) / 16,
-                       (c_out + 15) / 16, (int)n_slabs, n_chunks, fpart);
+                                 const int* tile_start, const Counters* ctr, long long tiles_cap, int n_chunks,
+                                 double* fpart, hipStream_t s) {
+    const BwdF64Shape p = bwd_f64_shape(g, c_in, c_out, tiles_cap);
+    const dim3 grid((unsigned)(p.slabs * n_chunks)), block((unsigned)(p.waves ? 64 * p.waves : 256));
+#define SCNN_BWD_F64(W, MULTI)                                                                                        \
+    hipLaunchKernelGGL((k_bwd_filter_f64<W, MULTI>), grid, block, 0, s, g, occ, occ_prefix, g_rows, gf, c_out, x, c_in, \
+                       tap_active, cand_lin, cand_start, tile_start, ctr, p.nt, p.no, p.n_icb, p.n_og, (int)p.slabs,  \
+                       n_chunks, fpart)
+    if (p.waves == 0)
+        hipLaunchKernelGGL(k_bwd_filter_valu, grid, block, 0, s, g, occ, occ_prefix, g_rows, gf, c_out, x, c_in,
+                           tap_active, cand_lin, cand_start, tile_start, ctr, (int)p.slabs, n_chunks, fpart);
+    else if (p.waves == 4)
+        SCNN_BWD_F64(4, 1);
+    else if (p.no > 1)
+        SCNN_BWD_F64(16, 1);
+    else
+        SCNN_BWD_F64(16, 0);
+#undef SCNN_BWD_F64
     return hipGetLastError();
 }
 
@@ -493,9 +632,14 @@ int bwd_filter_chunks(const Geom& g, int c_in, int c_out, long long tiles_cap, b
         if (chunks < kXcds) chunks = kXcds;
         if (chunks > 256) chunks = 256;
     } else {
-        // two workgroups per CU; every share's partial filter is stored and added up again
-        const long long slabs = bwd_f64_slabs(g, c_in, c_out);
-        chunks = (2 * device_cu_count() + slabs - 1) / slabs;
+        // every share's partial filter is stored and added up again
+        const BwdF64Shape p = bwd_f64_shape(g, c_in, c_out, tiles_cap);
+        if (p.waves == 0) {
+            chunks = (4096 + p.slabs - 1) / p.slabs;
+            if (chunks > 512) chunks = 512;
+        } else {
+            chunks = ((p.waves == 4 ? 4 : 2) * device_cu_count() + p.slabs - 1) / p.slabs;
+        }
     }
     if (chunks > tiles_cap) chunks = tiles_cap;
     if (chunks < 1) chunks = 1;

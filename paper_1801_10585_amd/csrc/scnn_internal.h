@@ -456,7 +456,7 @@ int bwd_filter_chunks(const Geom& g, int c_in, int c_out, long long tiles_cap, b
 hipError_t launch_bwd_filter_f64(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix,
                                   long long g_rows, const float* gf, int c_out, const float* x, int c_in,
                                   const int* tap_active, const unsigned* cand_lin, const int* cand_start,
-                                  const int* tile_start, const Counters* ctr, int n_chunks, double* fpart,
+                                  const int* tile_start, const Counters* ctr, long long tiles_cap, int n_chunks, double* fpart,
                                   hipStream_t s);
 hipError_t launch_bwd_filter_mfma(const Geom& g, const float* x, int c_in, const float* gf, int c_out,
                                   const unsigned* pairs, const unsigned short* tap_first, const uint2* tile_hdr,

@@ -1,5 +1,6 @@
 """The fp64 filter gradient at the sizes where it can go wrong: tiles of 128 rows with remainders, slabs of 32 taps and
-of 16 x 16 channels with remainders, samples without rows, one share and many."""
+of 16 x 16 channels with remainders, slabs of several channel blocks, samples without rows, one share and many, and the
+vector kernel for long filters of few channels."""
 import numpy as np
 import pytest
 
@@ -18,6 +19,12 @@ pytestmark = pytest.mark.gpu
     ((30, 31), 2, 17, 33, (3, 11), 300),          # 33 taps: a second slab of one tap
     ((9, 9, 9), 2, 33, 8, (5, 5, 5), 200),        # 125 taps, three blocks of input channels
     ((40, 40, 40), 2, 8, 8, (3, 3, 3), 70000),    # more tiles than shares
+    ((40, 40, 40), 2, 24, 24, (1, 1, 1), 70000),  # both blocks of output channels in one slab of four waves
+    ((40, 40, 40), 2, 17, 130, (1, 1, 1), 20000), # nine blocks: sixteen waves
+    ((40, 40, 40), 2, 5, 49, (1, 1, 3), 40000),   # twelve slots, the last block of one channel
+    ((40, 40, 40), 2, 20, 70, (3, 3, 1), 20000),  # five blocks three to a slab, the last slab of two
+    ((30, 30, 30), 1, 1, 8, (5, 5, 5), 12000),    # long filter, few channels: the vector kernel, four blocks of elements
+    ((300, 40), 1, 2, 7, (7, 7), 8300),           # its elements no multiple of a block
 ])
 def test_fp64_filter_gradient_edges(extent, batch, c_in, c_out, ksize, rows):
     rng = np.random.default_rng(rows)
