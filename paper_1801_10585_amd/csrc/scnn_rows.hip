@@ -462,17 +462,28 @@ __global__ __launch_bounds__(256) void k_dense_expand(const float* __restrict__ 
     }
 }
 
-// From this size on the planes are written once.  us per call, two launches / this: 280 MB (two samples of 90^3, 48
-// channels, a ninth of the sites occupied) 157 / 96, 537 MB (128^3 x 64, a fiftieth) 213 / 122, 101 MB 35 / 24, 35 MB
-// 16.1 / 15.4, but 17 MB of eight channels 12.4 / 15.1, and with one channel, where the notes are another two passes
-// over the whole array, 17 / 36.
+// Which form.  us per call, two launches / this: 280 MB (two samples of 90^3, 48 channels, a ninth of the sites occupied)
+// 157 / 96, 537 MB (128^3 x 64, a fiftieth) 213 / 122, 101 MB 35 / 24, 35 MB 16.1 / 15.4, but 17 MB of eight channels 12.4
+// / 15.1.  With few channels the notes' two passes over a plane are a larger part of the whole and have to be earned by
+// rows: 34 to 103 MB of 8 and 9 channels with 0.002 / 0.05 / 0.3 / 0.95 of the sites occupied 11.1-19.9 / 13.4-29.7 /
+// 19.3-47 / 28.8-72.8 against 15.2-31.9 / 15.7-35.2 / 17.7-44.1 / 22.3-57.4, 134 MB of 16 channels 25 / 39 / 63 against 26 /
+// 29 / 38.  Rows that are read channel by channel gain nothing where nearly every site has one (277 MB of 33 channels,
+// 0.95 occupied: 619 against 661; 0.3: 222 against 143).
 constexpr size_t kDenseOncePassBytes = (size_t)32 << 20;
-constexpr int kDenseOncePassChannels = 8;
+constexpr size_t kDenseAnyRowsBytes = (size_t)256 << 20;
+constexpr int kDenseOncePassChannels = 8, kDenseAnyRowsChannels = 24;
+static bool dense_in_one_pass(size_t n, int channels, long long rows, int batch, bool vec) {
+    const long long sites = (long long)(n / channels);
+    if (rows <= 0 || n * 4 < kDenseOncePassBytes || channels < kDenseOncePassChannels || batch > 65535) return false;
+    if (!vec && channels >= 16 && rows > sites / 4 * 3) return false;
+    return n * 4 >= kDenseAnyRowsBytes || channels >= kDenseAnyRowsChannels || rows >= sites * 12 / (channels * channels);
+}
 
 hipError_t launch_to_dense(const Geom& g, const int32_t* coords, const float* feats, long long rows,
                            const long long* rows_dev, int channels, float* dense, hipStream_t s) {
     const size_t sample = (size_t)channels * (size_t)g.N, n = (size_t)g.batch * sample;
-    if (rows > 0 && n * 4 >= kDenseOncePassBytes && channels >= kDenseOncePassChannels && g.batch <= 65535) {
+    const bool vec = channels % 4 == 0 && ((uintptr_t)feats & 15) == 0;
+    if (dense_in_one_pass(n, channels, rows, g.batch, vec)) {
         long long sb = (g.N + 255) / 256;
         if (sb * g.batch > 16384) sb = (16384 + g.batch - 1) / g.batch;
         long long rb = (rows + 255) / 256;
@@ -481,7 +492,7 @@ hipError_t launch_to_dense(const Geom& g, const int32_t* coords, const float* fe
         hipLaunchKernelGGL(k_dense_clear_plane, grid, dim3(256), 0, s, dense, g.N, sample);
         hipLaunchKernelGGL(k_dense_note_rows, dim3((unsigned)rb), dim3(256), 0, s, g, coords, rows, rows_dev, sample,
                            (unsigned*)dense);
-        if (channels % 4 == 0 && ((uintptr_t)feats & 15) == 0)
+        if (vec)
             hipLaunchKernelGGL(k_dense_expand<true>, grid, dim3(256), 0, s, feats, channels, g.N, sample, dense);
         else
             hipLaunchKernelGGL(k_dense_expand<false>, grid, dim3(256), 0, s, feats, channels, g.N, sample, dense);

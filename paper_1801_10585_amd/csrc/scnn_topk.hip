@@ -34,14 +34,15 @@ namespace scnn {
 
 // ------------------------------------------------------------------ layout conversion (standalone entry)
 // Sample ranges of a sorted row list: cand_start[b] = first row of sample b.
-constexpr int kBoundsByWave = 32;
+constexpr int kBoundsByWave = 16;
 __global__ __launch_bounds__(256) void k_rows_sample_bounds(Geom g, const int32_t* __restrict__ coords,
                                                             long long rows, int* __restrict__ cand_start,
                                                             int* __restrict__ tile_start, Counters* ctr) {
     const int stride = 1 + g.ndim;
     if (g.batch <= kBoundsByWave) {
         // few samples: a wave per boundary, 64 probes at a time (a thread's binary search is 18 dependent loads for
-        // 154 k rows: 10.2 us a launch, this 5.0)
+        // 154 k rows: 10.2 us a launch, this 5.0); the four waves take the boundaries in turn, three loads each, so that
+        // the threads are faster again from some twenty samples on (32 samples of 128 k rows: call 51 against 55)
         const int lane = threadIdx.x & 63;
         for (int b = threadIdx.x >> 6; b <= g.batch; b += 4) {
             long long lo = 0, hi = rows;

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("extent,batch,channels,density", [
-    ((64, 64, 64), 4, 8, 0.05),      # exactly 32 MiB: the smallest output of this form
-    ((65, 67, 63), 3, 13, 0.03),     # odd sizes, scalar row loads
-    ((900, 1100), 2, 20, 0.001),     # 2-D, nearly empty
+    ((64, 64, 64), 4, 8, 0.25),      # exactly 32 MiB: the smallest output of this form (at this many rows)
+    ((64, 64, 64), 4, 8, 0.05),      # .. and with fewer rows than the form asks for at this size
+    ((65, 67, 63), 3, 13, 0.08),     # odd sizes, scalar row loads
+    ((900, 1100), 2, 24, 0.001),     # 2-D, nearly empty
     ((50, 40, 70), 5, 64, 0.9),      # nearly full
+    ((33, 64, 64), 3, 33, 0.8),      # nearly full, scalar row loads: the two launches
 ])
 def test_large_dense_outputs(extent, batch, channels, density):
     rng = np.random.default_rng(channels)
@@ -35,9 +37,9 @@ def test_large_dense_outputs(extent, batch, channels, density):
     assert np.array_equal(host(scnn.sparse_to_dense(extent, batch, dev(c2), dev(f2), rows_dev=n, out=out)), want)
 
 
-@pytest.mark.parametrize("batch,channels", [(1, 3), (2, 64), (33, 68), (5, 130)])
+@pytest.mark.parametrize("batch,channels", [(1, 3), (2, 64), (16, 12), (17, 12), (33, 68), (5, 130)])
 def test_attention_on_few_and_many_samples(batch, channels):
-    """Sample bounds by waves (up to 32 samples) and by threads, row loads of 16 and of 4 bytes; empty samples."""
+    """Sample bounds by waves (up to 16 samples) and by threads, row loads of 16 and of 4 bytes; empty samples."""
     rng = np.random.default_rng(batch)
     extent = (9, 8, 7)
     coords = random_sparse_sites(rng, extent, batch, 0.4)
