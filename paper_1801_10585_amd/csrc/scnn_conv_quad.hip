@@ -16,8 +16,8 @@
 //
 // Waves are independent (no workgroup barrier anywhere): a workgroup is just four of them sharing a launch slot.
 //
-// It serves what k_conv_quad_split does not or does more slowly: eight input channels, small layers (its pieces of 16 to
-// 64 sites fill the chip where units of 256 do not) and inputs whose split copy would pass 2^31 bytes.
+// It serves what k_conv_quad_split does not or does more slowly: eight input channels, 16 in 2-D, small layers (its pieces
+// of 16 to 64 sites fill the chip where units of 256 do not) and inputs whose split copy would pass 2^31 bytes.
 #include <type_traits>
 
 #include "scnn_internal.h"

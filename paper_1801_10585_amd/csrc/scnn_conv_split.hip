@@ -350,7 +350,8 @@ __device__ __forceinline__ void split_units(
                 }
             };
             for (int p = 0;;) {
-                __syncthreads();  // the weights of pass p are in LDS
+                __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's share of them has arrived
+                __syncthreads();                     // the weights of pass p are in LDS
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
 #pragma unroll
@@ -451,6 +452,7 @@ __global__ __launch_bounds__(256, split_waves_per_simd(NB, ACC64)) void k_conv_q
                                            cand_lin, cand_start, tile_start, ctr, resp, n_tiles, act_mask);
 }
 
+// (The channel counts that conv_kernel_for's rule was measured at; the kernel would take any multiple of eight up to 128.)
 bool conv_split_supported(const Geom& g, int c_in, int c_out, long long nnz_in) {
     const bool shape = (c_in == 16 || c_in == 24 || c_in == 32 || c_in == 40 || c_in == 48 || c_in == 64 || c_in == 96 ||
                         c_in == 128) &&
