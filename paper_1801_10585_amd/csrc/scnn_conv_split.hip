@@ -44,8 +44,9 @@ __host__ __device__ constexpr int split_waves_per_simd(int nb, int acc64) { retu
 // clocks of it, absent neighbours included, so a step's three take 99 for the 384 clocks (NB = 4) that its 24 matrix
 // instructions hold one of the four SIMDs; the 12 KB of weights of a (tap, chunk) would take 180 per wave.  So the four
 // waves walk the taps together and get the weights through LDS: a wave fetches a quarter of the next ones while it
-// multiplies the current ones.  Matrix pipes busy half of the time.  Against k_conv_quad, 32 -> 64 channels, 27 taps:
-// 437 -> 218 us at 731 k candidates, 144 -> 80 at 146 k; one-wave units of 64 / 128 sites took 295 / 243 at 731 k.
+// multiplies the current ones.  Matrix pipes busy 47 % of the time.  Against k_conv_quad, 32 -> 64 channels, 27 taps:
+// 407 -> 220 us at 731 k candidates, 142 -> 78 at 146 k (HIP events); one-wave units of 64 / 128 sites took 295 / 243 at
+// 731 k where this took 218.
 // NCH = 32-channel chunks of the input; NB = blocks of 16 output channels (2 or 4);
 // ACC64: sums over taps and chunks in fp64, else fp32; K3 = 3x3x3 filter (its loops are straight code).
 // ODD: values that the parts do not hold (split_exact) are multiplied on fp32 instructions.
