@@ -469,7 +469,7 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
                                       ws.ctr, ws.resp, s));
             g_last_conv_kernel = "k_conv_mfma";
         } else {
-            SCNN_TRY(launch_conv_mfma_split(g, nnz_in, in_feats, c_in, ws.wsplit, w, c_out, bias, ws.pairs,
+            SCNN_TRY(launch_conv_mfma_split(g, nnz_in, in_feats, c_in, ws.wsplit, w, 0, c_out, bias, ws.pairs,
                                             ws.block_tap, ws.tile_hdr, ws.ctr, ws.resp, s));
             g_last_conv_kernel = "k_conv_mfma_split";
         }
@@ -522,13 +522,14 @@ struct BwdWs {
     float* resp;
     unsigned* pairs;
     unsigned short* block_tap;
-    float* wb;
+    float* wb;               // adjoint filter of the fp32 pair-list kernel
+    unsigned short* wsplit;  // .. of the split-operand one
     uint2* tile_hdr;
     unsigned short* tap_first;
     double* fpart;
     long long block_cap, tiles_cap;
     int c_in_pad, chunks_mfma, chunks_valu;
-    bool mfma_shape;
+    bool mfma_shape, split_shape;
     size_t total;
 };
 void carve_bwd(void* base, const Geom& g, long long nnz_in, int c_in, int c_out, long long g_rows, BwdWs* w) {
@@ -557,7 +558,9 @@ void carve_bwd(void* base, const Geom& g, long long nnz_in, int c_in, int c_out,
     w->pairs = c.take<unsigned>((size_t)w->block_cap * 16);
     w->block_tap = c.take<unsigned short>((size_t)w->block_cap);
     // (the adjoint filter in matrix-operand order: its input channels, C_out, padded to a whole 32-channel chunk)
-    w->wb = c.take<float>(w->mfma_shape ? (size_t)g.T * round_up(c_out, 32) * c_in : 0);
+    w->split_shape = w->mfma_shape && c_out % 32 == 0;
+    w->wb = c.take<float>(w->mfma_shape && !w->split_shape ? (size_t)g.T * round_up(c_out, 32) * c_in : 0);
+    w->wsplit = c.take<unsigned short>(w->split_shape ? split_filter_elems(g.T, c_out) : 0);
     w->tile_hdr = c.take<uint2>(w->mfma_shape ? w->tiles_cap : 0);
     w->tap_first = c.take<unsigned short>(w->mfma_shape ? (size_t)w->tiles_cap * (g.T + 1) : 0);
     const int chunks = w->chunks_mfma > w->chunks_valu ? w->chunks_mfma : w->chunks_valu;
@@ -607,16 +610,18 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
     const long long n_elem = (long long)g.T * c_in * c_out;
     const bool use_mfma = g_conv_path != 1 && ws.mfma_shape && nnz_in > 0 && ((uintptr_t)in_feats & 15) == 0 &&
                           ((uintptr_t)g_feats & 15) == 0;
+    // (bp_data on split operands; sixteen output channels would leave half of a chunk empty)
+    const bool split = use_mfma && ws.split_shape;
     const int n_chunks = use_mfma ? ws.chunks_mfma : ws.chunks_valu;
 
     StageTimer timer(s, kFwdStages, kBwdStages);
     timer.mark();
     // adjoint filter (taps negated, channels transposed) in the layout of the convolution kernel that will run;
     // the same launch clears the counters and the occupancy bitmap
-    SCNN_TRY(launch_prepare(g, w, c_out, c_in, 1, ws.c_in_pad, ws.wp, use_mfma ? ws.wb : nullptr, nullptr,
-                            nullptr, ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
-    SCNN_TRY(launch_index_build(g, g_coords, g_rows, nullptr, g_rows, ws.occ, ws.occ_prefix, ws.ctr, nullptr, 0,
-                                nullptr, nullptr, s));
+    SCNN_TRY(launch_prepare(g, w, c_out, c_in, 1, ws.c_in_pad, ws.wp, use_mfma && !split ? ws.wb : nullptr, nullptr,
+                            split ? ws.wsplit : nullptr, ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
+    SCNN_TRY(launch_index_build(g, g_coords, g_rows, nullptr, g_rows, ws.occ, ws.occ_prefix, ws.ctr,
+                                split ? g_feats : nullptr, c_out, nullptr, ws.tap_active, s));
     SCNN_TRY(launch_rows_sample_bounds(g, in_coords, nnz_in, ws.cand_start, ws.tile_start, ws.ctr, s));
     SCNN_TRY(launch_bwd_sites(g, in_coords, nnz_in, ws.cand_start, ws.cand_lin, ws.rows16_start, ws.ctr, s));
     timer.mark();
@@ -625,8 +630,12 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
                                    ws.cand_start, ws.tile_start, ws.rows16_start, ws.ctr, ws.pairs, ws.block_tap,
                                    ws.tile_hdr, ws.block_cap, ws.tiles_cap, ws.tap_first, s));
         timer.mark();
-        SCNN_TRY(launch_conv_mfma(g, g_rows, g_feats, c_out, ws.wb, c_in, nullptr, ws.pairs, ws.block_tap,
-                                  ws.tile_hdr, ws.ctr, ws.resp, s));
+        if (split)
+            SCNN_TRY(launch_conv_mfma_split(g, g_rows, g_feats, c_out, ws.wsplit, w, 1, c_in, nullptr, ws.pairs,
+                                            ws.block_tap, ws.tile_hdr, ws.ctr, ws.resp, s));
+        else
+            SCNN_TRY(launch_conv_mfma(g, g_rows, g_feats, c_out, ws.wb, c_in, nullptr, ws.pairs, ws.block_tap,
+                                      ws.tile_hdr, ws.ctr, ws.resp, s));
     } else {
         timer.mark();
         SCNN_TRY(launch_conv_valu(g, ws.occ, ws.occ_prefix, g_rows, g_feats, c_out, ws.wp, c_in, ws.c_in_pad, nullptr,

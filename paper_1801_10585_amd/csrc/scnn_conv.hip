@@ -1315,7 +1315,9 @@ static hipError_t launch_conv_mfma_t(int taps, long long nnz_in, const float* fe
 // channels, 125 taps, 1.3 M candidates: call 3.96 -> 2.50 ms, now bound by the weights and rows that vector memory
 // returns (a round's chunk asks for 12 + 4 KB for at most two blocks); error against 64 bits 1.08e-7 -> 4.6e-8 of the
 // result's norm, on rows with a sixth of their entries 5.4e-8 -> 3.8e-8.
-// The backward pass and layers of sixteen input channels keep the fp32 kernel above.
+// The adjoint convolution of the backward pass takes it too: 128^3 x 4, 32 -> 64 channels, 202 k rows: 327 -> 280 us, 23 of
+// which the look over the gradient rows' values takes back (call 658 -> 624 us); bound by the gathers, 5 TB/s of rows.
+// Sixteen input channels keep the fp32 kernel above.
 // Operands of one 32-channel chunk of a round (up to RB consecutive 16-pair blocks of ONE tap), fetched one chunk ahead
 // of their use.
 template <int NB, int RB>
@@ -1325,7 +1327,9 @@ struct ChunkRegs {
     u32x4 b[3][NB];   // filter in bf16 thirds (split3): lane holds w[tap][32 kc + 8 gq + i][16 cb + jj], i = 0..7
 };
 
-template <int KC /* C_in / 32 */, int NB /* C_out / 16 */>
+// (ADJOINT is of the kernel's instance and not an argument: as one it cost the forward call of 64 -> 64 channels with 125
+// taps 5 %, in registers.)
+template <int KC /* C_in / 32 */, int NB /* C_out / 16 */, int ADJOINT /* w is the adjoint's, see filter_at */>
 __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_split(int taps, long long nnz_in,
                                                                const float* __restrict__ feats,
                                                                const u32x4* __restrict__ ws,
@@ -1445,7 +1449,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
                                 const float x = row[i];
 #pragma unroll
                                 for (int cb = 0; cb < NB; ++cb) {
-                                    const float wv = w[((size_t)t * C_IN + ch + i) * C_OUT + cb * 16 + jj];
+                                    const float wv = filter_at(w, taps, C_IN, C_OUT, ADJOINT, t, ch + i, cb * 16 + jj);
                                     d[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wv, d[cb], 0, 0, 0);
                                 }
                             }
@@ -1642,22 +1646,22 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
     }
 }
 
-template <int KC, int NB>
+template <int KC, int NB, int ADJOINT>
 static hipError_t launch_conv_mfma_split_t(int taps, long long nnz_in, const float* feats, const u32x4* ws,
                                            const float* w, const float* bias,
-                                     const unsigned* pairs, const unsigned short* block_tap, const uint2* tile_hdr,
-                                     Counters* ctr, float* resp, hipStream_t s) {
+                                           const unsigned* pairs, const unsigned short* block_tap, const uint2* tile_hdr,
+                                           Counters* ctr, float* resp, hipStream_t s) {
     const size_t lds = conv_mfma_lds_bytes(NB * 16);
     // (set on every launch: the attribute belongs to the current device's copy of the kernel, and a flag remembering
     // that it was set would have to be kept per device and guarded between threads for the sake of a microsecond)
-    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_split<KC, NB>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_split<KC, NB, ADJOINT>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     int per_cu = (int)((160 * 1024) / lds);
     if (per_cu < 1) per_cu = 1;
     if (per_cu > 4) per_cu = 4;    // 16 waves per CU
     const int grid = (device_cu_count() * per_cu + kXcds - 1) / kXcds * kXcds;  // one span of tiles per XCD
-    hipLaunchKernelGGL((k_conv_mfma_split<KC, NB>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, ws,
+    hipLaunchKernelGGL((k_conv_mfma_split<KC, NB, ADJOINT>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, ws,
                        w, bias, pairs, block_tap, tile_hdr, ctr, resp);
     return hipGetLastError();
 }
@@ -1688,13 +1692,12 @@ hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats,
 }
 
 hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
-                                  const float* w, int c_out, const float* bias, const unsigned* pairs,
+                                  const float* w, int adjoint, int c_out, const float* bias, const unsigned* pairs,
                                   const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
                                   hipStream_t s) {
 #define SCNN_MFMA_CASE(KC_, NB_)                                                                                  \
     if (c_in == KC_ * 32 && c_out == NB_ * 16)                                                                    \
-        return launch_conv_mfma_split_t<KC_, NB_>(g.T, nnz_in, feats, (const u32x4*)ws, w, bias, pairs, block_tap,   \
-                                                  tile_hdr, ctr, resp, s);
+        return adjoint ? launch_conv_mfma_split_t<KC_, NB_, 1>(SCNN_MFMA_ARGS) : launch_conv_mfma_split_t<KC_, NB_, 0>(SCNN_MFMA_ARGS);
     SCNN_MFMA_CASE(1, 1) SCNN_MFMA_CASE(1, 2) SCNN_MFMA_CASE(1, 3) SCNN_MFMA_CASE(1, 4)
     SCNN_MFMA_CASE(2, 1) SCNN_MFMA_CASE(2, 2) SCNN_MFMA_CASE(2, 3) SCNN_MFMA_CASE(2, 4)
     SCNN_MFMA_CASE(3, 1) SCNN_MFMA_CASE(3, 2) SCNN_MFMA_CASE(3, 3) SCNN_MFMA_CASE(3, 4)
@@ -1703,4 +1706,6 @@ hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* 
     return hipErrorInvalidValue;
 }
 
+#define SCNN_MFMA_ARGS g.T, nnz_in, feats, (const u32x4*)ws, w, bias, pairs, block_tap, tile_hdr, ctr, resp, s
 }  // namespace scnn
+#undef SCNN_MFMA_ARGS

@@ -318,14 +318,7 @@ hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_
 // wb[((t * KC + kc) * NB + cb) * 64 + lane][s] = w[t][kc*32 + 8*gq + s][cb*16 + jj], lane = 16*gq + jj, so that a
 // lane fetches its eight values of one (tap, kc, cb) with two 16-byte loads) or wp (fp64, rows padded to
 // c_out_pad; the vector kernel).  The blocks from T on clear the zero-initialised part of the workspace.
-// With `adjoint` set the filter is read as the one of the adjoint convolution (back-propagation to the data):
-// `w` is then stored [T][c_out][c_in] and tap t of the adjoint is tap T-1-t of `w` (offset negated), i.e.
-// element (t, ic, oc) = w[T-1-t][oc][ic].
-__device__ inline float filter_at(const float* __restrict__ w, int T, int c_in, int c_out, int adjoint, int t, int ic,
-                                  int oc) {
-    return adjoint ? w[((size_t)(T - 1 - t) * c_out + oc) * c_in + ic] : w[((size_t)t * c_in + ic) * c_out + oc];
-}
-
+// With `adjoint` set the filter is read as the adjoint convolution's (filter_at).
 enum PrepareLayout { kLayoutVector, kLayoutPair, kLayoutQuad, kLayoutSplit };  // (one kernel each: a small layer waits for it)
 template <int LAYOUT>
 __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict__ w, int c_in, int c_out, int adjoint,

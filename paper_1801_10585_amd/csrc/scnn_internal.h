@@ -241,6 +241,14 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void split8(const u32x4 (&x)[2], u32x4 (&part)[3]) {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// Element (t, ic, oc) of a filter of c_in by c_out channels stored [T][c_in][c_out]; with `adjoint`, of the adjoint
+// convolution (back-propagation to the data), whose filter is the stored one, then [T][c_out][c_in], with tap t of the
+// adjoint at tap T-1-t (offset negated).
+__device__ inline float filter_at(const float* __restrict__ w, int T, int c_in, int c_out, int adjoint, int t, int ic,
+                                  int oc) {
+    return adjoint ? w[((size_t)(T - 1 - t) * c_out + oc) * c_in + ic] : w[((size_t)t * c_in + ic) * c_out + oc];
+}
+
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         f32x2 v;
@@ -419,7 +427,7 @@ hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats,
                             const uint2* tile_hdr, Counters* ctr, float* resp, hipStream_t s);
 // (on split operands: the forward pass; w = the filter as it is)
 hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
-                                  const float* w, int c_out, const float* bias, const unsigned* pairs,
+                                  const float* w, int adjoint, int c_out, const float* bias, const unsigned* pairs,
                                   const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
                                   hipStream_t s);
 

@@ -278,3 +278,41 @@ def test_backward_reports_bad_arguments_and_unsorted_rows():
     bad[0, 1] = 99
     _, _, info = scnn.sparse_conv_bwd(extent, 1, dev(bad), dev(feats), ksize, dev(w), dev(gc), dev(gf))
     assert int(info[2]) & scnn.FLAG_BAD_COORD
+
+
+@pytest.mark.parametrize("c_in,c_out,ksize", [(16, 32, (3, 3, 3)), (64, 64, (3, 3, 1)), (48, 96, (3, 3, 3)), (32, 128, (5, 5, 5))])
+@pytest.mark.parametrize("kind", ["rows", "weights", "tiny"])
+def test_backward_values_that_three_bf16_numbers_do_not_hold(c_in, c_out, ksize, kind):
+    """Infinite and NaN gradient rows, such weights, and values below 2^-109: every element of bp_data is what the sum
+    over its own (row, tap) pairs gives, finite ones to a few roundings of their products' magnitudes."""
+    rng = np.random.default_rng(c_in + c_out)
+    ext, t = (14, 13, 15), int(np.prod(ksize))
+    coords, gc = random_sparse_sites(rng, ext, 1, 0.1), random_sparse_sites(rng, ext, 1, 0.2)
+    x = np.ones((coords.shape[0], c_in), np.float32)
+    gf = rng.normal(size=(gc.shape[0], c_out)).astype(np.float32)
+    w = (rng.normal(size=(t, c_in, c_out)) * 0.1).astype(np.float32)
+    n = gc.shape[0]
+    if kind == "rows":
+        gf[n // 4, c_out - 1], gf[n // 2, 0], gf[3 * n // 4, 3] = np.inf, np.nan, -np.inf
+    elif kind == "weights":
+        w[1, 2, 5], w[t - 2, c_in - 1, c_out - 1], w[t // 2, 0, 0] = np.inf, np.nan, -np.inf
+    else:
+        gf, w = (gf * np.float32(2.0 ** -122)).astype(np.float32), (w * np.float32(2.0 ** 60)).astype(np.float32)
+    got = gpu_bwd(ext, 1, coords, x, ksize, w, gc, gf)[0]
+    half = [k // 2 for k in ksize]
+    grid = np.full([e + 2 * h for e, h in zip(ext, half)], -1)
+    grid[tuple(gc[:, 1 + a] + half[a] for a in range(3))] = np.arange(n)
+    ref, mag = np.zeros(got.shape), np.zeros(got.shape)
+    with np.errstate(invalid="ignore"):
+        for k, off in enumerate(np.ndindex(*ksize)):
+            r = grid[tuple(coords[:, 1 + a] - off[a] + 2 * half[a] for a in range(3))]
+            at = r >= 0
+            ref[at] += gf[r[at]].astype(np.float64) @ w[k].T.astype(np.float64)
+            mag[at] += np.abs(gf[r[at]]).astype(np.float64) @ np.abs(w[k]).T.astype(np.float64)
+    say(f"bwd special values {kind} {c_in}->{c_out} {ksize}: {int(np.isinf(ref).sum())} inf, {int(np.isnan(ref).sum())} NaN")
+    assert kind == "tiny" or not np.isfinite(ref).all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(got), got, 0), np.where(np.isinf(ref), ref, 0))
+    ok = np.isfinite(ref) & np.isfinite(mag)
+    # (fp32 chains of at most 32 products: half a rounding of their magnitudes on each; their sums are added in fp64)
+    assert ok.any() and (np.abs(got[ok] - ref[ok]) <= 33 * 2.0 ** -24 * mag[ok] + 2.0 ** -149).all()
