@@ -1695,6 +1695,7 @@ hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* 
                                   const float* w, int adjoint, int c_out, const float* bias, const unsigned* pairs,
                                   const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
                                   hipStream_t s) {
+#define SCNN_MFMA_ARGS g.T, nnz_in, feats, (const u32x4*)ws, w, bias, pairs, block_tap, tile_hdr, ctr, resp, s
 #define SCNN_MFMA_CASE(KC_, NB_)                                                                                  \
     if (c_in == KC_ * 32 && c_out == NB_ * 16)                                                                    \
         return adjoint ? launch_conv_mfma_split_t<KC_, NB_, 1>(SCNN_MFMA_ARGS) : launch_conv_mfma_split_t<KC_, NB_, 0>(SCNN_MFMA_ARGS);
@@ -1703,9 +1704,8 @@ hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* 
     SCNN_MFMA_CASE(3, 1) SCNN_MFMA_CASE(3, 2) SCNN_MFMA_CASE(3, 3) SCNN_MFMA_CASE(3, 4)
     SCNN_MFMA_CASE(4, 1) SCNN_MFMA_CASE(4, 2) SCNN_MFMA_CASE(4, 3) SCNN_MFMA_CASE(4, 4)
 #undef SCNN_MFMA_CASE
+#undef SCNN_MFMA_ARGS
     return hipErrorInvalidValue;
 }
 
-#define SCNN_MFMA_ARGS g.T, nnz_in, feats, (const u32x4*)ws, w, bias, pairs, block_tap, tile_hdr, ctr, resp, s
 }  // namespace scnn
-#undef SCNN_MFMA_ARGS

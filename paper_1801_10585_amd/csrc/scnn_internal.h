@@ -236,11 +236,6 @@ __device__ __forceinline__ void split3(float x, unsigned short& h, unsigned shor
     l = (unsigned short)rounded(r2);
 }
 
-// Eight fp32 values as eight h, eight m and eight l: split3 on pairs, with the conversion instruction.
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void split8(const u32x4 (&x)[2], u32x4 (&part)[3]) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // Element (t, ic, oc) of a filter of c_in by c_out channels stored [T][c_in][c_out]; with `adjoint`, of the adjoint
 // convolution (back-propagation to the data), whose filter is the stored one, then [T][c_out][c_in], with tap t of the
 // adjoint at tap T-1-t (offset negated).
@@ -249,6 +244,11 @@ __device__ inline float filter_at(const float* __restrict__ w, int T, int c_in, 
     return adjoint ? w[((size_t)(T - 1 - t) * c_out + oc) * c_in + ic] : w[((size_t)t * c_in + ic) * c_out + oc];
 }
 
+// Eight fp32 values as eight h, eight m and eight l: split3 on pairs, with the conversion instruction.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void split8(const u32x4 (&x)[2], u32x4 (&part)[3]) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         f32x2 v;
