@@ -171,6 +171,8 @@ __global__ __launch_bounds__(64 * W) void k_bwd_filter_f64(Geom g, const unsigne
         acc[j] = f64x4{0.0, 0.0, 0.0, 0.0};
     }
 
+    const int a_lo = g.T - 1 - t_hi, a_hi = g.T - 1 - t_lo;  // adjoint taps [a_lo, a_hi]
+    const unsigned act = active_taps(tap_active, a_lo, a_hi - a_lo + 1);
     for (int tile = chunk; tile < n_tiles; tile += n_chunks) {
         const int b = sample_of_tile(tile_start, g.batch, tile);
         const int first = cand_start[b] + (tile - tile_start[b]) * kTileRows;
@@ -194,7 +196,6 @@ __global__ __launch_bounds__(64 * W) void k_bwd_filter_f64(Geom g, const unsigne
         // look-ups run over the mirrored (adjoint) tap indices, per filter line: the taps of a line look at
         // adjacent sites and share one pair of bitmap words.  tap_active is in adjoint order already.
         {
-            const int a_lo = g.T - 1 - t_hi, a_hi = g.T - 1 - t_lo;  // adjoint taps [a_lo, a_hi]
             const int l_first = a_lo / g.K[2];
             const int n_seg = a_hi / g.K[2] - l_first + 1;
             for (int i = threadIdx.x; i < kTileRows * n_seg; i += NT) {
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(64 * W) void k_bwd_filter_f64(Geom g, const unsigne
                 const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
                 int* dst = &s_nbr[r][0];
                 lookup_line(g, occ, occ_prefix, g_rows, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2], t0,
-                            t1, aa - l * g.K[2], ab - aa, tap_active + aa,
+                            t1, aa - l * g.K[2], ab - aa, act >> (aa - a_lo),
                             [&](int k, int n) { dst[g.T - 1 - (aa + k) - t_lo] = n; });
             }
         }
@@ -308,6 +309,7 @@ __global__ __launch_bounds__(256) void k_bwd_filter_valu(Geom g, const unsigned 
             {
                 const int t_last = (tc + kBwdTapChunk - 1) < t_hi ? (tc + kBwdTapChunk - 1) : t_hi;
                 const int a_lo = g.T - 1 - t_last, a_hi = g.T - 1 - tc;  // adjoint taps [a_lo, a_hi]
+                const unsigned act = active_taps(tap_active, a_lo, a_hi - a_lo + 1);
                 const int l_first = a_lo / g.K[2];
                 const int n_seg = a_hi / g.K[2] - l_first + 1;
                 for (int i = threadIdx.x; i < kTileRows * n_seg; i += 256) {
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(256) void k_bwd_filter_valu(Geom g, const unsigned 
                     const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
                     int* dst = &s_nbr[r][0];
                     lookup_line(g, occ, occ_prefix, g_rows, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2], t0,
-                                t1, aa - l * g.K[2], ab - aa, tap_active + aa,
+                                t1, aa - l * g.K[2], ab - aa, act >> (aa - a_lo),
                                 [&](int k, int n) { dst[g.T - 1 - (aa + k) - tc] = n; });
                 }
             }

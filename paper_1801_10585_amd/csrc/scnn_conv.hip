@@ -85,6 +85,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_stream(Geom g, const unsigned
 
         for (int tc = 0; tc < g.T; tc += kTapChunk) {
             const int tmax = (g.T - tc) < kTapChunk ? (g.T - tc) : kTapChunk;
+            const unsigned act = active_taps(tap_active, tc, tmax);
             __syncthreads();
             // element i = line segment * 128 + row: the chunk's taps are cut into runs that share (t0, t1); a run's
             // neighbours are adjacent sites and are resolved from one pair of bitmap words
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_stream(Geom g, const unsigned
                     const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
                     int* dst = &s_nbr[r][ta - tc];
                     lookup_line(g, occ, occ_prefix, nnz_in, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2], t0,
-                                t1, ta - l * g.K[2], tb - ta, tap_active + ta, [&](int k, int n) { dst[k] = n; });
+                                t1, ta - l * g.K[2], tb - ta, act >> (ta - tc), [&](int k, int n) { dst[k] = n; });
                 }
             }
             __syncthreads();
@@ -265,6 +266,7 @@ __global__ __launch_bounds__(256) void k_conv_valu(Geom g, const unsigned long l
 
         for (int tc = 0; tc < g.T; tc += kTapChunk) {
             const int tmax = (g.T - tc) < kTapChunk ? (g.T - tc) : kTapChunk;
+            const unsigned act = active_taps(tap_active, tc, tmax);
             __syncthreads();
             // ---- neighbour rows of (row, tap): element i = line segment * 128 + row; the chunk's taps are cut into
             //      runs that share (t0, t1), whose neighbours are resolved from one pair of bitmap words
@@ -278,7 +280,7 @@ __global__ __launch_bounds__(256) void k_conv_valu(Geom g, const unsigned long l
                     const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
                     int* dst = &s_nbr[r][ta - tc];
                     lookup_line(g, occ, occ_prefix, nnz_in, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2], t0,
-                                t1, ta - l * g.K[2], tb - ta, tap_active + ta, [&](int k, int n) { dst[k] = n; });
+                                t1, ta - l * g.K[2], tb - ta, act >> (ta - tc), [&](int k, int n) { dst[k] = n; });
                 }
             }
             // ---- rounds = (block of CH input channels) x (group of TG taps).  The global loads of round q + 1 (the
@@ -620,6 +622,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
 #pragma unroll
                     for (int m = 0; m < WB; ++m) (&s_w[0][0][0])[threadIdx.x + m * 256] = wv[m];
                 };
+                const unsigned act = active_taps(tap_active, tc, tmax);
                 fetch_w(0);  // does not depend on the neighbours: in flight during the look-ups
                 __syncthreads();  // s_site written; the previous chunk's readers of s_nbr are done
                 {
@@ -632,7 +635,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                         const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
                         int* dst = &s_nbr[r][ta - tc];
                         lookup_line(g, occ, occ_prefix, nnz_in, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2],
-                                    t0, t1, ta - l * g.K[2], tb - ta, tap_active + ta,
+                                    t0, t1, ta - l * g.K[2], tb - ta, act >> (ta - tc),
                                     [&](int k, int n) { dst[k] = n; });
                     }
                 }
@@ -879,7 +882,8 @@ constexpr int kStageBlocks = 208;                 // 16-pair blocks staged in LD
 // (active taps) * (16-row groups of all earlier tiles); unused blocks of a reservation are simply never read.
 // One wave builds one tile (lanes = output rows lane and lane + 64) and walks the taps in order, so that it needs
 // neither barriers nor a scan; the taps are looked up kPairTapGroup at a time to overlap their loads.
-constexpr int kPairTapGroup = 4;
+constexpr int kPairTapGroup = 5;
+constexpr int kPairTapWords = 8;  // of 32 taps (block_tap holds a tap in one byte)
 __global__ __launch_bounds__(256) void k_pair_build(Geom g, const unsigned long long* __restrict__ occ,
                                                     const unsigned* __restrict__ occ_prefix, long long nnz_in,
                                                     const int* __restrict__ tap_active,
@@ -896,9 +900,14 @@ __global__ __launch_bounds__(256) void k_pair_build(Geom g, const unsigned long 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
     const int n_tiles = (int)ctr->n_tiles;
-    int active = 0;  // taps with a non-zero weight
-    for (int t0 = 0; t0 < g.T; t0 += 64)
-        active += __popcll(__ballot(t0 + lane < g.T && tap_active[t0 + lane < g.T ? t0 + lane : 0] != 0));
+    __shared__ unsigned s_act[kPairTapWords + 1];  // bit t of the whole: tap t has a non-zero weight
+    int active = 0;                                // how many have
+    for (int w = 0; w <= kPairTapWords; ++w) {
+        const unsigned a = w * 32 < g.T ? active_taps(tap_active, w * 32, g.T - w * 32 < 32 ? g.T - w * 32 : 32) : 0u;
+        active += __popc(a);
+        if (threadIdx.x == 0) s_act[w] = a;
+    }
+    __syncthreads();
 
     const int waves = (int)gridDim.x * 4;
     for (int tile = (int)blockIdx.x * 4 + wave; tile < n_tiles; tile += waves) {
@@ -943,12 +952,15 @@ __global__ __launch_bounds__(256) void k_pair_build(Geom g, const unsigned long 
                 if (sg0 + u >= n_seg) cnt = 0;
                 seg_tap[u] = line * g.K[2] + t2_lo;
                 seg_cnt[u] = cnt;
+                const unsigned long long act2 =
+                    (unsigned long long)s_act[(seg_tap[u] >> 5) + 1] << 32 | s_act[seg_tap[u] >> 5];
+                const unsigned act = (unsigned)(act2 >> (seg_tap[u] & 31));
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
 #pragma unroll
                     for (int k = 0; k < G; ++k) nbr[u][k][h] = 0xffffffffu;
                     lookup_line(g, occ, occ_prefix, nnz_in, cnt > 0 && h * 64 + lane < nrows, b, sc[h][0], sc[h][1],
-                                sc[h][2], t0l, t1l, t2_lo, cnt, tap_active + seg_tap[u],
+                                sc[h][2], t0l, t1l, t2_lo, cnt, act,
                                 [&](int k, int n) { nbr[u][k][h] = (unsigned)n; });
                 }
             }

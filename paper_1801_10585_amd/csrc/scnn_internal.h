@@ -156,42 +156,47 @@ __device__ inline int lookup_row(const Geom& g, const unsigned long long* __rest
 // Neighbour rows of one site along one filter line: the taps (t0, t1, t2_lo .. t2_lo + count - 1), count <= 32, look
 // at the sites (c0 + t0 - H0, c1 + t1 - H1, c2 + t2 - H2), which are adjacent along the last axis and therefore sit
 // in at most two adjacent 64-bit words of the occupancy bitmap.  Both words and their prefixes are loaded once and
-// every tap of the line is resolved from them: emit(k, row) is called for k = 0 .. count-1 with the neighbour's row
-// or -1.  `live` = false (a padding lane) emits -1 everywhere without touching memory contents that matter.
-// 32-bit arithmetic throughout: site indices and bitmap word indices fit 31 bits.
+// every tap of the line is resolved from them: emit(k, row) is called for k = 0 .. count-1 (count <= 32) with the
+// neighbour's row or -1; bit k of `act`: tap t2_lo + k has a non-zero weight.  `live` = false (a padding lane) emits -1
+// everywhere without touching memory contents that matter.
+// Vector issue is what the callers are bound by, so the line's occupancy is cut out of the two words once, as 32 bits,
+// and the rows, which are consecutive along a line, are counted up with it: five instructions a tap.
+// 32-bit arithmetic throughout: site, row and bitmap word indices fit 31 bits.
 template <typename Emit>
 __device__ inline void lookup_line(const Geom& g, const unsigned long long* __restrict__ occ,
                                    const unsigned* __restrict__ occ_prefix, long long nnz_in, bool live, int b, int c0,
-                                   int c1, int c2, int t0, int t1, int t2_lo, int count,
-                                   const int* __restrict__ tap_active_line /* [t2_lo + k] */, Emit&& emit) {
+                                   int c1, int c2, int t0, int t1, int t2_lo, int count, unsigned act, Emit&& emit) {
     const int q0 = c0 + t0 - g.H[0], q1 = c1 + t1 - g.H[1];
     const bool line_ok = live && (unsigned)b < (unsigned)g.batch && (unsigned)q0 < (unsigned)g.E[0] &&
                          (unsigned)q1 < (unsigned)g.E[1];
-    const int q2s = c2 + t2_lo - g.H[2];               // site of tap k is q2s + k
-    const int k_lo = q2s < 0 ? -q2s : 0;               // first tap whose site is on the line
-    const unsigned line_bit0 = (unsigned)((q0 * g.E[1] + q1) * g.E[2]);  // site index of (q0, q1, 0), if line_ok
-    const unsigned first_bit = line_ok ? line_bit0 + (unsigned)(q2s + k_lo) : 0u;
-    const unsigned w_rel = first_bit >> 6;             // word of the sample holding the first looked-at site
-    const unsigned w0 = (unsigned)b * (unsigned)g.Wps + w_rel;
+    const int q2s = c2 + t2_lo - g.H[2];                          // site of tap k is q2s + k
+    const int k_lo = q2s < 0 ? -q2s : 0;                          // first tap whose site is on the line
+    const int k_hi = g.E[2] - q2s < count ? g.E[2] - q2s : count;  // .. and the first past it
+    const unsigned first_bit = line_ok ? (unsigned)((q0 * g.E[1] + q1) * g.E[2] + q2s + k_lo) : 0u;
+    const unsigned p = first_bit & 63u;                           // position of tap k_lo's site in word_a
     const unsigned w_last = (unsigned)g.batch * (unsigned)g.Wps - 1u;
+    const unsigned w0 = (unsigned)b * (unsigned)g.Wps + (first_bit >> 6);
     const unsigned wa = line_ok ? (w0 < w_last ? w0 : w_last) : 0u, wb = wa < w_last ? wa + 1u : wa;
     const unsigned long long word_a = occ[wa], word_b = occ[wb];
     const unsigned pre_a = occ_prefix[wa], pre_b = occ_prefix[wb];
+    const unsigned window = (unsigned)(word_a >> p) | (unsigned)((word_b << 1) << (63u - p));
+    const int n_on = k_hi - k_lo;  // taps whose site is on the line
+    const unsigned raw = line_ok && n_on > 0 ? (window & (~0u >> (32 - n_on))) << k_lo : 0u;
+    const unsigned win = raw & act;
+    // rows count up from those of word_a before the line's first site, or, where word_a is empty (its row prefix then
+    // means nothing), from the first of word_b
+    unsigned row = word_a ? pre_a + (unsigned)__popcll(word_a & ((1ull << p) - 1ull)) : pre_b;
     for (int k = 0; k < count; ++k) {
-        int n = -1;
-        const int q2 = q2s + k;
-        if (line_ok && (unsigned)q2 < (unsigned)g.E[2] && tap_active_line[k] != 0) {
-            const unsigned bitpos = line_bit0 + (unsigned)q2;
-            const bool second = (bitpos >> 6) != w_rel;
-            const unsigned long long word = second ? word_b : word_a;
-            const unsigned bit = bitpos & 63u;
-            if ((word >> bit) & 1ull) {
-                const long long rr = (long long)(second ? pre_b : pre_a) + __popcll(word & ((1ull << bit) - 1ull));
-                if (rr < nnz_in) n = (int)rr;  // only an unsorted input can trip this guard
-            }
-        }
-        emit(k, n);
+        // (only an unsorted input can trip the guard)
+        emit(k, ((win >> k) & 1u) && row < (unsigned)nnz_in ? (int)row : -1);
+        row += (raw >> k) & 1u;
     }
+}
+
+// Bit k = tap_active[first + k] is not zero, k < count <= 32.  (whole wave)
+__device__ inline unsigned active_taps(const int* __restrict__ tap_active, int first, int count) {
+    const int lane = threadIdx.x & 63;
+    return (unsigned)__ballot(lane < count && tap_active[first + (lane < count ? lane : 0)] != 0);
 }
 
 // Bits destined for a bitmap, one (word index, bits) per lane, where lanes that address the same word sit next to
