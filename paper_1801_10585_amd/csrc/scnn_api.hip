@@ -296,7 +296,7 @@ static void carve_conv(void* base, const Geom& g, const Geom& gp, long long nnz_
     w->tile_state = c.take<unsigned long long>(w->tiles_cap);
     w->zero_bytes = c.total();
     w->part = c.take<uint2>(topk_small_columns(g) ? 0 : ncols * kTopkPartWords);
-    w->row_keep = c.take<unsigned long long>(marks ? 2 * w->tiles_cap : 0);
+    w->row_keep = c.take<unsigned long long>(c_out <= kMarkPlanes ? 2 * w->tiles_cap : 0);
     w->row_plane = c.take<unsigned long long>(marks ? 2 * w->tiles_cap * kMarkPlanes : 0);
     w->tile_base = c.take<long long>(marks ? w->tiles_cap : 0);
     w->occ_prefix = c.take<unsigned>(nw);
@@ -489,12 +489,12 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
     if (!pool) {
         SCNN_TRY(launch_select_write(g, c_out, topk_mode, relu, ws.cand_start, ws.tile_start, ws.cand_lin, ws.resp,
                                      ws.cols, ws.tile_state, ws.tiles_cap, ws.ctr, out_coords, out_feats,
-                                     out_capacity, (long long*)nnz_out, 0, 1, marks ? ws.tile_base : nullptr, s));
+                                     out_capacity, (long long*)nnz_out, 0, 1, ws.row_keep, marks ? ws.tile_base : nullptr, s));
         timer.mark();
     } else {
         SCNN_TRY(launch_select_write(g, c_out, topk_mode, relu, ws.cand_start, ws.tile_start, ws.cand_lin, ws.resp,
                                      ws.cols, ws.tile_state, ws.tiles_cap, ws.ctr, ws.tmp_coords, ws.tmp_feats,
-                                     ws.cand_cap, nullptr, 0, 0, marks ? ws.tile_base : nullptr, s));
+                                     ws.cand_cap, nullptr, 0, 0, ws.row_keep, marks ? ws.tile_base : nullptr, s));
         timer.mark();
         SCNN_TRY(launch_maxpool(g, gp, ws.tmp_coords, ws.tmp_feats, 0, &ws.ctr->n_rows, ws.cand_cap, c_out, 1,
                                 ws.occ_sel, ws.occ_prefix, ws.pbits, ws.pprefix, ws.block_sums, ws.pool_key,
@@ -763,7 +763,7 @@ void carve_topk(void* base, const Geom& g, long long rows, int channels, TopkWs*
     w->tile_state = c.take<unsigned long long>(w->tiles_cap);
     w->zero_bytes = c.total();
     w->part = c.take<uint2>(topk_small_columns(g) ? 0 : ncols * kTopkPartWords);
-    w->row_keep = c.take<unsigned long long>(w->marks ? 2 * w->tiles_cap : 0);
+    w->row_keep = c.take<unsigned long long>(channels <= kMarkPlanes ? 2 * w->tiles_cap : 0);
     w->row_plane = c.take<unsigned long long>(w->marks ? 2 * w->tiles_cap * kMarkPlanes : 0);
     w->tile_base = c.take<long long>(w->marks ? w->tiles_cap : 0);
     w->block_sums = c.take<unsigned>(scan_blocks(w->tiles_cap));
@@ -817,7 +817,7 @@ int attention_topk(int ndim, const int32_t* extent, int batch, const int32_t* co
                          ws.tiles_cap, ws.ctr, s));
     SCNN_TRY(launch_select_write(g, channels, topk_mode, 0, ws.cand_start, ws.tile_start, ws.cand_lin, ws.resp,
                                  ws.cols, ws.tile_state, ws.tiles_cap, ws.ctr, out_coords, out_feats, out_capacity,
-                                 (long long*)nnz_out, rows, 0, marks ? ws.tile_base : nullptr, s));
+                                 (long long*)nnz_out, rows, 0, ws.row_keep, marks ? ws.tile_base : nullptr, s));
     return SCNN_OK;
 }
 

@@ -513,7 +513,8 @@ hipError_t launch_select_write(const Geom& g, int channels, int mode, int relu, 
                                const ColState* cols, unsigned long long* tile_state, long long tiles_cap,
                                Counters* ctr, int32_t* out_coords, float* out_feats, long long out_capacity,
                                long long* nnz_out /* nullable: also write the result counters */, long long aux_imm,
-                               int aux_is_cand, const long long* tile_base /* nullable: from launch_topk */,
+                               int aux_is_cand, unsigned long long* row_keep /* two words per tile */,
+                               const long long* tile_base /* nullable: from launch_topk */,
                                hipStream_t s);
 
 // scnn_rows.hip

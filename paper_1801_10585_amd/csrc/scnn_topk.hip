@@ -1235,19 +1235,18 @@ __device__ inline long long lookback_wave(unsigned long long* tile_state, int ti
 // (one thread) The next `n` tiles of the compaction pass's queue.  Read-modify-writes of one address are served one
 // at a time, about 13 ns each on this chip (a plain load of the counter is no cheaper), so a pass over a few
 // thousand tiles can be bound by its tickets alone, and a thousand workgroups asking at once wait 13 us for theirs.
-// Hence: several tiles per ticket in the narrow kernel, whose tiles are small, and no ticket that is known to come
-// back empty: a launch with at least as many workgroups as tickets takes one ticket per workgroup (`once`), and a
+// Hence no ticket that is known to come back empty: a launch with at least as many workgroups as tickets takes one ticket per workgroup (`once`), and a
 // workgroup that has seen the queue empty does not ask again.
 __device__ inline unsigned take_ticket(Counters* ctr, unsigned n) { return atomicAdd(&ctr->ticket, n); }
 
 // The result counters, written by the last workgroup of the compaction pass to end (nnz_out may be null: a later
 // kernel writes them).  aux = second counter: the candidate count (aux_is_cand) or a host-side number.
 __device__ inline void finish_if_last(Counters* ctr, long long* nnz_out, long long aux_imm, int aux_is_cand,
-                                      long long out_capacity) {
+                                      long long out_capacity, unsigned workgroups) {
     if (!nnz_out) return;
     __syncthreads();  // (waits for the workgroup's counter updates, all device-scope atomics, to be acknowledged)
     if (threadIdx.x != 0) return;
-    if (atomicAdd(&ctr->finished, 1u) != gridDim.x - 1) return;
+    if (atomicAdd(&ctr->finished, 1u) != workgroups - 1) return;
     const long long rows = __hip_atomic_load(&ctr->n_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned flags = __hip_atomic_load(&ctr->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (rows > out_capacity) flags |= SCNN_FLAG_OUT_OVERFLOW;
@@ -1379,7 +1378,7 @@ __global__ __launch_bounds__(256) void k_select_write(Geom g, int channels, int 
             __syncthreads();
         }
     }
-    finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity);
+    finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity, gridDim.x);
 }
 
 // The same pass for up to 64 channels, software-pipelined over three tiles.  A workgroup holds tile X (being
@@ -1549,7 +1548,7 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
     // prologue: X = first ticket (loaded, decided), Y = second ticket (loads in flight)
     int tile_x = s_ticket;
     if (tile_x >= n_tiles) {
-        finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity);
+        finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity, gridDim.x);
         return;
     }
     load_tile(tile_x, va);
@@ -1606,7 +1605,7 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
         step(vb, va);
         if (tile_x >= n_tiles) break;
     }
-    finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity);
+    finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity, gridDim.x);
 }
 
 __global__ void k_finish(const Counters* __restrict__ ctr, int which_rows, long long aux_imm, int aux_is_cand,
@@ -1629,100 +1628,88 @@ hipError_t launch_finish(const Counters* ctr, int which_rows, long long aux_imm,
     return hipGetLastError();
 }
 
-// The same pass for narrow layers (at most 16 channels, the widths of the paper's own networks): a tile of 128 rows
-// holds too little data to pay for a ticket, a look-back and three barriers, so a workgroup takes kNarrowTiles
-// consecutive tiles per ticket (a "super-tile", one status word in tile_state) and a thread owns whole rows: it reads
-// a row's channels from the planar tile (coalesced across the wave), decides them, and writes the row itself.
-// UNI: the wave's tile and sample are made scalars, so that the look-ups of the sample's bounds and of the columns'
-// thresholds are scalar loads, once per wave, instead of vector loads per row and channel: fewer instructions, which
-// large layers are bound by (128^3 x 4 with 8 channels: 57 -> 48 us), but a chain of dependent scalar loads per row
-// group, which small layers, bound by latency, pay for (32^3 network: + 8 us with it everywhere); the host picks by
-// the workspace's tile capacity.
-constexpr long long kNarrowUniformTiles = 8192;
-template <int CMAX, int kNarrowTiles /* tiles per ticket at most: rows per thread = kNarrowTiles / 2 */, bool UNI>
-__global__ __launch_bounds__(256, 4) void k_select_write_narrow(Geom g, int channels, int mode, int relu,
-                                                                const int* __restrict__ cand_start,
-                                                                const int* __restrict__ tile_start,
-                                                                const unsigned* __restrict__ cand_lin,
-                                                                const float* __restrict__ resp,
-                                                                const ColState* __restrict__ cols,
-                                                                unsigned long long* tile_state, Counters* ctr,
-                                                                int32_t* __restrict__ out_coords,
-                                                                float* __restrict__ out_feats, long long out_capacity,
-                                                                long long* __restrict__ nnz_out, long long aux_imm,
-                                                                int aux_is_cand, int tps /* tiles per ticket */) {
-    constexpr int RPT = kNarrowTiles * kTileRows / 256;  // rows per thread
-    __shared__ int s_cnt[RPT * 4];                       // kept rows of each (row group, wave)
+// The same pass for narrow layers (at most 32 channels, the widths of the paper's own networks): a tile of 128 rows holds
+// too little data to pay for three barriers, so a thread owns a whole row: it reads the row's channels from the planar
+// tile (coalesced across the wave), decides them, and writes the row itself.
+// Zeroes a row's values that do not survive; any that does?
+template <int CMAX>
+__device__ __forceinline__ bool decide_row(int channels, int mode, int relu, const ColState* __restrict__ cols, unsigned pos,
+                                           float (&v)[CMAX]) {
+    bool any = false;
+#pragma unroll
+    for (int c = 0; c < CMAX; ++c) {
+        if (c < channels) {
+            const unsigned tau = cols[c].tau, cut = cols[c].cut;
+            bool keep = score_key(v[c], mode) > (pos <= cut ? tau - (tau != 0u ? 1u : 0u) : tau);
+            if (relu) keep = keep && (v[c] > 0.0f);
+            v[c] = keep ? v[c] : 0.0f;
+            any |= keep;
+        }
+    }
+    return any;
+}
+
+template <int CMAX>
+__device__ __forceinline__ void write_row(const Geom& g, int channels, int b, unsigned lin, const float (&v)[CMAX], long long o,
+                                          int32_t* __restrict__ out_coords, float* __restrict__ out_feats) {
+    int c0, c1, c2;
+    site_of(g, lin, c0, c1, c2);
+    store_site(g, out_coords + o * (1 + g.ndim), b, c0, c1, c2);
+    float* dst = out_feats + o * channels;
+    if ((channels & 3) == 0 && ((size_t)out_feats & 15) == 0) {
+#pragma unroll
+        for (int c = 0; c < CMAX; c += 4)
+            if (c < channels) *(float4*)(dst + c) = make_float4(v[c], v[c + 1], v[c + 2], v[c + 3]);
+    } else {
+#pragma unroll
+        for (int c = 0; c < CMAX; ++c)
+            if (c < channels) dst[c] = v[c];
+    }
+}
+
+// Small layers: one launch, two consecutive tiles per workgroup (one status word in tile_state), ordered by tickets and
+// look-back; the launch has a workgroup for every two tiles, and those past the layer's leave at once.
+template <int CMAX>
+__global__ __launch_bounds__(256) void k_select_write_narrow(Geom g, int channels, int mode, int relu,
+                                                             const int* __restrict__ cand_start,
+                                                             const int* __restrict__ tile_start,
+                                                             const unsigned* __restrict__ cand_lin,
+                                                             const float* __restrict__ resp,
+                                                             const ColState* __restrict__ cols,
+                                                             unsigned long long* tile_state, Counters* ctr,
+                                                             int32_t* __restrict__ out_coords,
+                                                             float* __restrict__ out_feats, long long out_capacity,
+                                                             long long* __restrict__ nnz_out, long long aux_imm,
+                                                             int aux_is_cand) {
+    __shared__ int s_cnt[4];  // kept rows of each wave
     __shared__ int s_ticket;
     __shared__ long long s_base;
-    const int n_tiles = (int)ctr->n_tiles;
-    const int n_super = (n_tiles + tps - 1) / tps;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
-    const bool vec4 = (channels & 3) == 0 && ((size_t)out_feats & 15) == 0;
-
-    for (;;) {
-        __syncthreads();  // the previous super-tile's readers of s_ticket / s_base / s_cnt are done
+    const int n_tiles = (int)ctr->n_tiles, n_super = (n_tiles + 1) / 2;
+    if ((int)blockIdx.x >= (n_super > 0 ? n_super : 1)) return;
+    if (n_super > 0) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         if (threadIdx.x == 0) s_ticket = (int)take_ticket(ctr, 1u);
         __syncthreads();
-        const int st = s_ticket;
-        if (st >= n_super) break;
-        const bool once = (int)gridDim.x >= n_super;  // one ticket per workgroup covers the layer: do not ask again
-        float v[RPT][CMAX];
-        bool keep_row[RPT];
-        int row_b[RPT], row_first[RPT];
-        // row q of the thread: tile st * tps + (q * 256 + threadIdx.x) / 128, local row (.. & 127); the 64
-        // rows of a wave always lie in one tile
+        const int st = s_ticket, tile = st * 2 + (int)(threadIdx.x >> 7), r = threadIdx.x & (kTileRows - 1);
+        float v[CMAX];
+        bool keep = false;
+        int b = 0, row = 0;
+        if (tile < n_tiles) {  // (uniform in the wave)
+            b = sample_of_tile(tile_start, g.batch, tile);
+            const int lt = tile - tile_start[b];
+            row = cand_start[b] + lt * kTileRows + r;
+            const float* seg = resp + (size_t)tile * channels * kTileRows + r;
 #pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            const int e = q * 256 + threadIdx.x;
-            const int tile_v = st * tps + (e >> 7), r = e & (kTileRows - 1);
-            const int tile = UNI ? __builtin_amdgcn_readfirstlane(tile_v) : tile_v;
-            keep_row[q] = false;
-            row_b[q] = 0;
-            row_first[q] = -1;
-            if ((e >> 7) < tps && tile < n_tiles) {  // (uniform in the wave)
-                const int b_v = sample_of_tile(tile_start, g.batch, tile);
-                const int b = UNI ? __builtin_amdgcn_readfirstlane(b_v) : b_v;
-                const int first = cand_start[b] + (tile - tile_start[b]) * kTileRows;
-                int nrows = cand_start[b + 1] - first;
-                if (nrows > kTileRows) nrows = kTileRows;
-                const unsigned pos = (unsigned)(tile - tile_start[b]) * kTileRows + (unsigned)r;
-                row_b[q] = b;
-                if (r < nrows) row_first[q] = first + r;
-                const float* seg = resp + (size_t)tile * channels * kTileRows + r;
-#pragma unroll
-                for (int c = 0; c < CMAX; ++c)
-                    if (c < channels) v[q][c] = seg[(size_t)c * kTileRows];
-                bool any = false;
-#pragma unroll
-                for (int c = 0; c < CMAX; ++c) {
-                    if (c < channels) {
-                        const ColState* cs = cols + (size_t)b * channels + c;
-                        const unsigned tau = cs->tau, cut = cs->cut;
-                        const float x = v[q][c];
-                        const unsigned key = score_key(x, mode);
-                        bool keep = key > (pos <= cut ? tau - (tau != 0u ? 1u : 0u) : tau);
-                        if (relu) keep = keep && (x > 0.0f);
-                        keep = keep && r < nrows;
-                        v[q][c] = keep ? x : 0.0f;
-                        any |= keep;
-                    }
-                }
-                keep_row[q] = any;
-            }
+            for (int c = 0; c < CMAX; ++c)
+                if (c < channels) v[c] = seg[(size_t)c * kTileRows];
+            keep = decide_row<CMAX>(channels, mode, relu, cols + (size_t)b * channels, (unsigned)(lt * kTileRows + r), v) &&
+                   row < cand_start[b + 1];
         }
-        unsigned long long ball[RPT];
-#pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            ball[q] = __ballot(keep_row[q]);
-            if (lane == 0) s_cnt[q * 4 + wave] = __popcll(ball[q]);
-        }
+        const unsigned long long m = __ballot(keep);
+        if (lane == 0) s_cnt[wave] = __popcll(m);
         __syncthreads();
         if (wave == 0) {
-            int total = 0;
-#pragma unroll
-            for (int i = 0; i < RPT * 4; ++i) total += s_cnt[i];
+            const int total = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
             const long long base = lookback_wave(tile_state, st, total, ctr);
             if (lane == 0) {
                 if (st == n_super - 1)
@@ -1731,65 +1718,157 @@ __global__ __launch_bounds__(256, 4) void k_select_write_narrow(Geom g, int chan
             }
         }
         __syncthreads();
-        const long long base = s_base;
-#pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            int before = 0;  // kept rows of the super-tile before this wave's group (groups ascend with q, then wave)
-            for (int i = 0; i < q * 4 + wave; ++i) before += s_cnt[i];
-            const long long o = base + before + __popcll(ball[q] & lt_mask);
-            if (keep_row[q] && o < out_capacity) {
-                int c0, c1, c2;
-                site_of(g, cand_lin[row_first[q]], c0, c1, c2);
-                store_site(g, out_coords + o * (1 + g.ndim), row_b[q], c0, c1, c2);
-                float* dst = out_feats + o * channels;
-                if (vec4) {
-#pragma unroll
-                    for (int c = 0; c < CMAX; c += 4)
-                        if (c < channels) *(float4*)(dst + c) = make_float4(v[q][c], v[q][c + 1], v[q][c + 2], v[q][c + 3]);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < CMAX; ++c)
-                        if (c < channels) dst[c] = v[q][c];
-                }
-            }
-        }
-        if (once) break;
+        long long o = s_base + __popcll(m & ((1ull << lane) - 1ull));
+        for (int w = 0; w < wave; ++w) o += s_cnt[w];
+        if (keep && o < out_capacity) write_row<CMAX>(g, channels, b, cand_lin[row], v, o, out_coords, out_feats);
     }
-    finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity);
+    finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity, n_super > 0 ? n_super : 1);
+}
+
+// The pass in two launches, without tickets, look-back or end counters, for narrow layers of more than kNarrowPairTiles
+// tiles of capacity: read-modify-writes of one address are served one after the other, and a ticket and an end mark from each of
+// several hundred workgroups were half of the one launch's time.  Workgroup i of both launches owns the same consecutive
+// tiles.  The first notes the rows that keep an entry (row_keep, two words per tile) and the workgroup's number of them;
+// in the second a workgroup adds up the numbers before its own and writes its rows, reading no others; the last one
+// writes the result counters.  A wave takes the 64 rows of half a tile at a time.
+// 8 channels, us: 128^3 x 4, 5 k tiles 36 -> 9 + 11; 256^3 scattered, 13 k tiles 63 -> 17 + 20; 28 x 28 x 1024, 3 k tiles
+// 34 -> 10 + 11; 32^3 x 4, capacity 1028 tiles, 11.8 -> 4.8 + 5.2.  Sixteen channels, 132 tiles: 9.5 against 7.0 + 6.7.
+constexpr long long kNarrowPairTiles = 512;
+__device__ inline int tiles_per_workgroup(int n_tiles) { return (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x; }
+
+template <int CMAX>
+__global__ __launch_bounds__(256) void k_select_rows_narrow(Geom g, int channels, int mode, int relu,
+                                                            const int* __restrict__ cand_start,
+                                                            const int* __restrict__ tile_start,
+                                                            const float* __restrict__ resp,
+                                                            const ColState* __restrict__ cols,
+                                                            const Counters* __restrict__ ctr,
+                                                            unsigned long long* __restrict__ row_keep,
+                                                            unsigned* __restrict__ counts) {
+    __shared__ unsigned s_cnt[4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_tiles = (int)ctr->n_tiles, per = tiles_per_workgroup(n_tiles);
+    const int first = (int)blockIdx.x * per, last = first + per < n_tiles ? first + per : n_tiles;
+    unsigned cnt = 0;
+    for (int u = 2 * first + wave; u < 2 * last; u += 4) {
+        const int tile = u >> 1;
+        const int b = __builtin_amdgcn_readfirstlane(sample_of_tile(tile_start, g.batch, tile));
+        const int lt = tile - tile_start[b], r = (u & 1) * 64 + lane;
+        const bool live = lt * kTileRows + r < cand_start[b + 1] - cand_start[b];
+        const float* seg = resp + (size_t)tile * channels * kTileRows + r;
+        float v[CMAX];
+#pragma unroll
+        for (int c = 0; c < CMAX; ++c)
+            if (c < channels) v[c] = seg[(size_t)c * kTileRows];
+        const bool any = decide_row<CMAX>(channels, mode, relu, cols + (size_t)b * channels, (unsigned)(lt * kTileRows + r), v);
+        const unsigned long long m = __ballot(any && live);
+        if (lane == 0) row_keep[u] = m;
+        cnt += (unsigned)__popcll(m);
+    }
+    if (lane == 0) s_cnt[wave] = cnt;
+    __syncthreads();
+    if (threadIdx.x == 0) counts[blockIdx.x] = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+}
+
+template <int CMAX>
+__global__ __launch_bounds__(256) void k_select_emit_narrow(Geom g, int channels, int mode, int relu,
+                                                            const int* __restrict__ cand_start,
+                                                            const int* __restrict__ tile_start,
+                                                            const unsigned* __restrict__ cand_lin,
+                                                            const float* __restrict__ resp,
+                                                            const ColState* __restrict__ cols, Counters* ctr,
+                                                            const unsigned long long* __restrict__ row_keep,
+                                                            const unsigned* __restrict__ counts,
+                                                            int32_t* __restrict__ out_coords,
+                                                            float* __restrict__ out_feats, long long out_capacity,
+                                                            long long* __restrict__ nnz_out, long long aux_imm,
+                                                            int aux_is_cand) {
+    __shared__ unsigned s_sum[4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_tiles = (int)ctr->n_tiles, per = tiles_per_workgroup(n_tiles);
+    const int first = (int)blockIdx.x * per, last = first + per < n_tiles ? first + per : n_tiles;
+    if (first >= last && blockIdx.x != 0) return;
+    unsigned before = 0;  // rows of the workgroups before this one (31 bits: at most as many as candidates)
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) before += counts[i];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) before += __shfl_xor(before, d, 64);
+    if (lane == 0) s_sum[wave] = before;
+    __syncthreads();
+    unsigned base = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+    if (last == n_tiles && threadIdx.x == 0) {
+        const long long rows = (long long)base + (first < last ? counts[blockIdx.x] : 0u);
+        ctr->n_rows = rows;
+        if (nnz_out) {
+            nnz_out[0] = rows;
+            nnz_out[1] = aux_is_cand ? ctr->n_cand : aux_imm;
+            nnz_out[2] = (long long)(ctr->flags | (rows > out_capacity ? SCNN_FLAG_OUT_OVERFLOW : 0u));
+            nnz_out[3] = (long long)ctr->bracket_failed;
+        }
+    }
+    for (int u0 = 2 * first; u0 < 2 * last; u0 += 64) {  // 64 half tiles at a time: lane j holds the rows before the j-th
+        const unsigned long long mine = u0 + lane < 2 * last ? row_keep[u0 + lane] : 0ull;
+        unsigned inc = (unsigned)__popcll(mine);
+        const unsigned own = inc;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const unsigned o = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += o;
+        }
+        const int n = 2 * last - u0 < 64 ? 2 * last - u0 : 64;
+        for (int j = wave; j < n; j += 4) {
+            const unsigned long long m =
+                (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(mine >> 32), j) << 32 |
+                (unsigned)__builtin_amdgcn_readlane((int)(unsigned)mine, j);
+            if (m == 0ull) continue;
+            const long long o = (long long)(base + (unsigned)__builtin_amdgcn_readlane((int)(inc - own), j)) +
+                                __popcll(m & ((1ull << lane) - 1ull));
+            if (!((m >> lane) & 1ull) || o >= out_capacity) continue;
+            const int u = u0 + j, tile = u >> 1;
+            const int b = __builtin_amdgcn_readfirstlane(sample_of_tile(tile_start, g.batch, tile));
+            const int lt = tile - tile_start[b], r = (u & 1) * 64 + lane;
+            const float* seg = resp + (size_t)tile * channels * kTileRows + r;
+            const unsigned lin = cand_lin[cand_start[b] + lt * kTileRows + r];
+            float v[CMAX];
+#pragma unroll
+            for (int c = 0; c < CMAX; ++c)
+                if (c < channels) v[c] = seg[(size_t)c * kTileRows];
+            (void)decide_row<CMAX>(channels, mode, relu, cols + (size_t)b * channels, (unsigned)(lt * kTileRows + r), v);
+            write_row<CMAX>(g, channels, b, lin, v, o, out_coords, out_feats);
+        }
+        base += (unsigned)__builtin_amdgcn_readlane((int)inc, 63);
+    }
 }
 
 hipError_t launch_select_write(const Geom& g, int channels, int mode, int relu, const int* cand_start,
                                const int* tile_start, const unsigned* cand_lin, const float* resp,
                                const ColState* cols, unsigned long long* tile_state, long long tiles_cap,
                                Counters* ctr, int32_t* out_coords, float* out_feats, long long out_capacity,
-                               long long* nnz_out, long long aux_imm, int aux_is_cand, const long long* tile_base,
-                               hipStream_t s) {
+                               long long* nnz_out, long long aux_imm, int aux_is_cand, unsigned long long* row_keep,
+                               const long long* tile_base, hipStream_t s) {
     // no more workgroups than can be resident at once (4 per CU by LDS), so that every ticket holder runs; three per
     // CU measured best for the wide kernels (cfg 4: 103 us against 107 with four and 110 with two)
     const long long cus = device_cu_count();
     long long blocks = tiles_cap < 1 ? 1 : (tiles_cap > cus * 3 ? cus * 3 : tiles_cap);
-    // Narrow layers: a ticket covers 1, 2, 4 .. NT_ tiles, the fewest that leave at most two tickets per CU (a small
-    // layer is bound by the tickets, taken one at a time, and every workgroup launched takes at least one; one per
-    // CU and four per CU both measured slower on the paper's networks).
-#define SCNN_NARROW_CASE(CMAX_, NT_)                                                                              \
+#define SCNN_NARROW_CASE(CMAX_)                                                                                   \
     do {                                                                                                          \
-        int tps = 1;                                                                                              \
-        while (tps < NT_ && tiles_cap > 512ll * tps) tps *= 2;                                                    \
-        long long nb = (tiles_cap + tps - 1) / tps;                                                               \
-        nb = nb < 1 ? 1 : (nb > cus * 3 ? cus * 3 : nb);                                                          \
-        if (tiles_cap >= kNarrowUniformTiles)                                                                     \
-            hipLaunchKernelGGL((k_select_write_narrow<CMAX_, NT_, true>), dim3((unsigned)nb), dim3(256), 0, s, g, \
-                               channels, mode, relu, cand_start, tile_start, cand_lin, resp, cols, tile_state,    \
-                               ctr, out_coords, out_feats, out_capacity, nnz_out, aux_imm, aux_is_cand, tps);     \
-        else                                                                                                      \
-            hipLaunchKernelGGL((k_select_write_narrow<CMAX_, NT_, false>), dim3((unsigned)nb), dim3(256), 0, s, g, \
-                               channels, mode, relu, cand_start, tile_start, cand_lin, resp, cols, tile_state,    \
-                               ctr, out_coords, out_feats, out_capacity, nnz_out, aux_imm, aux_is_cand, tps);     \
+        if (tiles_cap > kNarrowPairTiles) {                                                                       \
+            const unsigned grid = (unsigned)(tiles_cap > cus * 4 ? cus * 4 : tiles_cap);                          \
+            unsigned* counts = (unsigned*)tile_state;                                                             \
+            hipLaunchKernelGGL(k_select_rows_narrow<CMAX_>, dim3(grid), dim3(256), 0, s, g, channels, mode, relu, \
+                               cand_start, tile_start, resp, cols, ctr, row_keep, counts);                        \
+            hipLaunchKernelGGL(k_select_emit_narrow<CMAX_>, dim3(grid), dim3(256), 0, s, g, channels, mode, relu, \
+                               cand_start, tile_start, cand_lin, resp, cols, ctr, row_keep, counts, out_coords,   \
+                               out_feats, out_capacity, nnz_out, aux_imm, aux_is_cand);                           \
+        } else                                                                                                    \
+            hipLaunchKernelGGL(k_select_write_narrow<CMAX_>, dim3((unsigned)(tiles_cap < 1 ? 1 : (tiles_cap + 1) / 2)), \
+                               dim3(256), 0, s, g, channels, mode, relu, cand_start, tile_start, cand_lin, resp,  \
+                               cols, tile_state, ctr, out_coords, out_feats, out_capacity, nnz_out, aux_imm,      \
+                               aux_is_cand);                                                                      \
     } while (0)
-    if (channels <= 4) SCNN_NARROW_CASE(4, 8);
-    else if (channels <= 8) SCNN_NARROW_CASE(8, 8);
-    else if (channels <= 16) SCNN_NARROW_CASE(16, 8);
-    else if (channels <= 32 && !tile_base) SCNN_NARROW_CASE(32, 4);  // (with tile_base: the streaming kernel below)
+    if (channels <= 4) SCNN_NARROW_CASE(4);
+    else if (channels <= 8) SCNN_NARROW_CASE(8);
+    else if (channels <= 16) SCNN_NARROW_CASE(16);
+    else if (channels <= 32 && !tile_base) SCNN_NARROW_CASE(32);  // (with tile_base: the streaming kernel below)
     else if (channels <= 64) {
         // (streaming: four workgroups per CU; by look-back three measured best, and four cost it 5 %, which only the
         // rare launch that was given tile_base and cannot use it pays)

@@ -1,0 +1,52 @@
+"""Compaction of narrow layers: the one-launch and the two-launch form on either side of their border (512 tiles of
+capacity), few and no rows, samples without rows, odd channel counts, more surviving rows than the output holds."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1801_10585_amd as scnn
+from workloads import random_sparse_sites
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode", [scnn.ABS, scnn.SIGNED])
+@pytest.mark.parametrize("cap", [510 * 128, 510 * 128 + 1, 200000])
+@pytest.mark.parametrize("ext,c_out,density,rho,relu,pool", [
+    ((46, 40, 43), 8, 0.025, 0.1, True, False), ((46, 40, 43), 3, 0.025, 0.2, False, True), ((46, 40, 43), 16, 0.025, 0.05, True, True),
+    ((30, 50, 60), 31, 0.022, 0.1, False, False), ((30, 50, 60), 1, 0.022, 0.01, False, False), ((300, 310), 7, 0.07, 1.0, False, False)])
+def test_narrow_layers_on_either_side_of_the_launch_rule(ext, c_out, density, rho, relu, pool, cap, mode):
+    """Small whole numbers, many of them equal: the oracle's rows, bit for bit."""
+    rng = np.random.default_rng(c_out + ext[0])
+    ksize = (3,) * len(ext)
+    coords = random_sparse_sites(rng, ext, 2, density)
+    coords = coords[(coords[:, 0] == 1) | (rng.random(len(coords)) < 0.3)]
+    feats = rng.integers(1, 4, size=(len(coords), 2)).astype(np.float32)
+    w = rng.integers(-2, 3, size=(3 ** len(ext), 2, c_out)).astype(np.float32)
+    c, f, t = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (coords, feats, w))
+    print(ext, c_out, len(coords), cap, mode, flush=True)
+    rc, rf = oracle.sparse_conv_fwd(ext, 2, coords, feats, ksize, w, rho_up=rho, topk_mode=mode, relu=relu, pool=pool)
+    gc, gf, n = scnn.sparse_conv_fwd(ext, 2, c, f, ksize, t, rho_up=rho, topk_mode=mode, relu=relu, pool=pool,
+                                     cand_capacity=cap, out_capacity=cap)
+    assert len(coords) * 3 ** len(ext) > 511 * 128  # (the capacity asked for is the one that the call has)
+    assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf)
+    if not pool:  # a small output: its rows are the first ones, the count is the whole, the bit is set
+        out = (torch.full((70, 1 + len(ext)), -7, dtype=torch.int32, device="cuda"),
+               torch.full((70, c_out), -7.0, device="cuda"), torch.zeros(4, dtype=torch.int64, device="cuda"))
+        gc, gf, n = scnn.sparse_conv_fwd(ext, 2, c, f, ksize, t, rho_up=rho, topk_mode=mode, relu=relu, cand_capacity=200000,
+                                         out_capacity=64, out=out, sync=False)
+        assert int(n[0]) == len(rc) and int(n[2]) == 2
+        assert np.array_equal(out[0][:64].cpu().numpy(), rc[:64]) and np.array_equal(out[1][:64].cpu().numpy(), rf[:64])
+        assert bool((out[0][64:] == -7).all()) and bool((out[1][64:] == -7).all())
+
+
+def test_narrow_layers_without_rows():
+    for cap in (1000, 100000):
+        z = (torch.zeros((0, 4), dtype=torch.int32, device="cuda"), torch.zeros((0, 4), device="cuda"))
+        rows = torch.randint(0, 3, (50, 1), device="cuda")
+        c = torch.cat([torch.zeros_like(rows), torch.arange(50, device="cuda")[:, None], rows, rows], 1).to(torch.int32)
+        w = torch.zeros((27, 4, 8), device="cuda")  # (no tap is active: no candidate sites)
+        for coords, feats in (z, (c, torch.ones((50, 4), device="cuda"))):
+            oc, of, n = scnn.sparse_conv_fwd((60, 60, 60), 1, coords, feats, (3, 3, 3), w, rho_up=0.1, cand_capacity=cap)
+            assert oc.shape[0] == of.shape[0] == 0 and [int(v) for v in n] == [0, 0, 0, 0]
