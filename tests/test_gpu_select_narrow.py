@@ -50,3 +50,21 @@ def test_narrow_layers_without_rows():
         for coords, feats in (z, (c, torch.ones((50, 4), device="cuda"))):
             oc, of, n = scnn.sparse_conv_fwd((60, 60, 60), 1, coords, feats, (3, 3, 3), w, rho_up=0.1, cand_capacity=cap)
             assert oc.shape[0] == of.shape[0] == 0 and [int(v) for v in n] == [0, 0, 0, 0]
+
+
+@pytest.mark.parametrize("mode", [scnn.ABS, scnn.SIGNED])
+@pytest.mark.parametrize("c_out,relu,pool", [(8, False, False), (40, True, False), (70, False, True)])
+@pytest.mark.parametrize("ext,rho,below", [((50, 51, 52), 1.0, 0), ((50, 51, 52), 0.5, 0), ((50, 51, 52), 0.5, 1), ((12, 9), 1.0, 0)])
+def test_a_selection_that_keeps_everything(ext, rho, below, c_out, relu, pool, mode):
+    """k at the sites of the grid, at the capacity of the workspace, and one below it, where columns are selected."""
+    rng = np.random.default_rng(c_out)
+    ksize = (3,) * len(ext)
+    coords = random_sparse_sites(rng, ext, 1, 0.01 if len(ext) == 3 else 0.2)
+    feats = rng.integers(1, 4, size=(len(coords), 4)).astype(np.float32)
+    w = rng.integers(-2, 3, size=(3 ** len(ext), 4, c_out)).astype(np.float32)
+    rc, rf = oracle.sparse_conv_fwd(ext, 1, coords, feats, ksize, w, rho_up=rho, topk_mode=mode, relu=relu, pool=pool)
+    cap = 0 if rho == 1.0 else scnn.k_from_rho(rho, int(np.prod(ext))) + below
+    gc, gf, n = scnn.sparse_conv_fwd(ext, 1, *(torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (coords, feats)), ksize,
+                                     torch.from_numpy(w).cuda(), rho_up=rho, topk_mode=mode, relu=relu, pool=pool,
+                                     cand_capacity=cap)
+    assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf) and int(n[2]) == 0
