@@ -229,16 +229,18 @@ __device__ inline void split_rows(const float* __restrict__ feats, long long n, 
 // One thread per input row: set the row's bit; the first row of each word
 // records its own index as that word's prefix.  Rows outside the grid are
 // skipped and reported; a row not strictly above its predecessor is reported.
+// at_row(row, on the grid, b, c0, c1, c2) is called by the whole wave for each of its rows.
+template <typename AtRow>
 __device__ __forceinline__ void index_rows(const Geom& g, const int32_t* __restrict__ coords, long long n, int blocks,
                                            unsigned long long* __restrict__ occ, unsigned* __restrict__ occ_prefix,
-                                           Counters* ctr) {
+                                           Counters* ctr, AtRow&& at_row) {
     const int stride = 1 + g.ndim;
     const int lane = threadIdx.x & 63;
     for (long long base = (long long)blockIdx.x * blockDim.x; base < n; base += (long long)blocks * blockDim.x) {
         const long long r = base + threadIdx.x;
         long long key = -1;
+        int b = 0, c0 = 0, c1 = 0, c2 = 0;
         if (r < n) {
-            int b, c0, c1, c2;
             load_site(g, coords + r * stride, b, c0, c1, c2);
             if (site_in_grid(g, b, c0, c1, c2)) {
                 key = (long long)b * g.Npad + lin_of(g, c0, c1, c2);
@@ -260,7 +262,13 @@ __device__ __forceinline__ void index_rows(const Geom& g, const int32_t* __restr
         unsigned long long bits = key >= 0 ? (1ull << (key & 63)) : 0ull;
         const bool first = wave_or_runs(word, bits);
         if (key >= 0 && first) atomicOr(&occ[word], bits);
+        at_row(r, key >= 0, b, c0, c1, c2);
     }
+}
+__device__ __forceinline__ void index_rows(const Geom& g, const int32_t* __restrict__ coords, long long n, int blocks,
+                                           unsigned long long* __restrict__ occ, unsigned* __restrict__ occ_prefix,
+                                           Counters* ctr) {
+    index_rows(g, coords, n, blocks, occ, occ_prefix, ctr, [](long long, bool, int, int, int, int) {});
 }
 
 // A device-resident count never reaches past the arrays.
@@ -275,6 +283,54 @@ __global__ __launch_bounds__(256) void k_index_build(Geom g, const int32_t* __re
                                                      unsigned long long* __restrict__ occ,
                                                      unsigned* __restrict__ occ_prefix, Counters* ctr) {
     index_rows(g, coords, row_count(n_imm, n_dev, n_cap), (int)gridDim.x, occ, occ_prefix, ctr);
+}
+
+// The same for the pooling, with the bits of the output sites: a row sets that of its block of 2^d sites.
+// rows_have_entries != 0: the caller guarantees that every row holds a non-zero entry (skip the check).  (One launch: as
+// two, a 28 x 28 image took 4 us more.)
+__global__ __launch_bounds__(256) void k_index_build_pool(Geom g, Geom gp, const int32_t* __restrict__ coords,
+                                                          const float* __restrict__ feats, int channels,
+                                                          int rows_have_entries, long long n_imm,
+                                                          const long long* __restrict__ n_dev, long long n_cap,
+                                                          unsigned long long* __restrict__ occ,
+                                                          unsigned* __restrict__ occ_prefix,
+                                                          unsigned long long* __restrict__ pbits, Counters* ctr) {
+    const int lane = threadIdx.x & 63;
+    index_rows(g, coords, row_count(n_imm, n_dev, n_cap), (int)gridDim.x, occ, occ_prefix, ctr,
+               [&](long long r, bool any, int b, int c0, int c1, int c2) {
+        if (any && !rows_have_entries) {  // a row of zeros holds no entry and creates no output site
+            // (stops at the first non-zero value, which an ordinary row has in its first few channels; 16 bytes
+            // at a time where the rows allow it)
+            any = false;
+            const float* row = feats + r * channels;
+            if ((channels & 3) == 0 && (((size_t)feats) & 15) == 0) {
+                for (int c = 0; c < channels && !any; c += 4) {
+                    const float4 v = *reinterpret_cast<const float4*>(row + c);
+                    any = v.x != 0.0f || v.y != 0.0f || v.z != 0.0f || v.w != 0.0f;
+                }
+            } else {
+                for (int c = 0; c < channels && !any; ++c) any = row[c] != 0.0f;
+            }
+        }
+        const long long key = any ? (long long)b * gp.Npad + lin_of(gp, c0 >> 1, c1 >> 1, c2 >> 1) : -1;
+        // neighbouring rows fall into the same output word: one atomic per run of equal words
+        const long long word = any ? (key >> 6) : (long long)(-1 - lane);
+        unsigned long long bits = any ? (1ull << (key & 63)) : 0ull;
+        const bool first = wave_or_runs(word, bits);
+        if (any && first) atomicOr(&pbits[word], bits);
+    });
+}
+
+hipError_t launch_index_build_pool(const Geom& g, const Geom& gp, const int32_t* coords, const float* feats, int channels,
+                                   int rows_have_entries, long long n_imm, const long long* n_dev, long long n_cap,
+                                   unsigned long long* occ, unsigned* occ_prefix, unsigned long long* pbits, Counters* ctr,
+                                   hipStream_t s) {
+    long long blocks = (n_cap + 255) / 256;
+    if (blocks < 1) blocks = 1;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_index_build_pool, dim3((unsigned)blocks), dim3(256), 0, s, g, gp, coords, feats, channels,
+                       rows_have_entries, n_imm, n_dev, n_cap, occ, occ_prefix, pbits, ctr);
+    return hipGetLastError();
 }
 
 // The same for the split kernels: workgroups from index_blocks on take the rows' values.

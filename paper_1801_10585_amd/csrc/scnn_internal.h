@@ -372,6 +372,10 @@ hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_
                               long long n_cap, unsigned long long* occ, unsigned* occ_prefix, Counters* ctr,
                               const float* feats /* nullable: rows of a split kernel */, int c_in,
                               unsigned short* xs /* nullable: also split them */, const int* tap_active, hipStream_t s);
+hipError_t launch_index_build_pool(const Geom& g, const Geom& gp, const int32_t* coords, const float* feats, int channels,
+                                   int rows_have_entries, long long n_imm, const long long* n_dev, long long n_cap,
+                                   unsigned long long* occ, unsigned* occ_prefix, unsigned long long* pbits, Counters* ctr,
+                                   hipStream_t s);
 // wp / wb / wq / ws: the filter in the layout of the vector / fp32 pair-list / fp32 quad / split kernels (of wb, wq and
 // ws at most the one that will run is non-null; wp is used when all three are null)
 hipError_t launch_prepare(const Geom& g, const float* w, int c_in, int c_out, int adjoint, int c_out_pad, double* wp,

@@ -71,46 +71,6 @@ hipError_t launch_relu(const Geom& g, const int32_t* coords, const float* feats,
 }
 
 // ------------------------------------------------------------------ max-pooling
-// rows_have_entries != 0: the caller guarantees that every row holds a non-zero entry (skip the check).
-__global__ __launch_bounds__(256) void k_pool_mark(Geom g, Geom gp, const int32_t* __restrict__ coords,
-                                                   const float* __restrict__ feats, int channels,
-                                                   int rows_have_entries, long long n_imm,
-                                                   const long long* __restrict__ n_dev,
-                                                   unsigned long long* __restrict__ pbits) {
-    const long long n = n_dev ? *n_dev : n_imm;
-    const int stride = 1 + g.ndim;
-    const int lane = threadIdx.x & 63;
-    for (long long base = (long long)blockIdx.x * blockDim.x; base < n; base += (long long)gridDim.x * blockDim.x) {
-        const long long r = base + threadIdx.x;
-        long long key = -1;
-        if (r < n) {
-            int b, c0, c1, c2;
-            load_site(g, coords + r * stride, b, c0, c1, c2);
-            bool any = site_in_grid(g, b, c0, c1, c2);
-            if (any && !rows_have_entries) {  // a row of zeros holds no entry and creates no output site
-                // (stops at the first non-zero value, which an ordinary row has in its first few channels; 16 bytes
-                // at a time where the rows allow it)
-                any = false;
-                const float* row = feats + r * channels;
-                if ((channels & 3) == 0 && (((size_t)feats) & 15) == 0) {
-                    for (int c = 0; c < channels && !any; c += 4) {
-                        const float4 v = *reinterpret_cast<const float4*>(row + c);
-                        any = v.x != 0.0f || v.y != 0.0f || v.z != 0.0f || v.w != 0.0f;
-                    }
-                } else {
-                    for (int c = 0; c < channels && !any; ++c) any = row[c] != 0.0f;
-                }
-            }
-            if (any) key = (long long)b * gp.Npad + lin_of(gp, c0 >> 1, c1 >> 1, c2 >> 1);
-        }
-        // neighbouring rows fall into the same output word: one atomic per run of equal words
-        const long long word = key >= 0 ? (key >> 6) : (long long)(-1 - lane);
-        unsigned long long bits = key >= 0 ? (1ull << (key & 63)) : 0ull;
-        const bool first = wave_or_runs(word, bits);
-        if (key >= 0 && first) atomicOr(&pbits[word], bits);
-    }
-}
-
 // The result counters of a pooling call, written by the thread that knows the number of pooled rows (nnz_out may be
 // null: a later launch writes them).  Nothing after this point sets a status bit.
 __device__ inline void pool_counters(const Counters* ctr, long long rows, long long* nnz_out, long long aux_imm,
@@ -313,13 +273,10 @@ hipError_t launch_maxpool(const Geom& g, const Geom& gp, const int32_t* coords, 
                           int32_t* out_coords, float* out_feats, long long out_capacity, Counters* ctr,
                           long long* nnz_out, long long aux_imm, int aux_is_cand, hipStream_t s) {
     // occ / pbits must be zero on entry
-    hipError_t e = launch_index_build(g, coords, n_imm, n_dev, n_cap, occ, occ_prefix, ctr, nullptr, 0, nullptr, nullptr, s);
+    hipError_t e = launch_index_build_pool(g, gp, coords, feats, channels, rows_have_entries, n_imm, n_dev, n_cap, occ,
+                                           occ_prefix, pbits, ctr, s);
     if (e != hipSuccess) return e;
-    long long blocks = (n_cap + 255) / 256;
-    if (blocks < 1) blocks = 1;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_pool_mark, dim3((unsigned)blocks), dim3(256), 0, s, g, gp, coords, feats, channels,
-                       rows_have_entries, n_imm, n_dev, pbits);
+    long long blocks;
     const long long n_words = (long long)gp.batch * gp.Wps;
     if (n_words <= kEmitSmallWords) {
         hipLaunchKernelGGL(k_pool_emit_small, dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0, s, pbits,
