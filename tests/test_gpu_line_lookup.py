@@ -18,7 +18,7 @@ def _dev(*arrays):
 @pytest.mark.parametrize("ext,ksize,density", [
     ((6, 5, 1), (3, 3, 5), 0.5), ((5, 7, 3), (3, 3, 7), 0.5), ((9, 5, 64), (5, 5, 5), 0.1), ((4, 5, 65), (3, 3, 3), 0.4),
     ((40, 130), (1, 63), 0.2), ((30, 70), (3, 35), 0.3), ((33, 31), (7, 31), 1.0), ((3, 3, 200), (1, 3, 33), 0.3)])
-@pytest.mark.parametrize("c_in,c_out,path", [(1, 8, 1), (8, 8, 1), (32, 16, 3), (8, 40, 1)])
+@pytest.mark.parametrize("c_in,c_out,path", [(1, 8, 1), (1, 11, 1), (1, 16, 0), (8, 8, 1), (32, 16, 3), (8, 40, 1)])
 def test_neighbours_along_filter_lines(ext, ksize, density, c_in, c_out, path):
     """Small whole numbers: every sum is exact, so results are compared bit for bit."""
     rng = np.random.default_rng(len(ext) * 1000 + ext[-1] + c_in)
@@ -29,14 +29,15 @@ def test_neighbours_along_filter_lines(ext, ksize, density, c_in, c_out, path):
     gc = random_sparse_sites(rng, ext, 2, density)
     gf = rng.integers(-3, 4, size=(gc.shape[0], c_out)).astype(np.float32)
     print(ext, ksize, c_in, c_out, path, coords.shape[0], gc.shape[0], flush=True)
+    bias = rng.integers(-2, 3, size=c_out).astype(np.float32)
     scnn.set_conv_path(path)
     try:
-        oc, of, _ = scnn.sparse_conv_fwd(ext, 2, *_dev(coords, feats), ksize, *_dev(w))
+        oc, of, _ = scnn.sparse_conv_fwd(ext, 2, *_dev(coords, feats), ksize, *_dev(w, bias))
         scnn.set_conv_path(path if path == 1 else 0)
         data, filt, info = scnn.sparse_conv_bwd(ext, 2, *_dev(coords, feats), ksize, *_dev(w, gc, gf))
     finally:
         scnn.set_conv_path(0)
-    rc, rf = oracle.sparse_conv_fwd(ext, 2, coords, feats, ksize, w, rho_up=1.0)
+    rc, rf = oracle.sparse_conv_fwd(ext, 2, coords, feats, ksize, w, bias, rho_up=1.0)
     assert np.array_equal(oc.cpu().numpy(), rc) and np.array_equal(of.cpu().numpy(), rf)
     rd, rw = oracle.sparse_conv_bwd(ext, 2, coords, feats, ksize, w, gc, gf)
     assert int(info[2]) == 0
