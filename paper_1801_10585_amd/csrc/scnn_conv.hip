@@ -177,15 +177,20 @@ __global__ __launch_bounds__(256) void k_conv_valu_stream(Geom g, const unsigned
     }
 }
 
-// One input channel (the first layer of every network): a neighbour costs one value and C_out multiply-adds, so what the
-// forms above spend per tap and wave, whether a lane has the neighbour or not, is nearly all of their time.  Here a thread
-// owns a site and walks the neighbours that it has, lowest tap first, four values in flight, with the weights of its tap
+// One input channel (the first layer of every network), or eight: a neighbour costs few values and multiply-adds, so what
+// the forms above spend per tap and wave, whether a lane has the neighbour or not, is nearly all of their time.  Here a
+// thread owns a site and walks the neighbours that it has, lowest tap first, several in flight, with the weights of its tap
 // from LDS: a wave takes as many rounds as its richest site has neighbours (three of 27 taps on scattered sites, about
-// half of them on surfaces).  The sums are fp64 and in tap order.  Eight output channels, against the forms above: 256^3
-// scattered, 1.7 M sites, 104 -> 35 us; 28 x 28 x 1024 29 -> 17.5; one 28 x 28 image 9.8 -> 5.3.
+// half of them on surfaces).  The sums are fp64 and in tap order.  One input and eight output channels, against the forms
+// above: 256^3 scattered, 1.7 M sites, 104 -> 35 us; 28 x 28 x 1024 29 -> 17.5; one 28 x 28 image 9.8 -> 5.3.
+// Eight input channels are bound by the weights' way out of LDS (512 bytes a lane and neighbour): 128^3 x 4, 8 -> 8,
+// 91 -> 57 us; calls with 8 / 16 output channels on 48^3 x 4 115 / 124 -> 86 / 108, on 128^3 x 2 155 / 186 -> 122 / 166 (a
+// tenth of it the compaction's gain).  Small layers wait for a thread's chain instead: on 32^3 x 4, 464 tiles of capacity,
+// calls 74 / 78 -> 63 / 80, 16 output channels on 22^3 x 13, 662 tiles, 97 -> 107, on 132 tiles the kernel 22 -> 41;
+// hence the rule of the launch: 8 output channels from the 32-row form's end on, 16 where the streaming form takes over.
 constexpr int kOneLines = 9;  // filter lines at most (and 32 taps)
 constexpr long long kOneBlocks = 256 * 16;
-template <int OCB /* output channels at most: 8 or 16 */>
+template <int CI /* input channels: 1 or 8 */, int OCB /* output channels at most: 8 or 16 */>
 __global__ __launch_bounds__(256) void k_conv_valu_one(Geom g, const unsigned long long* __restrict__ occ,
                                                        const unsigned* __restrict__ occ_prefix, long long nnz_in,
                                                        const float* __restrict__ feats, const double* __restrict__ wp,
@@ -195,14 +200,16 @@ __global__ __launch_bounds__(256) void k_conv_valu_one(Geom g, const unsigned lo
                                                        const int* __restrict__ cand_start,
                                                        const int* __restrict__ tile_start,
                                                        const Counters* __restrict__ ctr, float* __restrict__ resp) {
-    constexpr int WS = OCB + 2;  // (lanes at different taps read different banks)
+    constexpr int U = CI == 1 ? 4 : 2;  // neighbours in flight
+    constexpr int WS = CI * OCB + 2;  // (lanes at different taps read different banks)
     __shared__ __align__(16) double s_w[32 * WS];
     __shared__ unsigned s_row[kOneLines][256];  // row of the first occupied site on the thread's window of each line
     __shared__ unsigned char s_line[32], s_k[32];  // line of a tap and its place there
     const int T = g.T, K1 = g.K[1], K2 = g.K[2], n_lines = g.K[0] * K1;
     const int tid = threadIdx.x, n_tiles = (int)ctr->n_tiles;
     const unsigned act = active_taps(tap_active, 0, T);
-    for (int i = tid; i < T * OCB; i += 256) s_w[i / OCB * WS + i % OCB] = wp[(size_t)(i / OCB) * c_out_pad + i % OCB];
+    for (int i = tid; i < T * CI * OCB; i += 256)
+        s_w[i / (CI * OCB) * WS + i % (CI * OCB)] = wp[(size_t)(i / OCB) * c_out_pad + i % OCB];
     if (tid < T) {
         s_line[tid] = (unsigned char)(tid / K2);
         s_k[tid] = (unsigned char)(tid % K2);
@@ -254,32 +261,40 @@ __global__ __launch_bounds__(256) void k_conv_valu_one(Geom g, const unsigned lo
         for (int o = 0; o < OCB; ++o) acc[o] = 0.0;
         const unsigned line_mask = K2 >= 32 ? ~0u : (1u << K2) - 1u;
         for (unsigned m = raw & act; m != 0u;) {
-            int t[4];
-            float x[4];
+            int t[U];
+            float x[U][CI];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < U; ++j) {
                 t[j] = -1;
-                x[j] = 0.0f;
                 if (m != 0u) {
                     const int tap = __builtin_ctz(m), line = s_line[tap], kk = s_k[tap];
                     m &= m - 1u;
                     const unsigned row = s_row[line][tid] + (unsigned)__popc((raw >> (tap - kk)) & line_mask & ((1u << kk) - 1u));
                     if (row < (unsigned)nnz_in) {  // (only an unsorted input can trip this guard)
                         t[j] = tap;
-                        x[j] = feats[row];
+                        if constexpr (CI == 1) {
+                            x[j][0] = feats[row];
+                        } else {
+                            const float4 u = *(const float4*)(feats + (size_t)row * CI), v = *(const float4*)(feats + (size_t)row * CI + 4);
+                            x[j][0] = u.x; x[j][1] = u.y; x[j][2] = u.z; x[j][3] = u.w;
+                            x[j][4] = v.x; x[j][5] = v.y; x[j][6] = v.z; x[j][7] = v.w;
+                        }
                     }
                 }
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < U; ++j)
                 if (t[j] >= 0) {
                     const double2* wr = (const double2*)(s_w + t[j] * WS);
-                    const double xd = (double)x[j];
 #pragma unroll
-                    for (int o = 0; o < OCB / 2; ++o) {
-                        const double2 w = wr[o];
-                        acc[2 * o] = fma(xd, w.x, acc[2 * o]);
-                        acc[2 * o + 1] = fma(xd, w.y, acc[2 * o + 1]);
+                    for (int ic = 0; ic < CI; ++ic) {
+                        const double xd = (double)x[j][ic];
+#pragma unroll
+                        for (int o = 0; o < OCB / 2; ++o) {
+                            const double2 w = wr[ic * (OCB / 2) + o];
+                            acc[2 * o] = fma(xd, w.x, acc[2 * o]);
+                            acc[2 * o + 1] = fma(xd, w.y, acc[2 * o + 1]);
+                        }
                     }
                 }
         }
@@ -916,13 +931,16 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
         hipLaunchKernelGGL(k_conv_valu_empty, dim3(256 * 8), dim3(256), 0, s, c_out, ctr, resp);
         return hipGetLastError();
     }
-    if (c_in == 1 && c_out <= 16 && g.T <= 32 && g.K[0] * g.K[1] <= kOneLines) {
+    const bool eight = c_in == 8 && ((uintptr_t)feats & 15) == 0 && tiles_cap > (c_out <= 8 ? kValuSmallItems : kValuLatencyItems);
+    if ((c_in == 1 || eight) && c_out <= 16 && g.T <= 32 && g.K[0] * g.K[1] <= kOneLines) {
         const unsigned blocks = (unsigned)(tiles_cap < 2 ? 1 : ((tiles_cap + 1) / 2 > kOneBlocks ? kOneBlocks : (tiles_cap + 1) / 2));
-#define SCNN_VALU_ONE(OCB_)                                                                                              \
-    hipLaunchKernelGGL(k_conv_valu_one<OCB_>, dim3(blocks), dim3(256), 0, s, g, occ, occ_prefix, nnz_in, feats, wp, c_out, \
+#define SCNN_VALU_ONE(CI_, OCB_)                                                                                              \
+    hipLaunchKernelGGL((k_conv_valu_one<CI_, OCB_>), dim3(blocks), dim3(256), 0, s, g, occ, occ_prefix, nnz_in, feats, wp, c_out, \
                        c_out_pad, bias, tap_active, cand_lin, cand_start, tile_start, ctr, resp)
-        if (c_out <= 8) SCNN_VALU_ONE(8);
-        else SCNN_VALU_ONE(16);
+        if (c_in == 1 && c_out <= 8) SCNN_VALU_ONE(1, 8);
+        else if (c_in == 1) SCNN_VALU_ONE(1, 16);
+        else if (c_out <= 8) SCNN_VALU_ONE(8, 8);
+        else SCNN_VALU_ONE(8, 16);
 #undef SCNN_VALU_ONE
         return hipGetLastError();
     }

@@ -42,3 +42,21 @@ def test_neighbours_along_filter_lines(ext, ksize, density, c_in, c_out, path):
     rd, rw = oracle.sparse_conv_bwd(ext, 2, coords, feats, ksize, w, gc, gf)
     assert int(info[2]) == 0
     assert np.array_equal(data.cpu().numpy(), rd) and np.array_equal(filt.cpu().numpy(), rw)
+
+
+@pytest.mark.parametrize("ext,batch", [((20, 21, 75), 2), ((46, 40, 43), 2), ((240, 250), 1)])
+@pytest.mark.parametrize("c_out", [5, 8, 9, 16])
+@pytest.mark.parametrize("rows_at", [0, 4])
+def test_eight_input_channels_by_size_and_alignment(ext, batch, c_out, rows_at):
+    """Layers from 257 tiles of capacity on, with rows at a 16-byte boundary and past one: small whole numbers, exact."""
+    rng = np.random.default_rng(c_out + ext[0])
+    k = (3,) * len(ext)
+    coords = random_sparse_sites(rng, ext, batch, 0.1)
+    feats = rng.integers(-3, 4, size=(coords.shape[0], 8)).astype(np.float32)
+    w = (rng.integers(-3, 4, size=(3 ** len(ext), 8, c_out)) * (rng.random((3 ** len(ext), 1, 1)) < 0.8)).astype(np.float32)
+    room = torch.zeros(feats.size + 4, device="cuda")
+    x = room[rows_at // 4:rows_at // 4 + feats.size].view(feats.shape)
+    x.copy_(torch.from_numpy(feats))
+    oc, of, _ = scnn.sparse_conv_fwd(ext, batch, _dev(coords)[0], x, k, *_dev(w))
+    rc, rf = oracle.sparse_conv_fwd(ext, batch, coords, feats, k, w, rho_up=1.0)
+    assert np.array_equal(oc.cpu().numpy(), rc) and np.array_equal(of.cpu().numpy(), rf)
