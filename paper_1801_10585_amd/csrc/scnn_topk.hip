@@ -991,68 +991,62 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(int mode, int ch
     }
 }
 
-// The same for columns of at most 1024 positions (eight tiles: 2-D grids up to 32 x 32, 3-D up to 10^3), one WAVE
-// per column and no shared memory: batches of thousands of such samples (a batch of small images) have thousands
-// of columns, and a workgroup of 1024 threads with five passes over a 2048-bin histogram costs each of them about
-// 10 us.  The k-th strongest key is found bit by bit, from the top: with the bits above already fixed, the keys
-// that have the next bit set are counted (a ballot per register); the tie cut is the position of the q-th equal key
-// in position order.  kTinyPerLane = 64 takes columns of up to 4096 positions (16^3 grids).  Both forms are used
-// when there are a thousand columns or more; with few columns a workgroup per column is as fast or a little faster
-// (the 32 dependent bit steps of a wave against five histogram passes of a workgroup).
+// The same for columns of at most 1024 positions (eight tiles: 2-D grids up to 32 x 32, 3-D up to 10^3), one WAVE per
+// column and no shared memory: a workgroup of 1024 threads with five passes over a 2048-bin histogram costs a column about
+// 10 us.  The k-th strongest key is found bit by bit, from the top: the largest value that at least k keys reach (a compare
+// and a ballot's count per register and bit, which is what it is bound by; hence as few registers as the column's tiles
+// need, a uniform choice); the tie cut is the position of the q-th equal key in position order.  28 x 28 x 1024, three
+// tiles a column, 8192 columns: 28.6 -> 14.8 us (sixteen registers always, the keys' leading bits compared, before); one
+// image, eight columns, 10.6 by a workgroup per column, 4.2 so.  kTinyPerLane = 64 takes columns of up to 4096 positions
+// (16^3 grids) where there are a thousand of them or more; with 64 a wave's 32 steps over 64 registers take 43 us and a
+// workgroup's histogram passes 11.
 constexpr long long kTinyColumn = 64 * 16;   // positions of a column at most, 16 keys per lane
 constexpr long long kTinyColumn64 = 64 * 64;  // ... 64 keys per lane
 constexpr int kTinyManyColumns = 1024;
 
-template <int kTinyPerLane>
-__global__ __launch_bounds__(256) void k_select_tiny(int mode, int channels, int ncols,
-                                                     const int* __restrict__ tile_start,
-                                                     const float* __restrict__ resp, long long k,
-                                                     ColState* __restrict__ cols) {
+template <int NU /* keys per lane: n <= 64 NU */>
+__device__ __forceinline__ void select_tiny(int mode, const float* __restrict__ column, size_t pitch, unsigned n, long long k,
+                                            ColState* __restrict__ out) {
     const int lane = threadIdx.x & 63;
-    const int col = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-    if (col >= ncols) return;  // (whole waves)
-    const int b = col / channels, oc = col - b * channels;
-    const int t0 = tile_start[b], t1 = tile_start[b + 1];
-    const unsigned n = (unsigned)(t1 - t0) * kTileRows;  // positions of the column (<= 64 kTinyPerLane, see the launcher)
     // key u of the lane sits at position u * 64 + lane
-    unsigned key[kTinyPerLane];
+    unsigned key[NU];
     unsigned n_nz = 0;
 #pragma unroll
-    for (int u = 0; u < kTinyPerLane; ++u) {
+    for (int u = 0; u < NU; ++u) {
         const unsigned i = (unsigned)u * 64u + (unsigned)lane;
-        key[u] = 0u;
-        if (i < n)
-            key[u] = score_key(resp[((size_t)(t0 + (int)(i >> 7)) * channels + oc) * kTileRows + (i & 127u)], mode);
-        n_nz += (unsigned)__popcll(__ballot(key[u] != 0u));
+        key[u] = i < n ? score_key(column[(size_t)(i >> 7) * pitch + (i & 127u)], mode) : 0u;
     }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) n_nz += (unsigned)__popcll(__ballot(key[u] != 0u));
     ColState st;
     st.tau = 0; st.cut = 0xffffffffu; st.n_eq = 0; st.q = 0; st.tau_lo = 0; st.tau_hi = 0; st.n_nz = n_nz;
     st.n_above = 0; st.side_fill = 0; st.done = 1; st.side_off = 0;
     if (k <= 0) st.tau = 0xffffffffu;  // no key is stronger: nothing survives
     if (k <= 0 || (long long)n_nz <= k) {  // or fewer entries than k: all survive (tau = 0)
-        if (lane == 0) cols[col] = st;
+        if (lane == 0) *out = st;
         return;
     }
     // 1 <= k < n_nz: the k-th strongest key is non-zero
-    unsigned prefix = 0, k_rem = (unsigned)k;
+    unsigned tau = 0;
     for (int bit = 31; bit >= 0; --bit) {
-        const unsigned want = (prefix >> bit) | 1u;  // the bits from `bit` up of a key with this bit set
+        const unsigned at = tau | 1u << bit;
         unsigned cnt = 0;
 #pragma unroll
-        for (int u = 0; u < kTinyPerLane; ++u) cnt += (unsigned)__popcll(__ballot((key[u] >> bit) == want));
-        if (cnt >= k_rem) prefix |= 1u << bit;  // the k-th strongest has the bit
-        else k_rem -= cnt;                      // it lies below the cnt keys that have it
+        for (int u = 0; u < NU; ++u) cnt += (unsigned)__popcll(__ballot(key[u] >= at));
+        if (cnt >= (unsigned)k) tau = at;
     }
-    const unsigned tau = prefix;
-    unsigned n_eq = 0;
+    unsigned n_eq = 0, above = 0;
 #pragma unroll
-    for (int u = 0; u < kTinyPerLane; ++u) n_eq += (unsigned)__popcll(__ballot(key[u] == tau));
-    const unsigned q = k_rem;  // 1 <= q <= n_eq: the entries equal to tau that survive, those of lowest position
+    for (int u = 0; u < NU; ++u) {
+        n_eq += (unsigned)__popcll(__ballot(key[u] == tau));
+        above += (unsigned)__popcll(__ballot(key[u] > tau));
+    }
+    const unsigned q = (unsigned)k - above;  // 1 <= q <= n_eq: the entries equal to tau that survive, those of lowest position
     unsigned cut = 0xffffffffu;
     if (q < n_eq) {
         unsigned left = q;
 #pragma unroll
-        for (int u = 0; u < kTinyPerLane; ++u) {
+        for (int u = 0; u < NU; ++u) {
             const unsigned long long m = __ballot(key[u] == tau);
             const unsigned c = (unsigned)__popcll(m);
             if (left >= 1u && left <= c) {  // (uniform) the q-th equal key is in this register: the lane of rank `left`
@@ -1070,7 +1064,30 @@ __global__ __launch_bounds__(256) void k_select_tiny(int mode, int channels, int
         st.n_eq = n_eq;
         st.q = q;
         st.cut = cut;
-        cols[col] = st;
+        *out = st;
+    }
+}
+
+template <int kTinyPerLane>
+__global__ __launch_bounds__(256) void k_select_tiny(int mode, int channels, int ncols,
+                                                     const int* __restrict__ tile_start,
+                                                     const float* __restrict__ resp, long long k,
+                                                     ColState* __restrict__ cols) {
+    const int col = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
+    if (col >= ncols) return;  // (whole waves)
+    const int b = col / channels, oc = col - b * channels;
+    const int t0 = tile_start[b], tiles = tile_start[b + 1] - t0;
+    const unsigned n = (unsigned)tiles * kTileRows;  // positions of the column (<= 64 kTinyPerLane, see the launcher)
+    const float* column = resp + ((size_t)t0 * channels + oc) * kTileRows;
+    const size_t pitch = (size_t)channels * kTileRows;
+    if constexpr (kTinyPerLane == 16) {
+        if (tiles <= 2) select_tiny<4>(mode, column, pitch, n, k, cols + col);
+        else if (tiles == 3) select_tiny<6>(mode, column, pitch, n, k, cols + col);
+        else if (tiles <= 5) select_tiny<10>(mode, column, pitch, n, k, cols + col);
+        else select_tiny<16>(mode, column, pitch, n, k, cols + col);
+    } else {
+        if (tiles <= 16) select_tiny<32>(mode, column, pitch, n, k, cols + col);
+        else select_tiny<64>(mode, column, pitch, n, k, cols + col);
     }
 }
 
@@ -1107,7 +1124,7 @@ hipError_t launch_topk(const Geom& g, int channels, long long k, int mode, int r
                        hipStream_t s) {
     const int ncols = g.batch * channels;
     if (ncols <= 0) return hipSuccess;
-    if (column_positions(g) <= kTinyColumn && ncols >= kTinyManyColumns) {
+    if (column_positions(g) <= kTinyColumn) {
         hipLaunchKernelGGL(k_select_tiny<16>, dim3((unsigned)((ncols + 3) / 4)), dim3(256), 0, s, mode, channels, ncols,
                            tile_start, resp, k, cols);
         return hipGetLastError();

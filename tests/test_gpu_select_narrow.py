@@ -68,3 +68,22 @@ def test_a_selection_that_keeps_everything(ext, rho, below, c_out, relu, pool, m
                                      torch.from_numpy(w).cuda(), rho_up=rho, topk_mode=mode, relu=relu, pool=pool,
                                      cand_capacity=cap)
     assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf) and int(n[2]) == 0
+
+
+@pytest.mark.parametrize("mode", [scnn.ABS, scnn.SIGNED])
+@pytest.mark.parametrize("ext,batch,c_out", [((10, 11), 2, 3), ((16, 16), 1, 1), ((18, 20), 3, 8), ((22, 23), 2, 5), ((25, 25), 300, 4),
+                                             ((28, 27), 2, 40), ((31, 33), 1, 70), ((10, 10, 10), 2, 8), ((16, 16, 16), 2, 16),
+                                             ((16, 15, 14), 130, 8), ((13, 12, 11), 140, 8)])
+@pytest.mark.parametrize("rho", [0.0, 0.004, 0.2, 0.6])
+def test_selection_of_short_columns(ext, batch, c_out, rho, mode):
+    """One to thirty-two tiles a column, few columns and many, runs of equal scores cut at the k-th."""
+    rng = np.random.default_rng(ext[0] + c_out)
+    k = (3,) * len(ext)
+    coords = random_sparse_sites(rng, ext, batch, 0.4)
+    coords = coords[(coords[:, 0] != 0) | (rng.random(len(coords)) < 0.1)]  # (columns of different lengths)
+    feats = rng.integers(1, 4, size=(len(coords), 1)).astype(np.float32)
+    w = rng.integers(-3, 4, size=(3 ** len(ext), 1, c_out)).astype(np.float32)
+    rc, rf = oracle.sparse_conv_fwd(ext, batch, coords, feats, k, w, rho_up=rho, topk_mode=mode)
+    gc, gf, n = scnn.sparse_conv_fwd(ext, batch, *(torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (coords, feats, )), k,
+                                     torch.from_numpy(w).cuda(), rho_up=rho, topk_mode=mode)
+    assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf) and int(n[2]) == 0
