@@ -434,7 +434,7 @@ hipError_t launch_pair_build(const Geom& g, const unsigned long long* occ, const
 hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats, int c_in, const float* wb, int c_out,
                             const float* bias, const unsigned* pairs, const unsigned short* block_tap,
                             const uint2* tile_hdr, Counters* ctr, float* resp, hipStream_t s);
-// (on split operands: the forward pass; w = the filter as it is)
+// (on split operands; w = the filter as it is, adjoint: read as the adjoint convolution's)
 hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
                                   const float* w, int adjoint, int c_out, const float* bias, const unsigned* pairs,
                                   const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,

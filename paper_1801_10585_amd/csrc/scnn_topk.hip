@@ -24,8 +24,9 @@
 // Compaction: where the selection has noted the rows (layers of 33 to 64
 // channels), the rows that survive in every tile are known before the last
 // pass, a scan gives each tile its first output row, and the write pass
-// streams with no ordering between tiles.  Elsewhere tiles are taken in order
-// and a tile learns its first output row by looking back at its predecessors.
+// streams with no ordering between tiles.  Narrow layers count and write in two
+// launches.  Elsewhere tiles are taken in order and a tile learns its first
+// output row by looking back at its predecessors.
 #include <type_traits>
 
 #include "scnn_internal.h"
