@@ -184,10 +184,9 @@ __global__ __launch_bounds__(256) void k_conv_valu_stream(Geom g, const unsigned
 // half of them on surfaces).  The sums are fp64 and in tap order.  One input and eight output channels, against the forms
 // above: 256^3 scattered, 1.7 M sites, 104 -> 35 us; 28 x 28 x 1024 29 -> 17.5; one 28 x 28 image 9.8 -> 5.3.
 // Eight input channels are bound by the weights' way out of LDS (512 bytes a lane and neighbour): 128^3 x 4, 8 -> 8,
-// 91 -> 57 us; calls with 8 / 16 output channels on 48^3 x 4 115 / 124 -> 86 / 108, on 128^3 x 2 155 / 186 -> 122 / 166 (a
-// tenth of it the compaction's gain).  Small layers wait for a thread's chain instead: on 32^3 x 4, 464 tiles of capacity,
-// calls 74 / 78 -> 63 / 80, 16 output channels on 22^3 x 13, 662 tiles, 97 -> 107, on 132 tiles the kernel 22 -> 41;
-// hence the rule of the launch: 8 output channels from the 32-row form's end on, 16 where the streaming form takes over.
+// 91 -> 57 us; calls on 48^3 x 4 115 -> 86, on 128^3 x 2 155 -> 122 (a tenth of it the compaction's gain), on 32^3 x 4,
+// 464 tiles of capacity, 74 -> 63: from the 32-row form's end on.  Sixteen output channels double that bound, and on the
+// dense surfaces that follow a pooling lose to the streaming form (64^3 x 4: 57 -> 80 us); they keep the forms above.
 constexpr int kOneLines = 9;  // filter lines at most (and 32 taps)
 constexpr long long kOneBlocks = 256 * 16;
 template <int CI /* input channels: 1 or 8 */, int OCB /* output channels at most: 8 or 16 */>
@@ -931,7 +930,7 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
         hipLaunchKernelGGL(k_conv_valu_empty, dim3(256 * 8), dim3(256), 0, s, c_out, ctr, resp);
         return hipGetLastError();
     }
-    const bool eight = c_in == 8 && ((uintptr_t)feats & 15) == 0 && tiles_cap > (c_out <= 8 ? kValuSmallItems : kValuLatencyItems);
+    const bool eight = c_in == 8 && c_out <= 8 && ((uintptr_t)feats & 15) == 0 && tiles_cap > kValuSmallItems;
     if ((c_in == 1 || eight) && c_out <= 16 && g.T <= 32 && g.K[0] * g.K[1] <= kOneLines) {
         const unsigned blocks = (unsigned)(tiles_cap < 2 ? 1 : ((tiles_cap + 1) / 2 > kOneBlocks ? kOneBlocks : (tiles_cap + 1) / 2));
 #define SCNN_VALU_ONE(CI_, OCB_)                                                                                              \
@@ -939,8 +938,7 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
                        c_out_pad, bias, tap_active, cand_lin, cand_start, tile_start, ctr, resp)
         if (c_in == 1 && c_out <= 8) SCNN_VALU_ONE(1, 8);
         else if (c_in == 1) SCNN_VALU_ONE(1, 16);
-        else if (c_out <= 8) SCNN_VALU_ONE(8, 8);
-        else SCNN_VALU_ONE(8, 16);
+        else SCNN_VALU_ONE(8, 8);
 #undef SCNN_VALU_ONE
         return hipGetLastError();
     }
