@@ -222,7 +222,8 @@ __global__ __launch_bounds__(256) void k_conv_valu_one(Geom g, const unsigned lo
         if (live) site_of(g, cand_lin[cand], c0, c1, c2);
         // ---- occupancy of the sites that the taps look at: bit t = tap t's (lookup_line, all lines' loads in flight)
         const int q2s = c2 - g.H[2];
-        const int k_lo = q2s < 0 ? -q2s : 0, k_hi = g.E[2] - q2s < K2 ? g.E[2] - q2s : K2;
+        int k_lo, k_hi;
+        taps_on_line(g.E[2], c2, -g.H[2], K2, k_lo, k_hi);
         const unsigned w_last = (unsigned)g.batch * (unsigned)g.Wps - 1u;
         const unsigned on_line = live && k_hi > k_lo ? (~0u >> (32 - (k_hi - k_lo))) << k_lo : 0u;
         unsigned raw = 0;

@@ -225,7 +225,8 @@ __global__ __launch_bounds__(kQuadWaves * 64, quad_waves_per_simd(C_IN, QPM, ACC
             const int n_lines = g.K[0] * g.K[1];
             const unsigned w_last = (unsigned)g.batch * (unsigned)g.Wps - 1u;
             const int q2s = c2 - g.H[2];                       // site of tap k of a line is q2s + k
-            const int k_lo = q2s < 0 ? -q2s : 0;               // first tap whose site is on the line
+            int k_lo, k_hi;                                    // taps on the line, k_lo <= k < k_hi
+            taps_on_line(g.E[2], c2, -g.H[2], g.K[2], k_lo, k_hi);
             for (int line0 = 0; line0 < n_lines; line0 += kLineBatch) {
                 unsigned long long word_a[kLineBatch], word_b[kLineBatch];
                 unsigned pre_a[kLineBatch], pre_b[kLineBatch], bit0[kLineBatch], w_rel[kLineBatch];
@@ -256,8 +257,7 @@ __global__ __launch_bounds__(kQuadWaves * 64, quad_waves_per_simd(C_IN, QPM, ACC
                     const unsigned p = first_bit & 63u;   // position of the window's first site in word_a
                     unsigned long long both = word_a[i] >> p;
                     if (p) both |= word_b[i] << (64u - p);
-                    // taps on the line: k_lo <= k < min(K2, E2 - q2s); and active
-                    const int k_hi = g.E[2] - q2s < g.K[2] ? g.E[2] - q2s : g.K[2];
+                    // taps on the line and active
                     unsigned valid = (k_hi >= 32 ? ~0u : ((1u << (k_hi > 0 ? k_hi : 0)) - 1u)) & ~((1u << k_lo) - 1u);
                     valid &= act_mask >> tap0;
                     const unsigned raw = (unsigned)both << k_lo;      // occupancy of the sites the taps look at

@@ -106,8 +106,8 @@ __device__ __forceinline__ void split_units(
         unsigned off[K3 ? 27 : 1];
         const unsigned w_last = (unsigned)g.batch * (unsigned)g.Wps - 1u;
         const int q2s = c2 - g.H[2];          // site of tap k of a line is q2s + k
-        const int k_lo = q2s < 0 ? -q2s : 0;  // first tap whose site is on the line
-        const int k_hi = g.E[2] - q2s < K2 ? g.E[2] - q2s : K2;
+        int k_lo, k_hi;                       // taps on the line, k_lo <= k < k_hi
+        taps_on_line(g.E[2], c2, -g.H[2], K2, k_lo, k_hi);
         const unsigned on_line = (k_hi >= 32 ? ~0u : ((1u << (k_hi > 0 ? k_hi : 0)) - 1u)) & ~((1u << k_lo) - 1u);
         const int n_lines = K0 * K1;
         constexpr int LB = 9;  // lines whose bitmap words are fetched together

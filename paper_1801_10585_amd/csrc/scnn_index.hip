@@ -520,6 +520,7 @@ __device__ __forceinline__ unsigned long long dilate_word(const Geom& g, const u
     int bit = 0;
     while (remaining > 0) {
         int len = g.E[2] - c2;
+        const int room = min(len, 128);  // (128: as good as any, and minus an offset it stays in range on the longest line)
         if (len > remaining) len = (int)remaining;
         unsigned long long run = 0;
         for (int l = sub; l < n_lines; l += kDilateLanes) {
@@ -540,9 +541,7 @@ __device__ __forceinline__ unsigned long long dilate_word(const Geom& g, const u
                 if (!act[t2]) continue;
                 const int d2 = t2 - g.H[2];
                 // source z = c2 + i + d2 must stay on the line: i in [lo, hi)
-                int lo = -d2 - c2, hi = g.E[2] - d2 - c2;
-                if (lo < 0) lo = 0;
-                if (hi > len) hi = len;
+                const int lo = max(max(-d2, 0) - c2, 0), hi = min(room - d2, len);
                 if (lo >= hi) continue;
                 const int o = (int)(s + d2 - wb * 64);  // 0 <= o < 128 for H2 <= 32
                 unsigned long long bits = o < 64 ? funnel64(win[0], win[1], o) : funnel64(win[1], win[2], o - 64);

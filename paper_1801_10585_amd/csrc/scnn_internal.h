@@ -153,6 +153,14 @@ __device__ inline int lookup_row(const Geom& g, const unsigned long long* __rest
     return row < nnz_in ? (int)row : -1;  // only an unsorted input can trip this guard
 }
 
+// Taps k_lo <= k < k_hi of 0 .. count-1 have their site c2 + off + k on a line of `extent` sites (k_hi <= k_lo: none has).
+// A line can hold 2^31 - 1 sites, so no sum here goes past its ends: taps and offsets stay below 64, and c2 and extent are
+// only compared, or subtracted from something not smaller in sign.
+__device__ __forceinline__ void taps_on_line(int extent, int c2, int off, int count, int& k_lo, int& k_hi) {
+    k_lo = max(max(-off, 0) - c2, 0);
+    k_hi = min(extent - c2, count + off) - off;
+}
+
 // Neighbour rows of one site along one filter line: the taps (t0, t1, t2_lo .. t2_lo + count - 1), count <= 32, look
 // at the sites (c0 + t0 - H0, c1 + t1 - H1, c2 + t2 - H2), which are adjacent along the last axis and therefore sit
 // in at most two adjacent 64-bit words of the occupancy bitmap.  Both words and their prefixes are loaded once and
@@ -169,10 +177,10 @@ __device__ inline void lookup_line(const Geom& g, const unsigned long long* __re
     const int q0 = c0 + t0 - g.H[0], q1 = c1 + t1 - g.H[1];
     const bool line_ok = live && (unsigned)b < (unsigned)g.batch && (unsigned)q0 < (unsigned)g.E[0] &&
                          (unsigned)q1 < (unsigned)g.E[1];
-    const int q2s = c2 + t2_lo - g.H[2];                          // site of tap k is q2s + k
-    const int k_lo = q2s < 0 ? -q2s : 0;                          // first tap whose site is on the line
-    const int k_hi = g.E[2] - q2s < count ? g.E[2] - q2s : count;  // .. and the first past it
-    const unsigned first_bit = line_ok ? (unsigned)((q0 * g.E[1] + q1) * g.E[2] + q2s + k_lo) : 0u;
+    const int off = t2_lo - g.H[2];                               // site of tap k is c2 + off + k
+    int k_lo, k_hi;
+    taps_on_line(g.E[2], c2, off, count, k_lo, k_hi);
+    const unsigned first_bit = line_ok ? (unsigned)((q0 * g.E[1] + q1) * g.E[2]) + (unsigned)c2 + (unsigned)(off + k_lo) : 0u;
     const unsigned p = first_bit & 63u;                           // position of tap k_lo's site in word_a
     const unsigned w_last = (unsigned)g.batch * (unsigned)g.Wps - 1u;
     const unsigned w0 = (unsigned)b * (unsigned)g.Wps + (first_bit >> 6);
