@@ -196,8 +196,9 @@ def bench_backward(args, wl, layer, w, coords, feats, wd):
     mfma = c_out % 32 == 0 and c_out <= 128 and c_in % 16 == 0 and c_in <= 64
     # the two contractions (bp_data and bp_filter) do one multiply-add per visit each
     dominant = "bwd_filter" if stage["bwd_filter"] >= stage["bwd_data_conv"] else "bwd_data_conv"
-    # (at these widths the adjoint convolution runs on split operands, the filter gradient on fp32 MFMA)
-    split = mfma and dominant == "bwd_data_conv"
+    # (the adjoint convolution of these widths, 32 -> 32 and narrower excepted, runs on split operands, the filter
+    # gradient on fp32 MFMA)
+    split = mfma and dominant == "bwd_data_conv" and (c_out > 32 or c_in > 32)
     peak = (PEAK_MFMA_SPLIT_TFLOPS if split else PEAK_MFMA_FP32_TFLOPS) if mfma else PEAK_FP64_VECTOR_TFLOPS
     tflops = 2.0 * visits / (stage[dominant] * 1e-3) / 1e12
     # HBM bytes of the dominant kernel per launch, from the committed counter runs of this command (see main())

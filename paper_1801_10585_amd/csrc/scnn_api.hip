@@ -465,7 +465,7 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
                                    ws.tile_hdr, ws.block_cap, ws.tiles_cap, nullptr, s));
         timer.mark();
         if (kernel == ConvKernel::kPair) {
-            SCNN_TRY(launch_conv_mfma(g, nnz_in, in_feats, c_in, ws.wb, c_out, bias, ws.pairs, ws.block_tap, ws.tile_hdr,
+            SCNN_TRY(launch_conv_mfma(g, nnz_in, 0, in_feats, c_in, ws.wb, c_out, bias, ws.pairs, ws.block_tap, ws.tile_hdr,
                                       ws.ctr, ws.resp, s));
             g_last_conv_kernel = "k_conv_mfma";
         } else {
@@ -562,9 +562,15 @@ void carve_bwd(void* base, const Geom& g, long long nnz_in, int c_in, int c_out,
     w->block_cap = w->mfma_shape ? (long long)g.T * (nnz_in / 16 + w->tiles_cap) : 0;
     w->pairs = c.take<unsigned>((size_t)w->block_cap * 16);
     w->block_tap = c.take<unsigned short>((size_t)w->block_cap);
-    // (the adjoint filter in matrix-operand order: its input channels, C_out, padded to a whole 32-channel chunk)
-    w->split_shape = w->mfma_shape && c_out % 32 == 0;
-    w->wb = c.take<float>(w->mfma_shape && !w->split_shape ? (size_t)g.T * round_up(c_out, 32) * c_in : 0);
+    // bp_data on split operands: multiples of 32 output channels (sixteen would leave half of a chunk empty), but 32 with at
+    // most 32 input channels not, where the look over the gradient's values takes back what the products give.  Whole call,
+    // fp32 products against split, us, on 16^3 / 32^3 x 4 / 128^3 x 4: 16->32 58.8 / 69.8 / 317 against 58.5 / 71.8 / 308,
+    // 32->32 68.5 / 84.6 / 383 against 65.4 / 83.5 / 400; 64->32 89 / 117 / 736 against 81 / 109 / 673, 32->64 89 / 113 /
+    // 651 against 84 / 107 / 613, 64->128 231 / 297 / 2804 against 161 / 203 / 1973.
+    w->split_shape = w->mfma_shape && c_out % 32 == 0 && (c_out > 32 || c_in > 32);
+    // (the adjoint filter in matrix-operand order: its input channels, C_out, padded to a whole 32-channel chunk; a split
+    // shape's is for the calls whose values the parts do not hold)
+    w->wb = c.take<float>(w->mfma_shape ? (size_t)g.T * round_up(c_out, 32) * c_in : 0);
     w->wsplit = c.take<unsigned short>(w->split_shape ? split_filter_elems(g.T, c_out) : 0);
     w->tile_hdr = c.take<uint2>(w->mfma_shape ? w->tiles_cap : 0);
     w->tap_first = c.take<unsigned short>(w->mfma_shape ? (size_t)w->tiles_cap * (g.T + 1) : 0);
@@ -615,7 +621,6 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
     const long long n_elem = (long long)g.T * c_in * c_out;
     const bool use_mfma = g_conv_path != 1 && ws.mfma_shape && nnz_in > 0 && ((uintptr_t)in_feats & 15) == 0 &&
                           ((uintptr_t)g_feats & 15) == 0;
-    // (bp_data on split operands; sixteen output channels would leave half of a chunk empty)
     const bool split = use_mfma && ws.split_shape;
     const int n_chunks = use_mfma ? ws.chunks_mfma : ws.chunks_valu;
 
@@ -623,7 +628,7 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
     timer.mark();
     // adjoint filter (taps negated, channels transposed) in the layout of the convolution kernel that will run;
     // the same launch clears the counters and the occupancy bitmap
-    SCNN_TRY(launch_prepare(g, w, c_out, c_in, 1, ws.c_in_pad, ws.wp, use_mfma && !split ? ws.wb : nullptr, nullptr,
+    SCNN_TRY(launch_prepare(g, w, c_out, c_in, 1, ws.c_in_pad, ws.wp, use_mfma ? ws.wb : nullptr, nullptr,
                             split ? ws.wsplit : nullptr, ws.tap_active, ws.tap_coord, workspace, ws.zero_bytes, s));
     SCNN_TRY(launch_index_build(g, g_coords, g_rows, nullptr, g_rows, ws.occ, ws.occ_prefix, ws.ctr,
                                 split ? g_feats : nullptr, c_out, nullptr, ws.tap_active, s));
@@ -635,12 +640,15 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
                                    ws.cand_start, ws.tile_start, ws.rows16_start, ws.ctr, ws.pairs, ws.block_tap,
                                    ws.tile_hdr, ws.block_cap, ws.tiles_cap, ws.tap_first, s));
         timer.mark();
+        // Of the two one leaves at once, by the values: a single tiny gradient (below 2^-109) is enough for the second.  By a
+        // loop for such values inside the split kernel it cost the call a third to two thirds; this way, us, 128^3 x 4 and
+        // 32^3 x 4, 32->64 982 / 155 -> 675 / 116, 16->128 1572 / 222 -> 1019 / 135, 64->64 1668 / 260 -> 1273 / 167 (fp32
+        // products alone 657 / 116, 962 / 134, 1248 / 167); the launch that leaves costs the others 2 us.
         if (split)
-            SCNN_TRY(launch_conv_mfma_split(g, g_rows, g_feats, c_out, ws.wsplit, w, 1, c_in, nullptr, ws.pairs,
+            SCNN_TRY(launch_conv_mfma_split(g, g_rows, g_feats, c_out, ws.wsplit, nullptr, 1, c_in, nullptr, ws.pairs,
                                             ws.block_tap, ws.tile_hdr, ws.ctr, ws.resp, s));
-        else
-            SCNN_TRY(launch_conv_mfma(g, g_rows, g_feats, c_out, ws.wb, c_in, nullptr, ws.pairs, ws.block_tap,
-                                      ws.tile_hdr, ws.ctr, ws.resp, s));
+        SCNN_TRY(launch_conv_mfma(g, g_rows, split ? 1 : 0, g_feats, c_out, ws.wb, c_in, nullptr, ws.pairs, ws.block_tap,
+                                  ws.tile_hdr, ws.ctr, ws.resp, s));
     } else {
         timer.mark();
         SCNN_TRY(launch_conv_valu(g, ws.occ, ws.occ_prefix, g_rows, g_feats, c_out, ws.wp, c_in, ws.c_in_pad, nullptr,

@@ -1179,8 +1179,9 @@ struct RoundRegs {
 // HALF: C_in = 16 (KC = 1): a lane's K slot gq stands for the four channels 4 gq .. 4 gq + 3 instead of eight, so a
 // block takes four matrix instructions per 16 output channels and the second halves of the operands stay unused
 // (the filter is prepared in the same 8-floats-per-lane layout, upper four zero).
+// only_odd: launched behind k_conv_mfma_split for the calls that it leaves (ctr->odd); leaves the others at once.
 template <int KC /* C_in / 32 */, int NB /* C_out / 16 */, int HALF = 0>
-__global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma(int taps, long long nnz_in,
+__global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma(int taps, long long nnz_in, int only_odd,
                                                                const float* __restrict__ feats,
                                                                const float* __restrict__ wb,
                                                                const float* __restrict__ bias,
@@ -1190,6 +1191,7 @@ __global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma(int taps, long lo
                                                                Counters* __restrict__ ctr,
                                                                float* __restrict__ resp) {
     static_assert(!HALF || KC == 1, "the half chunk stands alone");
+    if (only_odd && ctr->odd == 0) return;
     constexpr int C_IN = HALF ? 16 : KC * 32, C_OUT = NB * 16, CS = C_OUT + 1 /* padded accumulator row */;
     constexpr int RB = (KC * NB <= 4) ? 3 : ((KC * NB <= 8) ? 2 : 1);  // blocks per round
     constexpr int NT = kConvWaves * 64;
@@ -1444,7 +1446,7 @@ __global__ __launch_bounds__(kConvWaves * 64) void k_conv_mfma(int taps, long lo
 }
 
 template <int KC, int NB, int HALF = 0>
-static hipError_t launch_conv_mfma_t(int taps, long long nnz_in, const float* feats, const float* wb, const float* bias,
+static hipError_t launch_conv_mfma_t(int taps, long long nnz_in, int only_odd, const float* feats, const float* wb, const float* bias,
                                      const unsigned* pairs, const unsigned short* block_tap, const uint2* tile_hdr,
                                      Counters* ctr, float* resp, hipStream_t s) {
     const size_t lds = conv_mfma_lds_bytes(NB * 16);
@@ -1457,9 +1459,8 @@ static hipError_t launch_conv_mfma_t(int taps, long long nnz_in, const float* fe
     if (per_cu < 1) per_cu = 1;
     if (per_cu > 4) per_cu = 4;    // 16 waves per CU
     const int grid = (device_cu_count() * per_cu + kXcds - 1) / kXcds * kXcds;  // one span of tiles per XCD
-    hipLaunchKernelGGL((k_conv_mfma<KC, NB, HALF>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, wb,
-                       bias,
-                       pairs, block_tap, tile_hdr, ctr, resp);
+    hipLaunchKernelGGL((k_conv_mfma<KC, NB, HALF>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, only_odd, feats, wb,
+                       bias, pairs, block_tap, tile_hdr, ctr, resp);
     return hipGetLastError();
 }
 
@@ -1472,8 +1473,8 @@ static hipError_t launch_conv_mfma_t(int taps, long long nnz_in, const float* fe
 // returns (a round's chunk asks for 12 + 4 KB for at most two blocks); error against 64 bits 1.08e-7 -> 4.6e-8 of the
 // result's norm, on rows with a sixth of their entries 5.4e-8 -> 3.8e-8.
 // The adjoint convolution of the backward pass takes it too: 128^3 x 4, 32 -> 64 channels, 202 k rows: 327 -> 280 us, 23 of
-// which the look over the gradient rows' values takes back (call 658 -> 624 us); bound by the gathers, 5 TB/s of rows.
-// Sixteen input channels keep the fp32 kernel above.
+// which the look over the gradient rows' values takes back (call 652 -> 604 us); bound by the gathers, 5 TB/s of rows.
+// Sixteen input channels keep the fp32 kernel above, and the adjoint that of 32 -> 32 and 32 -> 16 (see carve_bwd).
 // Operands of one 32-channel chunk of a round (up to RB consecutive 16-pair blocks of ONE tap), fetched one chunk ahead
 // of their use.
 template <int NB, int RB>
@@ -1483,9 +1484,10 @@ struct ChunkRegs {
     u32x4 b[3][NB];   // filter in bf16 thirds (split3): lane holds w[tap][32 kc + 8 gq + i][16 cb + jj], i = 0..7
 };
 
-// (ADJOINT is of the kernel's instance and not an argument: as one it cost the forward call of 64 -> 64 channels with 125
-// taps 5 %, in registers.)
-template <int KC /* C_in / 32 */, int NB /* C_out / 16 */, int ADJOINT /* w is the adjoint's, see filter_at */>
+// Values that the parts do not hold (ctr->odd): the forward call's instances multiply them by the loop for them below; those
+// of the adjoint convolution (LEAVE_ODD), where one tiny gradient is enough and is nothing unusual, leave the whole call to
+// k_conv_mfma, launched behind them, which leaves the others.
+template <int KC /* C_in / 32 */, int NB /* C_out / 16 */, int LEAVE_ODD>
 __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_split(int taps, long long nnz_in,
                                                                const float* __restrict__ feats,
                                                                const u32x4* __restrict__ ws,
@@ -1514,7 +1516,11 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
     const int jj = lane & 15, gq = lane >> 4;
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
     const int n_tiles = (int)ctr->n_tiles;
-    const bool odd = __builtin_amdgcn_readfirstlane(ctr->odd) != 0;
+    bool odd = __builtin_amdgcn_readfirstlane(ctr->odd) != 0;
+    if constexpr (LEAVE_ODD) {
+        if (odd) return;
+        odd = false;
+    }
     // LDS byte address of this lane's channel in accumulator row 0 (a generic pointer to LDS carries the LDS
     // address in its low 32 bits); accumulator addresses are formed once per block, at load time
     const unsigned lane_off = (unsigned)(size_t)s_c + (unsigned)jj * (unsigned)sizeof(double);
@@ -1605,7 +1611,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
                                 const float x = row[i];
 #pragma unroll
                                 for (int cb = 0; cb < NB; ++cb) {
-                                    const float wv = filter_at(w, taps, C_IN, C_OUT, ADJOINT, t, ch + i, cb * 16 + jj);
+                                    const float wv = filter_at(w, taps, C_IN, C_OUT, 0, t, ch + i, cb * 16 + jj);
                                     d[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wv, d[cb], 0, 0, 0);
                                 }
                             }
@@ -1802,7 +1808,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
     }
 }
 
-template <int KC, int NB, int ADJOINT>
+template <int KC, int NB, int LEAVE_ODD>
 static hipError_t launch_conv_mfma_split_t(int taps, long long nnz_in, const float* feats, const u32x4* ws,
                                            const float* w, const float* bias,
                                            const unsigned* pairs, const unsigned short* block_tap, const uint2* tile_hdr,
@@ -1810,14 +1816,14 @@ static hipError_t launch_conv_mfma_split_t(int taps, long long nnz_in, const flo
     const size_t lds = conv_mfma_lds_bytes(NB * 16);
     // (set on every launch: the attribute belongs to the current device's copy of the kernel, and a flag remembering
     // that it was set would have to be kept per device and guarded between threads for the sake of a microsecond)
-    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_split<KC, NB, ADJOINT>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_conv_mfma_split<KC, NB, LEAVE_ODD>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     int per_cu = (int)((160 * 1024) / lds);
     if (per_cu < 1) per_cu = 1;
     if (per_cu > 4) per_cu = 4;    // 16 waves per CU
     const int grid = (device_cu_count() * per_cu + kXcds - 1) / kXcds * kXcds;  // one span of tiles per XCD
-    hipLaunchKernelGGL((k_conv_mfma_split<KC, NB, ADJOINT>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, ws,
+    hipLaunchKernelGGL((k_conv_mfma_split<KC, NB, LEAVE_ODD>), dim3(grid), dim3(kConvWaves * 64), lds, s, taps, nnz_in, feats, ws,
                        w, bias, pairs, block_tap, tile_hdr, ctr, resp);
     return hipGetLastError();
 }
@@ -1828,12 +1834,12 @@ bool conv_mfma_supported(const Geom& g, int c_in, int c_out, long long nnz_in) {
            nnz_in < (1ll << kPairRowShift);
 }
 
-hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats, int c_in, const float* wb, int c_out,
+hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, int only_odd, const float* feats, int c_in, const float* wb, int c_out,
                             const float* bias, const unsigned* pairs, const unsigned short* block_tap,
                             const uint2* tile_hdr, Counters* ctr, float* resp, hipStream_t s) {
 #define SCNN_MFMA_CASE(KC_, NB_)                                                                                  \
     if (c_in == KC_ * 32 && c_out == NB_ * 16)                                                                    \
-        return launch_conv_mfma_t<KC_, NB_>(g.T, nnz_in, feats, wb, bias, pairs, block_tap, tile_hdr, ctr, resp, s);
+        return launch_conv_mfma_t<KC_, NB_>(g.T, nnz_in, only_odd, feats, wb, bias, pairs, block_tap, tile_hdr, ctr, resp, s);
     SCNN_MFMA_CASE(1, 1) SCNN_MFMA_CASE(1, 2) SCNN_MFMA_CASE(1, 3) SCNN_MFMA_CASE(1, 4)
     SCNN_MFMA_CASE(2, 1) SCNN_MFMA_CASE(2, 2) SCNN_MFMA_CASE(2, 3) SCNN_MFMA_CASE(2, 4)
     SCNN_MFMA_CASE(3, 1) SCNN_MFMA_CASE(3, 2) SCNN_MFMA_CASE(3, 3) SCNN_MFMA_CASE(3, 4)
@@ -1841,20 +1847,20 @@ hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats,
 #undef SCNN_MFMA_CASE
 #define SCNN_MFMA_HALF(NB_)                                                                                       \
     if (c_in == 16 && c_out == NB_ * 16)                                                                          \
-        return launch_conv_mfma_t<1, NB_, 1>(g.T, nnz_in, feats, wb, bias, pairs, block_tap, tile_hdr, ctr, resp, s);
+        return launch_conv_mfma_t<1, NB_, 1>(g.T, nnz_in, only_odd, feats, wb, bias, pairs, block_tap, tile_hdr, ctr, resp, s);
     SCNN_MFMA_HALF(1) SCNN_MFMA_HALF(2) SCNN_MFMA_HALF(3) SCNN_MFMA_HALF(4)
 #undef SCNN_MFMA_HALF
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
-                                  const float* w, int adjoint, int c_out, const float* bias, const unsigned* pairs,
+                                  const float* w, int leave_odd, int c_out, const float* bias, const unsigned* pairs,
                                   const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
                                   hipStream_t s) {
 #define SCNN_MFMA_ARGS g.T, nnz_in, feats, (const u32x4*)ws, w, bias, pairs, block_tap, tile_hdr, ctr, resp, s
 #define SCNN_MFMA_CASE(KC_, NB_)                                                                                  \
     if (c_in == KC_ * 32 && c_out == NB_ * 16)                                                                    \
-        return adjoint ? launch_conv_mfma_split_t<KC_, NB_, 1>(SCNN_MFMA_ARGS) : launch_conv_mfma_split_t<KC_, NB_, 0>(SCNN_MFMA_ARGS);
+        return leave_odd ? launch_conv_mfma_split_t<KC_, NB_, 1>(SCNN_MFMA_ARGS) : launch_conv_mfma_split_t<KC_, NB_, 0>(SCNN_MFMA_ARGS);
     SCNN_MFMA_CASE(1, 1) SCNN_MFMA_CASE(1, 2) SCNN_MFMA_CASE(1, 3) SCNN_MFMA_CASE(1, 4)
     SCNN_MFMA_CASE(2, 1) SCNN_MFMA_CASE(2, 2) SCNN_MFMA_CASE(2, 3) SCNN_MFMA_CASE(2, 4)
     SCNN_MFMA_CASE(3, 1) SCNN_MFMA_CASE(3, 2) SCNN_MFMA_CASE(3, 3) SCNN_MFMA_CASE(3, 4)

@@ -373,25 +373,30 @@ hipError_t launch_index_build(const Geom& g, const int32_t* coords, long long n_
 // convolution kernel that will run -- wb (matrix-core operand order:
 // wb[((t * KC + kc) * NB + cb) * 64 + lane][s] = w[t][kc*32 + 8*gq + s][cb*16 + jj], lane = 16*gq + jj, so that a
 // lane fetches its eight values of one (tap, kc, cb) with two 16-byte loads) or wp (fp64, rows padded to
-// c_out_pad; the vector kernel).  The blocks from T on clear the zero-initialised part of the workspace.
+// c_out_pad; the vector kernel).  The blocks from T on clear the zero-initialised part of the workspace.  With two layouts
+// (kLayoutSplitPair) blocks T .. 2 T - 1 lay out the second: one after the other they took 64 -> 128 channels 5 us longer.
 // With `adjoint` set the filter is read as the adjoint convolution's (filter_at).
-enum PrepareLayout { kLayoutVector, kLayoutPair, kLayoutQuad, kLayoutSplit };  // (one kernel each: a small layer waits for it)
+enum PrepareLayout { kLayoutVector, kLayoutPair, kLayoutQuad, kLayoutSplit, kLayoutSplitPair };  // (one kernel each: a small layer waits for it)
 template <int LAYOUT>
 __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict__ w, int c_in, int c_out, int adjoint,
-                                                 int c_out_pad, void* __restrict__ dst, int* __restrict__ tap_active,
+                                                 int c_out_pad, void* __restrict__ dst, float* __restrict__ dst2,
+                                                 int* __restrict__ tap_active,
                                                  int* __restrict__ tap_coord, uint4* __restrict__ zero_p,
                                                  size_t zero_n16) {
-    if ((int)blockIdx.x >= g.T) {
-        const size_t stride = (size_t)(gridDim.x - g.T) * blockDim.x;
-        for (size_t i = (size_t)(blockIdx.x - g.T) * blockDim.x + threadIdx.x; i < zero_n16; i += stride)
+    constexpr bool kSplitParts = LAYOUT == kLayoutSplit || LAYOUT == kLayoutSplitPair;
+    const int tap_blocks = LAYOUT == kLayoutSplitPair ? 2 * g.T : g.T;
+    if ((int)blockIdx.x >= tap_blocks) {
+        const size_t stride = (size_t)(gridDim.x - tap_blocks) * blockDim.x;
+        for (size_t i = (size_t)(blockIdx.x - tap_blocks) * blockDim.x + threadIdx.x; i < zero_n16; i += stride)
             zero_p[i] = make_uint4(0, 0, 0, 0);
         return;
     }
+    const bool second = LAYOUT == kLayoutSplitPair && (int)blockIdx.x >= g.T;  // (of two layouts)
     __shared__ int s_any, s_odd;
-    const int t = blockIdx.x;
+    const int t = second ? (int)blockIdx.x - g.T : (int)blockIdx.x;
     if (threadIdx.x == 0) {
         s_any = 0;
-        if (LAYOUT == kLayoutSplit) s_odd = 0;
+        if (kSplitParts) s_odd = 0;
     }
     __syncthreads();
     int any = 0;
@@ -414,7 +419,8 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
                 any |= (v != 0.0f);
             }
         }
-    } else if constexpr (LAYOUT == kLayoutSplit) {
+    }
+    if (kSplitParts && !second) {
         unsigned short* __restrict__ ws = (unsigned short*)dst;
         // operand order of the split kernel: [tap][chunk][h | m | l][16 output channels][lane][8], lane = 16 * (channel
         // / 8) + output channel; columns past the real ones are zero.  Groups of 64 output channels one after the other.
@@ -432,8 +438,9 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
                 any |= (v != 0.0f) | (split_exact(__float_as_uint(v)) ? 0 : kTapOdd);
             }
         }
-    } else if constexpr (LAYOUT == kLayoutPair) {
-        float* __restrict__ wb = (float*)dst;
+    }
+    if (LAYOUT == kLayoutPair || second) {
+        float* __restrict__ wb = LAYOUT == kLayoutPair ? (float*)dst : dst2;
         // C_in = 16 is laid out like one 32-channel chunk: a lane's first four values are channels 4 gq .. 4 gq + 3,
         // its other four are zero
         const bool half = c_in == 16;
@@ -447,7 +454,8 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
             wb[(size_t)t * n + i] = v;
             any |= (v != 0.0f);
         }
-    } else {
+    }
+    if constexpr (LAYOUT == kLayoutVector) {
         double* __restrict__ wp = (double*)dst;
         const int n = c_in * c_out_pad;
         for (int i = threadIdx.x; i < n; i += blockDim.x) {
@@ -458,11 +466,12 @@ __global__ __launch_bounds__(256) void k_prepare(Geom g, const float* __restrict
             any |= (v != 0.0f);
         }
     }
+    if (second) return;
     if (any & 1) s_any = 1;
-    if (LAYOUT == kLayoutSplit && (any & kTapOdd)) s_odd = kTapOdd;
+    if (kSplitParts && (any & kTapOdd)) s_odd = kTapOdd;
     __syncthreads();
     if (threadIdx.x == 0) {
-        tap_active[t] = LAYOUT == kLayoutSplit ? s_any | s_odd : s_any;
+        tap_active[t] = kSplitParts ? s_any | s_odd : s_any;
         // tap coordinates (t0, t1, t2), one byte each: delta = coordinate - H
         tap_coord[t] = (t / (g.K[2] * g.K[1])) | (((t / g.K[2]) % g.K[1]) << 8) | ((t % g.K[2]) << 16);
     }
@@ -474,12 +483,14 @@ hipError_t launch_prepare(const Geom& g, const float* w, int c_in, int c_out, in
     const size_t n16 = (zero_bytes + 15) / 16;
     size_t zb = (n16 + 255) / 256;
     if (zb > 2048) zb = 2048;
-    const dim3 grid((unsigned)(g.T + zb)), block(256);
+    const dim3 grid((unsigned)(g.T * (ws && wb ? 2 : 1) + zb)), block(256);
 #define SCNN_PREPARE(LAYOUT, DST)                                                                                    \
-    hipLaunchKernelGGL(k_prepare<LAYOUT>, grid, block, 0, s, g, w, c_in, c_out, adjoint, c_out_pad, (void*)(DST), tap_active, \
+    hipLaunchKernelGGL(k_prepare<LAYOUT>, grid, block, 0, s, g, w, c_in, c_out, adjoint, c_out_pad, (void*)(DST), wb, tap_active, \
                        tap_coord, (uint4*)zero_p, n16)
     if (wq)
         SCNN_PREPARE(kLayoutQuad, wq);
+    else if (ws && wb)
+        SCNN_PREPARE(kLayoutSplitPair, ws);
     else if (ws)
         SCNN_PREPARE(kLayoutSplit, ws);
     else if (wb)

@@ -385,7 +385,7 @@ hipError_t launch_index_build_pool(const Geom& g, const Geom& gp, const int32_t*
                                    unsigned long long* occ, unsigned* occ_prefix, unsigned long long* pbits, Counters* ctr,
                                    hipStream_t s);
 // wp / wb / wq / ws: the filter in the layout of the vector / fp32 pair-list / fp32 quad / split kernels (of wb, wq and
-// ws at most the one that will run is non-null; wp is used when all three are null)
+// ws at most the one that will run is non-null, or both wb and ws; wp is used when all three are null)
 hipError_t launch_prepare(const Geom& g, const float* w, int c_in, int c_out, int adjoint, int c_out_pad, double* wp,
                           float* wb, float* wq, unsigned short* ws, int* tap_active, int* tap_coord, void* zero_p,
                           size_t zero_bytes, hipStream_t s);
@@ -439,12 +439,13 @@ hipError_t launch_pair_build(const Geom& g, const unsigned long long* occ, const
                              uint2* tile_hdr, long long block_cap, long long tiles_cap,
                              unsigned short* tap_first /* nullable: [tiles][T + 1] first block of each tap */,
                              hipStream_t s);
-hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, const float* feats, int c_in, const float* wb, int c_out,
+hipError_t launch_conv_mfma(const Geom& g, long long nnz_in, int only_odd, const float* feats, int c_in, const float* wb, int c_out,
                             const float* bias, const unsigned* pairs, const unsigned short* block_tap,
                             const uint2* tile_hdr, Counters* ctr, float* resp, hipStream_t s);
-// (on split operands; w = the filter as it is, adjoint: read as the adjoint convolution's)
+// (on split operands; w = the filter as it is; leave_odd: leaves a call with such values to launch_conv_mfma with only_odd,
+// and does not read w)
 hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* feats, int c_in, const unsigned short* ws,
-                                  const float* w, int adjoint, int c_out, const float* bias, const unsigned* pairs,
+                                  const float* w, int leave_odd, int c_out, const float* bias, const unsigned* pairs,
                                   const unsigned short* block_tap, const uint2* tile_hdr, Counters* ctr, float* resp,
                                   hipStream_t s);
 

@@ -316,3 +316,22 @@ def test_backward_values_that_three_bf16_numbers_do_not_hold(c_in, c_out, ksize,
     ok = np.isfinite(ref) & np.isfinite(mag)
     # (fp32 chains of at most 32 products: half a rounding of their magnitudes on each; their sums are added in fp64)
     assert ok.any() and (np.abs(got[ok] - ref[ok]) <= 33 * 2.0 ** -24 * mag[ok] + 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("c_out", [32, 64, 96, 128])
+@pytest.mark.parametrize("c_in", [16, 32, 48, 64])
+@pytest.mark.parametrize("where", ["gradient", "weight"])
+def test_backward_one_tiny_value(c_in, c_out, where):
+    """One value below 2^-109, which makes the whole call multiply in fp32, at every width of the matrix-core kernels."""
+    rng = np.random.default_rng(c_in * 1000 + c_out)
+    ext, ksize = (13, 18, 21), (3, 3, 3)
+    coords, gc = random_sparse_sites(rng, ext, 2, 0.1), random_sparse_sites(rng, ext, 2, 0.2)
+    feats = rng.normal(size=(coords.shape[0], c_in)).astype(np.float32)
+    gf = (rng.normal(size=(gc.shape[0], c_out)) * (rng.random((gc.shape[0], c_out)) < 0.3)).astype(np.float32)
+    w = (rng.normal(size=(27, c_in, c_out)) * 0.1).astype(np.float32)
+    if where == "gradient":
+        gf[gc.shape[0] - 1, c_out - 1] = 2.0 ** -120
+    else:
+        w[26, c_in - 1, c_out - 1] = 2.0 ** -120
+    say(f"bwd one tiny {where} {c_in}->{c_out}")
+    full_check(ext, 2, coords, feats, ksize, w, gc, gf, f"{c_in}->{c_out} {where}")
