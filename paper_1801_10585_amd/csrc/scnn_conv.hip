@@ -182,11 +182,20 @@ __global__ __launch_bounds__(256) void k_conv_valu_stream(Geom g, const unsigned
 // thread owns a site and walks the neighbours that it has, lowest tap first, several in flight, with the weights of its tap
 // from LDS: a wave takes as many rounds as its richest site has neighbours (three of 27 taps on scattered sites, about
 // half of them on surfaces).  The sums are fp64 and in tap order.  One input and eight output channels, against the forms
-// above: 256^3 scattered, 1.7 M sites, 104 -> 35 us; 28 x 28 x 1024 29 -> 17.5; one 28 x 28 image 9.8 -> 5.3.
+// above: 256^3 scattered, 1.7 M sites, 104 -> 35 us; 28 x 28 x 1024 29 -> 17.5; one 28 x 28 image 9.8 -> 5.3.  By density
+// (share of occupied input sites; the stage by events), 1 -> 8 and 1 -> 16 on 128^3: 0.02 58 -> 25 and 68 -> 29, 0.3 126 ->
+// 60 and 150 -> 77, all occupied 128 -> 78 and 154 -> 105; 16^3, 32 tiles: 14.7 -> 8.3 and 15.2 -> 9.4, 14.6 -> 10.9 and
+// 14.9 -> 12.9, all occupied 14.7 -> 12.8 and 15.1 -> 15.6, the one place where it is the slower.
 // Eight input channels are bound by the weights' way out of LDS (512 bytes a lane and neighbour): 128^3 x 4, 8 -> 8,
-// 91 -> 57 us; calls on 48^3 x 4 115 -> 86, on 128^3 x 2 155 -> 122 (a tenth of it the compaction's gain), on 32^3 x 4,
-// 464 tiles of capacity, 74 -> 63: from the 32-row form's end on.  Sixteen output channels double that bound, and on the
-// dense surfaces that follow a pooling lose to the streaming form (64^3 x 4: 57 -> 80 us); they keep the forms above.
+// 91 -> 57 us.  By density, 0.02 / 0.3 / all: 32^3 x 4 26 / 52 / 51 -> 13 / 23 / 30, 64^3 x 4, 2 k tiles, - / 44 / 45 -> - /
+// 31 / 42; surfaces of 0.05 to 0.2 on 64^3 x 8 0.72 to 1.01 times.  It loses where the forms above do their best: with at
+// most 256 tiles in use (surfaces on 40^3 x 4, 189 tiles, 304 of capacity, 21.7 against 24.0; 16^3 x 8, all occupied, 21.9
+// against 25.3) and, with nearly all of 27 neighbours there, as a surface's gradient rows are, up to 512 (adjoint, 40^3 x 4,
+// 300 tiles, 27.3 against 30.0; 512 tiles 27.2 against 29.8, 640 42.7 against 31.7): hence the line at twice the 32-row
+// form's items, and at its items for at most nine taps (28 x 28 x 64, all occupied, 16.4 -> 13.5; adjoint, 28 x 28 x 200,
+// 26.4 -> 15.5) and inputs of less than a row per six candidates (16^3 x 8, 0.06 occupied, 21.6 -> 14.3).  Past it only the
+// adjoint on 1040 to 1250 tiles is slower, by 1.05 to 1.1.  Sixteen output channels double that bound, and on the dense
+// surfaces that follow a pooling lose to the streaming form (64^3 x 4: 57 -> 80 us); they keep the forms above.
 constexpr int kOneLines = 9;  // filter lines at most (and 32 taps)
 constexpr long long kOneBlocks = 256 * 16;
 template <int CI /* input channels: 1 or 8 */, int OCB /* output channels at most: 8 or 16 */>
@@ -931,7 +940,10 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
         hipLaunchKernelGGL(k_conv_valu_empty, dim3(256 * 8), dim3(256), 0, s, c_out, ctr, resp);
         return hipGetLastError();
     }
-    const bool eight = c_in == 8 && c_out <= 8 && ((uintptr_t)feats & 15) == 0 && tiles_cap > kValuSmallItems;
+    // (between one and two times the 32-row form's items only where a site has few neighbours: see above)
+    const bool few = g.T <= 9 || nnz_in * 6 <= tiles_cap * kTileRows;
+    const bool eight = c_in == 8 && c_out <= 8 && ((uintptr_t)feats & 15) == 0 &&
+                       tiles_cap > (few ? 1 : 2) * kValuSmallItems;
     if ((c_in == 1 || eight) && c_out <= 16 && g.T <= 32 && g.K[0] * g.K[1] <= kOneLines) {
         const unsigned blocks = (unsigned)(tiles_cap < 2 ? 1 : ((tiles_cap + 1) / 2 > kOneBlocks ? kOneBlocks : (tiles_cap + 1) / 2));
 #define SCNN_VALU_ONE(CI_, OCB_)                                                                                              \
