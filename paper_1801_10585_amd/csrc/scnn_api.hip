@@ -477,7 +477,7 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
         timer.mark();
         SCNN_TRY(launch_conv_valu(g, ws.occ, ws.occ_prefix, nnz_in, in_feats, c_in, ws.wp, c_out, ws.c_out_pad, bias,
                                   ws.tap_active, ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, ws.tiles_cap,
-                                  ws.resp, s));
+                                  0, ws.resp, s));
         g_last_conv_kernel = "k_conv_valu";
     }
     timer.mark();
@@ -653,7 +653,7 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
         timer.mark();
         SCNN_TRY(launch_conv_valu(g, ws.occ, ws.occ_prefix, g_rows, g_feats, c_out, ws.wp, c_in, ws.c_in_pad, nullptr,
                                   ws.tap_active, ws.cand_lin, ws.cand_start, ws.tile_start, ws.ctr, ws.tiles_cap,
-                                  ws.resp, s));
+                                  1, ws.resp, s));
     }
     timer.mark();
     SCNN_TRY(launch_bwd_data_write(g, ws.resp, in_feats, c_in, ws.cand_start, ws.tile_start, ws.ctr, ws.tiles_cap,

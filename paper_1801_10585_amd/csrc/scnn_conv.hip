@@ -196,9 +196,14 @@ __global__ __launch_bounds__(256) void k_conv_valu_stream(Geom g, const unsigned
 // 26.4 -> 15.5) and inputs of less than a row per six candidates (16^3 x 8, 0.06 occupied, 21.6 -> 14.3).  Past it only the
 // adjoint on 1040 to 1250 tiles is slower, by 1.05 to 1.1.  Sixteen output channels double that bound, and on the dense
 // surfaces that follow a pooling lose to the streaming form (64^3 x 4: 57 -> 80 us); they keep the forms above.
+// Tiles: a workgroup's two are neighbours (SPREAD = 0), which share most of the rows they gather; two that the whole launch
+// lies between take 1.02 to 1.35 times as long.  The adjoint convolution is followed by a filter gradient that gathers the
+// same rows, tile i on XCD i % 8: there the tiles are spread likewise, so that it finds them in its L2 (8 -> 1 channels'
+// layer, 40^3 x 4, 141 k rows: filter gradient 132 -> 102 us, 104 behind the streaming form).  (An argument instead of an
+// instance took sixteen more registers of 1 -> 16 and 10 % of its time.)
 constexpr int kOneLines = 9;  // filter lines at most (and 32 taps)
 constexpr long long kOneBlocks = 256 * 16;
-template <int CI /* input channels: 1 or 8 */, int OCB /* output channels at most: 8 or 16 */>
+template <int CI /* input channels: 1 or 8 */, int OCB /* output channels at most: 8 or 16 */, int SPREAD>
 __global__ __launch_bounds__(256) void k_conv_valu_one(Geom g, const unsigned long long* __restrict__ occ,
                                                        const unsigned* __restrict__ occ_prefix, long long nnz_in,
                                                        const float* __restrict__ feats, const double* __restrict__ wp,
@@ -223,7 +228,8 @@ __global__ __launch_bounds__(256) void k_conv_valu_one(Geom g, const unsigned lo
         s_k[tid] = (unsigned char)(tid % K2);
     }
     __syncthreads();
-    for (int tile = (int)blockIdx.x * 2 + (tid >> 7); tile < n_tiles; tile += (int)gridDim.x * 2) {  // (uniform in the wave)
+    const int first_tile = SPREAD ? (int)blockIdx.x + (tid >> 7) * (int)gridDim.x : (int)blockIdx.x * 2 + (tid >> 7);
+    for (int tile = first_tile; tile < n_tiles; tile += (int)gridDim.x * 2) {  // (uniform in the wave)
         const int b = sample_of_tile(tile_start, g.batch, tile), r = tid & (kTileRows - 1);
         const int cand = cand_start[b] + (tile - tile_start[b]) * kTileRows + r;
         const bool live = cand < cand_start[b + 1];
@@ -935,7 +941,7 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
                             long long nnz_in, const float* feats, int c_in, const double* wp, int c_out,
                             int c_out_pad, const float* bias, const int* tap_active, const unsigned* cand_lin,
                             const int* cand_start, const int* tile_start, const Counters* ctr, long long tiles_cap,
-                            float* resp, hipStream_t s) {
+                            int spread, float* resp, hipStream_t s) {
     if (nnz_in <= 0) {  // no input row: every response tile is zero (the gather would have no row to point at)
         hipLaunchKernelGGL(k_conv_valu_empty, dim3(256 * 8), dim3(256), 0, s, c_out, ctr, resp);
         return hipGetLastError();
@@ -945,13 +951,19 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
     const bool eight = c_in == 8 && c_out <= 8 && ((uintptr_t)feats & 15) == 0 &&
                        tiles_cap > (few ? 1 : 2) * kValuSmallItems;
     if ((c_in == 1 || eight) && c_out <= 16 && g.T <= 32 && g.K[0] * g.K[1] <= kOneLines) {
-        const unsigned blocks = (unsigned)(tiles_cap < 2 ? 1 : ((tiles_cap + 1) / 2 > kOneBlocks ? kOneBlocks : (tiles_cap + 1) / 2));
-#define SCNN_VALU_ONE(CI_, OCB_)                                                                                              \
-    hipLaunchKernelGGL((k_conv_valu_one<CI_, OCB_>), dim3(blocks), dim3(256), 0, s, g, occ, occ_prefix, nnz_in, feats, wp, c_out, \
-                       c_out_pad, bias, tap_active, cand_lin, cand_start, tile_start, ctr, resp)
-        if (c_in == 1 && c_out <= 8) SCNN_VALU_ONE(1, 8);
-        else if (c_in == 1) SCNN_VALU_ONE(1, 16);
-        else SCNN_VALU_ONE(8, 8);
+        long long blocks = (tiles_cap + 1) / 2;
+        if (spread) blocks = round_up(blocks, kXcds);
+        if (blocks > kOneBlocks) blocks = kOneBlocks;
+#define SCNN_VALU_ONE(CI_, OCB_, SPREAD_)                                                                                     \
+    hipLaunchKernelGGL((k_conv_valu_one<CI_, OCB_, SPREAD_>), dim3((unsigned)blocks), dim3(256), 0, s, g, occ, occ_prefix, nnz_in, \
+                       feats, wp, c_out, c_out_pad, bias, tap_active, cand_lin, cand_start, tile_start, ctr, resp)
+        if (c_in == 1 && c_out <= 8) {
+            if (spread) SCNN_VALU_ONE(1, 8, 1); else SCNN_VALU_ONE(1, 8, 0);
+        } else if (c_in == 1) {
+            if (spread) SCNN_VALU_ONE(1, 16, 1); else SCNN_VALU_ONE(1, 16, 0);
+        } else {
+            if (spread) SCNN_VALU_ONE(8, 8, 1); else SCNN_VALU_ONE(8, 8, 0);
+        }
 #undef SCNN_VALU_ONE
         return hipGetLastError();
     }

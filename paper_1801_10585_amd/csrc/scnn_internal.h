@@ -429,7 +429,7 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
                             long long nnz_in, const float* feats, int c_in, const double* wp, int c_out,
                             int c_out_pad, const float* bias, const int* tap_active, const unsigned* cand_lin,
                             const int* cand_start, const int* tile_start, const Counters* ctr, long long tiles_cap,
-                            float* resp, hipStream_t s);
+                            int spread /* tile i on XCD i % 8, where that can be chosen */, float* resp, hipStream_t s);
 
 bool conv_mfma_supported(const Geom& g, int c_in, int c_out, long long nnz_in);
 hipError_t launch_pair_build(const Geom& g, const unsigned long long* occ, const unsigned* occ_prefix,
