@@ -1759,7 +1759,7 @@ __global__ __launch_bounds__(256) void k_select_write_narrow(Geom g, int channel
     finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity, n_super > 0 ? n_super : 1);
 }
 
-// The pass in two launches, without tickets, look-back or end counters, for narrow layers of more than kNarrowPairTiles
+// The pass in two launches, without tickets, look-back or end counters, for narrow layers of more than narrow_pair_tiles
 // tiles of capacity: read-modify-writes of one address are served one after the other, and a ticket and an end mark from each of
 // several hundred workgroups were half of the one launch's time.  Workgroup i of both launches owns the same consecutive
 // tiles.  The first notes the rows that keep an entry (row_keep, two words per tile) and the workgroup's number of them;
@@ -1767,8 +1767,19 @@ __global__ __launch_bounds__(256) void k_select_write_narrow(Geom g, int channel
 // writes the result counters.  A wave takes the 64 rows of half a tile at a time.
 // 8 channels, us: 128^3 x 4, 5 k tiles 36 -> 9 + 11; 256^3 scattered, 13 k tiles 63 -> 17 + 20; 28 x 28 x 1024, 3 k tiles
 // 34 -> 10 + 11; 32^3 x 4, capacity 1028 tiles, 11.8 -> 4.8 + 5.2.  Sixteen channels, 132 tiles: 9.5 against 7.0 + 6.7.
-constexpr long long kNarrowPairTiles = 512;
-__device__ inline int tiles_per_workgroup(int n_tiles) { return (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x; }
+// More than sixteen channels are read twice at a price: one launch against this one, 24 channels, 385 of 561 tiles of
+// capacity in use 16.6 against 22.7 us (the stage, by events), 727 / 1039 of 1056 23.6 / 28.7 against 23.9 / 27.5, 1092 /
+// 1559 of 1584 30.1 / 39.4 against 26.4 / 31.0; 32 channels 19.1 against 26.1, 25.4 / 33.1 against 27.7 / 32.9, 33.5 / 44.6
+// against 31.1 / 37.0: hence a later line for them.  There a workgroup also owns an even number of tiles: its four waves take
+// two at a time, and three took as long as four (2092 tiles, 32 channels, 56.9 -> 44.6 us, 24 channels 46.5 -> 34.4; the
+// launch has half as many workgroups again for it).
+constexpr long long narrow_pair_tiles(int cmax) { return cmax > 16 ? 1152 : 512; }
+template <int CMAX>
+__device__ inline int tiles_per_workgroup(int n_tiles) {
+    if constexpr (CMAX <= 16) return (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int n = (int)gridDim.x, most = n - n / 3, per = (n_tiles + most - 1) / most, even = per & ~1;
+    return even > 0 && (long long)even * n >= n_tiles ? even : per;
+}
 
 template <int CMAX>
 __global__ __launch_bounds__(256) void k_select_rows_narrow(Geom g, int channels, int mode, int relu,
@@ -1781,7 +1792,7 @@ __global__ __launch_bounds__(256) void k_select_rows_narrow(Geom g, int channels
                                                             unsigned* __restrict__ counts) {
     __shared__ unsigned s_cnt[4];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n_tiles = (int)ctr->n_tiles, per = tiles_per_workgroup(n_tiles);
+    const int n_tiles = (int)ctr->n_tiles, per = tiles_per_workgroup<CMAX>(n_tiles);
     const int first = (int)blockIdx.x * per, last = first + per < n_tiles ? first + per : n_tiles;
     unsigned cnt = 0;
     for (int u = 2 * first + wave; u < 2 * last; u += 4) {
@@ -1819,7 +1830,7 @@ __global__ __launch_bounds__(256) void k_select_emit_narrow(Geom g, int channels
                                                             int aux_is_cand) {
     __shared__ unsigned s_sum[4];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n_tiles = (int)ctr->n_tiles, per = tiles_per_workgroup(n_tiles);
+    const int n_tiles = (int)ctr->n_tiles, per = tiles_per_workgroup<CMAX>(n_tiles);
     const int first = (int)blockIdx.x * per, last = first + per < n_tiles ? first + per : n_tiles;
     if (first >= last && blockIdx.x != 0) return;
     unsigned before = 0;  // rows of the workgroups before this one (31 bits: at most as many as candidates)
@@ -1880,8 +1891,9 @@ hipError_t launch_select_write(const Geom& g, int channels, int mode, int relu, 
     long long blocks = tiles_cap < 1 ? 1 : (tiles_cap > cus * 3 ? cus * 3 : tiles_cap);
 #define SCNN_NARROW_CASE(CMAX_)                                                                                   \
     do {                                                                                                          \
-        if (tiles_cap > kNarrowPairTiles) {                                                                       \
-            const unsigned grid = (unsigned)(tiles_cap > cus * 4 ? cus * 4 : tiles_cap);                          \
+        if (tiles_cap > narrow_pair_tiles(CMAX_)) {                                                               \
+            const long long most = cus * (CMAX_ > 16 ? 6 : 4);                                                    \
+            const unsigned grid = (unsigned)(tiles_cap > most ? most : tiles_cap);                                \
             unsigned* counts = (unsigned*)tile_state;                                                             \
             hipLaunchKernelGGL(k_select_rows_narrow<CMAX_>, dim3(grid), dim3(256), 0, s, g, channels, mode, relu, \
                                cand_start, tile_start, resp, cols, ctr, row_keep, counts);                        \

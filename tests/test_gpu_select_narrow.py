@@ -1,4 +1,4 @@
-"""Compaction of narrow layers: the one-launch and the two-launch form on either side of their border (512 tiles of
+"""Compaction of narrow layers: the one-launch and the two-launch form on either side of their border (512 or 1152 tiles of
 capacity), few and no rows, samples without rows, odd channel counts, more surviving rows than the output holds."""
 import numpy as np
 import pytest
@@ -86,4 +86,21 @@ def test_selection_of_short_columns(ext, batch, c_out, rho, mode):
     rc, rf = oracle.sparse_conv_fwd(ext, batch, coords, feats, k, w, rho_up=rho, topk_mode=mode)
     gc, gf, n = scnn.sparse_conv_fwd(ext, batch, *(torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (coords, feats, )), k,
                                      torch.from_numpy(w).cuda(), rho_up=rho, topk_mode=mode)
+    assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf) and int(n[2]) == 0
+
+
+@pytest.mark.parametrize("c_out,relu", [(17, False), (24, True), (32, False)])
+@pytest.mark.parametrize("ext,density,cap", [((60, 60, 60), 0.025, 1151 * 128), ((60, 60, 60), 0.025, 1151 * 128 + 1), ((80, 80, 80), 0.0105, 0),
+                                             ((80, 80, 80), 0.0118, 0), ((80, 80, 80), 0.027, 0), ((80, 80, 81), 0.3, 0)])
+def test_compaction_of_seventeen_to_thirty_two_channels(ext, density, cap, c_out, relu):
+    """Either side of 1152 tiles of capacity, and from 1 k to 4 k tiles in use, one, two, three and four a workgroup: small
+    whole numbers, nothing selected."""
+    rng = np.random.default_rng(c_out)
+    coords = random_sparse_sites(rng, ext, 1, density)
+    feats = rng.integers(1, 4, size=(len(coords), 1)).astype(np.float32)
+    w = rng.integers(-2, 3, size=(27, 1, c_out)).astype(np.float32)
+    rc, rf = oracle.sparse_conv_fwd(ext, 1, coords, feats, (3, 3, 3), w, rho_up=1.0, relu=relu)
+    gc, gf, n = scnn.sparse_conv_fwd(ext, 1, *(torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (coords, feats)), (3, 3, 3),
+                                     torch.from_numpy(w).cuda(), rho_up=1.0, relu=relu, cand_capacity=cap)
+    print(ext, c_out, len(coords), int(n[1]) / 128, cap, flush=True)
     assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf) and int(n[2]) == 0
