@@ -60,3 +60,39 @@ def test_eight_input_channels_by_size_and_alignment(ext, batch, c_out, rows_at):
     oc, of, _ = scnn.sparse_conv_fwd(ext, batch, _dev(coords)[0], x, k, *_dev(w))
     rc, rf = oracle.sparse_conv_fwd(ext, batch, coords, feats, k, w, rho_up=1.0)
     assert np.array_equal(oc.cpu().numpy(), rc) and np.array_equal(of.cpu().numpy(), rf)
+
+
+@pytest.mark.parametrize("ext,ksize,density", [
+    ((40, 1), (1, 31), 0.6), ((40, 3), (1, 31), 0.5), ((30, 64), (1, 31), 0.3), ((30, 65), (1, 31), 0.3),
+    ((6, 5, 3), (1, 1, 9), 0.5), ((6, 5, 64), (1, 1, 9), 0.3), ((6, 5, 65), (1, 1, 9), 0.3),
+    ((33, 3), (3, 7), 0.5), ((33, 64), (3, 7), 0.3), ((33, 65), (3, 9), 1.0), ((5, 9, 4), (1, 3, 9), 0.4), ((5, 4, 65), (1, 3, 9), 0.4),
+    ((20, 65), (9, 3), 0.3), ((5, 65, 1), (3, 3, 1), 0.4), ((40, 65), (1, 1), 0.5)])
+@pytest.mark.parametrize("c_in,c_out,path", [(1, 3, 0), (1, 16, 0), (8, 1, 0), (13, 1, 0)])
+def test_one_channel_along_short_filters(ext, ksize, density, c_in, c_out, path):
+    """Filters of at most 32 taps in at most nine lines, which one input channel takes site by site: forward from one
+    channel, backward of layers with one output channel."""
+    test_neighbours_along_filter_lines(ext, ksize, density, c_in, c_out, path)
+
+
+@pytest.mark.parametrize("ext,ksize,density,g_density", [((47, 49, 48), (3, 3, 3), 0.7, 0.8), ((40, 41, 43), (3, 3, 3), 0.6, 0.02),
+                                                         ((301, 260), (3, 3), 0.5, 0.5), ((5, 150, 130), (1, 3, 9), 0.9, 0.5)])
+@pytest.mark.parametrize("c_in", [1, 5, 8])
+@pytest.mark.parametrize("rows_at", [0, 4])
+def test_backward_of_eight_output_channels_by_size(ext, ksize, density, g_density, c_in, rows_at):
+    """From 257 tiles of rows on where a row meets few gradients, from 513 elsewhere, and gradient rows past a 16-byte
+    boundary: small whole numbers, exact."""
+    rng = np.random.default_rng(c_in + ext[0])
+    coords, gc = random_sparse_sites(rng, ext, 1, density), random_sparse_sites(rng, ext, 1, g_density)
+    few = np.prod(ksize) <= 9 or len(gc) * 6 <= len(coords)
+    assert len(coords) > (256 if few else 512) * 128
+    feats = rng.integers(-3, 4, size=(len(coords), c_in)).astype(np.float32)
+    w = (rng.integers(-3, 4, size=(int(np.prod(ksize)), c_in, 8)) * (rng.random((int(np.prod(ksize)), 1, 1)) < 0.8)).astype(np.float32)
+    gf = rng.integers(-3, 4, size=(len(gc), 8)).astype(np.float32)
+    room = torch.zeros(gf.size + 4, device="cuda")
+    g = room[rows_at // 4:rows_at // 4 + gf.size].view(gf.shape)
+    g.copy_(torch.from_numpy(gf))
+    print(ext, ksize, c_in, rows_at, len(coords), len(gc), flush=True)
+    data, filt, info = scnn.sparse_conv_bwd(ext, 1, *_dev(coords, feats), ksize, *_dev(w, gc), g)
+    rd, rw = oracle.sparse_conv_bwd(ext, 1, coords, feats, ksize, w, gc, gf)
+    assert int(info[2]) == 0
+    assert np.array_equal(data.cpu().numpy(), rd) and np.array_equal(filt.cpu().numpy(), rw)
