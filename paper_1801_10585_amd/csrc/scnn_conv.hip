@@ -1635,7 +1635,7 @@ __global__ __launch_bounds__(kConvWaves * 64, NB == 4 ? 2 : 1) void k_conv_mfma_
                                 const float x = row[i];
 #pragma unroll
                                 for (int cb = 0; cb < NB; ++cb) {
-                                    const float wv = filter_at(w, taps, C_IN, C_OUT, 0, t, ch + i, cb * 16 + jj);
+                                    const float wv = w[((size_t)t * C_IN + ch + i) * C_OUT + cb * 16 + jj];
                                     d[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, wv, d[cb], 0, 0, 0);
                                 }
                             }
@@ -1885,10 +1885,13 @@ hipError_t launch_conv_mfma_split(const Geom& g, long long nnz_in, const float* 
 #define SCNN_MFMA_CASE(KC_, NB_)                                                                                  \
     if (c_in == KC_ * 32 && c_out == NB_ * 16)                                                                    \
         return leave_odd ? launch_conv_mfma_split_t<KC_, NB_, 1>(SCNN_MFMA_ARGS) : launch_conv_mfma_split_t<KC_, NB_, 0>(SCNN_MFMA_ARGS);
-    SCNN_MFMA_CASE(1, 1) SCNN_MFMA_CASE(1, 2) SCNN_MFMA_CASE(1, 3) SCNN_MFMA_CASE(1, 4)
+#define SCNN_MFMA_FORWARD(KC_, NB_) /* (the adjoint takes these on fp32 products) */                              \
+    if (c_in == KC_ * 32 && c_out == NB_ * 16 && !leave_odd) return launch_conv_mfma_split_t<KC_, NB_, 0>(SCNN_MFMA_ARGS);
+    SCNN_MFMA_FORWARD(1, 1) SCNN_MFMA_FORWARD(1, 2) SCNN_MFMA_CASE(1, 3) SCNN_MFMA_CASE(1, 4)
     SCNN_MFMA_CASE(2, 1) SCNN_MFMA_CASE(2, 2) SCNN_MFMA_CASE(2, 3) SCNN_MFMA_CASE(2, 4)
     SCNN_MFMA_CASE(3, 1) SCNN_MFMA_CASE(3, 2) SCNN_MFMA_CASE(3, 3) SCNN_MFMA_CASE(3, 4)
     SCNN_MFMA_CASE(4, 1) SCNN_MFMA_CASE(4, 2) SCNN_MFMA_CASE(4, 3) SCNN_MFMA_CASE(4, 4)
+#undef SCNN_MFMA_FORWARD
 #undef SCNN_MFMA_CASE
 #undef SCNN_MFMA_ARGS
     return hipErrorInvalidValue;

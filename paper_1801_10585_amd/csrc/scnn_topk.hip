@@ -21,12 +21,13 @@
 // final mask + compaction + write) and once in a sample of 1/S.  Columns short
 // enough for one workgroup's registers are selected in a single launch.
 //
-// Compaction: where the selection has noted the rows (layers of 33 to 64
-// channels), the rows that survive in every tile are known before the last
-// pass, a scan gives each tile its first output row, and the write pass
-// streams with no ordering between tiles.  Narrow layers count and write in two
-// launches.  Elsewhere tiles are taken in order and a tile learns its first
-// output row by looking back at its predecessors.
+// Compaction: where the selection has noted the rows (layers of 17 to 64
+// channels with columns of more than one workgroup's), the rows that survive in
+// every tile are known before the last pass, a scan gives each tile its first
+// output row, and the write pass streams with no ordering between tiles.  Other
+// layers of at most 32 channels count and write in two launches from some size
+// on (narrow_pair_tiles).  Elsewhere tiles are taken in order and a tile learns
+// its first output row by looking back at its predecessors.
 #include <type_traits>
 
 #include "scnn_internal.h"
@@ -1250,12 +1251,12 @@ __device__ inline long long lookback_wave(unsigned long long* tile_state, int ti
     return lookback_published(tile_state, tile, count, ctr);
 }
 
-// (one thread) The next `n` tiles of the compaction pass's queue.  Read-modify-writes of one address are served one
-// at a time, about 13 ns each on this chip (a plain load of the counter is no cheaper), so a pass over a few
-// thousand tiles can be bound by its tickets alone, and a thousand workgroups asking at once wait 13 us for theirs.
-// Hence no ticket that is known to come back empty: a launch with at least as many workgroups as tickets takes one ticket per workgroup (`once`), and a
-// workgroup that has seen the queue empty does not ask again.
-__device__ inline unsigned take_ticket(Counters* ctr, unsigned n) { return atomicAdd(&ctr->ticket, n); }
+// (one thread) The next of the compaction pass's queue.  Read-modify-writes of one address are served one at a time, about
+// 13 ns each on this chip (a plain load of the counter is no cheaper), so a pass over a few thousand tiles can be bound by
+// its tickets alone, and a thousand workgroups asking at once wait 13 us for theirs.  Hence no ticket that is known to come
+// back empty: a launch with at least as many workgroups as tickets takes one per workgroup (`once`), and a workgroup that
+// has seen the queue empty does not ask again.
+__device__ inline unsigned take_ticket(Counters* ctr) { return atomicAdd(&ctr->ticket, 1u); }
 
 // (one thread) The result counters.  aux = second counter: the candidate count (aux_is_cand) or a host-side number.
 // nnz_out may be null: a later kernel writes them.
@@ -1308,7 +1309,7 @@ __global__ __launch_bounds__(256) void k_select_write(Geom g, int channels, int 
 
     for (;;) {
         __syncthreads();  // s_ticket and the tile buffers of the previous round are no longer read
-        if (threadIdx.x == 0) s_ticket = (int)take_ticket(ctr, 1u);
+        if (threadIdx.x == 0) s_ticket = (int)take_ticket(ctr);
         __syncthreads();
         const int tile = s_ticket;
         if (tile >= n_tiles) break;
@@ -1571,7 +1572,7 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
             dealt = t + (int)gridDim.x;
             return t;
         }
-        const int t = (once && asked) ? n_tiles : (int)take_ticket(ctr, 1u);
+        const int t = (once && asked) ? n_tiles : (int)take_ticket(ctr);
         asked = true;
         return t;  // (at or past n_tiles: no tile)
     };
@@ -1722,7 +1723,7 @@ __global__ __launch_bounds__(256) void k_select_write_narrow(Geom g, int channel
     if ((int)blockIdx.x >= (n_super > 0 ? n_super : 1)) return;
     if (n_super > 0) {
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        if (threadIdx.x == 0) s_ticket = (int)take_ticket(ctr, 1u);
+        if (threadIdx.x == 0) s_ticket = (int)take_ticket(ctr);
         __syncthreads();
         const int st = s_ticket, tile = st * 2 + (int)(threadIdx.x >> 7), r = threadIdx.x & (kTileRows - 1);
         float v[CMAX];
