@@ -207,7 +207,8 @@ def bench_backward(args, wl, layer, w, coords, feats, wd):
     if not args.paper_runtime and os.path.exists(tpath):
         try:
             rec = json.load(open(tpath)).get(dominant)
-            if rec:
+            ran = "k_bwd_filter_mfma" if dominant == "bwd_filter" else "k_conv_mfma_split" if split else "k_conv_mfma"
+            if rec and mfma and rec.get("kernel", "").split("<")[0] == ran:
                 traffic = rec.get("hbm_bytes_per_launch")
                 traffic_source = "profiles/" + os.path.basename(tpath) + ": " + rec.get("source", "")
         except Exception:
