@@ -41,8 +41,9 @@
  * status bits where the kernels can see them cheaply.  With
  * SCNN_FLAG_BAD_COORD or SCNN_FLAG_UNSORTED set the results of the call are
  * undefined (a row with an out-of-range coordinate is never used as an
- * address, but the rows that share its 64-site bitmap word are then looked up
- * one row off); every access stays inside the caller's arrays.
+ * address, but rows near it, those of its 64-site bitmap word and up to a
+ * filter line past it, are then looked up one row off); every access stays
+ * inside the caller's arrays.
  */
 #ifndef SCNN_H_
 #define SCNN_H_
@@ -262,7 +263,12 @@ int scnn_validate_rows(int ndim, const int32_t* extent, int batch, const int32_t
  * matrix-core kernels (C_out = 16 or a multiple of 32 up to 128, C_in a multiple
  * of 16 up to 64, 16-byte aligned value arrays) first add up to 32 products (bp_data)
  * or the at most 128 products of one tap within one 128-row tile (bp_filter) in
- * fp32.  Error bound of the matrix-core kernels: with A the sum of the
+ * fp32.  bp_data multiplies on operands split into three bf16 numbers where C_out
+ * is a multiple of 32 and C_out or C_in is above 32; a gradient value or weight
+ * that the three do not hold (non-zero magnitudes below 2^-109 or from 2^58 up,
+ * infinities, NaN) makes the call multiply in fp32 instead, at the pace of the
+ * fp32 kernel.
+ * Error bound of the matrix-core kernels: with A the sum of the
  * magnitudes of the products behind an element, |result - exact| <=
  * 1e-5 |exact| + 1e-6 + c A with c = 2e-8 for bp_data and 1e-7 for bp_filter
  * (a third of, resp. 1.7 times, the fp32 unit roundoff 2^-24: the fp32 chains

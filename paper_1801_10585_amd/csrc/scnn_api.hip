@@ -566,7 +566,8 @@ void carve_bwd(void* base, const Geom& g, long long nnz_in, int c_in, int c_out,
     // most 32 input channels not, where the look over the gradient's values takes back what the products give.  Whole call,
     // fp32 products against split, us, on 16^3 / 32^3 x 4 / 128^3 x 4: 16->32 58.8 / 69.8 / 317 against 58.5 / 71.8 / 308,
     // 32->32 68.5 / 84.6 / 383 against 65.4 / 83.5 / 400; 64->32 89 / 117 / 736 against 81 / 109 / 673, 32->64 89 / 113 /
-    // 651 against 84 / 107 / 613, 64->128 231 / 297 / 2804 against 161 / 203 / 1973.
+    // 651 against 84 / 107 / 613, 64->128 231 / 297 / 2804 against 161 / 203 / 1973.  (Slower only where the launch that leaves
+    // is all there is to it: fourteen rows, 16->64, 50.5 against 53.7.)
     w->split_shape = w->mfma_shape && c_out % 32 == 0 && (c_out > 32 || c_in > 32);
     // (the adjoint filter in matrix-operand order: its input channels, C_out, padded to a whole 32-channel chunk; a split
     // shape's is for the calls whose values the parts do not hold)
