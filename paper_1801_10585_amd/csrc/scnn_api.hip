@@ -26,7 +26,7 @@ enum class ConvKernel { kValu, kPair, kPairSplit, kQuad, kSplit };
 // to 128 output channels (a launch per 64) with at most 32 taps; the quad kernel (fp32 matrix cores) eight input
 // channels, small layers, and inputs whose split copy does not fit 31-bit offsets; the pair-list kernel 96 and 128 input
 // channels and filters of more than 32 taps.
-// With 8, 16 or 24 input channels the matrix cores pay only on layers of enough tiles (128 or 1024, by shape) with
+// (Layers of small samples do not come this way: layer_tiny_shape.)  With 8, 16 or 24 input channels the matrix cores pay only on layers of enough tiles (128 or 1024, by shape) with
 // enough output channels; narrower and smaller layers take the vector kernels (fp64 sums).
 static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long nnz_in, long long tiles_cap) {
     if (g_conv_path == 1) return ConvKernel::kValu;
@@ -271,6 +271,10 @@ struct ConvWs {
     size_t total;
     long long cand_cap, tiles_cap, pool_cap;
     int c_out_pad;
+    bool tiny;  // a workgroup a sample computes the layer whole
+    unsigned* tiny_lin;
+    float* tiny_feats;
+    TinySample* tiny_info;
 };
 
 static void carve_conv(void* base, const Geom& g, const Geom& gp, long long nnz_in, int c_in, int c_out, unsigned fuse,
@@ -333,8 +337,14 @@ static void carve_conv(void* base, const Geom& g, const Geom& gp, long long nnz_
     w->tmp_coords = c.take<int32_t>(pool ? (size_t)cand_cap * (1 + g.ndim) : 0);
     w->tmp_feats = c.take<float>(pool ? (size_t)cand_cap * c_out : 0);
     w->pool_key = c.take<long long>(pool ? w->pool_cap : 0);
+    // (the staging area whatever the number of rows, so that a workspace asked for with more rows serves fewer)
+    const bool tiny_shape = layer_tiny_shape(g, c_in, c_out);
+    w->tiny = tiny_shape && g_conv_path == 0 && w->kernel == ConvKernel::kValu && layer_tiny_pays(g, c_in, c_out, nnz_in);
+    const size_t staged = tiny_shape && g.batch > 1 ? (size_t)g.batch * layer_tiny_stage_rows(g, gp, pool) : 0;
+    w->tiny_lin = c.take<unsigned>(staged);
+    w->tiny_feats = c.take<float>(staged * c_out);
+    w->tiny_info = c.take<TinySample>(staged ? g.batch : 0);
     w->total = c.total();
-    (void)nnz_in;
 }
 
 static int check_conv_sizes(const Geom& g, long long nnz_in, int c_in, int c_out, long long* cand_cap) {
@@ -420,6 +430,15 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
 
     StageTimer timer(s, 0, kFwdStages);
     timer.mark();
+    if (ws.tiny) {
+        for (int i = 0; i < kConvStage; ++i) timer.mark();  // (all of it counts as the convolution's stage)
+        SCNN_TRY(launch_layer_tiny(g, gp, in_coords, in_feats, nnz_in, (const long long*)nnz_in_dev, c_in, w, bias, c_out, k,
+                                   topk_mode, relu, pool, ws.cand_cap, ws.tiny_lin, ws.tiny_feats, ws.tiny_info, out_coords,
+                                   out_feats, out_capacity, (long long*)nnz_out, s));
+        g_last_conv_kernel = "k_layer_tiny";
+        timer.done();
+        return SCNN_OK;
+    }
     // the matrix-core kernels load input rows 16 bytes at a time
     const ConvKernel kernel = ((uintptr_t)in_feats & 15) == 0 ? ws.kernel : ConvKernel::kValu;
     SCNN_TRY(launch_prepare(g, w, c_in, c_out, 0, ws.c_out_pad, ws.wp,

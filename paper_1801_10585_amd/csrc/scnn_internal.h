@@ -352,6 +352,67 @@ __device__ inline int sample_ranges_256(int batch, const int* cand_start, int* t
     return (int)carry_t;
 }
 
+// First row of a sorted row list whose sample index is not below b, by 64 probes at a time.  (whole wave)
+__device__ __forceinline__ long long wave_first_row(const int32_t* __restrict__ coords, int stride, long long rows, int b) {
+    const int lane = threadIdx.x & 63;
+    long long lo = 0, hi = rows;
+    while (lo < hi) {
+        const long long step = (hi - lo + 63) / 64, at = lo + lane * step;
+        const unsigned long long below = __ballot(at < hi && coords[at * stride] < b);
+        const int n = ~below ? __builtin_ctzll(~below) : 64;  // probes before the first row that is not below
+        const long long top = lo + n * step;
+        if (top < hi) hi = top;
+        if (n > 0) lo += (n - 1) * step + 1;
+    }
+    return lo;
+}
+
+// Which of the keys that a wave holds (key u of a lane is position 64 u + lane; 0: not an entry) are the k strongest: those
+// above tau, and those equal to it up to position `cut`.  Found bit by bit from the top: the largest value that at least k
+// keys reach, a compare and a ballot's count per register and bit; a value that exactly k keys reach ends the search (real
+// values: after about half the bits).  What a step costs is its chain of scalar instructions and its branches, hence one
+// branch a step.  (whole wave)
+template <int NU>
+__device__ __forceinline__ void wave_threshold(const unsigned (&key)[NU], long long k, unsigned& n_nz, unsigned& tau,
+                                               unsigned& cut) {
+    const int lane = threadIdx.x & 63;
+    auto reach = [&](unsigned at) {
+        unsigned n = 0;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) n += (unsigned)__popcll(__ballot(key[u] >= at));
+        return n;
+    };
+    n_nz = reach(1u);
+    cut = 0xffffffffu;
+    tau = k <= 0 ? 0xffffffffu : 0u;  // no key is stronger: nothing survives; or fewer entries than k: all do
+    const unsigned want = k < 0x7fffffffll ? (unsigned)k : 0x7fffffffu;
+    if (k <= 0 || n_nz <= want) return;
+    // 1 <= k < n_nz: the k-th strongest key is non-zero
+    unsigned bit = 1u << 31, n = 0;
+#pragma unroll 1
+    do {
+        const unsigned at = tau | bit;
+        n = reach(at);
+        tau = n >= want ? at : tau;
+        bit = n == want ? 0u : bit >> 1;
+    } while (bit != 0u);
+    if (n == want) return;  // (all that reach it: the k-th may be stronger than tau, the next is weaker)
+    unsigned left = want - (tau == 0xffffffffu ? 0u : reach(tau + 1u));  // of the entries equal to tau survive
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const unsigned long long m = __ballot(key[u] == tau);
+        const unsigned c = (unsigned)__popcll(m);
+        if (left >= 1u && left <= c) {  // (uniform) the q-th equal key is in this register: the lane of rank `left`
+            const unsigned long long hit =
+                __ballot(key[u] == tau && (unsigned)__popcll(m & ((1ull << lane) - 1ull)) + 1u == left);
+            cut = (unsigned)u * 64u + (unsigned)(__ffsll((long long)hit) - 1);
+            left = 0u;
+        } else if (left > c) {
+            left -= c;
+        }
+    }
+}
+
 // ---- host-side launchers (one per kernel family), all asynchronous on `s` ----
 struct ScanBufs {
     unsigned* block_sums;  // ceil(capacity / kScanChunk) + 1 entries
@@ -470,6 +531,24 @@ hipError_t launch_conv_split(const Geom& g, const unsigned long long* occ, const
                              const unsigned short* ws, int c_out, const float* bias,
                              const int* tap_active, const unsigned* cand_lin, const int* cand_start,
                              const int* tile_start, Counters* ctr, float* resp, int cus, hipStream_t s);
+
+// scnn_tiny.hip
+struct TinySample {  // what a sample's workgroup leaves behind
+    int rows;        // output rows
+    int cands;       // candidate sites
+    unsigned flags;  // SCNN_FLAG_*
+    unsigned unused;
+};
+// Layers that one workgroup a sample computes whole: can it, is it the faster way for so many input rows, and rows of a
+// sample's staging area.
+bool layer_tiny_shape(const Geom& g, int c_in, int c_out);
+bool layer_tiny_pays(const Geom& g, int c_in, int c_out, long long rows);
+long long layer_tiny_stage_rows(const Geom& g, const Geom& gp, int pool);
+hipError_t launch_layer_tiny(const Geom& g, const Geom& gp, const int32_t* coords, const float* feats, long long n_imm,
+                             const long long* n_dev, int c_in, const float* w, const float* bias, int c_out, long long k,
+                             int mode, int relu, int pool, long long cand_cap, unsigned* stage_lin, float* stage_feats,
+                             TinySample* info, int32_t* out_coords, float* out_feats, long long out_capacity,
+                             long long* nnz_out, hipStream_t s);
 
 // scnn_bwd.hip
 hipError_t launch_bwd_sites(const Geom& g, const int32_t* coords, long long rows, const int* cand_start,

@@ -47,15 +47,7 @@ __global__ __launch_bounds__(256) void k_rows_sample_bounds(Geom g, const int32_
         // the threads are faster again from some twenty samples on (32 samples of 128 k rows: call 51 against 55)
         const int lane = threadIdx.x & 63;
         for (int b = threadIdx.x >> 6; b <= g.batch; b += 4) {
-            long long lo = 0, hi = rows;
-            while (lo < hi) {
-                const long long step = (hi - lo + 63) / 64, at = lo + lane * step;
-                const unsigned long long below = __ballot(at < hi && coords[at * stride] < b);
-                const int n = ~below ? __builtin_ctzll(~below) : 64;  // probes before the first row that is not below
-                const long long top = lo + n * step;
-                if (top < hi) hi = top;
-                if (n > 0) lo += (n - 1) * step + 1;
-            }
+            const long long lo = wave_first_row(coords, stride, rows, b);
             if (lane == 0) cand_start[b] = (int)lo;
         }
     } else
@@ -1012,62 +1004,15 @@ __device__ __forceinline__ void select_tiny(int mode, const float* __restrict__ 
     const int lane = threadIdx.x & 63;
     // key u of the lane sits at position u * 64 + lane
     unsigned key[NU];
-    unsigned n_nz = 0;
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
         const unsigned i = (unsigned)u * 64u + (unsigned)lane;
         key[u] = i < n ? score_key(column[(size_t)(i >> 7) * pitch + (i & 127u)], mode) : 0u;
     }
-#pragma unroll
-    for (int u = 0; u < NU; ++u) n_nz += (unsigned)__popcll(__ballot(key[u] != 0u));
     ColState st;
-    st.tau = 0; st.cut = 0xffffffffu; st.n_eq = 0; st.q = 0; st.tau_lo = 0; st.tau_hi = 0; st.n_nz = n_nz;
-    st.n_above = 0; st.side_fill = 0; st.done = 1; st.side_off = 0;
-    if (k <= 0) st.tau = 0xffffffffu;  // no key is stronger: nothing survives
-    if (k <= 0 || (long long)n_nz <= k) {  // or fewer entries than k: all survive (tau = 0)
-        if (lane == 0) *out = st;
-        return;
-    }
-    // 1 <= k < n_nz: the k-th strongest key is non-zero
-    unsigned tau = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-        const unsigned at = tau | 1u << bit;
-        unsigned cnt = 0;
-#pragma unroll
-        for (int u = 0; u < NU; ++u) cnt += (unsigned)__popcll(__ballot(key[u] >= at));
-        if (cnt >= (unsigned)k) tau = at;
-    }
-    unsigned n_eq = 0, above = 0;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        n_eq += (unsigned)__popcll(__ballot(key[u] == tau));
-        above += (unsigned)__popcll(__ballot(key[u] > tau));
-    }
-    const unsigned q = (unsigned)k - above;  // 1 <= q <= n_eq: the entries equal to tau that survive, those of lowest position
-    unsigned cut = 0xffffffffu;
-    if (q < n_eq) {
-        unsigned left = q;
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const unsigned long long m = __ballot(key[u] == tau);
-            const unsigned c = (unsigned)__popcll(m);
-            if (left >= 1u && left <= c) {  // (uniform) the q-th equal key is in this register: the lane of rank `left`
-                const unsigned long long hit =
-                    __ballot(key[u] == tau && (unsigned)__popcll(m & ((1ull << lane) - 1ull)) + 1u == left);
-                cut = (unsigned)u * 64u + (unsigned)(__ffsll((long long)hit) - 1);
-                left = 0u;
-            } else if (left > c) {
-                left -= c;
-            }
-        }
-    }
-    if (lane == 0) {
-        st.tau = tau;
-        st.n_eq = n_eq;
-        st.q = q;
-        st.cut = cut;
-        *out = st;
-    }
+    st.n_eq = 0; st.q = 0; st.tau_lo = 0; st.tau_hi = 0; st.n_above = 0; st.side_fill = 0; st.done = 1; st.side_off = 0;
+    wave_threshold<NU>(key, k, st.n_nz, st.tau, st.cut);
+    if (lane == 0) *out = st;
 }
 
 template <int kTinyPerLane>
