@@ -644,7 +644,10 @@ __global__ __launch_bounds__(256) void k_conv_valu(Geom g, const unsigned long l
 // (v_mfma_f64_16x16x4_f64) and the four waves' partial sums are added through LDS in the order of the waves.
 // CH = 2: the two halves of a wave take the two 16-channel blocks, or, when there is only one, every other input
 // channel, with fp64 FMAs; the eight partial sums per output are added through LDS in a fixed order.
-template <int CH /* 8, 4 or 2 */>
+// NB = 1: items of one 16-channel block.  With eight channels a round's weights then take 32 KB of LDS instead of 64 (103 KB in
+// all let one workgroup run on a compute unit, 71 KB two) and half the loads: 16^3 x 4, 16 -> 16, 512 items, call 71 -> 59 us,
+// 8 -> 8 61 -> 53, 8^3 x 4, 24 -> 24 (two blocks, 160 items) 64 -> 56.
+template <int CH /* 8, 4 or 2 */, int NB /* 16-channel blocks of a work item: 2, or 1 where the layer has no more */>
 __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned long long* __restrict__ occ,
                                                          const unsigned* __restrict__ occ_prefix, long long nnz_in,
                                                          const float* __restrict__ feats, int c_in,
@@ -659,19 +662,20 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
     constexpr int Q = kTileRows / R;         // work items per tile and channel block
     constexpr int XS = kTapChunk * CH + 4;   // row stride of the gathered values
     constexpr int GB = (R * kTapChunk) / 256;                     // (row, tap) pairs a thread gathers per round
-    constexpr int WB = (2 * kTapChunk * CH * kOcBlock) / 256;     // weights a thread stages per round
+    constexpr int WB = (NB * kTapChunk * CH * kOcBlock) / 256;    // weights a thread stages per round
     __shared__ int s_nbr[R][kTapChunk + 1];
     __shared__ int s_site[R][3];
     __shared__ __align__(16) float s_x[R][XS];
     // the round's weights, per 16-channel block; after the last round the same memory holds the partial sums of
     // the eight (wave, half) pairs
-    constexpr int kWElems = 2 * kTapChunk * CH * kOcBlock, kRedElems = 8 * R * (kOcBlock + 1);
+    constexpr int kWElems = NB * kTapChunk * CH * kOcBlock;
+    constexpr int kRedElems = CH >= 4 ? 4 * R * (NB * kOcBlock + 1) : 8 * R * (kOcBlock + 1);
     __shared__ __align__(16) double s_wr[kWElems > kRedElems ? kWElems : kRedElems];
     double (*s_w)[kTapChunk * CH][kOcBlock] = reinterpret_cast<double (*)[kTapChunk * CH][kOcBlock]>(&s_wr[0]);
     double (*s_red)[R][kOcBlock + 1] = reinterpret_cast<double (*)[R][kOcBlock + 1]>(&s_wr[0]);
 
     const int n_tiles = (int)ctr->n_tiles;
-    const int n_chunks = (c_out_pad + 2 * kOcBlock - 1) / (2 * kOcBlock);
+    const int n_chunks = (c_out_pad + NB * kOcBlock - 1) / (NB * kOcBlock);
     const long long n_items = (long long)n_tiles * n_chunks * Q;
     const int row = threadIdx.x & (R - 1);
     const int sl = threadIdx.x >> 5;          // (wave, half of the wave)
@@ -689,7 +693,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
         if (nrows > R) nrows = R;
         if (nrows < 0) nrows = 0;
         // the chunk's second 16-channel block does not exist: the halves of a wave share the input channels
-        const bool split = chunk * 2 * kOcBlock + kOcBlock >= c_out_pad;
+        const bool split = NB == 1 || chunk * NB * kOcBlock + kOcBlock >= c_out_pad;
         const int hb = split ? 0 : lh;
 
         double acc[kOcBlock];
@@ -697,11 +701,11 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
         for (int o = 0; o < kOcBlock; ++o) acc[o] = 0.0;
         // matrix-core form (CH >= 4): [16-row group][16-channel block]; lane (m, kq) holds output channel m of rows
         // kq, 4 + kq, 8 + kq, 12 + kq (the fp64 instruction's result layout)
-        f64x4 macc[2][2];
+        f64x4 macc[2][NB];
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) macc[a][c] = f64x4{0.0, 0.0, 0.0, 0.0};
+            for (int c = 0; c < NB; ++c) macc[a][c] = f64x4{0.0, 0.0, 0.0, 0.0};
         const int mi = threadIdx.x & 15, kq = (threadIdx.x >> 4) & 3;
 
         __syncthreads();  // previous item's readers of the shared arrays are done
@@ -727,7 +731,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                         const int o = e & (kOcBlock - 1), tj = (e >> 4) % (kTapChunk * CH);
                         const int hbw = e / (kTapChunk * CH * kOcBlock);
                         const int tg = tj / CH, j = tj - tg * CH;
-                        const int oc = chunk * 2 * kOcBlock + hbw * kOcBlock + o;
+                        const int oc = chunk * NB * kOcBlock + hbw * kOcBlock + o;
                         const bool ok = tg < tmax && oc < c_out_pad;
                         const size_t at = ok ? ((size_t)(tc + tg) * c_in + ic0 + j) * c_out_pad + oc : 0;
                         const double v = wp[at];
@@ -814,11 +818,12 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                                 const double b0 = s_w[0][tj][mi];
                                 macc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, macc[0][0], 0, 0, 0);
                                 macc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, macc[1][0], 0, 0, 0);
-                                if (!split) {
-                                    const double b1 = s_w[1][tj][mi];
-                                    macc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, macc[0][1], 0, 0, 0);
-                                    macc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, macc[1][1], 0, 0, 0);
-                                }
+                                if constexpr (NB > 1)
+                                    if (!split) {
+                                        const double b1 = s_w[1][tj][mi];
+                                        macc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, macc[0][1], 0, 0, 0);
+                                        macc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, macc[1][1], 0, 0, 0);
+                                    }
                             }
                         }
                         continue;
@@ -870,12 +875,11 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
         __syncthreads();  // the last round's weights have been read
         if constexpr (CH >= 4) {
             // ---- the four waves' partial sums (one per tap slice), added in the order of the waves
-            double (*s_rm)[R][2 * kOcBlock + 1] = reinterpret_cast<double (*)[R][2 * kOcBlock + 1]>(&s_wr[0]);
-            static_assert(4 * R * (2 * kOcBlock + 1) <= kRedElems, "the partial sums fit");
+            double (*s_rm)[R][NB * kOcBlock + 1] = reinterpret_cast<double (*)[R][NB * kOcBlock + 1]>(&s_wr[0]);
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
+                for (int c = 0; c < NB; ++c)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) s_rm[wave][a * 16 + 4 * v + kq][c * kOcBlock + mi] = macc[a][c][v];
             __syncthreads();
@@ -884,7 +888,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
             for (int i = 0; i < 4; ++i) {
                 if (i >= per) break;
                 const int c = sl * per + i;  // channel within the chunk
-                const int oc = chunk * 2 * kOcBlock + c;
+                const int oc = chunk * NB * kOcBlock + c;
                 if (oc >= c_out) continue;
                 double sum = 0.0;
 #pragma unroll
@@ -906,7 +910,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                 if (i >= per) break;
                 const int c = sl * per + i;               // channel within the chunk
                 const int hbo = c >> 4, o = c & (kOcBlock - 1);
-                const int oc = chunk * 2 * kOcBlock + c;
+                const int oc = chunk * NB * kOcBlock + c;
                 if (oc >= c_out) continue;
                 double sum = 0.0;
                 if (split) {
@@ -982,10 +986,22 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
     const bool stream_only = tiles_cap * n_chunks > kValuStreamOnlyItems;
     const bool both = !stream_only && tiles_cap * n_chunks > kValuLatencyItems;
     if (tiles_cap * n_chunks <= kValuSmallItems && ch >= 2) {  // cannot hold more than a few hundred tiles
-        const int blocks = (int)(tiles_cap * n_chunks * (kTileRows / 32));
-#define SCNN_VALU_SMALL(CH_)                                                                                         \
-    hipLaunchKernelGGL(k_conv_valu_small<CH_>, dim3(blocks), dim3(256), 0, s, g, occ, occ_prefix, nnz_in, feats,     \
-                       c_in, wp, c_out, c_out_pad, bias, tap_active, cand_lin, cand_start, tile_start, ctr, resp)
+        // One 16-channel block per item where the layer has no more, or where that many workgroups still run at once (two to a
+        // compute unit): 40 x 40 x 4, 16 -> 24, 520 items, keeps two blocks
+        const long long items = tiles_cap * (c_out_pad / kOcBlock) * (kTileRows / 32);
+        const bool one_block = c_out_pad <= kOcBlock || items <= 2 * device_cu_count();
+        const int blocks = (int)(one_block ? items : tiles_cap * n_chunks * (kTileRows / 32));
+#define SCNN_VALU_SMALL(CH_)                                                                                            \
+    do {                                                                                                                \
+        if (one_block)                                                                                                  \
+            hipLaunchKernelGGL((k_conv_valu_small<CH_, 1>), dim3(blocks), dim3(256), 0, s, g, occ, occ_prefix, nnz_in,  \
+                               feats, c_in, wp, c_out, c_out_pad, bias, tap_active, cand_lin, cand_start, tile_start,   \
+                               ctr, resp);                                                                              \
+        else                                                                                                            \
+            hipLaunchKernelGGL((k_conv_valu_small<CH_, 2>), dim3(blocks), dim3(256), 0, s, g, occ, occ_prefix, nnz_in,  \
+                               feats, c_in, wp, c_out, c_out_pad, bias, tap_active, cand_lin, cand_start, tile_start,   \
+                               ctr, resp);                                                                              \
+    } while (0)
         if (ch == 8) SCNN_VALU_SMALL(8);
         else if (ch == 4) SCNN_VALU_SMALL(4);
         else SCNN_VALU_SMALL(2);
