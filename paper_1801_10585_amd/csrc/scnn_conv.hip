@@ -324,6 +324,182 @@ __global__ __launch_bounds__(256) void k_conv_valu_one(Geom g, const unsigned lo
     }
 }
 
+// Eight input channels on middling layers, where k_conv_valu_one's workgroups are one round of the chip and a call waits for
+// the richest site of 64 in each: here four lanes share a site (its lines' look-ups, then every fourth neighbour; their sums
+// added at the end), a wave takes sixteen sites at a time, and persistent workgroups, each XCD on a run of consecutive tiles,
+// put the weights into LDS once.  It issues a third more vector instructions (each lane knows its site), so larger layers keep
+// the other form.  Calls, 8 -> 8, 27 taps, against it: 32^3 x 4, sites in use from 0.03 occupied to all, 59 / 77 / 85 us ->
+// 57 / 74 / 82, on surfaces 67 -> 56; 40^3 x 4, 2 k tiles, 76 / 101 / 112 -> 74 / 100 / 111, surfaces 87 -> 76; 64^3 x 2
+// 95 / 134 / 413 -> 97 / 134 / 418, surfaces 110 -> 101; 64^3 x 4, 8 k tiles, 110 / 175 / 512 -> 116 / 185 / 522; with nine
+// taps (100 x 100 x 16) 46 / 60 / 63 -> 44 / 61 / 66.  The nine-layer 32^3 network 595 -> 568.
+constexpr long long kEightTiles = 3072;  // of capacity, at most
+constexpr int kEightPerCu = 3;           // workgroups that run at once (80 registers)
+constexpr int kEightThreads = 512;       // a tile: four lanes a site, sixteen sites a wave
+__device__ __forceinline__ unsigned quad_swap1(unsigned x) { return (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true); }
+__device__ __forceinline__ unsigned quad_swap2(unsigned x) { return (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true); }
+__device__ __forceinline__ double quad_swap1(double x) {
+    return __hiloint2double((int)quad_swap1((unsigned)__double2hiint(x)), (int)quad_swap1((unsigned)__double2loint(x)));
+}
+__device__ __forceinline__ double quad_swap2(double x) {
+    return __hiloint2double((int)quad_swap2((unsigned)__double2hiint(x)), (int)quad_swap2((unsigned)__double2loint(x)));
+}
+__global__ __launch_bounds__(kEightThreads, 6) void k_conv_valu_eight(Geom g, const unsigned long long* __restrict__ occ,
+                                                         const unsigned* __restrict__ occ_prefix, long long nnz_in,
+                                                         const float* __restrict__ feats, const double* __restrict__ wp,
+                                                         int c_out, int c_out_pad, const float* __restrict__ bias,
+                                                         const int* __restrict__ tap_active,
+                                                         const unsigned* __restrict__ cand_lin,
+                                                         const int* __restrict__ cand_start,
+                                                         const int* __restrict__ tile_start,
+                                                         const Counters* __restrict__ ctr, float* __restrict__ resp) {
+    constexpr int CI = 8, OCB = 8, NT = kEightThreads, U = 2;  // U: neighbours in flight
+    constexpr int WS = CI * OCB + 2;                           // (lanes at different taps read different banks)
+    __shared__ __align__(16) double s_w[32 * WS];
+    __shared__ unsigned s_row[NT / 64][kOneLines][16];  // row of the first occupied site on the site's window of each line
+    __shared__ unsigned char s_line[32], s_k[32];       // line of a tap and its place there
+    const int T = g.T, K1 = g.K[1], K2 = g.K[2], n_lines = g.K[0] * K1;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = tid & 3, q = (tid & 63) >> 2;
+    const int n_tiles = (int)ctr->n_tiles;
+    // XCD x (workgroups x, x + 8, ..) takes a run of consecutive tiles
+    const int per = (n_tiles + kXcds - 1) / kXcds, base = ((int)blockIdx.x % kXcds) * per;
+    const int first = base + (int)blockIdx.x / kXcds, last = min(base + per, n_tiles), step = (int)gridDim.x / kXcds;
+    if (first >= last) return;
+    const unsigned act = active_taps(tap_active, 0, T);
+    {
+        constexpr int NW = (32 * CI * OCB + NT - 1) / NT;
+        double weight[NW];  // (all of a thread's loads in flight together)
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int e = tid + i * NT;
+            weight[i] = e < T * CI * OCB ? wp[(size_t)(e / OCB) * c_out_pad + e % OCB] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int e = tid + i * NT;
+            if (e < T * CI * OCB) s_w[e / (CI * OCB) * WS + e % (CI * OCB)] = weight[i];
+        }
+    }
+    if (tid < T) {
+        s_line[tid] = (unsigned char)(tid / K2);
+        s_k[tid] = (unsigned char)(tid % K2);
+    }
+    __syncthreads();
+    const unsigned line_mask = K2 >= 32 ? ~0u : (1u << K2) - 1u;
+    for (int tile = first; tile < last; tile += step) {
+        const int b = sample_of_tile(tile_start, g.batch, tile), r = wave * 16 + q;
+        const int cand = cand_start[b] + (tile - tile_start[b]) * kTileRows + r;
+        const bool live = cand < cand_start[b + 1];
+        int c0 = 0, c1 = 0, c2 = 0;
+        if (live) site_of(g, cand_lin[cand], c0, c1, c2);
+        // ---- occupancy of the sites that the taps look at: bit t = tap t's (lookup_line, a lane every fourth line)
+        const int q2s = c2 - g.H[2];
+        int k_lo, k_hi;
+        taps_on_line(g.E[2], c2, -g.H[2], K2, k_lo, k_hi);
+        const unsigned w_last = (unsigned)g.batch * (unsigned)g.Wps - 1u;
+        const unsigned on_line = live && k_hi > k_lo ? (~0u >> (32 - (k_hi - k_lo))) << k_lo : 0u;
+        unsigned raw = 0;
+        {
+            constexpr int LB = (kOneLines + 3) / 4;
+            unsigned long long word_a[LB], word_b[LB];
+            unsigned pre_a[LB], pre_b[LB], p[LB];
+            bool ok[LB];
+#pragma unroll
+            for (int i = 0; i < LB; ++i) {
+                const int line = j + 4 * i;
+                const int t0 = line / K1, t1 = line - t0 * K1;
+                const int q0 = c0 + t0 - g.H[0], q1 = c1 + t1 - g.H[1];
+                ok[i] = line < n_lines && on_line != 0u && (unsigned)q0 < (unsigned)g.E[0] && (unsigned)q1 < (unsigned)g.E[1];
+                const unsigned bit = ok[i] ? (unsigned)((q0 * g.E[1] + q1) * g.E[2] + q2s + k_lo) : 0u;
+                p[i] = bit & 63u;
+                const unsigned w0 = (unsigned)b * (unsigned)g.Wps + (bit >> 6);
+                const unsigned wa = w0 < w_last ? w0 : w_last, wb = wa < w_last ? wa + 1u : wa;
+                word_a[i] = occ[wa];
+                word_b[i] = occ[wb];
+                pre_a[i] = occ_prefix[wa];
+                pre_b[i] = occ_prefix[wb];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // (the last tile's rows have been read)
+#pragma unroll
+            for (int i = 0; i < LB; ++i) {
+                const int line = j + 4 * i;
+                if (line >= n_lines) continue;
+                const unsigned window = (unsigned)(word_a[i] >> p[i]) | (unsigned)((word_b[i] << 1) << (63u - p[i]));
+                raw |= (ok[i] ? (window << k_lo) & on_line : 0u) << (line * K2);
+                s_row[wave][line][q] = word_a[i] ? pre_a[i] + (unsigned)__popcll(word_a[i] & ((1ull << p[i]) - 1ull)) : pre_b[i];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        raw |= quad_swap1(raw);
+        raw |= quad_swap2(raw);
+        // ---- the site's neighbours, every fourth to a lane, several in flight
+        double acc[OCB];
+#pragma unroll
+        for (int o = 0; o < OCB; ++o) acc[o] = 0.0;
+        unsigned m = raw & act;
+        auto drop = [&](bool yes) { m = yes ? m & (m - 1u) : m; };
+        drop(j > 0);
+        drop(j > 1);
+        drop(j > 2);
+        while (m != 0u) {
+            int t[U];
+            float x[U][CI];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                t[u] = -1;
+                if (m != 0u) {
+                    const int tap = __builtin_ctz(m), line = s_line[tap], kk = s_k[tap];
+                    const unsigned row = s_row[wave][line][q] + (unsigned)__popc((raw >> (tap - kk)) & line_mask & ((1u << kk) - 1u));
+                    drop(true); drop(true); drop(true); drop(true);
+                    if (row < (unsigned)nnz_in) {  // (only an unsorted input can trip this guard)
+                        t[u] = tap;
+                        const float4 a = *(const float4*)(feats + (size_t)row * CI), c = *(const float4*)(feats + (size_t)row * CI + 4);
+                        x[u][0] = a.x; x[u][1] = a.y; x[u][2] = a.z; x[u][3] = a.w;
+                        x[u][4] = c.x; x[u][5] = c.y; x[u][6] = c.z; x[u][7] = c.w;
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (t[u] >= 0) {
+                    const double2* wr = (const double2*)(s_w + t[u] * WS);
+#pragma unroll
+                    for (int ic = 0; ic < CI; ++ic) {
+                        const double xd = (double)x[u][ic];
+#pragma unroll
+                        for (int o = 0; o < OCB / 2; ++o) {
+                            const double2 w = wr[ic * (OCB / 2) + o];
+                            acc[2 * o] = fma(xd, w.x, acc[2 * o]);
+                            acc[2 * o + 1] = fma(xd, w.y, acc[2 * o + 1]);
+                        }
+                    }
+                }
+        }
+        // ---- the four lanes' sums: lane j ends with channels 4 (j & 1) + (j & 2) and the one after
+        double half[4], sum[2];
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            const double mine = (j & 1) ? acc[o + 4] : acc[o], other = (j & 1) ? acc[o] : acc[o + 4];
+            half[o] = mine + quad_swap1(other);
+        }
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const double mine = (j & 2) ? half[o + 2] : half[o], other = (j & 2) ? half[o] : half[o + 2];
+            sum[o] = mine + quad_swap2(other);
+        }
+        const int o0 = 4 * (j & 1) + (j & 2);
+        float* dst = resp + ((size_t)tile * c_out + o0) * kTileRows + r;
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+            if (o0 + o < c_out) {
+                float v = (float)sum[o];
+                if (bias && v != 0.0f) v += bias[o0 + o];
+                dst[(size_t)o * kTileRows] = v;
+            }
+    }
+}
+
 // Response tiles of a layer without input rows (candidate sites cannot exist either; kept for completeness).
 __global__ __launch_bounds__(256) void k_conv_valu_empty(int c_out, const Counters* __restrict__ ctr,
                                                          float* __restrict__ resp) {
@@ -965,6 +1141,11 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
             if (spread) SCNN_VALU_ONE(1, 8, 1); else SCNN_VALU_ONE(1, 8, 0);
         } else if (c_in == 1) {
             if (spread) SCNN_VALU_ONE(1, 16, 1); else SCNN_VALU_ONE(1, 16, 0);
+        } else if (!spread && g.T > 9 && tiles_cap <= kEightTiles) {
+            const long long most = (long long)device_cu_count() * kEightPerCu;
+            blocks = round_up(tiles_cap < most ? tiles_cap : most, kXcds);
+            hipLaunchKernelGGL(k_conv_valu_eight, dim3((unsigned)blocks), dim3(kEightThreads), 0, s, g, occ, occ_prefix, nnz_in,
+                               feats, wp, c_out, c_out_pad, bias, tap_active, cand_lin, cand_start, tile_start, ctr, resp);
         } else {
             if (spread) SCNN_VALU_ONE(8, 8, 1); else SCNN_VALU_ONE(8, 8, 0);
         }
