@@ -299,16 +299,39 @@ __device__ __forceinline__ void split_products(const u32x4 (&x)[3], const u32x4&
     add(small, x[0], w_m);
 }
 
+// Scans and reductions across a wave without the LDS pipe: shuffles are ds_bpermute, of about a hundred clocks a step, where a
+// lane shift inside a vector instruction takes eight; a 64-lane scan is six steps.  (whole waves)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned lane_shift(unsigned v) {  // (0 where the row mask or the row's end has no source)
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ unsigned wave_inclusive_add(unsigned v) {
+    v += lane_shift<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8: within rows of sixteen lanes
+    v += lane_shift<0x112, 0xf>(v);
+    v += lane_shift<0x114, 0xf>(v);
+    v += lane_shift<0x118, 0xf>(v);
+    v += lane_shift<0x142, 0xa>(v);  // row_bcast:15: the last lane of rows 0 and 2 to rows 1 and 3
+    v += lane_shift<0x143, 0xc>(v);  // row_bcast:31: the last lane of the lower half to the upper
+    return v;
+}
+__device__ __forceinline__ unsigned wave_add(unsigned v) { return (unsigned)__builtin_amdgcn_readlane((int)wave_inclusive_add(v), 63); }
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
+    auto larger = [](unsigned x, unsigned y) { return x > y ? x : y; };
+    v = larger(v, lane_shift<0x111, 0xf>(v));
+    v = larger(v, lane_shift<0x112, 0xf>(v));
+    v = larger(v, lane_shift<0x114, 0xf>(v));
+    v = larger(v, lane_shift<0x118, 0xf>(v));
+    v = larger(v, lane_shift<0x142, 0xa>(v));
+    v = larger(v, lane_shift<0x143, 0xc>(v));
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned wave_min(unsigned v) { return ~wave_max(~v); }
+
 // Exclusive scan across a 256-thread block; `total` receives the block sum.
 // Contains __syncthreads(): every thread of the block must call it.
 __device__ inline unsigned block_exclusive_scan_256(unsigned v, unsigned* s_wave /*[4], shared*/, unsigned& total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned inc = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        unsigned t = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += t;
-    }
+    const unsigned inc = wave_inclusive_add(v);
     if (lane == 63) s_wave[wave] = inc;
     __syncthreads();
     unsigned base = 0, tot = 0;

@@ -71,12 +71,7 @@ long long layer_tiny_stage_rows(const Geom& g, const Geom& gp, int pool) { retur
 __device__ __forceinline__ unsigned word_sums(const unsigned long long* words, int n, unsigned& total) {
     const int lane = threadIdx.x & 63;
     const unsigned own = lane < n ? (unsigned)__popcll(words[lane]) : 0u;
-    unsigned inc = own;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned t = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += t;
-    }
+    const unsigned inc = wave_inclusive_add(own);
     total = (unsigned)__builtin_amdgcn_readlane((int)inc, 63);
     return inc - own;
 }

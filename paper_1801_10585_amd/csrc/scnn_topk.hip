@@ -151,47 +151,30 @@ hipError_t launch_rows_to_planar(const Geom& g, const int32_t* coords, const flo
 // the top bin; else from the bottom bin.  Returns the bin and the number of entries strictly before it in that
 // order.  1 <= kk <= total must hold.  Contains two __syncthreads(); s_res is two shared words that the next call
 // must not share (callers alternate between two pairs): the result is read after the last barrier.
-__device__ inline void block_pick(const unsigned* s_h, long long kk, bool descending, unsigned* s_wave, int* s_res,
-                                  int& bin_out, unsigned& before_out) {
-    // Works for any block size that is a multiple of 64 and at least 256: the first 256 threads search, every
-    // thread passes the same barriers.
-    const bool active = threadIdx.x < 256;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned local = 0;  // thread t owns bins [8t, 8t+8)
-    if (active) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) local += s_h[threadIdx.x * 8 + i];
-    }
-    unsigned inc = local;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned t = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += t;
-    }
-    if (active && lane == 63) s_wave[wave] = inc;
+constexpr int kPickThreads = 1024, kPickWaves = kPickThreads / 64;  // a thread owns two bins
+__device__ inline void block_pick(const unsigned* s_h /* 8-byte aligned */, long long kk, bool descending,
+                                  unsigned* s_wave /* [kPickWaves], 16-byte aligned */, int* s_res, int& bin_out,
+                                  unsigned& before_out) {
+    static_assert(kHistBins == 2 * kPickThreads, "two bins a thread");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint2 c = ((const uint2*)s_h)[threadIdx.x];
+    const unsigned local = c.x + c.y, inc = wave_inclusive_add(local);
+    if (lane == 63) s_wave[wave] = inc;
     __syncthreads();
-    if (active) {
-        unsigned base = 0, total = 0;
+    unsigned base = 0, total = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const unsigned x = s_wave[w];
-            if (w < wave) base += x;
-            total += x;
-        }
-        const unsigned excl = base + inc - local;
-        const unsigned before_threads = descending ? total - excl - local : excl;
-        if ((long long)before_threads < kk && kk <= (long long)before_threads + (long long)local) {
-            unsigned before = before_threads;
-            int bin = descending ? threadIdx.x * 8 + 7 : threadIdx.x * 8;
-            for (int i = 0; i < 7; ++i) {
-                const unsigned c = s_h[bin];
-                if (kk <= (long long)before + (long long)c) break;
-                before += c;
-                bin += descending ? -1 : 1;
-            }
-            s_res[0] = bin;
-            s_res[1] = (int)before;
-        }
+    for (int w = 0; w < kPickWaves; ++w) {
+        const unsigned x = s_wave[w];
+        base += w < wave ? x : 0u;
+        total += x;
+    }
+    const unsigned excl = base + inc - local;
+    const unsigned before = descending ? total - excl - local : excl;
+    if ((long long)before < kk && kk <= (long long)before + (long long)local) {
+        const unsigned first = descending ? c.y : c.x;
+        const bool second = kk > (long long)before + (long long)first;
+        s_res[0] = 2 * (int)threadIdx.x + (descending != second ? 1 : 0);
+        s_res[1] = (int)(before + (second ? first : 0u));
     }
     __syncthreads();
     bin_out = s_res[0];
@@ -216,8 +199,8 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
                                                              const int* __restrict__ tile_start,
                                                              const float* __restrict__ resp, long long k,
                                                              ColState* __restrict__ cols) {
-    __shared__ unsigned s_h[kHistBins], s_h2[kHistBins];
-    __shared__ unsigned s_wave[4];
+    __shared__ __align__(16) unsigned s_h[kHistBins], s_h2[kHistBins];
+    __shared__ __align__(16) unsigned s_wave[kPickWaves];
     __shared__ int s_res[4];
     __shared__ unsigned s_total;
     __shared__ unsigned s_range[2];
@@ -263,14 +246,11 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
             kmax = key[u] > kmax ? key[u] : kmax;
         }
     }
+    for (int i = threadIdx.x; i < kHistBins; i += kBracketThreads) s_h[i] = 0;
     __syncthreads();  // (s_total and the range words are set up)
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        mine += __shfl_xor(mine, d, 64);
-        const unsigned a = __shfl_xor(kmin, d, 64), c = __shfl_xor(kmax, d, 64);
-        kmin = a < kmin ? a : kmin;
-        kmax = c > kmax ? c : kmax;
-    }
+    mine = wave_add(mine);
+    kmin = wave_min(kmin);
+    kmax = wave_max(kmax);
     if ((threadIdx.x & 63) == 0 && mine) {
         atomicAdd(&s_total, mine);
         atomicMin(&s_range[0], kmin);
@@ -297,8 +277,6 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
     const int sh1 = nb > 11 ? nb - 11 : 0;       // first digit: bits [sh1, nb)
     const int sh2 = sh1 > 11 ? sh1 - 11 : 0;     // second digit: bits [sh2, sh1)
     const unsigned mask2 = (1u << (sh1 - sh2)) - 1u;
-    for (int i = threadIdx.x; i < kHistBins; i += kBracketThreads) s_h[i] = 0;
-    __syncthreads();
 #pragma unroll
     for (int u = 0; u < kBracketPerThread; ++u)
         if (key[u] != 0u) atomicAdd(&s_h[(key[u] - kmin) >> sh1], 1u);
@@ -650,8 +628,8 @@ void k_settle(int mode, int relu, int channels, long long k,
                                                          const uint2* __restrict__ part, int slices,
                                                          unsigned long long* row_keep,
                                                          long long* __restrict__ tile_base, Counters* ctr) {
-    __shared__ unsigned s_h[kHistBins];
-    __shared__ unsigned s_wave[4];
+    __shared__ __align__(16) unsigned s_h[kHistBins];
+    __shared__ __align__(16) unsigned s_wave[kPickWaves];
     __shared__ int s_res[4];
     __shared__ uint2 s_part[4];
     constexpr unsigned kSettleRegs = kSettleRegsOf<kSettleCached>;
@@ -666,12 +644,7 @@ void k_settle(int mode, int relu, int channels, long long k,
     uint2 my_part = make_uint2(0u, 0u);
     if ((int)threadIdx.x < slices) my_part = part[(size_t)col * slices + threadIdx.x];
     if (!st.done) {
-        unsigned sum_nz = my_part.x, sum_above = my_part.y;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            sum_nz += __shfl_xor(sum_nz, d, 64);
-            sum_above += __shfl_xor(sum_above, d, 64);
-        }
+        const unsigned sum_nz = wave_add(my_part.x), sum_above = wave_add(my_part.y);
         if (threadIdx.x < 256 && (threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = make_uint2(sum_nz, sum_above);
         __syncthreads();
         st.n_nz = s_part[0].x + s_part[1].x + s_part[2].x + s_part[3].x;
@@ -893,53 +866,74 @@ void k_settle(int mode, int relu, int channels, long long k,
 }
 
 // The whole selection of a column in one workgroup, for columns that fit its registers (grids of at most 32768
-// sites per sample: the paper's networks from the second resolution level on).  The same digit passes as above,
-// 11 + 11 + 10 key bits and, when the equal entries do not all fit, 11 + 4 position bits, over keys read once;
-// no global histogram, no side buffer and one launch instead of three (what such a layer costs is launches).
+// sites per sample: the paper's networks from the second resolution level on), over keys read once; no global histogram, no
+// side buffer and one launch instead of three (what such a layer costs is launches).  The digits, 11 bits at most, are taken
+// from the distance to the smallest key, most significant first, until the bin of the k-th key holds at most 64 entries (columns of 4096
+// positions: nearly always the first digit) or all of its entries survive; a wave then ranks these by key and position.  Runs
+// of more equal keys end in a radix select on the position.  Bound by its barriers and the latency of the steps between them.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallPerThread = 32;
 constexpr long long kSmallColumn = (long long)kSmallThreads * kSmallPerThread;  // entries of a column at most
+constexpr int kSmallFew = 64;
 
+template <int NU /* keys per thread: columns of at most 1024 NU positions */>
 __global__ __launch_bounds__(kSmallThreads) void k_select_small(int mode, int channels,
                                                                 const int* __restrict__ tile_start,
                                                                 const float* __restrict__ resp, long long k,
                                                                 ColState* __restrict__ cols) {
-    __shared__ unsigned s_h[kHistBins];
-    __shared__ unsigned s_wave[4];
+    __shared__ __align__(16) unsigned s_h[kHistBins];
+    __shared__ __align__(16) unsigned s_wave[kPickWaves];
     __shared__ int s_res[4];
-    __shared__ unsigned s_total;
+    __shared__ unsigned s_total, s_range[2], s_fill;
+    __shared__ uint2 s_few[kSmallFew];
     const int col = blockIdx.x;
     const int b = col / channels, oc = col - b * channels;
     const int t0 = tile_start[b], t1 = tile_start[b + 1];
-    const unsigned n = (unsigned)(t1 - t0) * kTileRows;  // positions of the column (<= kSmallColumn, see the launcher)
-    if (threadIdx.x == 0) s_total = 0;
+    const unsigned n = (unsigned)(t1 - t0) * kTileRows;  // positions of the column (<= 1024 NU, see the launcher)
+    if (threadIdx.x == 0) {
+        s_total = s_fill = 0u;
+        s_range[0] = 0xffffffffu;
+        s_range[1] = 0u;
+    }
+    auto clear = [&]() {
+        for (int i = threadIdx.x; i < kHistBins; i += kSmallThreads) s_h[i] = 0;
+    };
+    clear();
     // entry u of the thread sits at position u * 1024 + thread: a wave reads 64 consecutive rows of one tile
-    unsigned key[kSmallPerThread];
-    unsigned mine = 0;
+    unsigned key[NU];
+    unsigned mine = 0, kmin = 0xffffffffu, kmax = 0u;
+    {
+        const float* first = resp + ((size_t)(t0 + (int)(threadIdx.x >> 7)) * channels + oc) * kTileRows + (threadIdx.x & 127u);
+        const size_t pitch = (size_t)(kSmallThreads / kTileRows) * channels * kTileRows;  // from a thread's entry to its next
+        constexpr int G = NU < 8 ? NU : 8;                                                // loads in flight together
 #pragma unroll
-    for (int u = 0; u < kSmallPerThread; ++u) {
-        const unsigned i = (unsigned)u * kSmallThreads + threadIdx.x;
-        key[u] = 0u;
-        if (i < n)
-            key[u] = score_key(resp[((size_t)(t0 + (int)(i >> 7)) * channels + oc) * kTileRows + (i & 127u)], mode);
-        mine += key[u] != 0u ? 1u : 0u;
+        for (int u0 = 0; u0 < NU; u0 += G) {
+            float x[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const bool has = (unsigned)(u0 + u) * kSmallThreads + threadIdx.x < n;
+                x[u] = has ? first[(size_t)(u0 + u) * pitch] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const unsigned v = score_key(x[u], mode);
+                key[u0 + u] = v;
+                mine += v != 0u ? 1u : 0u;
+                kmin = v != 0u && v < kmin ? v : kmin;
+                kmax = v > kmax ? v : kmax;
+            }
+        }
     }
     __syncthreads();
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d, 64);
-    if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&s_total, mine);
-    // histogram of digit(key, position) over the entries that pass(key, position)
-    auto histogram = [&](auto pass, auto digit) {
-        for (int i = threadIdx.x; i < kHistBins; i += kSmallThreads) s_h[i] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kSmallPerThread; ++u) {
-            const unsigned i = (unsigned)u * kSmallThreads + threadIdx.x;
-            if (key[u] != 0u && pass(key[u], i)) atomicAdd(&s_h[digit(key[u], i)], 1u);
-        }
-        __syncthreads();
-    };
-    histogram([](unsigned, unsigned) { return true; }, [](unsigned x, unsigned) { return x >> 21; });
+    mine = wave_add(mine);
+    kmin = wave_min(kmin);
+    kmax = wave_max(kmax);
+    if ((threadIdx.x & 63) == 0 && mine) {
+        atomicAdd(&s_total, mine);
+        atomicMin(&s_range[0], kmin);
+        atomicMax(&s_range[1], kmax);
+    }
+    __syncthreads();
     ColState st;
     st.tau = 0; st.cut = 0xffffffffu; st.n_eq = 0; st.q = 0; st.tau_lo = 0; st.tau_hi = 0; st.n_nz = s_total;
     st.n_above = 0; st.side_fill = 0; st.done = 1; st.side_off = 0;
@@ -948,39 +942,92 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(int mode, int ch
         if (threadIdx.x == 0) cols[col] = st;
         return;
     }
-    int bin;
-    unsigned before;
-    block_pick(s_h, k, true, s_wave, s_res, bin, before);  // key bits [31:21]
-    const unsigned prefix1 = (unsigned)bin;
-    long long k_rem = k - (long long)before;
-    histogram([prefix1](unsigned x, unsigned) { return (x >> 21) == prefix1; },
-              [](unsigned x, unsigned) { return (x >> 10) & 0x7ffu; });
-    block_pick(s_h, k_rem, true, s_wave, s_res + 2, bin, before);  // key bits [20:10]
-    const unsigned prefix2 = (prefix1 << 11) | (unsigned)bin;
-    k_rem -= (long long)before;
-    histogram([prefix2](unsigned x, unsigned) { return (x >> 10) == prefix2; },
-              [](unsigned x, unsigned) { return x & 0x3ffu; });
-    block_pick(s_h, k_rem, true, s_wave, s_res, bin, before);  // key bits [9:0]
-    const unsigned tau = (prefix2 << 10) | (unsigned)bin;
-    const unsigned n_eq = s_h[bin];
-    const unsigned q = (unsigned)(k_rem - (long long)before);  // 1 <= q <= n_eq
-    __syncthreads();
-    unsigned cut = 0xffffffffu;
-    if (q < n_eq) {  // q-th smallest position among the entries equal to tau (positions have 15 bits)
-        histogram([tau](unsigned x, unsigned) { return x == tau; }, [](unsigned, unsigned i) { return i >> 4; });
-        block_pick(s_h, (long long)q, false, s_wave, s_res + 2, bin, before);
-        const unsigned phi = (unsigned)bin;
-        const long long rank = (long long)q - (long long)before;
-        histogram([tau, phi](unsigned x, unsigned i) { return x == tau && (i >> 4) == phi; },
-                  [](unsigned, unsigned i) { return i & 15u; });
-        block_pick(s_h, rank, false, s_wave, s_res, bin, before);
-        cut = (phi << 4) | (unsigned)bin;
+    // keys from here on: key - smallest + 1, still 0 where there is no entry
+    const unsigned base = s_range[0] - 1u, span = s_range[1] - base;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) key[u] = key[u] != 0u ? key[u] - base : 0u;
+    int open = 32 - __clz(span);  // low bits still open
+    unsigned prefix = 0, in_bin = 0, before = 0;  // the bits above them
+    long long k_rem = k;
+    int bin = 0, picks = 0;
+    // of the entries that pass(key, position), histogram of digit(key, position); s_h is clear
+    auto histogram = [&](auto pass, auto digit) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const unsigned i = (unsigned)u * kSmallThreads + threadIdx.x;
+            if (key[u] != 0u && pass(key[u], i)) atomicAdd(&s_h[digit(key[u], i)], 1u);
+        }
+        __syncthreads();
+    };
+    auto pick = [&](bool descending) {
+        block_pick(s_h, k_rem, descending, s_wave, s_res + 2 * (picks++ & 1), bin, before);
+        k_rem -= (long long)before;
+    };
+    auto fresh = [&]() {  // (the last histogram has been read)
+        __syncthreads();
+        clear();
+        __syncthreads();
+    };
+    {
+        const int w = open < 11 ? open : 11;
+        open -= w;
+        histogram([](unsigned, unsigned) { return true; }, [=](unsigned x, unsigned) { return x >> open; });
+        pick(true);
+        in_bin = s_h[bin];
+        prefix = (unsigned)bin;
     }
+#pragma unroll 1
+    while (open > 0 && in_bin > (unsigned)kSmallFew && (long long)in_bin != k_rem) {  // (uniform)
+        const int w = open < 11 ? open : 11, shift = open - w, above = open;
+        fresh();
+        histogram([=](unsigned x, unsigned) { return (x >> above) == prefix; },
+                  [=](unsigned x, unsigned) { return (x >> shift) & ((1u << w) - 1u); });
+        pick(true);
+        in_bin = s_h[bin];
+        prefix = (prefix << w) | (unsigned)bin;
+        open = shift;
+    }
+    if ((long long)in_bin == k_rem) {  // all of the bin survive
+        if (threadIdx.x == 0) {
+            const unsigned least = prefix << open;
+            st.tau = base + (least ? least : 1u);
+            cols[col] = st;
+        }
+        return;
+    }
+    if (in_bin <= (unsigned)kSmallFew) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            if (key[u] != 0u && key[u] >> open == prefix)
+                s_few[atomicAdd(&s_fill, 1u)] = make_uint2(key[u], (unsigned)u * kSmallThreads + threadIdx.x);
+        __syncthreads();
+        if (threadIdx.x >= in_bin) return;
+        const uint2 own = s_few[threadIdx.x];
+        int rank = 0;  // entries that go before it: stronger, or as strong at a lower position
+        for (int i = 0; i < (int)in_bin; ++i) {
+            const uint2 o = s_few[i];
+            rank += o.x > own.x || (o.x == own.x && o.y < own.y) ? 1 : 0;
+        }
+        if (rank == (int)k_rem - 1) {
+            st.tau = base + own.x;
+            st.cut = own.y;
+            cols[col] = st;
+        }
+        return;
+    }
+    // a run of equal keys (no bit is open): the position of the k_rem-th (positions have 15 bits)
+    const unsigned tau = prefix;
+    fresh();
+    histogram([tau](unsigned x, unsigned) { return x == tau; }, [](unsigned, unsigned i) { return i >> 4; });
+    pick(false);
+    const unsigned phi = (unsigned)bin;
+    fresh();
+    histogram([tau, phi](unsigned x, unsigned i) { return x == tau && (i >> 4) == phi; },
+              [](unsigned, unsigned i) { return i & 15u; });
+    pick(false);
     if (threadIdx.x == 0) {
-        st.tau = tau;
-        st.n_eq = n_eq;
-        st.q = q;
-        st.cut = cut;
+        st.tau = base + tau;
+        st.cut = (phi << 4) | (unsigned)bin;
         cols[col] = st;
     }
 }
@@ -1082,8 +1129,13 @@ hipError_t launch_topk(const Geom& g, int channels, long long k, int mode, int r
         return hipGetLastError();
     }
     if (topk_small_columns(g)) {
-        hipLaunchKernelGGL(k_select_small, dim3(ncols), dim3(kSmallThreads), 0, s, mode, channels, tile_start, resp, k,
-                           cols);
+        const long long n = column_positions(g);
+#define SCNN_SELECT_SMALL(NU)                                                                                              \
+    hipLaunchKernelGGL(k_select_small<NU>, dim3(ncols), dim3(kSmallThreads), 0, s, mode, channels, tile_start, resp, k, cols)
+        if (n <= 4 * kSmallThreads) SCNN_SELECT_SMALL(4);
+        else if (n <= 16 * kSmallThreads) SCNN_SELECT_SMALL(16);
+        else SCNN_SELECT_SMALL(kSmallPerThread);
+#undef SCNN_SELECT_SMALL
         return hipGetLastError();
     }
     const int groups = g.batch * ((channels + kClassifyWaves - 1) / kClassifyWaves);
