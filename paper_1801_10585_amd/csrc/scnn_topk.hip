@@ -152,9 +152,10 @@ hipError_t launch_rows_to_planar(const Geom& g, const int32_t* coords, const flo
 // order.  1 <= kk <= total must hold.  Contains two __syncthreads(); s_res is two shared words that the next call
 // must not share (callers alternate between two pairs): the result is read after the last barrier.
 constexpr int kPickThreads = 1024, kPickWaves = kPickThreads / 64;  // a thread owns two bins
-__device__ inline void block_pick(const unsigned* s_h /* 8-byte aligned */, long long kk, bool descending,
-                                  unsigned* s_wave /* [kPickWaves], 16-byte aligned */, int* s_res, int& bin_out,
-                                  unsigned& before_out) {
+template <int RANKS /* searched for together: s_res is two words for each */>
+__device__ inline void block_pick(const unsigned* s_h /* 8-byte aligned */, const long long (&ranks)[RANKS], bool descending,
+                                  unsigned* s_wave /* [kPickWaves], 16-byte aligned */, int* s_res, int (&bin_out)[RANKS],
+                                  unsigned (&before_out)[RANKS]) {
     static_assert(kHistBins == 2 * kPickThreads, "two bins a thread");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint2 c = ((const uint2*)s_h)[threadIdx.x];
@@ -170,15 +171,31 @@ __device__ inline void block_pick(const unsigned* s_h /* 8-byte aligned */, long
     }
     const unsigned excl = base + inc - local;
     const unsigned before = descending ? total - excl - local : excl;
-    if ((long long)before < kk && kk <= (long long)before + (long long)local) {
-        const unsigned first = descending ? c.y : c.x;
-        const bool second = kk > (long long)before + (long long)first;
-        s_res[0] = 2 * (int)threadIdx.x + (descending != second ? 1 : 0);
-        s_res[1] = (int)(before + (second ? first : 0u));
+#pragma unroll
+    for (int i = 0; i < RANKS; ++i) {
+        const long long kk = ranks[i];
+        if ((long long)before < kk && kk <= (long long)before + (long long)local) {
+            const unsigned first = descending ? c.y : c.x;
+            const bool second = kk > (long long)before + (long long)first;
+            s_res[2 * i] = 2 * (int)threadIdx.x + (descending != second ? 1 : 0);
+            s_res[2 * i + 1] = (int)(before + (second ? first : 0u));
+        }
     }
     __syncthreads();
-    bin_out = s_res[0];
-    before_out = (unsigned)s_res[1];
+#pragma unroll
+    for (int i = 0; i < RANKS; ++i) {
+        bin_out[i] = s_res[2 * i];
+        before_out[i] = (unsigned)s_res[2 * i + 1];
+    }
+}
+__device__ inline void block_pick(const unsigned* s_h, long long kk, bool descending, unsigned* s_wave, int* s_res, int& bin_out,
+                                  unsigned& before_out) {
+    const long long ranks[1] = {kk};
+    int bin[1];
+    unsigned before[1];
+    block_pick<1>(s_h, ranks, descending, s_wave, s_res, bin, before);
+    bin_out = bin[0];
+    before_out = before[0];
 }
 
 // First launch: a bracket [tau_lo, tau_hi] around the k-th strongest key of every column, from a sample of the
@@ -192,6 +209,7 @@ __device__ inline void block_pick(const unsigned* s_h /* 8-byte aligned */, long
 // the third one checks that the k-th entry fell inside, and settles the column from the response matrix itself when
 // it did not.
 constexpr int kBracketThreads = 1024;
+constexpr int kBracketBin = 32;  // entries of a bin that the bracket ends within, at most
 constexpr int kBracketPerThread = 16;
 constexpr int kBracketTiles = kBracketThreads * kBracketPerThread / kTileRows;  // 128
 
@@ -271,7 +289,7 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
     // sample's entries on the strong side nothing is above the bracket; past them on the weak side every entry is in
     // it or above it.
     const bool want_up = r_up >= 1.0 && (long long)r_up <= nz, want_dn = r_dn >= 1.0 && r_dn <= (double)nz;  // (uniform)
-    long long rank_up = want_up ? (long long)r_up : 1, rank_dn = want_dn ? (long long)r_dn : 1;
+    const long long rank_up = want_up ? (long long)r_up : 1, rank_dn = want_dn ? (long long)r_dn : 1;
     const unsigned span = nz > 0 ? kmax - kmin : 0u;
     const int nb = span ? 32 - __clz(span) : 1;  // bits of key - kmin
     const int sh1 = nb > 11 ? nb - 11 : 0;       // first digit: bits [sh1, nb)
@@ -281,16 +299,17 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
     for (int u = 0; u < kBracketPerThread; ++u)
         if (key[u] != 0u) atomicAdd(&s_h[(key[u] - kmin) >> sh1], 1u);
     __syncthreads();
-    int bin_up = 0, bin_dn = 0;
-    unsigned before = 0;
-    if (nz > 0) {
-        block_pick(s_h, rank_up, true, s_wave, s_res, bin_up, before);
-        rank_up -= (long long)before;
-        block_pick(s_h, rank_dn, true, s_wave, s_res + 2, bin_dn, before);
-        rank_dn -= (long long)before;
-    }
-    int sub_up = 0, sub_dn = 0;
-    if (sh1 > 0) {  // (uniform)
+    int bin[2] = {0, 0}, sub[2] = {0, 0};  // of the upper end and of the lower
+    unsigned before[2] = {0, 0};
+    long long rank[2] = {rank_up, rank_dn};
+    int sh = sh1;  // bits that the digits taken leave open
+    if (nz > 0) block_pick<2>(s_h, rank, true, s_wave, s_res, bin, before);
+    // a second digit where an end's bin holds more than a few entries (below a quarter of a percent of a whole sample the
+    // bracket may as well end at the bin's ends)
+    if (sh1 > 0 && (s_h[bin[0]] > (unsigned)kBracketBin || s_h[bin[1]] > (unsigned)kBracketBin)) {  // (uniform)
+        rank[0] -= (long long)before[0];
+        rank[1] -= (long long)before[1];
+        __syncthreads();  // (the bins' counts have been read)
         for (int i = threadIdx.x; i < kHistBins; i += kBracketThreads) {
             s_h[i] = 0;
             s_h2[i] = 0;
@@ -300,21 +319,20 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
         for (int u = 0; u < kBracketPerThread; ++u) {
             if (key[u] == 0u) continue;
             const unsigned d = key[u] - kmin;
-            if ((int)(d >> sh1) == bin_up) atomicAdd(&s_h[(d >> sh2) & mask2], 1u);
-            if ((int)(d >> sh1) == bin_dn) atomicAdd(&s_h2[(d >> sh2) & mask2], 1u);
+            if ((int)(d >> sh1) == bin[0]) atomicAdd(&s_h[(d >> sh2) & mask2], 1u);
+            if ((int)(d >> sh1) == bin[1]) atomicAdd(&s_h2[(d >> sh2) & mask2], 1u);
         }
         __syncthreads();
-        if (nz > 0) {
-            block_pick(s_h, rank_up, true, s_wave, s_res, sub_up, before);
-            block_pick(s_h2, rank_dn, true, s_wave, s_res + 2, sub_dn, before);
-        }
+        block_pick(s_h, rank[0], true, s_wave, s_res, sub[0], before[0]);
+        block_pick(s_h2, rank[1], true, s_wave, s_res + 2, sub[1], before[1]);
+        sh = sh2;
     }
     st.tau_hi = 0xffffffffu;  // rank < 1: nothing is above
-    if (r_up >= 1.0)  // (the upper end of the two-digit bin)
+    if (r_up >= 1.0)  // (the upper end of the bin)
         st.tau_hi =
-            want_up ? clamp_add(kmin, ((unsigned)bin_up << sh1) | ((unsigned)sub_up << sh2) | ((1u << sh2) - 1u)) : 0u;
+            want_up ? clamp_add(kmin, ((unsigned)bin[0] << sh1) | ((unsigned)sub[0] << sh2) | ((1u << sh) - 1u)) : 0u;
     if (want_dn) {
-        const unsigned lo = kmin + (((unsigned)bin_dn << sh1) | ((unsigned)sub_dn << sh2));
+        const unsigned lo = kmin + (((unsigned)bin[1] << sh1) | ((unsigned)sub[1] << sh2));
         st.tau_lo = lo ? lo : 1u;
     }
     if (threadIdx.x == 0) cols[col] = st;
@@ -513,10 +531,10 @@ struct ColumnEntries {  // slot i of a column of the response matrix (key 0: not
     }
 };
 
-// tau = the kk-th strongest key among m entries {key, position} whose keys lie in [key_lo, key_hi] (key 0: not an
-// entry); n_eq entries equal it, the q of lowest position survive: those at positions <= cut.  1 <= kk <= number of
-// entries.  The digits of the radix select, 11 bits at most, are taken from key - key_lo, most significant first, so
-// that a narrow bracket is settled in two passes.  Between the passes up to kSettleCached entries per thread are held
+// The kk strongest of m entries {key, position} whose keys lie in [key_lo, key_hi] (key 0: not an entry), of equal keys those
+// of lowest position, are the ones above tau and the ones equal to tau at positions <= cut.  1 <= kk <= number of
+// entries.  The digits of the radix select, 11 bits at most, are taken from key - key_lo, most significant first, until at
+// most 64 entries share them (a bracket of some ten thousand: the first) or all that share them survive.  Between the passes up to kSettleCached entries per thread are held
 // in registers and kSettleLds more per workgroup in LDS (brackets that hold long runs of equal scores run to 30 000
 // entries on the paper's first layers).  (whole workgroup)
 // Two sizes: 20 per thread + 12288 (one workgroup per compute unit: its registers and LDS), the rule; 4 per thread +
@@ -525,11 +543,17 @@ template <int kSettleCached> constexpr unsigned kSettleRegsOf = (unsigned)kSettl
 
 // held: the entries threadIdx.x + 1024 * u of the column, more: the entries from kSettleRegs on, if cached
 // (m <= kSettleRegs + kSettleLds); both loaded by the caller.
+constexpr int kSettleFew = 64;
+struct SettleFew {  // (LDS)
+    uint2 entry[kSettleFew], found;
+    unsigned fill;
+};
+
 template <int kSettleCached, class Entries>
-__device__ inline void settle_column(const Entries& entry, unsigned m, const uint2 (&held)[kSettleCached],
+__device__ __forceinline__ void settle_column(const Entries& entry, unsigned m, const uint2 (&held)[kSettleCached],
                                      const uint2* more, bool cached, unsigned key_lo, unsigned key_hi, long long kk,
-                                     unsigned* s_h, unsigned* s_wave, int* s_res, unsigned& tau, unsigned& n_eq,
-                                     unsigned& q, unsigned& cut) {
+                                     unsigned* s_h, unsigned* s_wave, int* s_res, SettleFew& few, unsigned& tau,
+                                     unsigned& cut) {
     constexpr unsigned kSettleRegs = kSettleRegsOf<kSettleCached>;
     auto clear = [&]() {
         for (int i = threadIdx.x; i < kHistBins; i += kSideThreads) s_h[i] = 0;
@@ -582,44 +606,88 @@ __device__ inline void settle_column(const Entries& entry, unsigned m, const uin
         }
         __syncthreads();
     };
+    // f(entry) for all of them
+    auto each = [&](auto f) {
+        if (cached) {
+#pragma unroll
+            for (int u = 0; u < kSettleCached; ++u) f(held[u]);
+            if (m > kSettleRegs)
+                for (unsigned j = threadIdx.x; j < m - kSettleRegs; j += kSideThreads) f(more[j]);
+        } else {
+            for (unsigned i0 = threadIdx.x; i0 < m; i0 += kSideThreads * 8) {
+                uint2 x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const unsigned i = i0 + (unsigned)kSideThreads * u;
+                    x[u] = i < m ? entry(i) : make_uint2(0u, 0u);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) f(x[u]);
+            }
+        }
+    };
     int bin = 0, picks = 0;
-    unsigned before = 0;
+    unsigned before = 0, in_bin = 0;
     const unsigned span = key_hi - key_lo;
     int nb = span ? 32 - __clz(span) : 1;  // bits of key - key_lo still open
     unsigned prefix = 0;                   // the bits above them
-    while (nb > 0) {
+    if (threadIdx.x == 0) few.fill = 0u;   // (the histogram's barriers lie between)
+    do {  // (uniform)
         const int w = nb < 11 ? nb : 11, shift = nb - w;
         const int above = nb;  // (captured by value)
+        if (picks > 0) __syncthreads();  // (the last histogram has been read)
         histogram([=](uint2 x) { return (unsigned)((unsigned long long)(x.x - key_lo) >> above) == prefix; },
                   [=](uint2 x) { return ((x.x - key_lo) >> shift) & ((1u << w) - 1u); });
         block_pick(s_h, kk, true, s_wave, s_res + 2 * (picks++ & 1), bin, before);
         kk -= (long long)before;
+        in_bin = s_h[bin];
         prefix = (prefix << w) | (unsigned)bin;
         nb = shift;
-    }
-    tau = key_lo + prefix;
-    n_eq = s_h[bin];
-    q = (unsigned)kk;  // 1 <= q <= n_eq
-    __syncthreads();
+    } while (nb > 0 && in_bin > (unsigned)kSettleFew && (long long)in_bin != kk);
+    tau = key_lo + (prefix << nb);  // the least of the bin's keys
     cut = 0xffffffffu;
-    if (q < n_eq) {
-        // q-th smallest position among the entries equal to tau: ascending radix select on the position
-        const unsigned t = tau;
-        unsigned pprefix = 0;
-        long long rank = q;
-        for (int pass = 0; pass < 3; ++pass) {
-            const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0), bits = pass == 2 ? 10 : 11;
-            histogram([=](uint2 x) { return x.x == t && (pass == 0 || (x.y >> (shift + bits)) == pprefix); },
-                      [=](uint2 x) { return (x.y >> shift) & ((1u << bits) - 1u); });
-            block_pick(s_h, rank, false, s_wave, s_res + 2 * (picks++ & 1), bin, before);
-            pprefix = (pprefix << bits) | (unsigned)bin;
-            rank -= (long long)before;
-        }
-        cut = pprefix;
+    if ((long long)in_bin == kk) {  // all of the bin survive
+        __syncthreads();
+        return;
     }
+    if (in_bin <= (unsigned)kSettleFew) {
+        // few share these bits: a wave ranks them by key and position
+        const int low = nb;
+        each([&](uint2 x) {
+            if (x.x != 0u && (x.x - key_lo) >> low == prefix) few.entry[atomicAdd(&few.fill, 1u)] = x;
+        });
+        __syncthreads();
+        if (threadIdx.x < in_bin) {
+            const uint2 own = few.entry[threadIdx.x];
+            int rank = 0;  // entries that go before it: stronger, or as strong at a lower position
+            for (int i = 0; i < (int)in_bin; ++i) {
+                const uint2 o = few.entry[i];
+                rank += o.x > own.x || (o.x == own.x && o.y < own.y) ? 1 : 0;
+            }
+            if (rank == (int)kk - 1) few.found = own;
+        }
+        __syncthreads();
+        tau = few.found.x;
+        cut = few.found.y;
+        return;
+    }
+    // a run of equal keys (no bit is open), not all of which fit: ascending radix select on the position
+    const unsigned t = tau;
+    unsigned pprefix = 0;
+    long long rank = kk;
+    for (int pass = 0; pass < 3; ++pass) {
+        const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0), bits = pass == 2 ? 10 : 11;
+        __syncthreads();
+        histogram([=](uint2 x) { return x.x == t && (pass == 0 || (x.y >> (shift + bits)) == pprefix); },
+                  [=](uint2 x) { return (x.y >> shift) & ((1u << bits) - 1u); });
+        block_pick(s_h, rank, false, s_wave, s_res + 2 * (picks++ & 1), bin, before);
+        pprefix = (pprefix << bits) | (unsigned)bin;
+        rank -= (long long)before;
+    }
+    cut = pprefix;
 }
 
-template <int kSettleCached, unsigned kSettleLds>
+template <int kSettleCached, unsigned kSettleLds, bool MARKS /* row_keep and tile_base given */>
 __global__ __launch_bounds__(kSideThreads) __attribute__((amdgpu_waves_per_eu(kSettleCached > 8 ? 4 : 8)))
 void k_settle(int mode, int relu, int channels, long long k,
                                                          const int* __restrict__ tile_start,
@@ -635,6 +703,7 @@ void k_settle(int mode, int relu, int channels, long long k,
     constexpr unsigned kSettleRegs = kSettleRegsOf<kSettleCached>;
     __shared__ uint2 s_more[kSettleLds];
     __shared__ unsigned s_cnt;
+    __shared__ SettleFew s_few;
     const int col = blockIdx.x;
     const int b = col / channels, oc = col - b * channels;
     const int t0 = tile_start[b], t1 = tile_start[b + 1];
@@ -698,16 +767,18 @@ void k_settle(int mode, int relu, int channels, long long k,
                 for (int i = threadIdx.x; i < kHistBins; i += kSideThreads) s_h[i] = 0;
                 if (threadIdx.x == 0) s_cnt = 0;
                 __syncthreads();
-                for (unsigned i0 = threadIdx.x; i0 < m; i0 += kSideThreads * 8) {  // eight entries in flight per thread
-                    uint2 x[8];
+                for (unsigned i0 = threadIdx.x; i0 < m; i0 += kSideThreads * 16) {  // sixteen values in flight per thread
+                    unsigned x[16];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
+                    for (int u = 0; u < 16; ++u) {
                         const unsigned i = i0 + (unsigned)kSideThreads * u;
-                        x[u] = i < m ? e(i) : make_uint2(0u, 0u);
+                        x[u] = i < m ? e.e[i].x : 0u;
                     }
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (x[u].x != 0u) atomicAdd(&s_h[digit(x[u])], 1u);
+                    for (int u = 0; u < 16; ++u) {
+                        const unsigned key = score_key(__uint_as_float(x[u]), mode);
+                        if (key != 0u) atomicAdd(&s_h[digit(make_uint2(key, 0u))], 1u);
+                    }
                 }
                 __syncthreads();
                 int bin;
@@ -716,55 +787,61 @@ void k_settle(int mode, int relu, int channels, long long k,
                 const unsigned in_bin = s_h[bin];
                 __syncthreads();  // (every thread has read the count before the histogram is cleared again)
                 if (in_bin <= kSettleLds) {  // (uniform)
-                    for (unsigned i0 = threadIdx.x; i0 < m; i0 += kSideThreads * 8) {
-                        uint2 x[8];
-                        unsigned long long have[8];
+                    constexpr int F = MARKS ? 8 : 16;  // entries in flight per thread
+                    for (unsigned i0 = threadIdx.x; i0 < m; i0 += kSideThreads * F) {
+                        uint2 x[F];
+                        unsigned long long have[MARKS ? F : 1];
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) {
+                        for (int u = 0; u < F; ++u) {
                             const unsigned i = i0 + (unsigned)kSideThreads * u;
                             x[u] = i < m ? e(i) : make_uint2(0u, 0u);
                         }
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) {
+                        for (int u = 0; u < (MARKS ? F : 0); ++u) {
                             have[u] = ~0ull;
-                            if (row_keep && x[u].x != 0u && (int)digit(x[u]) > bin)
+                            if (x[u].x != 0u && (int)digit(x[u]) > bin)
                                 have[u] = __hip_atomic_load(word_of(x[u]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         }
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) {
+                        for (int u = 0; u < F; ++u) {
                             if (x[u].x == 0u) continue;
                             const int d = (int)digit(x[u]);
                             if (d == bin) s_more[atomicAdd(&s_cnt, 1u)] = x[u];
-                            else if (row_keep && d > bin) mark(x[u], have[u]);
+                            else if (MARKS && d > bin) mark(x[u], have[MARKS ? u : 0]);
                         }
                     }
+                    uint2 none[kSettleCached];
 #pragma unroll
-                    for (int u = 0; u < kSettleCached; ++u) kept[u] = make_uint2(0u, 0u);
+                    for (int u = 0; u < kSettleCached; ++u) none[u] = make_uint2(0u, 0u);
+                    if constexpr (MARKS) {
+#pragma unroll
+                        for (int u = 0; u < kSettleCached; ++u) kept[u] = none[u];
+                    }
                     __syncthreads();
                     const unsigned long long lo2 = (unsigned long long)lo + ((unsigned long long)(unsigned)bin << shift);
                     unsigned long long hi2 = lo2 + ((1ull << shift) - 1ull);
                     if (hi2 > st.tau_hi) hi2 = st.tau_hi;
                     m_eff = kSettleRegs + in_bin;  // (the first kSettleRegs entries are the empty registers)
                     cached_eff = true;
-                    settle_column<kSettleCached>(e, m_eff, kept, s_more, true, (unsigned)lo2, (unsigned)hi2, k_rem - (long long)before, s_h,
-                                  s_wave, s_res, st.tau, st.n_eq, st.q, st.cut);
+                    settle_column<kSettleCached>(e, m_eff, none, s_more, true, (unsigned)lo2, (unsigned)hi2, k_rem - (long long)before, s_h,
+                                  s_wave, s_res, s_few, st.tau, st.cut);
                     settled = true;
                 }
             }
             if (settled) {
             } else if (held)
-                settle_column<kSettleCached>(e, m, kept, s_more, cached, st.tau_lo, st.tau_hi, k_rem, s_h, s_wave, s_res, st.tau, st.n_eq,
-                              st.q, st.cut);
+                settle_column<kSettleCached>(e, m, kept, s_more, cached, st.tau_lo, st.tau_hi, k_rem, s_h, s_wave, s_res, s_few, st.tau,
+                              st.cut);
             else
                 settle_column<kSettleCached>(ColumnEntries{col0, pitch, mode}, (unsigned)(t1 - t0) * kTileRows, kept, s_more, false, 0u,
-                              0xffffffffu, k, s_h, s_wave, s_res, st.tau, st.n_eq, st.q, st.cut);
+                              0xffffffffu, k, s_h, s_wave, s_res, s_few, st.tau, st.cut);
         }
         if (threadIdx.x == 0) {
             st.done = 1;
             cols[col] = st;
             if (!held) atomicOr(&ctr->bracket_failed, 1u);  // the rows marked so far cannot be relied on
         }
-        if (row_keep && held) {
+        if (MARKS && held) {
             // the bracket's entries that survive keep their rows too
             auto survives = [&](uint2 x) { return x.x > st.tau || (x.x == st.tau && x.x != 0u && x.y <= st.cut); };
             if (cached_eff) {
@@ -806,7 +883,7 @@ void k_settle(int mode, int relu, int channels, long long k,
             }
         }
     }
-    if (!tile_base) return;
+    if constexpr (!MARKS) return;
     // The workgroup that ends last turns the marked rows into the output row at which every tile starts.  The marks
     // are only ever touched by device-scope atomics, which are performed at the point of coherence; the barrier waits
     // for this workgroup's to be acknowledged, so no cache write-back (a fence, tens of microseconds here) is needed
@@ -1161,13 +1238,18 @@ hipError_t launch_topk(const Geom& g, int channels, long long k, int mode, int r
         hipLaunchKernelGGL(k_combine_marks, dim3((unsigned)cb), dim3(64), 0, s, channels, row_plane, 2 * tiles_cap, ctr,
                            row_keep);
     }
-    if (ncols > 256)  // (more columns than compute units: two light workgroups per unit)
-        hipLaunchKernelGGL((k_settle<4, 2048u>), dim3(ncols), dim3(kSideThreads), 0, s, mode, relu, channels, k, tile_start,
-                           resp, cols, side, part, slices, marks ? row_keep : nullptr, marks ? tile_base : nullptr, ctr);
-    else
-        hipLaunchKernelGGL((k_settle<20, 12288u>), dim3(ncols), dim3(kSideThreads), 0, s, mode, relu, channels, k,
-                           tile_start, resp, cols, side, part, slices, marks ? row_keep : nullptr,
-                           marks ? tile_base : nullptr, ctr);
+#define SCNN_SETTLE(CACHED, LDS, MARKS_)                                                                               \
+    hipLaunchKernelGGL((k_settle<CACHED, LDS, MARKS_>), dim3(ncols), dim3(kSideThreads), 0, s, mode, relu, channels, k,  \
+                       tile_start, resp, cols, side, part, slices, marks ? row_keep : nullptr,                           \
+                       marks ? tile_base : nullptr, ctr)
+    if (ncols > 256) {  // (more columns than compute units: two light workgroups per unit)
+        if (marks) SCNN_SETTLE(4, 2048u, true);
+        else SCNN_SETTLE(4, 2048u, false);
+    } else {
+        if (marks) SCNN_SETTLE(20, 12288u, true);
+        else SCNN_SETTLE(20, 12288u, false);
+    }
+#undef SCNN_SETTLE
     return hipGetLastError();
 }
 
