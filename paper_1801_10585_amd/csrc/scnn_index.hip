@@ -592,6 +592,56 @@ __global__ __launch_bounds__(256) void k_cand_dilate(Geom g, const unsigned long
     }
 }
 
+// Small grids of short lines: a wave takes a word, a lane each of its sites.  A word of an 8^3 grid holds eight lines, which
+// the form above walks one after the other (8^3 x 4: 10.5 us); here a site looks at its own lines, several lines' loads in
+// flight, and the ballot is the word.
+constexpr int kDilateBatch = 5;  // lines in flight
+constexpr long long kDilateSiteWords = 4096;
+__global__ __launch_bounds__(256) void k_cand_dilate_sites(Geom g, const unsigned long long* __restrict__ occ,
+                                                           const int* __restrict__ tap_active,
+                                                           unsigned long long* __restrict__ cand,
+                                                           unsigned* __restrict__ cand_count) {
+    const int n_words = g.batch * g.Wps, lane = threadIdx.x & 63, n_lines = g.K[0] * g.K[1];
+    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (w >= n_words) return;  // (whole waves)
+    const int b = w / g.Wps, first = b * g.Wps;
+    const unsigned site = (unsigned)(w - first) * 64u + (unsigned)lane;
+    const bool real = (long long)site < g.N;
+    int c0 = 0, c1 = 0, c2 = 0, k_lo, k_hi;
+    if (real) site_of(g, site, c0, c1, c2);
+    taps_on_line(g.E[2], c2, -g.H[2], g.K[2], k_lo, k_hi);
+    const unsigned on_line = real && k_hi > k_lo ? (~0u >> (32 - (k_hi - k_lo))) << k_lo : 0u;
+    unsigned any = 0;
+    for (int l0 = 0; l0 < n_lines; l0 += kDilateBatch) {
+        unsigned long long word_a[kDilateBatch], word_b[kDilateBatch];
+        unsigned p[kDilateBatch], act[kDilateBatch];
+        bool ok[kDilateBatch];
+#pragma unroll
+        for (int i = 0; i < kDilateBatch; ++i) {
+            const int l = l0 + i < n_lines ? l0 + i : n_lines - 1;  // (a line taken twice gives the same)
+            const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
+            const int q0 = c0 + t0 - g.H[0], q1 = c1 + t1 - g.H[1];
+            ok[i] = on_line != 0u && (unsigned)q0 < (unsigned)g.E[0] && (unsigned)q1 < (unsigned)g.E[1];
+            const unsigned bit = ok[i] ? (unsigned)((q0 * g.E[1] + q1) * g.E[2] + c2 - g.H[2] + k_lo) : 0u;
+            p[i] = bit & 63u;
+            const int wa = (int)(bit >> 6), wb = wa + 1 < g.Wps ? wa + 1 : wa;  // (a line ends inside its sample)
+            word_a[i] = occ[first + wa];
+            word_b[i] = occ[first + wb];
+            act[i] = active_taps(tap_active, l * g.K[2], g.K[2]);
+        }
+#pragma unroll
+        for (int i = 0; i < kDilateBatch; ++i) {
+            const unsigned window = (unsigned)(word_a[i] >> p[i]) | (unsigned)((word_b[i] << 1) << (63u - p[i]));
+            any |= ok[i] ? (window << k_lo) & on_line & act[i] : 0u;
+        }
+    }
+    const unsigned long long out = __ballot(any != 0u);
+    if (lane == 0) {
+        cand[w] = out;
+        cand_count[w] = (unsigned)__popcll(out);
+    }
+}
+
 // The same for bitmaps of up to kEmitMidWords words: a workgroup takes chunks of 256 / LANES consecutive words and also
 // leaves each chunk's candidate count, from which k_cand_emit_mid finds its place in the candidate list without a
 // scan launch in between.
@@ -640,6 +690,11 @@ hipError_t launch_cand_dilate(const Geom& g, const unsigned long long* occ, cons
         else
             hipLaunchKernelGGL(k_cand_dilate_chunks<1>, dim3((unsigned)blocks), dim3(256), 0, s, g, occ, tap_active,
                                cand, cand_count, chunk_sums);
+        return hipGetLastError();
+    }
+    if (n_words <= kDilateSiteWords && g.E[2] < 64 && g.K[2] <= 32) {
+        hipLaunchKernelGGL(k_cand_dilate_sites, dim3((unsigned)((n_words + 3) / 4)), dim3(256), 0, s, g, occ, tap_active, cand,
+                           cand_count);
         return hipGetLastError();
     }
     long long blocks = (n_words * lanes + 255) / 256;
@@ -712,8 +767,31 @@ __global__ __launch_bounds__(256) void k_cand_emit(Geom g, const unsigned long l
     }
 }
 
+// Writes the site indices of the set bits of the wave's `count` words (lane j < count holds word j: its bits, the place of its
+// first site in the list, and the site of its bit 0; 0 in the lanes past them).  A word at a time, 64 lanes to one run of the
+// list; or, where all words hold few bits (scattered sites: 256^3, 13.7 -> 9.7 us), a lane to its own word's bits, which
+// writes to as many places of the list at a time.  (whole wave)
+__device__ __forceinline__ void emit_words(unsigned long long bits, unsigned o, unsigned base, int count,
+                                           unsigned* __restrict__ cand_lin, long long cand_cap) {
+    const int lane = threadIdx.x & 63;
+    if (wave_max((unsigned)__popcll(bits)) < (unsigned)__popcll(__ballot(bits != 0ull))) {  // (uniform) fewer steps
+        for (; bits; bits &= bits - 1ull, ++o)
+            if ((long long)o < cand_cap) cand_lin[o] = base + (unsigned)__builtin_ctzll(bits);
+        return;
+    }
+    for (int j = 0; j < count; ++j) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)bits, j);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(bits >> 32), j);
+        if ((lo | hi) == 0u) continue;  // (uniform)
+        const unsigned place = (unsigned)__builtin_amdgcn_readlane((int)o, j), site = (unsigned)__builtin_amdgcn_readlane((int)base, j);
+        const unsigned at = place + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+        const bool set = ((lane < 32 ? lo : hi) >> (lane & 31)) & 1u;
+        if (set && (long long)at < cand_cap) cand_lin[at] = site + (unsigned)lane;
+    }
+}
+
 // The same for short bitmaps (at most kEmitSmallWords words), without a scan launch before it: a block sums the counts
-// of the words before its own (a few thousand numbers out of L2) and scans its 256 words itself; the last block scans
+// of the words before its own (a few thousand numbers out of L2) and scans its 64 words itself; the last block scans
 // the whole array once to find the per-sample ranges.  `cand_count` holds the words' candidate counts, unscanned.
 __global__ __launch_bounds__(256) void k_cand_emit_small(Geom g, const unsigned long long* __restrict__ cand,
                                                          const unsigned* __restrict__ cand_count, int n_words,
@@ -757,7 +835,8 @@ __global__ __launch_bounds__(256) void k_cand_emit_small(Geom g, const unsigned 
         }
         return;
     }
-    const int w0 = blockIdx.x * 256;
+    // 64 words: every wave takes sixteen of them, and finds out by itself what lies before
+    const int w0 = blockIdx.x * 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned below = 0;
     for (int i0 = threadIdx.x; i0 < w0; i0 += 256 * 8) {  // eight loads in flight per thread
         unsigned x[8];
@@ -766,19 +845,18 @@ __global__ __launch_bounds__(256) void k_cand_emit_small(Geom g, const unsigned 
 #pragma unroll
         for (int u = 0; u < 8; ++u) below += x[u];
     }
-    unsigned before_block;
-    (void)block_exclusive_scan_256(below, s_wave, before_block);  // (the total is what is wanted)
-    const int w = w0 + threadIdx.x;
-    unsigned long long bits = w < n_words ? cand[w] : 0ull;
-    unsigned block_total;
-    long long o = (long long)before_block + block_exclusive_scan_256((unsigned)__popcll(bits), s_wave, block_total);
-    const unsigned base = w < n_words ? (unsigned)((w % g.Wps) * 64) : 0u;
-    while (bits) {
-        const int bit = __ffsll((long long)bits) - 1;
-        bits &= bits - 1;
-        if (o < cand_cap) cand_lin[o] = base + (unsigned)bit;
-        ++o;
-    }
+    const int w = w0 + lane;
+    const unsigned long long bits = w < n_words ? cand[w] : 0ull;
+    below = wave_add(below);
+    if (lane == 0) s_wave[wave] = below;
+    __syncthreads();
+    const unsigned own = (unsigned)__popcll(bits);
+    const unsigned o = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3] + wave_inclusive_add(own) - own;
+    const unsigned base = w < n_words ? (unsigned)((w % (int)g.Wps) * 64) : 0u;
+    // (lane j of the wave: word 16 wave + j)
+    const int src = (wave * 16 + lane) & 63;
+    const unsigned long long mine = __shfl(bits, src, 64);
+    emit_words(lane < 16 ? mine : 0ull, __shfl(o, src, 64), __shfl(base, src, 64), 16, cand_lin, cand_cap);
 }
 
 // The same for bitmaps of up to kEmitMidWords words, after k_cand_dilate_chunks: a block owns 256 words, adds up the
@@ -855,16 +933,10 @@ __global__ __launch_bounds__(256) void k_cand_emit_mid(Geom g, const unsigned lo
     unsigned before_block;
     (void)block_exclusive_scan_256(below, s_wave, before_block);  // (the total is what is wanted)
     const long long w = (long long)c * 256 + threadIdx.x;
-    unsigned long long bits = w < n_words ? cand[w] : 0ull;
+    const unsigned long long bits = w < n_words ? cand[w] : 0ull;
     unsigned block_total;
-    long long o = (long long)before_block + block_exclusive_scan_256((unsigned)__popcll(bits), s_wave, block_total);
-    const unsigned base = w < n_words ? (unsigned)((w % g.Wps) * 64) : 0u;
-    while (bits) {
-        const int bit = __ffsll((long long)bits) - 1;
-        bits &= bits - 1;
-        if (o < cand_cap) cand_lin[o] = base + (unsigned)bit;
-        ++o;
-    }
+    const unsigned o = before_block + block_exclusive_scan_256((unsigned)__popcll(bits), s_wave, block_total);
+    emit_words(bits, o, w < n_words ? (unsigned)((w % g.Wps) * 64) : 0u, 64, cand_lin, cand_cap);
 }
 
 hipError_t launch_cand_emit_mid(const Geom& g, const unsigned long long* cand, const unsigned* cand_count,
@@ -891,7 +963,7 @@ hipError_t launch_cand_emit(const Geom& g, const unsigned long long* cand, const
 hipError_t launch_cand_emit_small(const Geom& g, const unsigned long long* cand, const unsigned* cand_count,
                                   long long n_words, unsigned* cand_lin, long long cand_cap, int* cand_start,
                                   int* tile_start, int* rows16_start, Counters* ctr, hipStream_t s) {
-    const unsigned blocks = (unsigned)((n_words + 255) / 256);
+    const unsigned blocks = (unsigned)((n_words + 63) / 64);
     hipLaunchKernelGGL(k_cand_emit_small, dim3(blocks + 1), dim3(256), 0, s, g, cand, cand_count, (int)n_words,
                        cand_lin, cand_cap, cand_start, tile_start, rows16_start, ctr);
     return hipGetLastError();

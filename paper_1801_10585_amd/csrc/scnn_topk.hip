@@ -209,7 +209,7 @@ __device__ inline void block_pick(const unsigned* s_h, long long kk, bool descen
 // the third one checks that the k-th entry fell inside, and settles the column from the response matrix itself when
 // it did not.
 constexpr int kBracketThreads = 1024;
-constexpr int kBracketBin = 32;  // entries of a bin that the bracket ends within, at most
+constexpr int kBracketBin = 16;
 constexpr int kBracketPerThread = 16;
 constexpr int kBracketTiles = kBracketThreads * kBracketPerThread / kTileRows;  // 128
 
@@ -245,15 +245,24 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
         s_range[0] = 0xffffffffu;
         s_range[1] = 0u;
     }
+    // entry u of the thread is row threadIdx.x % 128 of sampled tile 8 u + threadIdx.x / 128, the same in all of a wave; past
+    // the sample the last tile is read again and dropped, so that all loads are in flight together
     unsigned key[kBracketPerThread];
     unsigned mine = 0;
+    {
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        float x[kBracketPerThread];
 #pragma unroll
-    for (int u = 0; u < kBracketPerThread; ++u) {
-        const unsigned i = (unsigned)u * kBracketThreads + threadIdx.x;
-        key[u] = 0u;
-        if (i < m_s)
-            key[u] = score_key(resp[((size_t)(t0 + (int)(i >> 7) * S) * channels + oc) * kTileRows + (i & 127u)], mode);
-        mine += key[u] != 0u ? 1u : 0u;
+        for (int u = 0; u < kBracketPerThread; ++u) {
+            const int at = u * (kBracketThreads / kTileRows) + (wave >> 1);
+            const float* tile = resp + ((size_t)(t0 + (at < ns_tiles ? at : ns_tiles - 1) * S) * channels + oc) * kTileRows;
+            x[u] = tile[threadIdx.x & (kTileRows - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < kBracketPerThread; ++u) {
+            key[u] = u * (kBracketThreads / kTileRows) + (wave >> 1) < ns_tiles ? score_key(x[u], mode) : 0u;
+            mine += key[u] != 0u ? 1u : 0u;
+        }
     }
     // the sample's entries, and the range of their keys
     unsigned kmin = 0xffffffffu, kmax = 0u;
@@ -304,9 +313,9 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
     long long rank[2] = {rank_up, rank_dn};
     int sh = sh1;  // bits that the digits taken leave open
     if (nz > 0) block_pick<2>(s_h, rank, true, s_wave, s_res, bin, before);
-    // a second digit where an end's bin holds more than a few entries (below a quarter of a percent of a whole sample the
-    // bracket may as well end at the bin's ends)
-    if (sh1 > 0 && (s_h[bin[0]] > (unsigned)kBracketBin || s_h[bin[1]] > (unsigned)kBracketBin)) {  // (uniform)
+    // a second digit where an end's bin holds more entries than widen the bracket by an eighth (it is 2.9 us of this kernel)
+    const unsigned few = (unsigned)kBracketBin + (unsigned)(delta * 0.25);
+    if (sh1 > 0 && (s_h[bin[0]] > few || s_h[bin[1]] > few)) {  // (uniform)
         rank[0] -= (long long)before[0];
         rank[1] -= (long long)before[1];
         __syncthreads();  // (the bins' counts have been read)
