@@ -513,12 +513,12 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
     if (!pool) {
         SCNN_TRY(launch_select_write(g, c_out, topk_mode, relu, ws.cand_start, ws.tile_start, ws.cand_lin, ws.resp,
                                      ws.cols, ws.tile_state, ws.tiles_cap, ws.ctr, out_coords, out_feats,
-                                     out_capacity, (long long*)nnz_out, 0, 1, ws.row_keep, marks ? ws.tile_base : nullptr, s));
+                                     out_capacity, (long long*)nnz_out, 0, 1, ws.row_keep, marks ? ws.tile_base : nullptr, all ? 1 : 0, s));
         timer.mark();
     } else {
         SCNN_TRY(launch_select_write(g, c_out, topk_mode, relu, ws.cand_start, ws.tile_start, ws.cand_lin, ws.resp,
                                      ws.cols, ws.tile_state, ws.tiles_cap, ws.ctr, ws.tmp_coords, ws.tmp_feats,
-                                     ws.cand_cap, nullptr, 0, 0, ws.row_keep, marks ? ws.tile_base : nullptr, s));
+                                     ws.cand_cap, nullptr, 0, 0, ws.row_keep, marks ? ws.tile_base : nullptr, all ? 1 : 0, s));
         timer.mark();
         SCNN_TRY(launch_maxpool(g, gp, ws.tmp_coords, ws.tmp_feats, 0, &ws.ctr->n_rows, ws.cand_cap, c_out, 1,
                                 ws.occ_sel, ws.occ_prefix, ws.pbits, ws.pprefix, ws.block_sums, ws.pool_key,
@@ -850,7 +850,7 @@ int attention_topk(int ndim, const int32_t* extent, int batch, const int32_t* co
                          ws.tiles_cap, ws.ctr, s));
     SCNN_TRY(launch_select_write(g, channels, topk_mode, 0, ws.cand_start, ws.tile_start, ws.cand_lin, ws.resp,
                                  ws.cols, ws.tile_state, ws.tiles_cap, ws.ctr, out_coords, out_feats, out_capacity,
-                                 (long long*)nnz_out, rows, 0, ws.row_keep, marks ? ws.tile_base : nullptr, s));
+                                 (long long*)nnz_out, rows, 0, ws.row_keep, marks ? ws.tile_base : nullptr, 0, s));
     return SCNN_OK;
 }
 

@@ -630,7 +630,7 @@ hipError_t launch_select_write(const Geom& g, int channels, int mode, int relu, 
                                long long* nnz_out /* nullable: also write the result counters */, long long aux_imm,
                                int aux_is_cand, unsigned long long* row_keep /* two words per tile */,
                                const long long* tile_base /* nullable: from launch_topk */,
-                               hipStream_t s);
+                               int keeps_all /* every entry survives the selection */, hipStream_t s);
 
 // scnn_rows.hip
 hipError_t launch_relu(const Geom& g, const int32_t* coords, const float* feats, long long rows, int channels,

@@ -1506,6 +1506,8 @@ __global__ __launch_bounds__(256) void k_select_write(Geom g, int channels, int 
 // selection): tiles are dealt out by workgroup index, nothing is published or looked back at, and no tile waits for
 // another.  The selection can find, late, that its marks are not to be relied on (ctr->bracket_failed): the kernel
 // then works by look-back although it was given tile_base (the choice is uniform over the launch).
+// RANGED: a workgroup owns consecutive tiles, and the rows of those before them are counted (k_select_count64).
+template <bool RANGED>
 __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels, int mode, int relu,
                                                         const int* __restrict__ cand_start,
                                                         const int* __restrict__ tile_start,
@@ -1516,8 +1518,9 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
                                                         int32_t* __restrict__ out_coords,
                                                         float* __restrict__ out_feats, long long out_capacity,
                                                         long long* __restrict__ nnz_out, long long aux_imm,
-                                                        int aux_is_cand, const long long* __restrict__ tile_base) {
-    const bool STREAM = tile_base != nullptr && ctr->bracket_failed == 0u;
+                                                        int aux_is_cand, const long long* __restrict__ tile_base,
+                                                        const unsigned* __restrict__ counts) {
+    const bool STREAM = !RANGED && tile_base != nullptr && ctr->bracket_failed == 0u;
     __shared__ uint4 s_thr[64];  // per channel: {threshold if the position passes the cut, threshold if not, cut, -}
     __shared__ unsigned long long s_mask[3][2];
     __shared__ int s_rank[kTileRows];  // output row of a kept row of the tile being written, relative; -1 = dropped
@@ -1530,6 +1533,7 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
     // address take 7 us for it where they end together (53 x 75 x 94 x 3, 64 channels: 27.3 -> 21.0 us; on the largest
     // layers, 128^3 x 4: 77 either way).
     auto finish = [&]() {
+        if (RANGED) return;  // (written by the workgroup of the last tiles)
         if (!STREAM)
             finish_if_last(ctr, nnz_out, aux_imm, aux_is_cand, out_capacity, gridDim.x);
         else if (blockIdx.x == 0 && threadIdx.x == 0)
@@ -1653,8 +1657,30 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
     // (thread 0) the next tile of this workgroup; a launch with a workgroup per tile asks once
     const bool once = (long long)gridDim.x >= n_tiles;
     bool asked = false;
-    int dealt = (int)blockIdx.x;  // (STREAM) the next tile of this workgroup
+    int dealt = (int)blockIdx.x;  // (STREAM, RANGED) the next tile of this workgroup
+    // (RANGED) consecutive tiles, the rows before them known from the counts of the launch before
+    int last_own = 0;
+    unsigned run = 0;  // (the first wave) the next tile's first output row (31 bits: at most as many as candidates)
+    if constexpr (RANGED) {
+        const int per = (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x, first_own = (int)blockIdx.x * per;
+        last_own = first_own + per < n_tiles ? first_own + per : n_tiles;
+        if (first_own >= last_own && blockIdx.x != 0) return;
+        dealt = first_own;
+        __shared__ unsigned s_sum[4];
+        unsigned before = 0;
+        for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) before += counts[i];
+        before = wave_add(before);
+        if (lane == 0) s_sum[wave] = before;
+        __syncthreads();
+        run = (s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]);
+        if (last_own == n_tiles && threadIdx.x == 0) {
+            const long long rows = (long long)run + (first_own < last_own ? counts[blockIdx.x] : 0u);
+            ctr->n_rows = rows;
+            write_counters(ctr, rows, nnz_out, aux_imm, aux_is_cand, out_capacity);
+        }
+    }
     auto next_tile = [&]() -> int {
+        if (RANGED) return dealt < last_own ? dealt++ : n_tiles;
         if (STREAM) {
             const int t = dealt < n_tiles ? dealt : n_tiles;
             dealt = t + (int)gridDim.x;
@@ -1681,7 +1707,7 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
     __syncthreads();
     int tile_y = s_ticket;
     if (tile_y < n_tiles) load_tile(tile_y, vb);
-    if (!STREAM && threadIdx.x == 0)
+    if (!STREAM && !RANGED && threadIdx.x == 0)
         publish_count(tile_state, tile_x, __popcll(s_mask[0][0]) + __popcll(s_mask[0][1]));
     int slot_x = 0, slot_y = 1, slot_z = 2;
     // One step: (P, Q) hold (X, Y).  Decide Y, move X to LDS, fetch Z into P's registers, write X.
@@ -1698,10 +1724,13 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
             if (lane == 0) {
                 s_mask[slot_z][0] = 0ull;  // (last read before this step's first barrier, next used after its last)
                 s_mask[slot_z][1] = 0ull;
-                if (!STREAM && tile_y < n_tiles)
+                if (!STREAM && !RANGED && tile_y < n_tiles)
                     publish_count(tile_state, tile_y, __popcll(s_mask[slot_y][0]) + __popcll(s_mask[slot_y][1]));
             }
-            if (STREAM) {
+            if (RANGED) {
+                if (lane == 0) s_base = (long long)run;
+                run += (unsigned)(__popcll(s_mask[slot_x][0]) + __popcll(s_mask[slot_x][1]));
+            } else if (STREAM) {
                 if (lane == 0) s_base = tile_base[tile_x];
             } else {
                 const int count = __popcll(s_mask[slot_x][0]) + __popcll(s_mask[slot_x][1]);
@@ -1729,6 +1758,50 @@ __global__ __launch_bounds__(256, 4) void k_select_write64(Geom g, int channels,
         if (tile_x >= n_tiles) break;
     }
     finish();
+}
+
+// The rows that keep an entry, counted for every workgroup's consecutive tiles, so that k_select_write64 (counts) writes without
+// tickets or look-back.  A row is settled by its first channel that survives: four at a time are read, and no further than the
+// row of the 64 that takes longest.
+__global__ __launch_bounds__(256) void k_select_count64(Geom g, int channels, int mode, int relu,
+                                                        const int* __restrict__ cand_start,
+                                                        const int* __restrict__ tile_start,
+                                                        const float* __restrict__ resp,
+                                                        const ColState* __restrict__ cols,
+                                                        const Counters* __restrict__ ctr, unsigned* __restrict__ counts) {
+    __shared__ unsigned s_cnt[4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n_tiles = (int)ctr->n_tiles, per = (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int first = (int)blockIdx.x * per, last = first + per < n_tiles ? first + per : n_tiles;
+    unsigned cnt = 0;
+    for (int u = 2 * first + wave; u < 2 * last; u += 4) {  // half tiles
+        const int tile = u >> 1;
+        const int b = __builtin_amdgcn_readfirstlane(sample_of_tile(tile_start, g.batch, tile));
+        const int lt = tile - tile_start[b], r = (u & 1) * 64 + lane;
+        const unsigned pos = (unsigned)(lt * kTileRows + r);
+        const bool live = (int)pos < cand_start[b + 1] - cand_start[b];
+        const float* seg = resp + (size_t)tile * channels * kTileRows + r;
+        const ColState* own = cols + (size_t)b * channels;
+        bool any = false;
+        for (int c0 = 0; c0 < channels; c0 += 4) {
+            float x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = seg[(size_t)(c0 + i < channels ? c0 + i : c0) * kTileRows];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const ColState* st = own + (c0 + i < channels ? c0 + i : c0);
+                const unsigned tau = st->tau, cut = st->cut;
+                bool keep = score_key(x[i], mode) > (pos <= cut ? tau - (tau != 0u ? 1u : 0u) : tau);
+                if (relu) keep = keep && x[i] > 0.0f;
+                any |= keep;
+            }
+            if (__ballot(live && !any) == 0ull) break;  // (uniform)
+        }
+        cnt += (unsigned)__popcll(__ballot(any && live));
+    }
+    if (lane == 0) s_cnt[wave] = cnt;
+    __syncthreads();
+    if (threadIdx.x == 0) counts[blockIdx.x] = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
 }
 
 __global__ void k_finish(const Counters* __restrict__ ctr, int which_rows, long long aux_imm, int aux_is_cand,
@@ -1968,12 +2041,13 @@ __global__ __launch_bounds__(256) void k_select_emit_narrow(Geom g, int channels
     }
 }
 
+constexpr long long kCountedTiles = 2048;
 hipError_t launch_select_write(const Geom& g, int channels, int mode, int relu, const int* cand_start,
                                const int* tile_start, const unsigned* cand_lin, const float* resp,
                                const ColState* cols, unsigned long long* tile_state, long long tiles_cap,
                                Counters* ctr, int32_t* out_coords, float* out_feats, long long out_capacity,
                                long long* nnz_out, long long aux_imm, int aux_is_cand, unsigned long long* row_keep,
-                               const long long* tile_base, hipStream_t s) {
+                               const long long* tile_base, int keeps_all, hipStream_t s) {
     // no more workgroups than can be resident at once (4 per CU by LDS), so that every ticket holder runs; three per
     // CU measured best for the wide kernels (cfg 4: 103 us against 107 with four and 110 with two)
     const long long cus = device_cu_count();
@@ -2003,9 +2077,25 @@ hipError_t launch_select_write(const Geom& g, int channels, int mode, int relu, 
         // (streaming: four workgroups per CU; by look-back three measured best, and four cost it 5 %, which only the
         // rare launch that was given tile_base and cannot use it pays)
         if (tile_base) blocks = tiles_cap < 1 ? 1 : (tiles_cap > cus * 4 ? cus * 4 : tiles_cap);
-        hipLaunchKernelGGL(k_select_write64, dim3((unsigned)blocks), dim3(256), 0, s, g, channels, mode, relu,
-                           cand_start, tile_start, cand_lin, resp, cols, tile_state, ctr, out_coords, out_feats,
-                           out_capacity, nnz_out, aux_imm, aux_is_cand, tile_base);
+        // Without the selection's marks: counted first where nothing is selected, a row being settled by its first channel
+        // then, and on layers of many tiles (whole calls, 32 -> 64 channels on surfaces, look-back against counted: plain,
+        // 16^3 x 4 72 -> 69 us, 32^3 x 2 83 -> 78, 53 x 75 x 94 x 3 148 -> 131; a tenth selected, 32^3 x 2, 200 tiles, 99 -> 112, x 6, 570 tiles (1540 of capacity), 142 -> 147,
+        // x 16, 1500 tiles, 216 -> 209, 33 channels 198 -> 180)
+        const bool ranged = !tile_base && (keeps_all || tiles_cap > kCountedTiles);
+        if (ranged) blocks = tiles_cap < 1 ? 1 : (tiles_cap > cus * 4 ? cus * 4 : tiles_cap);
+        const unsigned* counts = (const unsigned*)tile_state;
+#define SCNN_WRITE64(RANGED)                                                                                           \
+    hipLaunchKernelGGL(k_select_write64<RANGED>, dim3((unsigned)blocks), dim3(256), 0, s, g, channels, mode, relu,     \
+                       cand_start, tile_start, cand_lin, resp, cols, tile_state, ctr, out_coords, out_feats,           \
+                       out_capacity, nnz_out, aux_imm, aux_is_cand, tile_base, counts)
+        if (ranged) {
+            hipLaunchKernelGGL(k_select_count64, dim3((unsigned)blocks), dim3(256), 0, s, g, channels, mode, relu, cand_start,
+                               tile_start, resp, cols, ctr, (unsigned*)tile_state);
+            SCNN_WRITE64(true);
+        } else {
+            SCNN_WRITE64(false);
+        }
+#undef SCNN_WRITE64
     } else
         hipLaunchKernelGGL(k_select_write, dim3((unsigned)blocks), dim3(256), 0, s, g, channels, mode, relu,
                            cand_start, tile_start, cand_lin, resp, cols, tile_state, ctr, out_coords, out_feats,

@@ -104,3 +104,30 @@ def test_compaction_of_seventeen_to_thirty_two_channels(ext, density, cap, c_out
                                      torch.from_numpy(w).cuda(), rho_up=1.0, relu=relu, cand_capacity=cap)
     print(ext, c_out, len(coords), int(n[1]) / 128, cap, flush=True)
     assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf) and int(n[2]) == 0
+
+
+@pytest.mark.parametrize("c_out,mode,relu,pool", [(33, scnn.ABS, False, False), (64, scnn.SIGNED, True, False), (50, scnn.ABS, True, True)])
+@pytest.mark.parametrize("ext,batch,density,rho,cap", [((20, 21, 22), 17, 0.03, 0.2, 0), ((20, 21, 22), 37, 0.03, 0.2, 0), ((3, 5), 2, 0.5, 1.0, 0),
+                                                       ((9, 10, 11), 40, 0.2, 1.0, 0), ((20, 21, 22), 17, 0.0005, 1.0, 0), ((120, 150), 13, 0.2, 0.3, 0)])
+def test_compaction_of_wide_layers_without_marks(ext, batch, density, rho, cap, c_out, mode, relu, pool):
+    """Counted first, where nothing is selected and above 2048 tiles of capacity, and by look-back: samples without rows, one
+    tile and many a workgroup, a small output.  Small whole numbers, the oracle's rows."""
+    rng = np.random.default_rng(c_out + batch)
+    k = (3,) * len(ext)
+    coords = random_sparse_sites(rng, ext, batch, density)
+    coords = coords[coords[:, 0] % 5 != 1]
+    feats = rng.integers(1, 4, size=(len(coords), 2)).astype(np.float32)
+    w = rng.integers(-2, 3, size=(3 ** len(ext), 2, c_out)).astype(np.float32)
+    w[:, :, :6] *= rng.random((3 ** len(ext), 1, 1)) < 0.3  # (rows whose first channels are zero)
+    c, f, t = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (coords, feats, w))
+    rc, rf = oracle.sparse_conv_fwd(ext, batch, coords, feats, k, w, rho_up=rho, topk_mode=mode, relu=relu, pool=pool)
+    gc, gf, n = scnn.sparse_conv_fwd(ext, batch, c, f, k, t, rho_up=rho, topk_mode=mode, relu=relu, pool=pool, cand_capacity=cap)
+    print(ext, c_out, len(coords), n.tolist(), flush=True)
+    assert int(n[2]) == 0 and np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf)
+    if len(rc) > 100:
+        out = (torch.full((70, 1 + len(ext)), -7, dtype=torch.int32, device="cuda"), torch.full((70, c_out), -7.0, device="cuda"),
+               torch.zeros(4, dtype=torch.int64, device="cuda"))
+        scnn.sparse_conv_fwd(ext, batch, c, f, k, t, rho_up=rho, topk_mode=mode, relu=relu, pool=pool, cand_capacity=cap, out_capacity=64, out=out,
+                             sync=False)
+        assert int(out[2][0]) == len(rc) and int(out[2][2]) == 2 and np.array_equal(out[0][:64].cpu().numpy(), rc[:64])
+        assert np.array_equal(out[1][:64].cpu().numpy(), rf[:64]) and bool((out[0][64:] == -7).all()) and bool((out[1][64:] == -7).all())
