@@ -1166,7 +1166,15 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
     // layer whose workspace is that much larger than its data runs slower on it, a large layer saves a launch).
     const bool stream_only = tiles_cap * n_chunks > kValuStreamOnlyItems;
     const bool both = !stream_only && tiles_cap * n_chunks > kValuLatencyItems;
-    if (tiles_cap * n_chunks <= kValuSmallItems && ch >= 2) {  // cannot hold more than a few hundred tiles
+    // .. or, with items of one block, more: four channels a gather, or sixteen input channels and more, 27 taps, where sites
+    // miss at least half of their neighbours (a wave skips the taps that none of its rows has).  Surfaces and level sets of a
+    // tenth and four tenths of the sites, calls, us, against the forms below: 20^3 x 6, 16 -> 16 63 / 67 -> 47 / 61, 4 -> 16
+    // 47 / 51 -> 41 / 47; 24^3 x 8, 860 tiles, 24 -> 16 96 / 134 -> 83 / 116; 32^3 x 4 16 -> 8 84 / 116 -> 84 / 109; all
+    // occupied 78 -> 81 (24^3 x 4, 16 -> 8) and 122 -> 136 (32^3 x 4); 8 -> 16 55 / 63 / 65 -> 52 / 62 / 72; nine taps, 80 x 80
+    // x 12, 16 -> 16, 54 / 61 / 74 -> 57 / 69 / 88.
+    const bool thin = c_out_pad <= kOcBlock && g.T > 9 && (ch == 4 || (ch == 8 && c_in >= 16)) &&
+                      nnz_in * 2 <= tiles_cap * kTileRows && tiles_cap <= 4 * kValuSmallItems;
+    if ((tiles_cap * n_chunks <= kValuSmallItems || thin) && ch >= 2) {  // cannot hold more than a few hundred tiles
         // One 16-channel block per item where the layer has no more, or where that many workgroups still run at once (two to a
         // compute unit): 40 x 40 x 4, 16 -> 24, 520 items, keeps two blocks
         const long long items = tiles_cap * (c_out_pad / kOcBlock) * (kTileRows / 32);
