@@ -128,14 +128,18 @@ hipError_t launch_bwd_data_write(const Geom& g, const float* resp, const float* 
 // (slab, share of the tiles), a slab being one block of 16 input channels against up to 32 (tap, block of 16 output
 // channels) slots, two to a wave.  The tile's values of x and its neighbour rows, looked up once per tile, are shared
 // through LDS.  Inputs of the paper's own layers have a gradient row behind nearly every (row, tap), so the rows are not
-// packed.  Bound by the latency of the look-ups and of the gathers (8 -> 16 channels, 47 k rows, 27 taps: 319 k
-// instructions, 10 us of matrix time; 53 us measured, 167 with a thread per filter element that read both operands of
-// every product).  Partial sums of a share are stored (no atomics), zero included.
+// packed (27 taps of 47 k rows: 57 us packed, 53 not).  Bound by the latency of the look-ups and of the gathers (8 -> 16
+// channels, 47 k rows, 27 taps: 319 k instructions, 10 us of matrix time).  So sixteen waves are held to 64 registers, two
+// workgroups to a CU: x is read from LDS at the product and eight gathers are in flight, their masks in one register: 33 us;
+// 53 with x and sixteen gathers in registers, one workgroup to a CU (40 with four masked gathers, 46 with eight; a few
+// registers of the look-up spill); 167 with a thread per filter element that read both operands of every product.  Calls,
+// us, before and after: 8->8, 27 taps, 12 k rows 52 / 50, 125 taps, 126 k rows 474 / 432; 24->24, 27 taps, 126 k rows
+// 458 / 393; one tap, 47 k rows, 100->100 232 / 156.  Partial sums of a share are stored (no atomics), zero included.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 // W waves of two (tap, block of 16 output channels) slots each; nt taps and no blocks to a slab, nt * no <= 2 W (MULTI:
 // no may be more than 1).
 template <int W, int MULTI>
-__global__ __launch_bounds__(64 * W) void k_bwd_filter_f64(Geom g, const unsigned long long* __restrict__ occ,
+__global__ __launch_bounds__(64 * W, W == 16 ? 8 : 4) void k_bwd_filter_f64(Geom g, const unsigned long long* __restrict__ occ,
                                                         const unsigned* __restrict__ occ_prefix, long long g_rows,
                                                         const float* __restrict__ gf, int c_out,
                                                         const float* __restrict__ x, int c_in,
@@ -146,7 +150,7 @@ __global__ __launch_bounds__(64 * W) void k_bwd_filter_f64(Geom g, const unsigne
                                                         const Counters* __restrict__ ctr, int nt, int no, int n_icb,
                                                         int n_og, int n_slabs, int n_chunks,
                                                         double* __restrict__ fpart) {
-    constexpr int NT = 64 * W;
+    constexpr int NT = 64 * W, F = 8;  // (F: gathers in flight)
     __shared__ int s_nbr[kTileRows][2 * W + 1];
     __shared__ int s_site[kTileRows][3];
     __shared__ float s_x[kTileRows][17];
@@ -210,30 +214,30 @@ __global__ __launch_bounds__(64 * W) void k_bwd_filter_f64(Geom g, const unsigne
             }
         }
         __syncthreads();
-        if (!on[0] && !on[1]) continue;
-        float a[kTileRows / 4];
-#pragma unroll
-        for (int s = 0; s < kTileRows / 4; ++s) a[s] = s_x[4 * s + kq][m];
+        if (g_rows < 1) continue;  // (every product is 0; the gathers below read row 0 for an absent neighbour)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             if (!on[j]) continue;
-            const int c = col[j] + m;
-            const float* gcol = gf + c;
+            // (a column past the layer's reads its last one; nothing is stored for it)
+            const float* gcol = gf + (col[j] + m < c_out ? col[j] + m : c_out - 1);
+#pragma unroll 1
+            for (int s0 = 0; 4 * s0 < nrows; s0 += F) {
+                float gv[F];
+                unsigned there = 0;
 #pragma unroll
-            for (int s0 = 0; s0 < kTileRows / 4; s0 += 16) {
-                if (4 * s0 >= nrows) continue;
-                float gv[16], xv[16];
-#pragma unroll
-                for (int s = 0; s < 16; ++s) {
-                    // no gradient row: nothing is read, and the product is 0 * 0 whatever the row holds (an infinity or
-                    // NaN of x belongs to the pairs that exist)
+                for (int s = 0; s < F; ++s) {
                     const int n = s_nbr[4 * (s0 + s) + kq][tap[j]];
-                    gv[s] = n >= 0 && c < c_out ? gcol[(size_t)n * c_out] : 0.0f;
-                    xv[s] = n >= 0 ? a[s0 + s] : 0.0f;
+                    gv[s] = gcol[(size_t)(n < 0 ? 0 : n) * c_out];
+                    there |= n < 0 ? 0u : 1u << s;
                 }
 #pragma unroll
-                for (int s = 0; s < 16; ++s)
-                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xv[s], (double)gv[s], acc[j], 0, 0, 0);
+                for (int s = 0; s < F; ++s) {
+                    // no gradient row: the product is 0 * 0 whatever the rows hold (an infinity or NaN belongs to the
+                    // pairs that exist)
+                    const bool pair = there & (1u << s);
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(pair ? (double)s_x[4 * (s0 + s) + kq][m] : 0.0,
+                                                                  pair ? (double)gv[s] : 0.0, acc[j], 0, 0, 0);
+                }
             }
         }
     }
@@ -257,10 +261,9 @@ __global__ __launch_bounds__(64 * W) void k_bwd_filter_f64(Geom g, const unsigne
 // has a row at q - delta_t.  The neighbour rows of a tile are looked up once per tap and shared through LDS.
 // fp64 throughout; the partial sum of the share is stored (no atomics), zero included.
 // Where a 16 x 16 block of channels holds at most 16 products the matrix form above does sixteen times the work of this
-// one and is slower once there are more than two slabs of taps: 125 taps, 47 k / 105 k rows, call in us, this / that:
-// 1->8 209 / 385 against 289 / 578, 1->16 333 / 631 against 373 / 736, 3->5 304 / 562 against 329 / 626; 49 taps, 32 k
-// rows of 2-D: 98 against 102, 141 against 132, 125 against 128; but 8->8 470 against 293, 27 taps 1->8 101 against 90,
-// and on 2.6 k rows 125 taps 77 against 71.
+// one and is slower once there are more than two slabs of taps: 125 taps, 47 k / 126 k rows, call in us, this / that:
+// 1->8 141 / 304 against 196 / 425, 1->16 242 / 504 against 264 / 552, 3->5 222 / 463 against 251 / 528; 49 taps, 31 k
+// rows of 2-D: 73 against 84, 90 against 98, 102 against 111; but 1->1, 125 taps, on 12 k rows 134 against 90.
 constexpr int kBwdTapChunk = 32;  // taps whose neighbour rows are staged in LDS at a time
 __global__ __launch_bounds__(256) void k_bwd_filter_valu(Geom g, const unsigned long long* __restrict__ occ,
                                                          const unsigned* __restrict__ occ_prefix, long long g_rows,
@@ -350,8 +353,8 @@ __global__ __launch_bounds__(256) void k_bwd_filter_valu(Geom g, const unsigned 
 
 // How bp_filter outside the matrix-core lists is cut.  waves = 0: the vector kernel, `slabs` blocks of 256 elements.
 // Taps x blocks of output channels of at most 8 take four waves and everything in one slab (1 x 1, 47 k rows: 24->24 118
-// -> 61 us a call, 100->100 1300 -> 240 with all blocks of channels in the workgroup that looks the rows up; 9 taps 24->24
-// 160 -> 136); but a workgroup per block where these do not fill the chip (one 28 x 28 image, 24->24: 50 us against 57).
+// -> 53 us a call, 100->100 1300 -> 156 with all blocks of channels in the workgroup that looks the rows up; 9 taps 24->24
+// 160 -> 98); but a workgroup per block where these do not fill the chip (one 28 x 28 image, 24->24: 50 us against 57).
 struct BwdF64Shape {
     int waves, nt, no, n_icb, n_og;
     long long slabs;
