@@ -337,10 +337,11 @@ static void carve_conv(void* base, const Geom& g, const Geom& gp, long long nnz_
     w->tmp_coords = c.take<int32_t>(pool ? (size_t)cand_cap * (1 + g.ndim) : 0);
     w->tmp_feats = c.take<float>(pool ? (size_t)cand_cap * c_out : 0);
     w->pool_key = c.take<long long>(pool ? w->pool_cap : 0);
-    // (the staging area whatever the number of rows, so that a workspace asked for with more rows serves fewer)
+    // (the staging area whatever the number of rows and the fused steps, so that a workspace asked for with more rows serves
+    // fewer, and one asked for with pooling a call without)
     const bool tiny_shape = layer_tiny_shape(g, c_in, c_out);
     w->tiny = tiny_shape && g_conv_path == 0 && w->kernel == ConvKernel::kValu && layer_tiny_pays(g, c_in, c_out, nnz_in);
-    const size_t staged = tiny_shape && g.batch > 1 ? (size_t)g.batch * layer_tiny_stage_rows(g, gp, pool) : 0;
+    const size_t staged = tiny_shape && g.batch > 1 ? (size_t)g.batch * g.N : 0;
     w->tiny_lin = c.take<unsigned>(staged);
     w->tiny_feats = c.take<float>(staged * c_out);
     w->tiny_info = c.take<TinySample>(staged ? g.batch : 0);

@@ -32,8 +32,6 @@ struct Geom {
 struct ColState {
     unsigned tau;       // threshold key: the k-th strongest key of the column
     unsigned cut;       // entries equal to tau survive up to this position in the column (0xffffffff: all of them)
-    unsigned n_eq;      // entries whose key equals tau
-    unsigned q;         // how many of those survive (lowest lin first)
     unsigned tau_lo;    // bracket expected to hold tau, from a sample of the column: keys in [tau_lo, tau_hi] go to the
     unsigned tau_hi;    //   side buffer, keys above tau_hi are only counted
     unsigned n_nz;      // non-zero entries in the column
@@ -562,11 +560,10 @@ struct TinySample {  // what a sample's workgroup leaves behind
     unsigned flags;  // SCNN_FLAG_*
     unsigned unused;
 };
-// Layers that one workgroup a sample computes whole: can it, is it the faster way for so many input rows, and rows of a
-// sample's staging area.
+// Layers that one workgroup a sample computes whole: can it, and is it the faster way for so many input rows.  The staging
+// area (batch > 1) is of as many rows as the grid has sites.
 bool layer_tiny_shape(const Geom& g, int c_in, int c_out);
 bool layer_tiny_pays(const Geom& g, int c_in, int c_out, long long rows);
-long long layer_tiny_stage_rows(const Geom& g, const Geom& gp, int pool);
 hipError_t launch_layer_tiny(const Geom& g, const Geom& gp, const int32_t* coords, const float* feats, long long n_imm,
                              const long long* n_dev, int c_in, const float* w, const float* bias, int c_out, long long k,
                              int mode, int relu, int pool, long long cand_cap, unsigned* stage_lin, float* stage_feats,

@@ -65,8 +65,6 @@ bool layer_tiny_pays(const Geom& g, int c_in, int c_out, long long rows) {
     return rows * g.T * c_in * (c_out <= 8 ? 8 : 16) <= kTinyProducts * g.batch;
 }
 
-long long layer_tiny_stage_rows(const Geom& g, const Geom& gp, int pool) { return pool ? gp.N : g.N; }
-
 // Exclusive sums of the popcounts of up to 64 words (lane i: the words before i); total: all of them.  (whole wave)
 __device__ __forceinline__ unsigned word_sums(const unsigned long long* words, int n, unsigned& total) {
     const int lane = threadIdx.x & 63;
@@ -485,7 +483,7 @@ hipError_t launch_layer_tiny(const Geom& g, const Geom& gp, const int32_t* coord
                              long long* nnz_out, hipStream_t s) {
     const int ocb = c_out <= 8 ? 8 : 16;
     const size_t lds = tiny_layout(g, c_in, c_out).total;
-    const long long stage_rows = layer_tiny_stage_rows(g, gp, pool);
+    const long long stage_rows = pool ? gp.N : g.N;  // (at most g.N)
     // Few samples leave most of the chip idle and are done when their one workgroup is: all the waves a unit takes.
     const bool wide = g.batch <= device_cu_count() || lds > 40 * 1024;
     hipError_t e;

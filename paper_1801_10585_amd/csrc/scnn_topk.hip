@@ -9,12 +9,13 @@
 // counts, per column, the entries above the bracket, copies the few percent
 // inside it (value and position in the column) to a side buffer, and notes
 // which rows hold an entry above the bracket.  A workgroup per column settles
-// the rest on the side buffer: the exact k-th largest key tau, the number n_eq
-// of entries equal to it and how many of those, q, still fit.  An entry
-// survives iff  key > tau, or key == tau and it is among the q equal entries
-// of lowest lin; candidate sites are stored in ascending lin, so "lowest lin"
-// is "smallest position", and the q-th smallest position among the equal
-// entries (a second, ascending radix select on the side buffer) is the cut.
+// the rest on the side buffer: the exact k-th largest key tau and how many of
+// the entries equal to it, q, still fit.  An entry survives iff  key > tau, or
+// key == tau and it is among the q equal entries of lowest lin; candidate sites
+// are stored in ascending lin, so "lowest lin" is "smallest position", and the
+// q-th smallest position among the equal entries is the cut.  Both come from
+// digit passes until at most 64 entries are left, which one wave ranks by
+// (key, position).
 // A bracket that turns out not to hold the k-th entry costs time, never
 // exactness: the column is then settled from the response matrix itself.
 // The response matrix is read twice in full (the classifying pass, and the
@@ -26,8 +27,9 @@
 // every tile are known before the last pass, a scan gives each tile its first
 // output row, and the write pass streams with no ordering between tiles.  Other
 // layers of at most 32 channels count and write in two launches from some size
-// on (narrow_pair_tiles).  Elsewhere tiles are taken in order and a tile learns
-// its first output row by looking back at its predecessors.
+// on (narrow_pair_tiles), and so do wider ones where nothing is selected or from
+// kCountedTiles on.  Elsewhere tiles are taken in order and a tile learns its
+// first output row by looking back at its predecessors.
 #include <type_traits>
 
 #include "scnn_internal.h"
@@ -228,7 +230,7 @@ __global__ __launch_bounds__(kBracketThreads) void k_bracket(int mode, int chann
     const int t0 = tile_start[b], t1 = tile_start[b + 1];
     const int T = t1 - t0;
     ColState st;
-    st.tau = 0; st.cut = 0xffffffffu; st.n_eq = 0; st.q = 0; st.tau_lo = 1u; st.tau_hi = 0u; st.n_nz = 0; st.n_above = 0;
+    st.tau = 0; st.cut = 0xffffffffu; st.tau_lo = 1u; st.tau_hi = 0u; st.n_nz = 0; st.n_above = 0;
     st.side_fill = 0; st.done = 0;
     st.side_off = ((unsigned long long)t0 * channels + (unsigned long long)oc * T) * kTileRows;
     if (k <= 0 || T == 0) {
@@ -1021,7 +1023,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_select_small(int mode, int ch
     }
     __syncthreads();
     ColState st;
-    st.tau = 0; st.cut = 0xffffffffu; st.n_eq = 0; st.q = 0; st.tau_lo = 0; st.tau_hi = 0; st.n_nz = s_total;
+    st.tau = 0; st.cut = 0xffffffffu; st.tau_lo = 0; st.tau_hi = 0; st.n_nz = s_total;
     st.n_above = 0; st.side_fill = 0; st.done = 1; st.side_off = 0;
     if (k <= 0) st.tau = 0xffffffffu;  // no key is stronger: nothing survives
     if (k <= 0 || (long long)st.n_nz <= k) {  // or fewer entries than k: all survive (tau = 0)
@@ -1143,7 +1145,7 @@ __device__ __forceinline__ void select_tiny(int mode, const float* __restrict__ 
         key[u] = i < n ? score_key(column[(size_t)(i >> 7) * pitch + (i & 127u)], mode) : 0u;
     }
     ColState st;
-    st.n_eq = 0; st.q = 0; st.tau_lo = 0; st.tau_hi = 0; st.n_above = 0; st.side_fill = 0; st.done = 1; st.side_off = 0;
+    st.tau_lo = 0; st.tau_hi = 0; st.n_above = 0; st.side_fill = 0; st.done = 1; st.side_off = 0;
     wave_threshold<NU>(key, k, st.n_nz, st.tau, st.cut);
     if (lane == 0) *out = st;
 }
