@@ -820,11 +820,15 @@ __global__ __launch_bounds__(256) void k_conv_valu(Geom g, const unsigned long l
 // (v_mfma_f64_16x16x4_f64) and the four waves' partial sums are added through LDS in the order of the waves.
 // CH = 2: the two halves of a wave take the two 16-channel blocks, or, when there is only one, every other input
 // channel, with fp64 FMAs; the eight partial sums per output are added through LDS in a fixed order.
-// NB = 1: items of one 16-channel block.  With eight channels a round's weights then take 32 KB of LDS instead of 64 (103 KB in
-// all let one workgroup run on a compute unit, 71 KB two) and half the loads: 16^3 x 4, 16 -> 16, 512 items, call 71 -> 59 us,
-// 8 -> 8 61 -> 53, 8^3 x 4, 24 -> 24 (two blocks, 160 items) 64 -> 56.
-template <int CH /* 8, 4 or 2 */, int NB /* 16-channel blocks of a work item: 2, or 1 where the layer has no more */>
-__global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned long long* __restrict__ occ,
+// For the matrix cores a round's weights lie in LDS as the fp32 numbers that they are and are widened at the product: with eight
+// channels and two blocks an item takes 70 KB, two workgroups to a compute unit (103 KB and one with fp64 weights): 56 x 56 x 4,
+// calls in us, before and after: 16 -> 24 54 / 48, 16 -> 64 66 / 58, 25 taps, 24 -> 24 70 / 58, 16 -> 64 87 / 69; the same time
+// where one round of workgroups is enough.  Three to a unit with one block (168 registers, some spilled) gains 5 % or loses 3,
+// as the rounds fall: not taken.
+// NB = 1: items of one 16-channel block, half the weights to load: 16^3 x 4, 16 -> 16, 512 items, call 71 -> 59 us, 8 -> 8
+// 61 -> 53, 8^3 x 4, 24 -> 24 (two blocks, 160 items) 64 -> 56 (against two blocks and one workgroup to a unit).
+template <int CH /* 8, 4 or 2 */, int NB /* 16-channel blocks of a work item: 2, or 1 */>
+__global__ __launch_bounds__(256, 2) void k_conv_valu_small(Geom g, const unsigned long long* __restrict__ occ,
                                                          const unsigned* __restrict__ occ_prefix, long long nnz_in,
                                                          const float* __restrict__ feats, int c_in,
                                                          const double* __restrict__ wp, int c_out, int c_out_pad,
@@ -839,16 +843,18 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
     constexpr int XS = kTapChunk * CH + 4;   // row stride of the gathered values
     constexpr int GB = (R * kTapChunk) / 256;                     // (row, tap) pairs a thread gathers per round
     constexpr int WB = (NB * kTapChunk * CH * kOcBlock) / 256;    // weights a thread stages per round
-    __shared__ int s_nbr[R][kTapChunk + 1];
-    __shared__ int s_site[R][3];
-    __shared__ __align__(16) float s_x[R][XS];
-    // the round's weights, per 16-channel block; after the last round the same memory holds the partial sums of
-    // the eight (wave, half) pairs
-    constexpr int kWElems = NB * kTapChunk * CH * kOcBlock;
-    constexpr int kRedElems = CH >= 4 ? 4 * R * (NB * kOcBlock + 1) : 8 * R * (kOcBlock + 1);
-    __shared__ __align__(16) double s_wr[kWElems > kRedElems ? kWElems : kRedElems];
-    double (*s_w)[kTapChunk * CH][kOcBlock] = reinterpret_cast<double (*)[kTapChunk * CH][kOcBlock]>(&s_wr[0]);
-    double (*s_red)[R][kOcBlock + 1] = reinterpret_cast<double (*)[R][kOcBlock + 1]>(&s_wr[0]);
+    // One block of memory: the round's weights per 16-channel block, then the gathered values, whose padding holds the rows'
+    // sites; after the last round the partial sums of the waves (CH = 2: of the eight (wave, half) pairs).
+    using WT = std::conditional_t<(CH >= 4), float, double>;
+    constexpr int kWBytes = NB * kTapChunk * CH * kOcBlock * (int)sizeof(WT);
+    constexpr int kXBytes = R * XS * 4;
+    constexpr int kRedBytes = (CH >= 4 ? 4 * R * (NB * kOcBlock + 1) : 8 * R * (kOcBlock + 1)) * 8;
+    __shared__ __align__(16) unsigned char s_mem[kWBytes + kXBytes > kRedBytes ? kWBytes + kXBytes : kRedBytes];
+    __shared__ int s_nbr[kTapChunk][R];
+    WT (*s_w)[kTapChunk * CH][kOcBlock] = reinterpret_cast<WT (*)[kTapChunk * CH][kOcBlock]>(&s_mem[0]);
+    float (*s_x)[XS] = reinterpret_cast<float (*)[XS]>(&s_mem[kWBytes]);
+    double (*s_red)[R][kOcBlock + 1] = reinterpret_cast<double (*)[R][kOcBlock + 1]>(&s_mem[0]);
+    auto site = [&](int r) { return reinterpret_cast<int*>(&s_x[r][kTapChunk * CH]); };
 
     const int n_tiles = (int)ctr->n_tiles;
     const int n_chunks = (c_out_pad + NB * kOcBlock - 1) / (NB * kOcBlock);
@@ -889,15 +895,15 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
             if (threadIdx.x < R) {
                 int c0 = 0, c1 = 0, c2 = 0;
                 if (threadIdx.x < nrows) site_of(g, cand_lin[first + threadIdx.x], c0, c1, c2);
-                s_site[threadIdx.x][0] = c0;
-                s_site[threadIdx.x][1] = c1;
-                s_site[threadIdx.x][2] = c2;
+                site(threadIdx.x)[0] = c0;
+                site(threadIdx.x)[1] = c1;
+                site(threadIdx.x)[2] = c2;
             }
             for (int tc = 0; tc < g.T; tc += kTapChunk) {
                 const int tmax = (g.T - tc) < kTapChunk ? (g.T - tc) : kTapChunk;
                 const int n_rounds = c_in / CH;
                 float xv[GB][CH];
-                double wv[WB];
+                WT wv[WB];
                 // the round's weights: element e = (block hb, tap tg, channel j, o) <- w[tc + tg][ic0 + j][16 hb + o]
                 auto fetch_w = [&](int q) {
                     const int ic0 = q * CH;
@@ -910,8 +916,8 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                         const int oc = chunk * NB * kOcBlock + hbw * kOcBlock + o;
                         const bool ok = tg < tmax && oc < c_out_pad;
                         const size_t at = ok ? ((size_t)(tc + tg) * c_in + ic0 + j) * c_out_pad + oc : 0;
-                        const double v = wp[at];
-                        wv[m] = ok ? v : 0.0;
+                        const WT v = (WT)wp[at];  // (an fp32 number, whatever it is held in)
+                        wv[m] = ok ? v : (WT)0;
                     }
                 };
                 // the neighbours' values; a site without the neighbour multiplies zeros
@@ -921,7 +927,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                     for (int m = 0; m < GB; ++m) {
                         const int e = threadIdx.x + m * 256;
                         const int r = e & (R - 1), tg = e >> 5;
-                        const int n = (tg < tmax) ? s_nbr[r][tg] : -1;
+                        const int n = (tg < tmax) ? s_nbr[tg][r] : -1;
                         const float* __restrict__ xp = feats + (size_t)(n < 0 ? 0 : n) * c_in + ic0;
                         if constexpr (CH == 8) {
                             const float4 u = *(const float4*)xp, v = *(const float4*)(xp + 4);
@@ -951,7 +957,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                 };
                 const unsigned act = active_taps(tap_active, tc, tmax);
                 fetch_w(0);  // does not depend on the neighbours: in flight during the look-ups
-                __syncthreads();  // s_site written; the previous chunk's readers of s_nbr are done
+                __syncthreads();  // the sites are written; the previous chunk's readers of s_nbr are done
                 {
                     const int l_first = tc / g.K[2];
                     const int n_seg = (tc + tmax - 1) / g.K[2] - l_first + 1;
@@ -960,10 +966,10 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                         const int ta = tc > l * g.K[2] ? tc : l * g.K[2];
                         const int tb = (tc + tmax) < (l + 1) * g.K[2] ? (tc + tmax) : (l + 1) * g.K[2];
                         const int t0 = l / g.K[1], t1 = l - t0 * g.K[1];
-                        int* dst = &s_nbr[r][ta - tc];
-                        lookup_line(g, occ, occ_prefix, nnz_in, r < nrows, b, s_site[r][0], s_site[r][1], s_site[r][2],
+                        int* dst = &s_nbr[ta - tc][r];
+                        lookup_line(g, occ, occ_prefix, nnz_in, r < nrows, b, site(r)[0], site(r)[1], site(r)[2],
                                     t0, t1, ta - l * g.K[2], tb - ta, act >> (ta - tc),
-                                    [&](int k, int n) { dst[k] = n; });
+                                    [&](int k, int n) { dst[k * R] = n; });
                     }
                 }
                 __syncthreads();  // s_nbr complete
@@ -971,7 +977,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                 // taps of the chunk that some row of this wave has
                 unsigned live = 0;
                 for (int tg = wave; tg < tmax; tg += 4)
-                    if (__ballot(s_nbr[row][tg] >= 0) != 0ull) live |= 1u << tg;
+                    if (__ballot(s_nbr[tg][row] >= 0) != 0ull) live |= 1u << tg;
                 for (int q = 0; q < n_rounds; ++q) {
                     __syncthreads();  // the previous round's readers of s_x / s_w are done
                     commit();
@@ -991,12 +997,12 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
                             for (int jb = 0; jb < CH / 4; ++jb) {
                                 const int tj = tg * CH + jb * 4 + kq;
                                 const double a0 = (double)s_x[mi][tj], a1 = (double)s_x[16 + mi][tj];
-                                const double b0 = s_w[0][tj][mi];
+                                const double b0 = (double)s_w[0][tj][mi];
                                 macc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, macc[0][0], 0, 0, 0);
                                 macc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, macc[1][0], 0, 0, 0);
                                 if constexpr (NB > 1)
                                     if (!split) {
-                                        const double b1 = s_w[1][tj][mi];
+                                        const double b1 = (double)s_w[1][tj][mi];
                                         macc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, macc[0][1], 0, 0, 0);
                                         macc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, macc[1][1], 0, 0, 0);
                                     }
@@ -1051,7 +1057,7 @@ __global__ __launch_bounds__(256) void k_conv_valu_small(Geom g, const unsigned 
         __syncthreads();  // the last round's weights have been read
         if constexpr (CH >= 4) {
             // ---- the four waves' partial sums (one per tap slice), added in the order of the waves
-            double (*s_rm)[R][NB * kOcBlock + 1] = reinterpret_cast<double (*)[R][NB * kOcBlock + 1]>(&s_wr[0]);
+            double (*s_rm)[R][NB * kOcBlock + 1] = reinterpret_cast<double (*)[R][NB * kOcBlock + 1]>(&s_mem[0]);
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
