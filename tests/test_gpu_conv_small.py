@@ -28,3 +28,22 @@ def test_smallest_layers(ext, batch, c_in, c_out):
         scnn.set_conv_path(0)
     assert scnn.last_conv_kernel() == "k_conv_valu" and int(n[2]) == 0
     assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf)
+
+
+@pytest.mark.parametrize("ext,batch,ksize", [((20, 21), 2, (5, 7)), ((33, 40), 3, (7, 7)), ((6, 7, 8), 2, (5, 5, 5))])
+@pytest.mark.parametrize("c_in,c_out", [(8, 16), (24, 24), (16, 50), (12, 33), (4, 8), (6, 20)])
+def test_smallest_layers_of_long_filters(ext, batch, ksize, c_in, c_out):
+    """Filters of two and four groups of 32 taps, weights of all 24 bits: the sums are exact in fp64 and rounded once."""
+    rng = np.random.default_rng(c_in * c_out)
+    coords = random_sparse_sites(rng, ext, batch, 0.2)
+    feats = rng.integers(1, 4, size=(len(coords), c_in)).astype(np.float32)
+    w = rng.integers(-(2 ** 24) + 1, 2 ** 24, size=(int(np.prod(ksize)), c_in, c_out)).astype(np.float32)
+    rc, rf = oracle.sparse_conv_fwd(ext, batch, coords, feats, ksize, w, rho_up=0.2, relu=True)
+    scnn.set_conv_path(1)
+    try:
+        gc, gf, n = scnn.sparse_conv_fwd(ext, batch, *(torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (coords, feats)), ksize,
+                                         torch.from_numpy(w).cuda(), rho_up=0.2, relu=True)
+    finally:
+        scnn.set_conv_path(0)
+    assert scnn.last_conv_kernel() == "k_conv_valu" and int(n[2]) == 0
+    assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf)
