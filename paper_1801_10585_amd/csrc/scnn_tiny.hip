@@ -48,21 +48,29 @@ __host__ __device__ inline TinyLayout tiny_layout(const Geom& g, int c_in, int c
 
 // Which layers.  One workgroup does all of a sample's work, so there is a line where the general path, whose launches use
 // the whole chip, wins: in the products of a sample (rows x taps x channels, of which each costs 8 bytes of weights out of
-// LDS) and in the entries that are selected from.  General path against this, us, 1, 8, 300 and 1000 samples:
-//   28 x 28, 1 -> 8, a tenth occupied 44 / 45 / 65 / 81 against 15 / 19 / 31 / 40; all occupied, pooled or not, 1.4 times and more
-//   10^3, 8 -> 8, 0.3 occupied (518 k products) 66 / 68 / 110 / 208 against 46 / 52 / 91 / 189
-//   28 x 28, 8 -> 8, all occupied (451 k) 47 / 49 / 81 / 130 against 35 / 38 / 73 / 145
-//   45 x 45, 4 -> 8, all occupied (583 k) 43 / 49 / 117 / 250 against 43 / 51 / 102 / 199
-//   12^3, 8 -> 8, all occupied (3 M) 48 / 61 / 154 / 352 against 112 / 120 / 240 / 480
-//   45 x 45, 1 -> 16, all occupied (32 k entries) 45 / 51 / 132 / 281 against 48 / 57 / 122 / 249
-// Never slower up to 400 k products and 24 k entries.
+// LDS) and in the entries that are selected from.  The launch lasts as long as its richest sample, and all that the host knows
+// of that one is that it has no more rows than the call and the grid, so the line is drawn for the richest that the call can
+// hold.  Calls, us, general path against this:
+//   one sample: 28 x 28, 1 -> 8, a tenth occupied 32 / 14; 8 -> 16, half (452 k products) 39 / 38; 20 x 20, 8 -> 16, all (461 k)
+//     35 / 33; 45 x 45, 4 -> 8, half (291 k) 34 / 36, all (583 k) 33 / 44; 1 -> 12, all (292 k) 36 / 41; 12^3, 8 -> 8, all (3 M) 37 / 113
+//   eight, one occupied and the others empty: 28 x 28, 8 -> 8 (452 k) 37 / 36; 12^3, 8 -> 8 (3 M) 37 / 117; 45 x 45, 1 -> 8 (146 k)
+//     34 / 36; 1 -> 12 (292 k) 36 / 47, a fifth of the one (58 k) 35 / 39 (the second launch is 6 us)
+//   64, one occupied: 28 x 28, 8 -> 8 39 / 36; 45 x 45, 1 -> 8 37 / 36, 1 -> 12 41 / 47; 12^3, 8 -> 8 41 / 118
+//   300, one occupied: 12^3, 4 -> 8 (1.5 M) 63 / 69, half of it (746 k) 60 / 51; 8^3, 8 -> 8 (885 k) 44 / 45; all half occupied,
+//     28 x 28, 8 -> 8 (226 k on average) 68 / 57, 6^3, 8 -> 16, 1000 of them (373 k) 121 / 139
+// Still on the slower side: layers of 16 k entries and more with some 100 k products and more, where the general path is up to
+// 1.3 times as fast, for one sample and where one of 64 and more is rich.
 constexpr long long kTinyProducts = 400000, kTinyEntries = 24576;
 bool layer_tiny_shape(const Geom& g, int c_in, int c_out) {
     return c_in <= kTinyCin && c_out <= kTinyCout && g.T <= kTinyTaps && g.N <= kTinyMaxSites &&
            g.N * c_out <= kTinyEntries && tiny_layout(g, c_in, c_out).total <= kTinyLds;
 }
 bool layer_tiny_pays(const Geom& g, int c_in, int c_out, long long rows) {
-    return rows * g.T * c_in * (c_out <= 8 ? 8 : 16) <= kTinyProducts * g.batch;
+    const long long row = (long long)g.T * c_in * (c_out <= 8 ? 8 : 16);  // products
+    const long long richest = (rows < g.N ? rows : g.N) * row;
+    if (g.batch < 256)
+        return richest <= kTinyProducts && (g.batch == 1 || g.batch >= 64 || richest + 15 * g.N * c_out <= 470000);
+    return richest <= 750000 && rows * row <= 300000ll * g.batch;
 }
 
 // Exclusive sums of the popcounts of up to 64 words (lane i: the words before i); total: all of them.  (whole wave)

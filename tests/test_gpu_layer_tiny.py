@@ -65,6 +65,31 @@ def test_which_layers_it_takes(ext, batch, c_in, c_out, rows, kernel):
     assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("ext,batch,c_in,c_out,rich,rows,kernel", [
+    ((12, 12, 12), 8, 8, 8, 1728, 0, "k_conv_valu"), ((12, 12, 12), 64, 8, 8, 1728, 0, "k_conv_valu"), ((12, 12, 12), 300, 8, 8, 1728, 1, "k_conv_valu"),
+    ((20, 20), 8, 8, 16, 324, 0, "k_layer_tiny"), ((20, 20), 8, 8, 16, 325, 0, "k_conv_valu"), ((20, 20), 256, 8, 16, 400, 0, "k_layer_tiny"),
+    ((45, 45), 8, 1, 12, 731, 0, "k_layer_tiny"), ((45, 45), 8, 1, 12, 733, 0, "k_conv_valu"), ((45, 45), 64, 1, 12, 2025, 0, "k_layer_tiny"),
+    ((45, 45), 1024, 1, 8, 100, 1, "k_layer_tiny")])
+def test_samples_of_unequal_rows(ext, batch, c_in, c_out, rich, rows, kernel):
+    """The richest sample is what the launch waits for: one of `rich` rows among others of `rows`, the general path's bits."""
+    n = int(np.prod(ext))
+    lin = np.concatenate([np.arange(b * n, b * n + (rich if b == batch // 2 else rows)) for b in range(batch)])
+    coords = np.stack(np.unravel_index(lin, (batch, *ext)), 1).astype(np.int32)
+    rng = np.random.default_rng(rich)
+    feats = rng.integers(1, 4, size=(len(coords), c_in)).astype(np.float32)
+    w = rng.integers(-2, 3, size=(3 ** len(ext), c_in, c_out)).astype(np.float32)
+    c, f, t = gpu(coords, feats, w)
+    print(ext, batch, c_in, c_out, len(coords), flush=True)
+    gc, gf, nnz = scnn.sparse_conv_fwd(ext, batch, c, f, (3,) * len(ext), t, rho_up=0.3, relu=True, pool=True)
+    assert scnn.last_conv_kernel() == kernel
+    scnn.set_conv_path(1)
+    try:
+        gc1, gf1, nnz1 = scnn.sparse_conv_fwd(ext, batch, c, f, (3,) * len(ext), t, rho_up=0.3, relu=True, pool=True)
+    finally:
+        scnn.set_conv_path(0)
+    assert torch.equal(gc, gc1) and torch.equal(gf, gf1) and torch.equal(nnz, nnz1)
+
+
 @pytest.mark.parametrize("pool", [False, True])
 @pytest.mark.parametrize("batch", [1, 5])
 def test_capacities_and_counts(batch, pool):
