@@ -59,8 +59,14 @@ __host__ __device__ inline TinyLayout tiny_layout(const Geom& g, int c_in, int c
 //   300, one occupied: 12^3, 4 -> 8 (1.5 M) 63 / 69, half of it (746 k) 60 / 51; 8^3, 8 -> 8 (885 k) 44 / 45; all half occupied,
 //     28 x 28, 8 -> 8 (226 k on average) 68 / 57, 6^3, 8 -> 16, 1000 of them (373 k) 121 / 139
 // Still on the slower side: layers of 16 k entries and more with some 100 k products and more, where the general path is up to
-// 1.3 times as fast, for one sample and where one of 64 and more is rich.
+// 1.3 times as fast, for one sample and where one of 64 and more is rich.  Many samples are many rounds of workgroups, of which one without a row still loads
+// the weights and passes the barriers.  Workgroups of 1024 threads (kTinyWide), 45 x 45, 1 -> 8, ten rows a sample, 1024 / 1536 /
+// 4096 / 262144 samples 55 / 61 / 125 / 5046 against 44 / 63 / 160 / 11761; of 256 threads, 28 x 28, 1 -> 8, one row a sample,
+// 4096 / 131072 / 262144 105 / 6988 / 3898 against 55 / 1565 / 3179, a row in one sample of fifty 80 / 6022 / 1506 against 46 /
+// 1095 / 2244; 8 x 8, 8 -> 16 (1152 weights), 4096 / 16384 / 65536 69 / 171 / 575 against 58 / 186 / 667, one row a sample
+// 117 / 408 / 1660 against 79 / 290 / 1111.
 constexpr long long kTinyProducts = 400000, kTinyEntries = 24576;
+constexpr size_t kTinyWide = 40 * 1024;  // LDS from which on four workgroups do not share a CU: all the threads it takes, then
 bool layer_tiny_shape(const Geom& g, int c_in, int c_out) {
     return c_in <= kTinyCin && c_out <= kTinyCout && g.T <= kTinyTaps && g.N <= kTinyMaxSites &&
            g.N * c_out <= kTinyEntries && tiny_layout(g, c_in, c_out).total <= kTinyLds;
@@ -70,7 +76,9 @@ bool layer_tiny_pays(const Geom& g, int c_in, int c_out, long long rows) {
     const long long richest = (rows < g.N ? rows : g.N) * row;
     if (g.batch < 256)
         return richest <= kTinyProducts && (g.batch == 1 || g.batch >= 64 || richest + 15 * g.N * c_out <= 470000);
-    return richest <= 750000 && rows * row <= 300000ll * g.batch;
+    if (richest > 750000 || rows * row > 300000ll * g.batch) return false;
+    if (g.batch > 4096 && row > 1000 && rows < g.batch / 4) return false;
+    return tiny_layout(g, c_in, c_out).total > kTinyWide ? g.batch <= 1024 : (long long)g.batch * g.Wps <= 1ll << 21;
 }
 
 // Exclusive sums of the popcounts of up to 64 words (lane i: the words before i); total: all of them.  (whole wave)
@@ -493,7 +501,7 @@ hipError_t launch_layer_tiny(const Geom& g, const Geom& gp, const int32_t* coord
     const size_t lds = tiny_layout(g, c_in, c_out).total;
     const long long stage_rows = pool ? gp.N : g.N;  // (at most g.N)
     // Few samples leave most of the chip idle and are done when their one workgroup is: all the waves a unit takes.
-    const bool wide = g.batch <= device_cu_count() || lds > 40 * 1024;
+    const bool wide = g.batch <= device_cu_count() || lds > kTinyWide;
     hipError_t e;
 #define SCNN_TINY(NT_, CI_, OCB_)                                                                                        \
     e = launch_tiny_t<NT_, CI_, OCB_>(g, lds, s, gp, coords, feats, n_imm, n_dev, c_in, w, bias, c_out, k, mode, relu, pool, \

@@ -69,7 +69,8 @@ def test_which_layers_it_takes(ext, batch, c_in, c_out, rows, kernel):
     ((12, 12, 12), 8, 8, 8, 1728, 0, "k_conv_valu"), ((12, 12, 12), 64, 8, 8, 1728, 0, "k_conv_valu"), ((12, 12, 12), 300, 8, 8, 1728, 1, "k_conv_valu"),
     ((20, 20), 8, 8, 16, 324, 0, "k_layer_tiny"), ((20, 20), 8, 8, 16, 325, 0, "k_conv_valu"), ((20, 20), 256, 8, 16, 400, 0, "k_layer_tiny"),
     ((45, 45), 8, 1, 12, 731, 0, "k_layer_tiny"), ((45, 45), 8, 1, 12, 733, 0, "k_conv_valu"), ((45, 45), 64, 1, 12, 2025, 0, "k_layer_tiny"),
-    ((45, 45), 1024, 1, 8, 100, 1, "k_layer_tiny")])
+    ((45, 45), 1024, 1, 8, 100, 1, "k_layer_tiny"), ((45, 45), 1025, 1, 8, 100, 1, "k_conv_valu"), ((28, 28), 5000, 1, 8, 100, 1, "k_layer_tiny"),
+    ((3, 3), 5000, 8, 16, 9, 0, "k_conv_valu"), ((3, 3), 5000, 8, 16, 9, 1, "k_layer_tiny")])
 def test_samples_of_unequal_rows(ext, batch, c_in, c_out, rich, rows, kernel):
     """The richest sample is what the launch waits for: one of `rich` rows among others of `rows`, the general path's bits."""
     n = int(np.prod(ext))
