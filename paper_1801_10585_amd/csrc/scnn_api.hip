@@ -272,6 +272,7 @@ struct ConvWs {
     long long cand_cap, tiles_cap, pool_cap;
     int c_out_pad;
     bool tiny;  // a workgroup a sample computes the layer whole
+    long long tiny_cap;  // rows that its staging area holds
     unsigned* tiny_lin;
     float* tiny_feats;
     TinySample* tiny_info;
@@ -337,15 +338,19 @@ static void carve_conv(void* base, const Geom& g, const Geom& gp, long long nnz_
     w->tmp_coords = c.take<int32_t>(pool ? (size_t)cand_cap * (1 + g.ndim) : 0);
     w->tmp_feats = c.take<float>(pool ? (size_t)cand_cap * c_out : 0);
     w->pool_key = c.take<long long>(pool ? w->pool_cap : 0);
-    // (the staging area whatever the number of rows and the fused steps, so that a workspace asked for with more rows serves
-    // fewer, and one asked for with pooling a call without)
-    const bool tiny_shape = layer_tiny_shape(g, c_in, c_out);
-    w->tiny = tiny_shape && g_conv_path == 0 && w->kernel == ConvKernel::kValu && layer_tiny_pays(g, c_in, c_out, nnz_in);
-    const size_t staged = tiny_shape && g.batch > 1 ? (size_t)g.batch * g.N : 0;
-    w->tiny_lin = c.take<unsigned>(staged);
-    w->tiny_feats = c.take<float>(staged * c_out);
-    w->tiny_info = c.take<TinySample>(staged ? g.batch : 0);
-    w->total = c.total();
+    // The staging area of small samples lies over the general path's buffers, which such a call does not use: where it does not
+    // fit (a cand_capacity far below what the rows can reach) the general path takes the layer.  As an area of its own, a row for
+    // every site, 4096 samples of 45 x 45 with ten rows each, 1 -> 8 channels, asked for 391 MB instead of 92.
+    const size_t total = c.total();
+    Carver t(base);
+    const long long staged = g.batch > 1 ? default_cand_bound(g, nnz_in) : 0;
+    w->tiny_cap = staged;
+    w->tiny_lin = t.take<unsigned>(staged);
+    w->tiny_feats = t.take<float>((size_t)staged * c_out);
+    w->tiny_info = t.take<TinySample>(staged ? g.batch : 0);
+    w->tiny = g_conv_path == 0 && w->kernel == ConvKernel::kValu && layer_tiny_shape(g, c_in, c_out) &&
+              layer_tiny_pays(g, c_in, c_out, nnz_in) && t.total() <= total;
+    w->total = total;
 }
 
 static int check_conv_sizes(const Geom& g, long long nnz_in, int c_in, int c_out, long long* cand_cap) {
@@ -434,8 +439,8 @@ static int conv_fwd_impl(int ndim, const int32_t* extent, int batch, const int32
     if (ws.tiny) {
         for (int i = 0; i < kConvStage; ++i) timer.mark();  // (all of it counts as the convolution's stage)
         SCNN_TRY(launch_layer_tiny(g, gp, in_coords, in_feats, nnz_in, (const long long*)nnz_in_dev, c_in, w, bias, c_out, k,
-                                   topk_mode, relu, pool, ws.cand_cap, ws.tiny_lin, ws.tiny_feats, ws.tiny_info, out_coords,
-                                   out_feats, out_capacity, (long long*)nnz_out, s));
+                                   topk_mode, relu, pool, ws.cand_cap, ws.tiny_cap, ws.tiny_lin, ws.tiny_feats, ws.tiny_info,
+                                   out_coords, out_feats, out_capacity, (long long*)nnz_out, s));
         g_last_conv_kernel = "k_layer_tiny";
         timer.done();
         return SCNN_OK;

@@ -558,16 +558,16 @@ struct TinySample {  // what a sample's workgroup leaves behind
     int rows;        // output rows
     int cands;       // candidate sites
     unsigned flags;  // SCNN_FLAG_*
-    unsigned unused;
+    unsigned first;  // where they lie in the staging area
 };
 // Layers that one workgroup a sample computes whole: can it, and is it the faster way for so many input rows.  The staging
-// area (batch > 1) is of as many rows as the grid has sites.
+// area (batch > 1) holds as many rows as the input can reach sites: stage_cap.
 bool layer_tiny_shape(const Geom& g, int c_in, int c_out);
 bool layer_tiny_pays(const Geom& g, int c_in, int c_out, long long rows);
 hipError_t launch_layer_tiny(const Geom& g, const Geom& gp, const int32_t* coords, const float* feats, long long n_imm,
                              const long long* n_dev, int c_in, const float* w, const float* bias, int c_out, long long k,
-                             int mode, int relu, int pool, long long cand_cap, unsigned* stage_lin, float* stage_feats,
-                             TinySample* info, int32_t* out_coords, float* out_feats, long long out_capacity,
+                             int mode, int relu, int pool, long long cand_cap, long long stage_cap, unsigned* stage_lin,
+                             float* stage_feats, TinySample* info, int32_t* out_coords, float* out_feats, long long out_capacity,
                              long long* nnz_out, hipStream_t s);
 
 // scnn_bwd.hip

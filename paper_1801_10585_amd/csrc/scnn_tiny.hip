@@ -133,7 +133,7 @@ __global__ __launch_bounds__(NT) void k_layer_tiny(Geom g, Geom gp, const int32_
                                                    const float* __restrict__ w, const float* __restrict__ bias, int c_out,
                                                    long long k, int mode, int relu, int pool, long long cand_cap,
                                                    unsigned* __restrict__ stage_lin, float* __restrict__ stage_feats,
-                                                   long long stage_rows, TinySample* __restrict__ info,
+                                                   long long stage_cap, TinySample* __restrict__ info,
                                                    int32_t* __restrict__ out_coords, float* __restrict__ out_feats,
                                                    long long out_capacity, long long* __restrict__ nnz_out) {
     extern __shared__ __align__(16) char s_mem[];
@@ -307,8 +307,12 @@ __global__ __launch_bounds__(NT) void k_layer_tiny(Geom g, Geom gp, const int32_
     __syncthreads();
 
     // ---- output rows
-    const long long first = g.batch == 1 ? 0 : (long long)b * stage_rows;
-    const long long room = g.batch == 1 ? (overflow ? 0 : out_capacity) : stage_rows;
+    // Several samples: a sample has at most as many rows as its input rows reach sites and as there are sites, so the samples
+    // before it take at most min(their rows * taps, their sites) of the staging area.  (Rows that are not sorted can make the
+    // ranges overlap: the room keeps the writes inside.)
+    const long long at_rows = s_range[0] * T, at_sites = (long long)b * g.N;
+    const long long first = g.batch == 1 ? 0 : (at_rows < at_sites ? at_rows : at_sites);
+    const long long room = g.batch == 1 ? (overflow ? 0 : out_capacity) : stage_cap - first;
     float* const dst = g.batch == 1 ? out_feats : stage_feats + first * c_out;
     const bool vec = (c_out & 3) == 0 && ((size_t)dst & 15) == 0;
     // row o of the sample: site lin of the output grid go, v its channels
@@ -391,7 +395,7 @@ __global__ __launch_bounds__(NT) void k_layer_tiny(Geom g, Geom gp, const int32_
     }
     if (tid != 0) return;
     if (g.batch > 1) {
-        info[b] = TinySample{(int)rows, (int)n_cand, s_flags, 0u};
+        info[b] = TinySample{(long long)rows < room ? (int)rows : (int)room, (int)n_cand, s_flags, (unsigned)first};
         return;
     }
     unsigned f = s_flags;
@@ -411,10 +415,9 @@ __global__ __launch_bounds__(NT) void k_layer_tiny(Geom g, Geom gp, const int32_
 constexpr int kTinyEmitBlocks = 2048;
 __global__ __launch_bounds__(256) void k_tiny_emit(Geom go, int channels, const TinySample* __restrict__ info,
                                                    const unsigned* __restrict__ stage_lin,
-                                                   const float* __restrict__ stage_feats, long long stage_rows,
-                                                   long long cand_cap, int32_t* __restrict__ out_coords,
-                                                   float* __restrict__ out_feats, long long out_capacity,
-                                                   long long* __restrict__ nnz_out) {
+                                                   const float* __restrict__ stage_feats, long long cand_cap,
+                                                   int32_t* __restrict__ out_coords, float* __restrict__ out_feats,
+                                                   long long out_capacity, long long* __restrict__ nnz_out) {
     __shared__ unsigned long long s_rows[4], s_cands[4];
     __shared__ unsigned s_flags[4];
     const int per = (go.batch + (int)gridDim.x - 1) / (int)gridDim.x;
@@ -463,8 +466,8 @@ __global__ __launch_bounds__(256) void k_tiny_emit(Geom go, int channels, const 
     const bool vec = (channels & 3) == 0 && ((size_t)out_feats & 15) == 0;
     for (int b = first; b < last; ++b) {
         const int rows = info[b].rows;
+        const size_t at = info[b].first;
         const int room = base + rows <= out_capacity ? rows : (base < out_capacity ? (int)(out_capacity - base) : 0);
-        const size_t at = (size_t)b * stage_rows;
         for (int r = threadIdx.x; r < room; r += 256) {
             int c0, c1, c2;
             site_of(go, stage_lin[at + r], c0, c1, c2);
@@ -494,18 +497,17 @@ static hipError_t launch_tiny_t(const Geom& g, size_t lds, hipStream_t s, Args..
 
 hipError_t launch_layer_tiny(const Geom& g, const Geom& gp, const int32_t* coords, const float* feats, long long n_imm,
                              const long long* n_dev, int c_in, const float* w, const float* bias, int c_out, long long k,
-                             int mode, int relu, int pool, long long cand_cap, unsigned* stage_lin, float* stage_feats,
-                             TinySample* info, int32_t* out_coords, float* out_feats, long long out_capacity,
+                             int mode, int relu, int pool, long long cand_cap, long long stage_cap, unsigned* stage_lin,
+                             float* stage_feats, TinySample* info, int32_t* out_coords, float* out_feats, long long out_capacity,
                              long long* nnz_out, hipStream_t s) {
     const int ocb = c_out <= 8 ? 8 : 16;
     const size_t lds = tiny_layout(g, c_in, c_out).total;
-    const long long stage_rows = pool ? gp.N : g.N;  // (at most g.N)
     // Few samples leave most of the chip idle and are done when their one workgroup is: all the waves a unit takes.
     const bool wide = g.batch <= device_cu_count() || lds > kTinyWide;
     hipError_t e;
 #define SCNN_TINY(NT_, CI_, OCB_)                                                                                        \
     e = launch_tiny_t<NT_, CI_, OCB_>(g, lds, s, gp, coords, feats, n_imm, n_dev, c_in, w, bias, c_out, k, mode, relu, pool, \
-                                      cand_cap, stage_lin, stage_feats, stage_rows, info, out_coords, out_feats,         \
+                                      cand_cap, stage_lin, stage_feats, stage_cap, info, out_coords, out_feats,          \
                                       out_capacity, nnz_out)
 #define SCNN_TINY_OCB(NT_, CI_)                   \
     do {                                          \
@@ -524,8 +526,8 @@ hipError_t launch_layer_tiny(const Geom& g, const Geom& gp, const int32_t* coord
     if (e != hipSuccess || g.batch == 1) return e;
     const Geom& go = pool ? gp : g;
     const unsigned blocks = (unsigned)(g.batch < kTinyEmitBlocks ? g.batch : kTinyEmitBlocks);
-    hipLaunchKernelGGL(k_tiny_emit, dim3(blocks), dim3(256), 0, s, go, c_out, info, stage_lin, stage_feats, stage_rows,
-                       cand_cap, out_coords, out_feats, out_capacity, nnz_out);
+    hipLaunchKernelGGL(k_tiny_emit, dim3(blocks), dim3(256), 0, s, go, c_out, info, stage_lin, stage_feats, cand_cap,
+                       out_coords, out_feats, out_capacity, nnz_out);
     return hipGetLastError();
 }
 

@@ -124,6 +124,38 @@ def test_capacities_and_counts(batch, pool):
         assert np.array_equal(cc[:len(rc)].cpu().numpy(), rc) and np.array_equal(ff[:len(rc)].cpu().numpy(), rf)
 
 
+@pytest.mark.parametrize("pool", [False, True])
+@pytest.mark.parametrize("ext,batch,c_out,rows", [((19, 21), 40, 6, 3), ((45, 45), 9, 8, 40), ((45, 45), 300, 4, 20), ((6, 7, 8), 33, 12, 100)])
+def test_staged_rows_lie_within_the_workspace(ext, batch, c_out, rows, pool):
+    """Capacities from the candidates in use down to where the staged rows no longer fit and the general path takes the layer:
+    samples without a row, with a few and full ones, the bytes past the workspace asked for untouched."""
+    k, n = (3,) * len(ext), int(np.prod(ext))
+    rng = np.random.default_rng(batch)
+    counts = [0 if b % 3 == 0 else n if b == batch - 2 else int(rng.integers(1, rows)) for b in range(batch)]
+    lin = np.concatenate([b * n + np.sort(rng.permutation(n)[:m]) for b, m in enumerate(counts)])
+    coords = np.stack(np.unravel_index(lin, (batch, *ext)), 1).astype(np.int32)
+    feats = rng.integers(1, 4, size=(len(coords), 1)).astype(np.float32)
+    w = rng.integers(-2, 3, size=(3 ** len(ext), 1, c_out)).astype(np.float32)
+    c, f, t = gpu(coords, feats, w)
+    rc, rf = oracle.sparse_conv_fwd(ext, batch, coords, feats, k, w, rho_up=0.3, pool=pool)
+    used = int(scnn.sparse_conv_fwd(ext, batch, c, f, k, t, rho_up=0.3, pool=pool)[2][1])
+    ran = set()
+    for cap in (0, used, max(1, used // 2), 1):
+        need = scnn.sparse_conv_fwd_workspace(ext, batch, len(coords), 1, c_out, k, 2 if pool else 0, cap)
+        room = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        print(ext, batch, len(coords), used, cap, need, flush=True)
+        gc, gf, nnz = scnn.sparse_conv_fwd(ext, batch, c, f, k, t, rho_up=0.3, pool=pool, cand_capacity=cap, workspace=room[:need],
+                                           out_capacity=len(rc), sync=False)
+        ran.add(scnn.last_conv_kernel())
+        assert bool((room[need:] == 0x5A).all())
+        if cap == 0 or cap >= used:
+            assert nnz.cpu().tolist() == [len(rc), used, 0, 0]
+            assert np.array_equal(gc[:len(rc)].cpu().numpy(), rc) and np.array_equal(gf[:len(rc)].cpu().numpy(), rf)
+        else:
+            assert nnz.cpu().tolist()[::2] == [0, 1]
+    assert "k_layer_tiny" in ran
+
+
 @pytest.mark.parametrize("batch", [1, 4])
 def test_bad_rows_are_reported(batch):
     ext, k = (12, 13), (3, 3)

@@ -1,6 +1,7 @@
 """CPU-only checks of the C-ABI library: it loads, exports what the header declares,
 and rejects bad arguments on the host before anything is launched."""
 import ctypes
+import math
 import os
 import re
 
@@ -116,6 +117,18 @@ def test_host_argument_checks_of_the_widening_entry_points():
     assert L.prune_weights(fake, fake, 10, ctypes.c_float(-1.0), fake, None) == -1
     assert L.prune_weights(None, fake, 10, ctypes.c_float(0.1), fake, None) == -1
     assert L.prune_weights(fake, fake, 10, ctypes.c_float(0.1), None, None) == -1
+
+
+@pytest.mark.parametrize("ext,batch,rows,c_out", [((45, 45), 4096, 10, 8), ((32, 64), 1000, 20, 12), ((28, 28), 2, 784, 16), ((10, 10, 10), 300, 5, 1)])
+def test_workspace_of_small_samples_follows_the_capacity(ext, batch, rows, c_out):
+    """Per candidate site of the capacity (a tile of 128 more for every sample): responses, a slot of the selection twice their
+    size and 16 bytes; bits and counts per 64 sites; the rest is small, whatever the grid's number of sites."""
+    for taps_used in (2, 3 ** len(ext)):
+        cap = min(batch * rows * taps_used, batch * math.prod(ext))
+        need = scnn.sparse_conv_fwd_workspace(ext, batch, batch * rows, 1, c_out, (3,) * len(ext), 1, cap)
+        tiles = -(-cap // 128) + batch
+        words = batch * -(-math.prod(ext) // 64)
+        assert 0 < need <= tiles * 128 * (12 * c_out + 16) + 64 * (words + batch * c_out) + (1 << 20)
 
 
 def test_measurement_switches_reject_unknown_modes():
