@@ -522,8 +522,9 @@ static hipError_t launch_conv_quad_t(const Geom& g, const unsigned long long* oc
                                      const int* cand_start, const int* tile_start, Counters* ctr, float* resp, int cus,
                                      hipStream_t s) {
     const size_t lds = (size_t)quad_lds_words(C_IN, g.T) * 4 * kQuadWaves;
-    hipError_t e = hipFuncSetAttribute((const void*)k_conv_quad<C_IN, QPM, ACC64>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    // (the same for every filter: another thread's launch may lie between this and ours)
+    hipError_t e = hipFuncSetAttribute((const void*)k_conv_quad<C_IN, QPM, ACC64>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       quad_lds_words(C_IN, kQuadMaxTaps) * 4 * kQuadWaves);
     if (e != hipSuccess) return e;
     // one workgroup (four waves) per SIMD wave slot of every CU, as far as the CU's 160 KiB of LDS hold them (every
     // workgroup must be resident: they are persistent); a multiple of kXcds: one span of tiles per XCD

@@ -19,6 +19,7 @@
 namespace scnn {
 
 constexpr int kSplitSites = 256;             // candidate sites per unit of work (a workgroup of four waves)
+constexpr int kSplitMaxTaps = 32;            // per filter (one bit each in a site's neighbour pattern)
 constexpr int kSplitSteal = 2;               // XCDs after its own that a workgroup helps once its own has nothing left
 constexpr int kSplitChunkMin = 32;           // shortest chunk (units) of the tile order
 constexpr int kSplitChunks = 8;              // chunks per XCD
@@ -458,7 +459,7 @@ bool conv_split_supported(const Geom& g, int c_in, int c_out, long long nnz_in) 
     const bool shape = (c_in == 16 || c_in == 24 || c_in == 32 || c_in == 40 || c_in == 48 || c_in == 64 || c_in == 96 ||
                         c_in == 128) &&
                        c_out >= 1 && c_out <= kQuadMaxCout;
-    return g.T <= 32 && shape && nnz_in > 0 && nnz_in * round_up(c_in, 32) * 6 < (1ll << 31);
+    return g.T <= kSplitMaxTaps && shape && nnz_in > 0 && nnz_in * round_up(c_in, 32) * 6 < (1ll << 31);
 }
 
 template <int NCH, int NB, int ACC64, int K3>
@@ -469,8 +470,9 @@ static hipError_t launch_conv_split_t(const Geom& g, const unsigned long long* o
                                       const int* cand_start, const int* tile_start, Counters* ctr, float* resp, int cus,
                                       hipStream_t s) {
     const size_t lds = (size_t)split_lds_words(g.T, NCH, NB) * 4;
+    // (the same for every filter: another thread's launch may lie between this and ours)
     hipError_t e = hipFuncSetAttribute((const void*)k_conv_quad_split<NCH, NB, ACC64, K3>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, split_lds_words(kSplitMaxTaps, NCH, NB) * 4);
     if (e != hipSuccess) return e;
     // as many workgroups as run at once (they are persistent); a multiple of kXcds: one span of units per XCD
     int per_cu = split_waves_per_simd(NB, ACC64);

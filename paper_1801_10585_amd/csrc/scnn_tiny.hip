@@ -486,9 +486,9 @@ __global__ __launch_bounds__(256) void k_tiny_emit(Geom go, int channels, const 
 
 template <int NT, int CI, int OCB, typename... Args>
 static hipError_t launch_tiny_t(const Geom& g, size_t lds, hipStream_t s, Args... args) {
-    if (lds > 64 * 1024) {
+    if (lds > 64 * 1024) {  // (the same for every layer: another thread's launch may lie between this and ours)
         hipError_t e = hipFuncSetAttribute((const void*)k_layer_tiny<NT, CI, OCB>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds);
+                                           (int)kTinyLds);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((k_layer_tiny<NT, CI, OCB>), dim3((unsigned)g.batch), dim3(NT), lds, s, g, args...);
