@@ -98,18 +98,22 @@ def test_backward_of_eight_output_channels_by_size(ext, ksize, density, g_densit
     assert np.array_equal(data.cpu().numpy(), rd) and np.array_equal(filt.cpu().numpy(), rw)
 
 
-@pytest.mark.parametrize("ext,batch,ksize,density,cap", [
-    ((37, 40, 65), 1, (3, 3, 3), 0.08, 3071 * 128), ((37, 40, 65), 4, (3, 3, 3), 0.3, 3069 * 128), ((37, 40, 65), 4, (3, 3, 3), 0.3, 0),
-    ((5, 150, 130), 2, (1, 3, 9), 0.2, 0), ((60, 70, 15), 3, (1, 1, 31), 0.2, 0), ((2, 200, 150), 1, (9, 1, 3), 0.9, 0), ((11, 12, 13), 150, (3, 3, 3), 0.6, 0)])
+@pytest.mark.parametrize("ext,batch,ksize,density,cap,tiles", [
+    ((37, 40, 65), 1, (3, 3, 3), 0.08, 3071 * 128, 753), ((37, 40, 65), 4, (3, 3, 3), 0.3, 0, 3011), ((44, 47, 61), 4, (3, 3, 3), 0.1, 3068 * 128, 3072),
+    ((44, 47, 61), 4, (3, 3, 3), 0.1, 3069 * 128, 3073), ((44, 47, 61), 4, (3, 3, 3), 0.1, 0, 3947),
+    ((5, 150, 130), 2, (1, 3, 9), 0.2, 0, 1526), ((60, 70, 15), 3, (1, 1, 31), 0.2, 0, 1480), ((2, 200, 150), 1, (9, 1, 3), 0.9, 0, 470),
+    ((11, 12, 13), 150, (3, 3, 3), 0.6, 0, 2161)])
 @pytest.mark.parametrize("c_out", [1, 6, 8])
-def test_eight_input_channels_four_lanes_a_site(ext, batch, ksize, density, cap, c_out):
-    """More than nine taps on 257 tiles of capacity and more, up to 3072 and past them; few and many tiles in use, the tiles'
-    ends, samples of different sizes: small whole numbers, exact."""
+def test_eight_input_channels_four_lanes_a_site(ext, batch, ksize, density, cap, tiles, c_out):
+    """More than nine taps on 257 tiles of capacity and more, up to 3072, where four lanes share a site, and past them, where each
+    has a thread: few and many tiles in use, the tiles' ends, samples of different sizes: small whole numbers, exact."""
     rng = np.random.default_rng(c_out + ext[1])
     coords = random_sparse_sites(rng, ext, batch, density)
     coords = coords[(coords[:, 0] % 2 == 0) | (rng.random(len(coords)) < 0.2)]
     feats = rng.integers(-3, 4, size=(coords.shape[0], 8)).astype(np.float32)
     t = int(np.prod(ksize))
+    bound = min(batch * int(np.prod(ext)), len(coords) * t)
+    assert -(-(min(cap, bound) if cap else bound) // 128) + batch == tiles
     w = (rng.integers(-3, 4, size=(t, 8, c_out)) * (rng.random((t, 1, 1)) < 0.8)).astype(np.float32)
     bias = rng.integers(-2, 3, size=c_out).astype(np.float32)
     oc, of, n = scnn.sparse_conv_fwd(ext, batch, *_dev(coords, feats), ksize, *_dev(w, bias), cand_capacity=cap)

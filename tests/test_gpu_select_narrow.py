@@ -110,8 +110,8 @@ def test_compaction_of_seventeen_to_thirty_two_channels(ext, density, cap, c_out
 @pytest.mark.parametrize("ext,batch,density,rho,cap", [((20, 21, 22), 17, 0.03, 0.2, 0), ((20, 21, 22), 37, 0.03, 0.2, 0), ((3, 5), 2, 0.5, 1.0, 0),
                                                        ((9, 10, 11), 40, 0.2, 1.0, 0), ((20, 21, 22), 17, 0.0005, 1.0, 0), ((120, 150), 13, 0.2, 0.3, 0)])
 def test_compaction_of_wide_layers_without_marks(ext, batch, density, rho, cap, c_out, mode, relu, pool):
-    """Counted first, where nothing is selected and above 2048 tiles of capacity, and by look-back: samples without rows, one
-    tile and many a workgroup, a small output.  Small whole numbers, the oracle's rows."""
+    """Counted first, where nothing is selected, and by look-back: samples without rows, a tile a workgroup and none, a small
+    output.  Small whole numbers, the oracle's rows."""
     rng = np.random.default_rng(c_out + batch)
     k = (3,) * len(ext)
     coords = random_sparse_sites(rng, ext, batch, density)
@@ -131,3 +131,25 @@ def test_compaction_of_wide_layers_without_marks(ext, batch, density, rho, cap, 
                              sync=False)
         assert int(out[2][0]) == len(rc) and int(out[2][2]) == 2 and np.array_equal(out[0][:64].cpu().numpy(), rc[:64])
         assert np.array_equal(out[1][:64].cpu().numpy(), rf[:64]) and bool((out[0][64:] == -7).all()) and bool((out[1][64:] == -7).all())
+
+
+@pytest.mark.parametrize("c_out,mode,relu,pool", [(33, scnn.ABS, False, False), (64, scnn.SIGNED, True, False), (50, scnn.ABS, True, True)])
+@pytest.mark.parametrize("ext,batch,density,rho", [((20, 21, 22), 60, 0.03, 0.2), ((20, 21, 22), 60, 0.03, 0.5), ((110, 120), 26, 0.3, 0.3), ((60, 60, 80), 1, 0.03, 1.0),
+                                                   ((64, 66, 70), 2, 0.02, 1.0)])
+def test_counted_compaction_of_several_tiles_a_workgroup(ext, batch, density, rho, c_out, mode, relu, pool):
+    """The same from 1025 tiles in use on, where workgroups own two tiles and more and the last ones fewer: selecting layers of
+    more than 2048 tiles of capacity (many equal scores, cut inside a tile) and layers that select nothing."""
+    rng = np.random.default_rng(c_out + batch)
+    coords = random_sparse_sites(rng, ext, batch, density)
+    coords = coords[(coords[:, 0] % 5 != 1) | (batch < 5)]
+    n_sites = int(np.prod(ext))
+    assert rho == 1.0 or (n_sites <= 32768 and min(batch * n_sites, len(coords) * 3 ** len(ext)) // 128 + batch > 2048)
+    feats = rng.integers(1, 4, size=(len(coords), 2)).astype(np.float32)
+    w = rng.integers(-2, 3, size=(3 ** len(ext), 2, c_out)).astype(np.float32)
+    w[:, :, :6] *= rng.random((3 ** len(ext), 1, 1)) < 0.3  # (rows whose first channels are zero)
+    rc, rf = oracle.sparse_conv_fwd(ext, batch, coords, feats, (3,) * len(ext), w, rho_up=rho, topk_mode=mode, relu=relu, pool=pool, threads=8)
+    gc, gf, n = scnn.sparse_conv_fwd(ext, batch, *(torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (coords, feats)), (3,) * len(ext),
+                                     torch.from_numpy(w).cuda(), rho_up=rho, topk_mode=mode, relu=relu, pool=pool)
+    print(ext, batch, c_out, len(coords), n.tolist(), flush=True)
+    assert int(n[1]) > 1024 * 128 and int(n[2]) == 0
+    assert np.array_equal(gc.cpu().numpy(), rc) and np.array_equal(gf.cpu().numpy(), rf)
