@@ -27,9 +27,10 @@
 // every tile are known before the last pass, a scan gives each tile its first
 // output row, and the write pass streams with no ordering between tiles.  Other
 // layers of at most 32 channels count and write in two launches from some size
-// on (narrow_pair_tiles), and so do wider ones where nothing is selected or from
-// kCountedTiles on.  Elsewhere tiles are taken in order and a tile learns its
-// first output row by looking back at its predecessors.
+// on (narrow_pair_tiles), and so do wider ones from kCountedTiles on, from
+// kCountedPlainTiles on where nothing is selected.  Elsewhere tiles are taken
+// in order and a tile learns its first output row by looking back at its
+// predecessors.
 #include <type_traits>
 
 #include "scnn_internal.h"
@@ -2043,7 +2044,7 @@ __global__ __launch_bounds__(256) void k_select_emit_narrow(Geom g, int channels
     }
 }
 
-constexpr long long kCountedTiles = 2048;
+constexpr long long kCountedTiles = 2048, kCountedPlainTiles = 256;
 hipError_t launch_select_write(const Geom& g, int channels, int mode, int relu, const int* cand_start,
                                const int* tile_start, const unsigned* cand_lin, const float* resp,
                                const ColState* cols, unsigned long long* tile_state, long long tiles_cap,
@@ -2079,11 +2080,12 @@ hipError_t launch_select_write(const Geom& g, int channels, int mode, int relu, 
         // (streaming: four workgroups per CU; by look-back three measured best, and four cost it 5 %, which only the
         // rare launch that was given tile_base and cannot use it pays)
         if (tile_base) blocks = tiles_cap < 1 ? 1 : (tiles_cap > cus * 4 ? cus * 4 : tiles_cap);
-        // Without the selection's marks: counted first where nothing is selected, a row being settled by its first channel
-        // then, and on layers of many tiles (whole calls, 32 -> 64 channels on surfaces, look-back against counted: plain,
-        // 16^3 x 4 72 -> 69 us, 32^3 x 2 83 -> 78, 53 x 75 x 94 x 3 148 -> 131; a tenth selected, 32^3 x 2, 200 tiles, 99 -> 112, x 6, 570 tiles (1540 of capacity), 142 -> 147,
-        // x 16, 1500 tiles, 216 -> 209, 33 channels 198 -> 180)
-        const bool ranged = !tile_base && (keeps_all || tiles_cap > kCountedTiles);
+        // Without the selection's marks: counted first on layers of many tiles, and where nothing is selected, a row being settled
+        // by its first channel then, on all but small ones.  Whole calls, us, look-back against counted: plain, 33 to 64 channels,
+        // 15 / 65 / 134 / 199 / 257 / 396 / 794 tiles of capacity, 34 / 38 / 46 / 51 / 53 / 69 / 85 against 36 / 40 / 47 / 51 / 53 /
+        // 66 / 75 (the launch that counts is 4 us), 53 x 75 x 94 x 3 148 against 131; a tenth selected, 32 -> 64 on surfaces, 32^3 x 2,
+        // 200 tiles, 99 -> 112, x 6, 570 tiles (1540 of capacity), 142 -> 147, x 16, 1500 tiles, 216 -> 209, 33 channels 198 -> 180
+        const bool ranged = !tile_base && (tiles_cap > kCountedTiles || (keeps_all && tiles_cap > kCountedPlainTiles));
         if (ranged) blocks = tiles_cap < 1 ? 1 : (tiles_cap > cus * 4 ? cus * 4 : tiles_cap);
         const unsigned* counts = (const unsigned*)tile_state;
 #define SCNN_WRITE64(RANGED)                                                                                           \

@@ -110,8 +110,8 @@ def test_compaction_of_seventeen_to_thirty_two_channels(ext, density, cap, c_out
 @pytest.mark.parametrize("ext,batch,density,rho,cap", [((20, 21, 22), 17, 0.03, 0.2, 0), ((20, 21, 22), 37, 0.03, 0.2, 0), ((3, 5), 2, 0.5, 1.0, 0),
                                                        ((9, 10, 11), 40, 0.2, 1.0, 0), ((20, 21, 22), 17, 0.0005, 1.0, 0), ((120, 150), 13, 0.2, 0.3, 0)])
 def test_compaction_of_wide_layers_without_marks(ext, batch, density, rho, cap, c_out, mode, relu, pool):
-    """Counted first, where nothing is selected, and by look-back: samples without rows, a tile a workgroup and none, a small
-    output.  Small whole numbers, the oracle's rows."""
+    """Counted first, where nothing is selected on more than 256 tiles of capacity, and by look-back: samples without rows, a tile a
+    workgroup and none, a small output.  Small whole numbers, the oracle's rows."""
     rng = np.random.default_rng(c_out + batch)
     k = (3,) * len(ext)
     coords = random_sparse_sites(rng, ext, batch, density)
