@@ -1172,15 +1172,18 @@ hipError_t launch_conv_valu(const Geom& g, const unsigned long long* occ, const 
     // layer whose workspace is that much larger than its data runs slower on it, a large layer saves a launch).
     const bool stream_only = tiles_cap * n_chunks > kValuStreamOnlyItems;
     const bool both = !stream_only && tiles_cap * n_chunks > kValuLatencyItems;
-    // .. or, with items of one block, more: four channels a gather, or sixteen input channels and more, 27 taps, where sites
-    // miss at least half of their neighbours (a wave skips the taps that none of its rows has).  Surfaces and level sets of a
-    // tenth and four tenths of the sites, calls, us, against the forms below: 20^3 x 6, 16 -> 16 63 / 67 -> 47 / 61, 4 -> 16
+    // .. or, with items of one block, more, where sites miss at least half of their neighbours (a wave skips the taps that none of
+    // its rows has): four channels a gather, or sixteen input channels and more with a cube of taps.  Surfaces and level sets of
+    // a tenth and four tenths of the sites, calls, us, against the forms below: 20^3 x 6, 16 -> 16 63 / 67 -> 47 / 61, 4 -> 16
     // 47 / 51 -> 41 / 47; 24^3 x 8, 860 tiles, 24 -> 16 96 / 134 -> 83 / 116; 32^3 x 4 16 -> 8 84 / 116 -> 84 / 109; all
     // occupied 78 -> 81 (24^3 x 4, 16 -> 8) and 122 -> 136 (32^3 x 4); 8 -> 16 55 / 63 / 65 -> 52 / 62 / 72; nine taps, 80 x 80
-    // x 12, 16 -> 16, 54 / 61 / 74 -> 57 / 69 / 88.
-    const bool thin = c_out_pad <= kOcBlock && g.T > 9 && (ch == 4 || (ch == 8 && c_in >= 16)) &&
+    // x 12, 16 -> 16, 54 / 61 / 74 -> 57 / 69 / 88.  Four channels a gather gain on every filter (9 to 125 taps 0.98 to 2.0 times
+    // as fast).  With eight, 27 and 125 taps gain 0.94 to 1.4 times; of filters longer one way only some groups of 32 taps are
+    // full: 5 x 3 x 3 0.82 to 1.18, 5 x 5 0.88 to 1.20, 9 x 9 0.86 to 1.33 (56 x 73 x 16, 24 -> 16 182 -> 200 us), 7 x 7 0.89 to 1.25.
+    const bool cube = g.K[0] == g.K[1] && g.K[1] == g.K[2];
+    const bool thin = c_out_pad <= kOcBlock && g.T > 9 && (ch == 4 || (ch == 8 && c_in >= 16 && cube)) &&
                       nnz_in * 2 <= tiles_cap * kTileRows && tiles_cap <= 4 * kValuSmallItems;
-    if ((tiles_cap * n_chunks <= kValuSmallItems || thin) && ch >= 2) {  // cannot hold more than a few hundred tiles
+    if ((tiles_cap * n_chunks <= kValuSmallItems || thin) && ch >= 2) {  // cannot hold more than a thousand tiles
         // One 16-channel block per item where the layer has no more, or where that many workgroups still run at once (two to a
         // compute unit): 40 x 40 x 4, 16 -> 24, 520 items, keeps two blocks
         const long long items = tiles_cap * (c_out_pad / kOcBlock) * (kTileRows / 32);

@@ -36,7 +36,8 @@ def reference(ext, batch, coords, feats, k, w):
     ((60, 70, 15), 2, (1, 1, 31), 8, 5, 0.1, 800, "k_conv_valu"), ((150, 200), 5, (3, 3), 8, 8, 0.3, 1177, "k_conv_valu"),
     # 32-row items of one 16-channel block up to 1024 tiles where sites have few neighbours, else up to 256; of two blocks
     ((50, 50, 53), 1, (3, 3, 3), 16, 16, 0.05, 1024, "k_conv_valu"), ((50, 50, 53), 1, (3, 3, 3), 16, 16, 0.05, 1025, "k_conv_valu"),
-    ((50, 50, 53), 1, (3, 3, 3), 4, 12, 0.05, 1000, "k_conv_valu"), ((30, 30, 36), 1, (3, 3, 3), 16, 16, 0.6, 255, "k_conv_valu"),
+    ((50, 50, 53), 1, (3, 3, 3), 4, 12, 0.05, 1000, "k_conv_valu"),
+    ((40, 41, 40), 1, (5, 5, 5), 24, 16, 0.1, 514, "k_conv_valu"), ((40, 41, 40), 1, (5, 3, 3), 24, 16, 0.1, 514, "k_conv_valu"), ((30, 30, 36), 1, (3, 3, 3), 16, 16, 0.6, 255, "k_conv_valu"),
     ((30, 30, 40), 1, (3, 3, 3), 16, 16, 0.6, 283, "k_conv_valu"), ((60, 61), 1, (3, 3), 24, 24, 0.2, 27, "k_conv_valu"),
     ((60, 61), 4, (5, 5), 12, 33, 0.1, 119, "k_conv_valu"), ((60, 61), 4, (5, 5), 16, 24, 0.1, 119, "k_conv_valu"), ((60, 61), 4, (3, 3), 6, 20, 0.2, 119, "k_conv_valu"),
     # one input channel; the general forms
