@@ -193,3 +193,36 @@ def test_infinities_reach_the_sums_they_belong_to(batch):
         assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][2], got[1][2])
         assert torch.equal(got[0][1].nan_to_num(nan=1e30), got[1][1].nan_to_num(nan=1e30))
         assert not bool(torch.isfinite(got[0][1]).all())
+
+
+@pytest.mark.parametrize("batch", [1, 5])
+def test_two_layers_captured_in_a_graph(batch):
+    """Chained, with device-resident row counts: every replay against call by call, other rows in the same buffers each time."""
+    rng = np.random.default_rng(batch)
+    ext, k, cap = (28, 28), (3, 3), batch * 200
+    w1 = gpu(rng.integers(-2, 3, size=(9, 1, 8)).astype(np.float32))[0]
+    w2 = gpu(rng.integers(-2, 3, size=(9, 8, 16)).astype(np.float32))[0]
+    l1 = scnn.ChainedLayer(ext, batch, cap, 1, k, w1, rho_up=0.2, relu=True, pool=True)
+    l2 = scnn.ChainedLayer(l1.out_extent, batch, l1.out_capacity, 8, k, w2, rho_up=0.3, relu=True)
+    c, f = torch.zeros((cap, 3), dtype=torch.int32, device="cuda"), torch.ones((cap, 1), device="cuda")
+    n = torch.zeros(1, dtype=torch.int64, device="cuda")
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        l2(*l1(c, f, n))
+        assert scnn.last_conv_kernel() == "k_layer_tiny"
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        oc, of, nnz = l2(*l1(c, f, n))
+    for density in (0.15, 0.02, 0.2, 0.0):
+        coords = random_sparse_sites(rng, ext, batch, density)[:cap]
+        c[:len(coords)] = gpu(coords)[0]
+        n.fill_(len(coords))
+        oc.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        c1, f1, _ = scnn.sparse_conv_fwd(ext, batch, c[:len(coords)], f[:len(coords)], k, w1, rho_up=0.2, relu=True, pool=True)
+        c2, f2, n2 = scnn.sparse_conv_fwd((14, 14), batch, c1, f1, k, w2, rho_up=0.3, relu=True)
+        assert nnz.cpu().tolist() == n2.tolist()
+        assert torch.equal(oc[:len(c2)], c2) and torch.equal(of[:len(c2)], f2) and bool((oc[len(c2):] == -1).all())
