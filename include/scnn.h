@@ -42,8 +42,9 @@
  * SCNN_FLAG_BAD_COORD or SCNN_FLAG_UNSORTED set the results of the call are
  * undefined (a row with an out-of-range coordinate is never used as an
  * address, but rows near it, those of its 64-site bitmap word and up to a
- * filter line past it, are then looked up one row off); every access stays
- * inside the caller's arrays.
+ * filter line past it, are then looked up one row off; layers of small samples
+ * can miss the rows of the samples that a misplaced sample index lies between);
+ * every access stays inside the caller's arrays.
  */
 #ifndef SCNN_H_
 #define SCNN_H_
@@ -120,8 +121,8 @@ size_t sparse_conv_fwd_workspace(int ndim, const int32_t* extent, int batch, int
  * roundings of partial sums of that size), which the stated tolerance covers
  * while A stays below about 50 (the r = 128 workload: A around 20);
  * scnn_set_conv_path(1) sums everything in fp64 for data beyond that.  The
- * vector kernels and the quad kernels add in an order fixed by the data alone
- * and are reproducible bit for bit; the pair-list kernel adds its per-tap
+ * vector kernels and the quad kernels add in an order fixed by the data and the
+ * sizes of the call and are reproducible bit for bit; the pair-list kernel adds its per-tap
  * partial sums with LDS atomics in no fixed order, so a run can differ from
  * another in the last bits of the fp64 sum, which survives the rounding to fp32
  * for about one response in 10^8.  Responses that are
@@ -305,8 +306,17 @@ int sparse_conv_bwd(int ndim, const int32_t* extent, int batch, const int32_t* i
  *     Filters of more taps with C_in 16 or a multiple of 32 up to 128 and C_out a
  *     multiple of 16 up to 64: the pair-list kernel, with C_in = 16 on fp32 matrix
  *     cores ("k_conv_mfma").
- *     Everything else takes the vector kernels ("k_conv_valu");
- * 1 = always the vector kernels;
+ *     Everything else takes the vector kernels ("k_conv_valu"), but layers of
+ *     small samples one kernel for the whole layer, from index to output rows, a
+ *     workgroup a sample ("k_layer_tiny"): samples of at most 2048 sites, C_in
+ *     up to 8, C_out up to 16, at most 32 taps, sites * C_out at most 24576,
+ *     where even the richest sample that nnz_in rows can make (as many rows as
+ *     the sample has sites) stays at 400 000 products rows * taps * C_in * C_out
+ *     (C_out counted as 8 or 16; 750 000 from 256 samples on; less for 2 to 63
+ *     samples of many entries), samples are not too many (1024 where they fill
+ *     40 KB of on-chip memory, else some hundred thousand), and cand_capacity is
+ *     not far below what the rows can reach.  Same sums, same result;
+ * 1 = always the vector kernels, never the one for whole layers;
  * 2 = the fp32 quad kernel wherever it takes the shape, whatever the size, else
  *     the pair-list kernel wherever that does;
  * 3 = the pair-list matrix-core kernel where it takes the shape (C_in = 16 or
@@ -325,9 +335,10 @@ int scnn_set_conv_path(int path);
  * thread, every sparse_conv_fwd call records HIP events on its stream at the
  * boundaries of its stages (workspace clear + filter preparation + index build,
  * candidate sites, pair lists, convolution, k-selection, compaction + write,
- * pooling), and every sparse_conv_bwd call at the boundaries of its own
- * (filter preparation + index of the gradient rows, pair lists, adjoint
- * convolution, bp_data write, bp_filter).  scnn_profile_collect waits for
+ * pooling; a layer that "k_layer_tiny" computes whole counts as convolution),
+ * and every sparse_conv_bwd call at the boundaries of its own (filter
+ * preparation + index of the gradient rows, pair lists, adjoint convolution,
+ * bp_data write, bp_filter).  scnn_profile_collect waits for
  * the recorded calls, adds their per-stage milliseconds into stage_ms
  * [scnn_profile_stage_count()] and the number of calls into *calls, then
  * forgets them.  on = 1: every boundary; on = 2: only the two events around

@@ -26,8 +26,9 @@ enum class ConvKernel { kValu, kPair, kPairSplit, kQuad, kSplit };
 // to 128 output channels (a launch per 64) with at most 32 taps; the quad kernel (fp32 matrix cores) eight input
 // channels, small layers, and inputs whose split copy does not fit 31-bit offsets; the pair-list kernel 96 and 128 input
 // channels and filters of more than 32 taps.
-// (Layers of small samples do not come this way: layer_tiny_shape.)  With 8, 16 or 24 input channels the matrix cores pay only on layers of enough tiles (128 or 1024, by shape) with
-// enough output channels; narrower and smaller layers take the vector kernels (fp64 sums).
+// With 8, 16 or 24 input channels the matrix cores pay only on layers of enough tiles (128 or 1024, by shape) with
+// enough output channels; narrower and smaller layers take the vector kernels (fp64 sums), those of small samples the
+// kernel that computes a layer whole (layer_tiny_shape, layer_tiny_pays).
 static ConvKernel conv_kernel_for(const Geom& g, int c_in, int c_out, long long nnz_in, long long tiles_cap) {
     if (g_conv_path == 1) return ConvKernel::kValu;
     // (pair lists of sixteen channels: half of a split chunk would be empty.  125 taps, 96^3, fp32 against split, us:

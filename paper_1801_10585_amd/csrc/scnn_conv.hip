@@ -812,8 +812,8 @@ __global__ __launch_bounds__(256) void k_conv_valu(Geom g, const unsigned long l
     }
 }
 
-// The same kernel shape for the smallest layers (at most a few hundred tiles: the deep, pooled layers of the paper's
-// networks), where 128-row work items would leave most of the chip idle.  Work item = (quarter of a tile = 32 rows,
+// The same kernel shape for the smallest layers (a few hundred tiles: the deep, pooled layers of the paper's
+// networks; narrow ones of up to a thousand), where 128-row work items would leave most of the chip idle.  Work item = (quarter of a tile = 32 rows,
 // block of 32 output channels).  The four waves of the workgroup share the taps (wave w takes taps w, w + 4, ...);
 // A round covers all taps of the chunk for CH input channels, so that a 3^d filter over 24 channels takes three
 // rounds.  CH >= 4: a wave multiplies its taps for all 32 rows and channels on the fp64 matrix cores
