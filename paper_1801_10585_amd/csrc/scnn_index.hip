@@ -597,17 +597,19 @@ __global__ __launch_bounds__(256) void k_cand_dilate(Geom g, const unsigned long
 // loads in flight, and the ballot is the word.
 constexpr int kDilateBatch = 5;  // lines in flight
 constexpr long long kDilateSiteWords = 4096;
-// The form above takes about 0.3 us + 0.2 for every tap of a line, for every line that a word holds part of and every sixteen
-// lines of the filter; this one 1.4 us for every five lines of the filter, 2.1 where 4096 words share the chip.  Calls, the form
-// above less this one, us: 3 x 3 x 3 on 8^3 x 4 / 16^3 x 16 / 32^3 / 32^3 x 8 +5.7 / +1.8 / -0.3 / -2.2, 5 x 5 x 5 +15 / +4.7 /
-// -0.8 / -4.6, 31 x 1 x 1 +0.4 / -4.3 / -8 / -12, 9 x 1 x 1 +2.4 / -0.1 / -1.5 / -3.1; 3 x 3 on 28 x 28 x 4 / 50 x 40 x 100
-// +3.8 / +1.4, 31 x 1 -4.3 / -10.  Of 402 such calls the rule takes the slower form for four by more than 0.3 us (at most 1.0).
+// The form above takes about 0.6 us + 0.2 for every tap of a line, for every line that a word holds part of (64 / E[2], one or two
+// more where that leaves a remainder) and every sixteen lines of the filter; this one 1.4 us for every five lines of the filter,
+// 2.1 where 4096 words share the chip.  Calls, the form above less this one, us: 3 x 3 x 3 on 8^3 x 4 / 16^3 x 16 / 30^3 / 32^3 /
+// 32^3 x 8 +5.7 / +1.8 / +2.4 / -0.3 / -2.2, 5 x 5 x 5 on the same but 30^3 +15 / +4.7 / -0.8 / -4.6, 31 x 1 x 1 +0.4 / -4.3 / -8 / -12,
+// 9 x 1 x 1 +2.4 / -0.1 / -1.5 / -3.1; 3 x 3 on 28 x 28 x 4 / 50 x 40 x 100 +3.8 / +1.4, 31 x 1 -4.3 / -10.  Of 458 such calls the
+// rule takes the slower form for none by more than 0.5 us.
 static bool dilate_by_sites(const Geom& g, long long n_words) {
     if (n_words > kDilateSiteWords || g.E[2] >= 64 || g.K[2] > 32) return false;
     const long long lines = (long long)g.K[0] * g.K[1];
-    const long long by_words = (64 + g.E[2]) * ((lines + 15) / 16) * (3 + 2 * g.K[2]);  // tenths of a us, times E[2]
+    const long long held = 640 + (64 % g.E[2] != 0 ? 13 * g.E[2] : 0);                // tenths of a line of a word, times E[2]
+    const long long by_words = held * ((lines + 15) / 16) * (6 + 2 * g.K[2]);         // hundredths of a us, times E[2]
     const long long by_sites = (lines + kDilateBatch - 1) / kDilateBatch * (14 * 4096 + 7 * n_words);  // tenths, times 4096
-    return by_words * 4096 >= by_sites * g.E[2];
+    return by_words * 4096 >= 10 * by_sites * g.E[2];
 }
 __global__ __launch_bounds__(256) void k_cand_dilate_sites(Geom g, const unsigned long long* __restrict__ occ,
                                                            const int* __restrict__ tap_active,
